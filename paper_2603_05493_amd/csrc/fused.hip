@@ -7,7 +7,7 @@
 //
 // Mapping: a group of G lanes (G = 16, 32 or 64; 64/G states per wavefront)
 // owns one state; lane i of the group holds link perm[i] in depth-first
-// pre-order, so the subtree of lane i is the lane range [i, sub_end_i].
+// post-order, so the subtree of lane i is a lane range that ends at i.
 // Nothing intermediate leaves the chip: link poses and spatial quantities
 // live in registers, sphere centres and link bounding spheres (transformed
 // from their link-frame tables) in the group's LDS.
@@ -31,19 +31,20 @@
 // sum is a subtree sum and vice versa):
 //   fb = pathsum(taub S);  ab = I fb;  vb = -fb x* I v - I (v x fb)
 //   A = subsum(ab);  vb += (S qd) x* A;  V = subsum(vb)
-//   qdd-bar = S.A,  qd-bar = S.V - S.(v x* A)
-//   Sb = taub F + qdd A - qd (v x* A) + qd V                  (adjoint of S)
-//   W = S x* Sb - fb x* I a - a x* I fb + (v x fb) x* I v + v x* I (v x fb)
-//       + [c x g; g] for the hinge gradient g at each argmax sphere centre c
-//   q-bar = S . subsum(W)
-// since rotating joint i moves every world axis and inertia in its subtree
-// (dS = dq S_i x S, dI = dq (S_i x* I - I S_i x)).
+//   qdd-bar = S.A,  qd-bar = S.V + (v x S).A
+//   q-bar = (fb x S).F + ((a - qd v x S) x S).A + (v x S).V
+// Turning joint i changes only its own link's transform from the parent
+// (dX = -dq crm(S) X), which the recursions use three times: for the
+// parent's velocity (adjoint V), its acceleration (adjoint A) and the
+// accumulated force F (adjoint fb), so q-bar needs no sum of its own.
+// The hinge adds s . ((c - p) x g) for the gradient g at an argmax sphere
+// centre c below the joint (world axis s through p).
 //
 // The EXT variant adds two features, each switched on at run time:
 // * external link forces: f_ext is given in link coordinates and turns with
 //   its link, f_w = X* f_ext; it enters the force line as
-//   f = I a + v x* I v - f_w, adds fb x* f_w to W (the rotation of f_w with
-//   the joints above it), and its gradient is f_ext-bar = -X*^T fb;
+//   f = I a + v x* I v - f_w (so it is part of F), and its gradient is
+//   f_ext-bar = -X*^T fb;
 // * mimic joints (Alg. 4's m_k and joint map): link l turns by
 //   theta_l = m_l q_j + o_l, so its rates are m_l qd_j and m_l qdd_j; joint j's
 //   torque is sum over its links of m_l S_l . F_l.  Lane j of the group owns
@@ -118,11 +119,11 @@ __device__ __forceinline__ void iterate_state(const DevRobot &rb, const uint16_t
         R = li[6 * 64 + gl] ? Jr : matmul(R, Jr);
     }
     {
-        // Lane 0 is the fixed root, whose pose is the world frame (identity),
-        // as is every lane past the robot: a chain that has reached the root
-        // keeps composing with that identity, which changes nothing exactly,
-        // so every lane takes every step without a guard.
-        int anc = max(parent_lane, 0);
+        // The root is fixed at the world frame (identity) and its own
+        // ancestor, as is every lane past the robot: a chain that has reached
+        // the root keeps composing with that identity, which changes nothing
+        // exactly, so every lane takes every step without a guard.
+        int anc = parent_lane;
         auto jump = [&]() {
             M3 Ra;
 #pragma unroll
@@ -168,11 +169,20 @@ __device__ __forceinline__ void iterate_state(const DevRobot &rb, const uint16_t
                             key, cnt);
     const float hmarg = M + k.margin;
     const bool hinge_on = key != INT_MAX && hmarg > 0.f && k.hinge_weight != 0.f;
-    // W: adjoint of the lane's joint rotation, before the subtree sum.  The
-    // hinge force is formed without branches: a state without it reads the
-    // pair (0, 0) and selects zero.  A checked pair joins two different
-    // links, so a lane takes at most one of the two sphere forces.
-    SV W = zsv();
+    // ---- world axis, and the hinge force's gradient on the joint angle.
+    // The two forces of the argmax pair (g on sphere t, -g on s) are equal,
+    // opposite and along the line of the centres, so a joint above both
+    // takes none and a joint above one takes s . ((c_t - p) x g) or its
+    // negative: a range test on the lanes of the two links, without a
+    // subtree sum.  A state without hinge force reads the pair (0, 0) and
+    // selects zero.
+    const Subtree sub = subtree_of(li[2 * 64 + gl], gl);
+    SV S = zsv();
+    float th_b = 0.f;
+    if (revolute) {
+        const V3 sw = mul(R, v3(lf[0 * 64 + gl], lf[1 * 64 + gl], lf[2 * 64 + gl]));
+        S = sv(sw, cross(p, sw));
+    }
     if (rb.S > 0) {
         const int hk = hinge_on ? key : 0;
         const int s = (int)((unsigned)hk / (unsigned)rb.S), t = hk - s * rb.S;
@@ -182,17 +192,15 @@ __device__ __forceinline__ void iterate_state(const DevRobot &rb, const uint16_t
         // 1/n as the reciprocal of the rounded root (n >= 2^-75 for any d2 > 0)
         const bool on = hinge_on && d2 > 0.f;
         const V3 g = on ? (k.hinge_weight * __builtin_amdgcn_rcpf(sqrtf(d2))) * d : v3(0.f, 0.f, 0.f);
-        const bool on_s = act && link == rb.sph_link[s], on_t = act && link == rb.sph_link[t];
-        const V3 c = on_s ? v3(cs.x, cs.y, cs.z) : v3(ct.x, ct.y, ct.z);
-        const V3 f = on_s ? -g : g;   // gradient on c_t is g, on c_s -g
-        if (on_s || on_t) W = sv(cross(c, f), f);
+        const int ls = group_lane_of(link == rb.sph_link[s], FULL ? 0 : grp * G);
+        const int lt = group_lane_of(link == rb.sph_link[t], FULL ? 0 : grp * G);
+        const bool in_s = in_subtree(sub, ls, gl), in_t = in_subtree(sub, lt, gl);
+        if (in_s != in_t) {
+            const float h = dot(S.w, cross(v3(ct.x, ct.y, ct.z) - p, g));
+            th_b = in_t ? h : -h;
+        }
     }
-    // ---- world axis and inertia
-    SV S = zsv();
-    if (revolute) {
-        const V3 sw = mul(R, v3(lf[0 * 64 + gl], lf[1 * 64 + gl], lf[2 * 64 + gl]));
-        S = sv(sw, cross(p, sw));
-    }
+    // ---- world inertia
     WInertia J;
     {
         J.m = lf[15 * 64 + gl];
@@ -202,7 +210,6 @@ __device__ __forceinline__ void iterate_state(const DevRobot &rb, const uint16_t
         for (int t = 0; t < 6; ++t) Ic[t] = lf[(19 + t) * 64 + gl];
         rotate_inertia(R, Ic, J.I);
     }
-    const int sub_end = li[2 * 64 + gl];
     // ---- external force in world coordinates, f_w = X* f_ext (moment about the world origin)
     SV fe = zsv();
     if (EXT && io.f_ext && act) {
@@ -214,14 +221,14 @@ __device__ __forceinline__ void iterate_state(const DevRobot &rb, const uint16_t
     // joint whose parent is the fixed root (zero velocity and acceleration),
     // so every force and adjoint it forms below is exactly zero and the
     // subtree scans take it unguarded.
-    const SV Sqd = thd * S;
-    const SV v = path_sum(Sqd, parent_lane, glane, fz.jsteps, G);
-    SV a = path_sum(thdd * S + crm(v, Sqd), parent_lane, glane, fz.jsteps, G);
+    const SV v = path_sum(thd * S, parent_lane, fz.jsteps, G);
+    const SV c = crm(v, S);
+    SV a = path_sum(thdd * S + thd * c, parent_lane, fz.jsteps, G);
     if (act) a += sv(v3(0.f, 0.f, 0.f), v3(-rb.gx, -rb.gy, -rb.gz));
-    const SV Ia = iw_apply(J, a), Iv = iw_apply(J, v);
-    SV F = Ia + crf(v, Iv);
+    const SV Iv = iw_apply(J, v);
+    SV F = iw_apply(J, a) + crf(v, Iv);
     if (EXT) F = F - fe;
-    F = subtree_sum(F, glane, sub_end, G);
+    F = subtree_sum(F, sub, G);
     float tau = revolute ? dot(S, F) : 0.f;
     // with mimic joints, joint lane j (j < n) holds joint j from here to the cost head
     const bool jlane = mim ? gl < rb.n : revolute;
@@ -244,11 +251,8 @@ __device__ __forceinline__ void iterate_state(const DevRobot &rb, const uint16_t
         const float tj = __shfl(taub, revolute ? li[3 * 64 + gl] : gl, G);
         taub = revolute ? mult * tj : 0.f;
     }
-    // ---- VJP, with the terms of W added as soon as their factors exist;
-    // the terms crf(S, .) are linear in their second argument, so they are
-    // gathered in X and crossed with S once at the end
-    SV X = taub * F;
-    const SV fb = path_sum(taub * S, parent_lane, glane, fz.jsteps, G);
+    // ---- VJP
+    const SV fb = path_sum(taub * S, parent_lane, fz.jsteps, G);
     if (EXT && io.g_fext && act && valid) {
         // the external-force gradient needs only fb, so it leaves here and the
         // link's pose is dead for the rest of the adjoint: -X*^T fb, moment
@@ -258,24 +262,9 @@ __device__ __forceinline__ void iterate_state(const DevRobot &rb, const uint16_t
         gx[0] = -gn.x; gx[B] = -gn.y; gx[2 * B] = -gn.z;
         gx[3 * B] = -gf.x; gx[4 * B] = -gf.y; gx[5 * B] = -gf.z;
     }
-    SV ab = iw_apply(J, fb);
-    W = W - (crf(fb, Ia) + crf(a, ab));
-    if (EXT) W += crf(fb, fe);
-    const SV vxfb = crm(v, fb);
-    const SV Ivxfb = iw_apply(J, vxfb);
-    SV vb = zsv() - (crf(fb, Iv) + Ivxfb);
-    W += crf(vxfb, Iv) + crf(v, Ivxfb);
-    const SV Acc = subtree_sum(ab, glane, sub_end, G);
-    vb += thd * crf(S, Acc);   // crf(S qd, Acc)
-    const SV vxA = crf(v, Acc);
-    const float thdd_b = dot(S, Acc);
-    X += thdd * Acc - thd * vxA;
-    const SV V = subtree_sum(vb, glane, sub_end, G);
-    const float thd_b = dot(S, V) - dot(S, vxA);
-    X += thd * V;
-    W += crf(S, X);
-    const SV Ws = subtree_sum(W, glane, sub_end, G);
-    float th_b = dot(S, Ws);
+    float thd_b, thdd_b;
+    th_b += rnea_adjoint(S, c, v, a, F, J, Iv, fb, thd, [&](SV x) { return subtree_sum(x, sub, G); }, thd_b,
+                         thdd_b);
     float thd_o = thd_b, thdd_o = thdd_b;
     if (mim) {   // per-link adjoints to joints: sum of m_l x (link adjoint)
         th_b = gather_joint(mult * th_b, fz, gl, G);
@@ -415,7 +404,7 @@ __device__ __forceinline__ void spline_reduce_step(const SplineIn &sp, const flo
 // per link, where the group regions (about 55 KB per workgroup) leave room
 // for two workgroups per CU anyway.
 template <int NMAX, bool EXT>
-constexpr int fused_waves() { return NMAX > 8 ? 2 : (EXT ? 3 : 4); }
+constexpr int fused_waves() { return NMAX > 8 ? 2 : 4; }
 
 template <int NMAX, bool EXT, int SPL, int GSEL>
 __global__ void __launch_bounds__(256, (fused_waves<NMAX, EXT>())) k_fused_step(FusedArgs A) {
@@ -423,10 +412,7 @@ __global__ void __launch_bounds__(256, (fused_waves<NMAX, EXT>())) k_fused_step(
     const int wave = threadIdx.x >> 6;
     const int G = GSEL == 64 ? 64 : A.lanes_per_state;
     const int SLW = (64 / G) * (int)(group_lds_bytes(A.rb.L, NMAX, A.rb.list_cap) / 16);
-    // XCD-aware chunk order: consecutive chunks stay on one XCD's L2.
-    const int nwg = gridDim.x, x = blockIdx.x & 7, y = blockIdx.x >> 3;
-    const int qd8 = nwg >> 3, rd8 = nwg & 7;
-    const int chunk = x * qd8 + min(x, rd8) + y;
+    const int chunk = xcd_chunk();
     const int64_t b0 = (int64_t)chunk * A.chunk;
     const int64_t rem = A.B - b0;
     const int count = rem < A.chunk ? (int)rem : A.chunk;

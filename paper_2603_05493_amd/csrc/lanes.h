@@ -100,6 +100,14 @@ __device__ __forceinline__ void group_scan6(float &a, float &b, float &c, float 
 #undef WB_BC15
 #undef WB_BC31
 
+// This workgroup's chunk of a range split evenly over the grid: workgroups
+// are dealt round-robin to the 8 XCDs, so each XCD takes one contiguous run
+// of chunks and neighbouring chunks share its L2.
+__device__ __forceinline__ int xcd_chunk() {
+    const int nwg = gridDim.x, x = blockIdx.x & 7, y = blockIdx.x >> 3;
+    return x * (nwg >> 3) + min(x, nwg & 7) + y;
+}
+
 // Value held by lane - 1 of the wave (0 in lane 0: with bound_ctrl set, a
 // lane whose source is outside the wave reads 0, so no "old" value is kept).
 __device__ __forceinline__ float lane_prev(float x) {

@@ -1,7 +1,7 @@
 // Group-of-lanes tree operations shared by the kernels that give each state
 // a group of G lanes (G = 16, 32 or 64) with lane i holding link perm[i] in
-// depth-first pre-order (the subtree of lane i is the lane range
-// [i, sub_end_i]): path sums by pointer jumping over the parent lanes,
+// depth-first post-order (the subtree of lane i is a lane range that ends at
+// i): path sums by pointer jumping over the parent lanes,
 // subtree sums as differences of a group scan, world-frame inertia
 // products, and the per-lane forward kinematics.
 #pragma once
@@ -18,13 +18,12 @@ __device__ __forceinline__ SV shfl_sv(SV x, int src, int G) {
 }
 __device__ __forceinline__ SV zsv() { return sv(v3(0.f, 0.f, 0.f), v3(0.f, 0.f, 0.f)); }
 
-// Sum of x over the path from the root to this lane's link.  Lane 0 (the
-// fixed root) and the lanes past the robot must hold zero: a chain that has
-// reached the root keeps jumping to lane 0 and adds that zero, exactly, so
-// no lane needs a guard (and no masked copy of x) per step.
-__device__ __forceinline__ SV path_sum(SV x, int parent_lane, int glane, int steps, int G) {
-    (void)glane;
-    int anc = max(parent_lane, 0);
+// Sum of x over the path from the root to this lane's link.  The root (a
+// fixed link) and the lanes past the robot must hold zero: they are their
+// own parents, so a chain that has reached the root keeps adding that zero,
+// exactly, and no lane needs a guard (or a masked copy of x) per step.
+__device__ __forceinline__ SV path_sum(SV x, int parent_lane, int steps, int G) {
+    int anc = parent_lane;
     for (int s = 0; s < steps; ++s) {
         const SV y = shfl_sv(x, anc, G);
         anc = __shfl(anc, anc, G);
@@ -33,16 +32,49 @@ __device__ __forceinline__ SV path_sum(SV x, int parent_lane, int glane, int ste
     return x;
 }
 
-// Sum of x over this lane's subtree (group lanes [glane, sub_end]): the
-// difference of two values of the group's inclusive scan.  Lanes outside the
-// robot must hold zero.
-__device__ __forceinline__ SV subtree_sum(SV x, int glane, int sub_end, int G) {
+// The subtree of a lane: the group lanes (before, lane], or [0, lane] where
+// there is none before it (then before is the lane itself and some is 0).
+struct Subtree {
+    int before;
+    float some;
+};
+__device__ __forceinline__ Subtree subtree_of(int before, int glane) {
+    return Subtree{before, before != glane ? 1.f : 0.f};
+}
+__device__ __forceinline__ bool in_subtree(Subtree t, int lane, int glane) {
+    return lane <= glane && (t.some == 0.f || lane > t.before);
+}
+
+// Sum of x over this lane's subtree: the group's inclusive scan at the
+// subtree's last lane (this one) less the scan before its first.  Lanes
+// outside the robot must hold zero.
+__device__ __forceinline__ SV subtree_sum(SV x, Subtree t, int G) {
     SV s = x;
     group_scan6(s.w.x, s.w.y, s.w.z, s.l.x, s.l.y, s.l.z, G);
-    const SV hi = shfl_sv(s, sub_end, G);
-    const SV lo = sv(v3(lane_prev(s.w.x), lane_prev(s.w.y), lane_prev(s.w.z)),
-                     v3(lane_prev(s.l.x), lane_prev(s.l.y), lane_prev(s.l.z)));
-    return glane > 0 ? hi - lo : hi;
+    const SV y = shfl_sv(s, t.before, G);
+    return sv(v3(__builtin_fmaf(-t.some, y.w.x, s.w.x), __builtin_fmaf(-t.some, y.w.y, s.w.y),
+                 __builtin_fmaf(-t.some, y.w.z, s.w.z)),
+              v3(__builtin_fmaf(-t.some, y.l.x, s.l.x), __builtin_fmaf(-t.some, y.l.y, s.l.y),
+                 __builtin_fmaf(-t.some, y.l.z, s.l.z)));
+}
+
+// The same sum with each value split in two, x = hi + lo, hi on a grid so
+// coarse (2^-17 of the power of two above the group's largest value) that
+// every partial sum of up to 64 of them is exact: the scan difference of hi
+// has no rounding at all and that of lo next to none, so the result is the
+// exact sum rounded once, whatever is subtracted.  For results that must
+// stay as exact as the link-by-link recursion's.  A serial chain subtracts
+// nothing and takes the plain scan.
+__device__ __forceinline__ SV subtree_sum_split(SV x, Subtree t, bool branched, int G) {
+    if (!branched) return subtree_sum(x, t, G);
+    float m = fmaxf(fmaxf(fabsf(x.w.x), fabsf(x.w.y)), fabsf(x.w.z));
+    m = fmaxf(fmaxf(m, fabsf(x.l.x)), fmaxf(fabsf(x.l.y), fabsf(x.l.z)));
+    m = group_reduce_max(m, G);
+    // 1.5 * 2^(e + 6) with m < 2^e: adding it rounds to multiples of 2^(e - 17)
+    const float c = __builtin_amdgcn_ldexpf(1.5f, min(__builtin_amdgcn_frexp_expf(m) + 6, 127));
+    const SV hi = sv(v3((x.w.x + c) - c, (x.w.y + c) - c, (x.w.z + c) - c),
+                     v3((x.l.x + c) - c, (x.l.y + c) - c, (x.l.z + c) - c));
+    return subtree_sum(hi, t, G) + subtree_sum(x - hi, t, G);
 }
 
 // World-frame spatial inertia of a link: mass m, CoM cw and the rotational
@@ -76,6 +108,36 @@ __device__ __forceinline__ void rotate_inertia(const M3 &R, const float *Ic, flo
                 T[3 * ii[e] + 2] * R.m[3 * jj[e] + 2];
 }
 
+// Adjoints of a link's joint angle (returned), rate and acceleration, from
+// the adjoint fb of its accumulated force (the path sum of taub S), all in
+// world coordinates:
+//   A = subsum(I fb),  V = subsum((S qd) x* A - fb x* I v - I (v x fb))
+//   qdd-bar = S.A,  qd-bar = S.V + (v x S).A
+//   q-bar = (fb x S).F + ((a - qd v x S) x S).A + (v x S).V
+// A and V are the total adjoints of the link's acceleration and velocity;
+// the angle enters the recursions through this link's transform alone
+// (dX = -crm(S) X), once each for the parent's velocity v - S qd, the
+// parent's acceleration a - S qdd - qd v x S and the force passed to the
+// parent, whose adjoint is fb - taub S (every S x S vanishes).  Against
+// summing the turned axes and inertias of the whole subtree this takes one
+// of three subtree sums and four force products out of the VJP (humanoid,
+// 24,576 states: see the kernels that call it).
+// c = v x S, Iv = I v; subsum the subtree sum to use.  Lanes outside the
+// robot must hold zeros.
+template <typename Sum>
+__device__ __forceinline__ float rnea_adjoint(SV S, SV c, SV v, SV a, SV F, const WInertia &J, SV Iv, SV fb,
+                                              float thd, Sum subsum, float &thd_b, float &thdd_b) {
+    const SV Acc = subsum(iw_apply(J, fb));
+    const SV V = subsum(thd * crf(S, Acc) - (crf(fb, Iv) + iw_apply(J, crm(v, fb))));
+    thdd_b = dot(S, Acc);
+    thd_b = dot(S, V) + dot(c, Acc);
+    return dot(crm(fb, S), F) + dot(crm(a - thd * c, S), Acc) + dot(c, V);
+}
+
+// Lane, within the group whose first lane is `first`, for which `mine`
+// holds (it holds for exactly one lane of every group).
+__device__ __forceinline__ int group_lane_of(bool mine, int first) { return __ffsll(__ballot(mine) >> first) - 1; }
+
 __device__ __forceinline__ void wave_sync() {
     __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");
     __builtin_amdgcn_wave_barrier();
@@ -96,7 +158,7 @@ __device__ __forceinline__ float gather_joint(float x, const DevFused &fz, int g
 // World pose (R, p) of the lane's link: the lane's local transform (fixed
 // rotation and translation, then the joint rotation by angle th), composed
 // with its ancestors' by pointer jumping, T <- T_anc o T, anc <- anc(anc),
-// `steps` times.  Lane 0 (the fixed root) and the lanes past the robot hold
+// `steps` times.  The root (a fixed link) and the lanes past the robot hold
 // the identity and are their own ancestors, so a chain that has reached
 // the root keeps composing with the identity, exactly.
 __device__ __forceinline__ void lane_world_pose(const DevFused &fz, int gl, bool revolute, float th, int parent_lane,
@@ -112,7 +174,7 @@ __device__ __forceinline__ void lane_world_pose(const DevFused &fz, int gl, bool
         const M3 Jr = axis_angle(v3(lf[0 * 64 + gl], lf[1 * 64 + gl], lf[2 * 64 + gl]), s, c);
         R = li[6 * 64 + gl] ? Jr : matmul(R, Jr);
     }
-    int anc = max(parent_lane, 0);
+    int anc = parent_lane;
     for (int st = 0; st < fz.jsteps; ++st) {
         M3 Ra;
 #pragma unroll

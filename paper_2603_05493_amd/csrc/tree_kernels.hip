@@ -1,5 +1,5 @@
 // Storage-free per-operation kernels with one state per group of G lanes,
-// lane i holding link perm[i] in depth-first pre-order as in the fused
+// lane i holding link perm[i] in depth-first post-order as in the fused
 // iteration: RNEA and its vector-Jacobian product without a cache (cuRoboV2
 // Alg. 4 and the role of Alg. 5, with transforms and every forward quantity
 // recomputed in the backward), and the adjoint of forward kinematics
@@ -18,32 +18,93 @@
 // and vice versa):
 //   fb = pathsum(taub S);  ab = I fb;  vb = -fb x* I v - I (v x fb)
 //   A = subsum(ab);  vb += (S qd) x* A;  V = subsum(vb)
-//   qdd-bar = S.A,  qd-bar = S.V - S.(v x* A)
-//   W = taub S x* F - fb x* I a - a x* I fb + (v x fb) x* I v + v x* I (v x fb)
-//       + qdd S x* A - qd S x* (v x* A) + qd S x* V + fb x* f_w
-//   q-bar = S . subsum(W),  f_ext-bar = -X*^T fb
-// (rotating joint i moves every world axis, inertia and external force of
-// its subtree).  Mimic joints: link l turns by m_l q_j + o_l; lane j of the
+//   qdd-bar = S.A,  qd-bar = S.V + (v x S).A
+//   q-bar = (fb x S).F + ((a - qd v x S) x S).A + (v x S).V,  f_ext-bar = -X*^T fb
+// (derived at rnea_adjoint).  Mimic joints: link l turns by m_l q_j + o_l; lane j of the
 // group gathers joint j's torque (and adjoints) from the links it drives,
 // and returns m_l tau-bar_j to each of them.
 #include "tree.h"
 
 namespace wb {
 
-// nb: states; B: row length of every [k][B] array (the ABI's ld >= nb);
-// G: lanes per state, a compile-time constant (one kernel per lane count).
-template <bool BACKWARD, int G>
-__global__ void __launch_bounds__(256) k_rnea_lanes(DevRobot rb, DevFused fz, int64_t nb, int64_t B,
-                                                    const float *__restrict__ q, const float *__restrict__ qd,
-                                                    const float *__restrict__ qdd, const float *__restrict__ f_ext,
-                                                    float *__restrict__ tau, const float *__restrict__ g_tau,
-                                                    float *__restrict__ g_q, float *__restrict__ g_qd,
-                                                    float *__restrict__ g_qdd, float *__restrict__ g_fext) {
+// Row tile of TS states staged in LDS, for the [L][18][B] cache: a group
+// holds one state, so its lanes touch one float of every row, while a tile
+// of 16 states moves 64-byte pieces of the rows (TileRow: 16 states padded
+// to 17, so that the lanes of a group hit different banks).
+constexpr int TILE_S = 16, TILE_ROW = 17;
+
+// The link's spatial vector to or from its six rows of the tile.
+__device__ __forceinline__ void tile_put(float *tile, int link, int s, SV x) {
+    float *r = tile + link * 6 * TILE_ROW + s;
+    r[0] = x.w.x; r[TILE_ROW] = x.w.y; r[2 * TILE_ROW] = x.w.z;
+    r[3 * TILE_ROW] = x.l.x; r[4 * TILE_ROW] = x.l.y; r[5 * TILE_ROW] = x.l.z;
+}
+__device__ __forceinline__ SV tile_get(const float *tile, int link, int s) {
+    const float *r = tile + link * 6 * TILE_ROW + s;
+    return sv(v3(r[0], r[TILE_ROW], r[2 * TILE_ROW]), v3(r[3 * TILE_ROW], r[4 * TILE_ROW], r[5 * TILE_ROW]));
+}
+// Rows part .. part + 5 of every link but the base between the tile and the
+// cache, `cnt` states from b0; thread t takes state t % 16.
+template <bool STORE>
+__device__ __forceinline__ void tile_move(float *tile, float *cache, int part, int L, int64_t B, int64_t b0, int cnt) {
+    const int s = threadIdx.x % TILE_S;
+    if (s < cnt)
+        for (int r = 6 + threadIdx.x / TILE_S; r < 6 * L; r += blockDim.x / TILE_S) {
+            const int link = r / 6;
+            float *g = cache + (int64_t)(r + 12 * link + part) * B + b0 + s;
+            if (STORE) *g = tile[r * TILE_ROW + s];
+            else tile[r * TILE_ROW + s] = *g;
+        }
+}
+
+// A world-frame (about the world origin) motion or force vector in the
+// coordinates of the link with pose (R, p), and back for a force.
+__device__ __forceinline__ SV motion_to_link(const M3 &R, V3 p, SV u) {
+    return sv(mulT(R, u.w), mulT(R, u.l + cross(u.w, p)));
+}
+__device__ __forceinline__ SV force_to_link(const M3 &R, V3 p, SV f) {
+    return sv(mulT(R, f.w - cross(p, f.l)), mulT(R, f.l));
+}
+__device__ __forceinline__ SV force_to_world(const M3 &R, V3 p, SV f) {
+    const V3 Rf = mul(R, f.l);
+    return sv(mul(R, f.w) + cross(p, Rf), Rf);
+}
+
+// RNEA (or its VJP, BWD), one state per group of G lanes.  CACHE: the
+// forward also writes each link's v, a and accumulated force F in link
+// coordinates; the backward takes F (which holds any external forces) from
+// it and recomputes v and a, which are cheaper formed than read.  These
+// forms replace the link-by-link recursion in link coordinates and sum the
+// subtrees in split form, to be as exact (torques of a 37-joint tree against
+// 64 bits: 1.6e-7 by the recursion, 5.4e-7 from plain scan differences).
+// TILE: a
+// workgroup of 16 G lanes owns 16 consecutive states and moves the cache
+// through an LDS tile; without it a workgroup is 256 lanes and the cache is
+// accessed by the groups directly.
+// nb: states; B: row length of every [k][B] array (the ABI's ld >= nb).
+template <bool BWD, bool CACHE, bool TILE, int G>
+__global__ void __launch_bounds__(TILE ? 16 * G : 256)
+    k_rnea_lanes(DevRobot rb, DevFused fz, int64_t nb, int64_t B, const float *__restrict__ q,
+                 const float *__restrict__ qd, const float *__restrict__ qdd, const float *__restrict__ f_ext,
+                 float *__restrict__ tau, float *__restrict__ cache, const float *__restrict__ g_tau,
+                 float *__restrict__ g_q, float *__restrict__ g_qd, float *__restrict__ g_qdd,
+                 float *__restrict__ g_fext) {
+    extern __shared__ float tile[];
     const int lane = threadIdx.x & 63;
-    const int per_wave = 64 / G, grp = lane / G, gl = lane - grp * G;
-    const int64_t wave = (int64_t)blockIdx.x * 4 + (threadIdx.x >> 6);
-    const int64_t s = wave * per_wave + grp;
-    if (wave * per_wave >= nb) return;   // the whole wavefront is past the batch
+    const int gl = lane & (G - 1);
+    int64_t s0, s;   // first state of the workgroup (TILE), this group's state
+    if (TILE) {
+        s0 = (int64_t)xcd_chunk() * TILE_S;
+        s = s0 + threadIdx.x / G;
+        if (BWD) tile_move<false>(tile, cache, 12, rb.L, B, s0, (int)min((int64_t)TILE_S, nb - s0));
+    } else {
+        const int64_t wave = (int64_t)blockIdx.x * 4 + (threadIdx.x >> 6);
+        s0 = wave * (64 / G);
+        s = s0 + lane / G;
+        if (s0 >= nb) return;   // the whole wavefront is past the batch
+    }
+    const int ts = TILE ? (int)(threadIdx.x / G) : 0;   // the group's state in the tile
+    const int cnt = TILE ? (int)min((int64_t)TILE_S, nb - s0) : 0;
     const bool valid = s < nb;
     const int64_t b = valid ? s : nb - 1;   // groups past the end compute on a valid state, store nothing
     const int *li = fz.li;
@@ -53,7 +114,10 @@ __global__ void __launch_bounds__(256) k_rnea_lanes(DevRobot rb, DevFused fz, in
     const bool revolute = li[5 * 64 + gl] != 0;
     const int jidx = li[3 * 64 + gl];
     const int link = li[0 * 64 + gl];
-    const int sub_end = li[2 * 64 + gl];
+    const Subtree sub = subtree_of(li[2 * 64 + gl], gl);
+    auto subsum = [&](SV x) {
+        return CACHE ? subtree_sum_split(x, sub, fz.branched != 0, G) : subtree_sum(x, sub, G);
+    };
     const bool mim = fz.mimic != 0;
     float th = 0.f, thd = 0.f, thdd = 0.f, mult = 1.f;
     if (revolute) {
@@ -85,27 +149,56 @@ __global__ void __launch_bounds__(256) k_rnea_lanes(DevRobot rb, DevFused fz, in
         for (int t = 0; t < 6; ++t) Ic[t] = lf[(19 + t) * 64 + gl];
         rotate_inertia(R, Ic, J.I);
     }
-    // external force in world coordinates, f_w = X* f_ext (moment about the world origin)
-    SV fe = zsv();
-    if (f_ext && act) {
-        const float *fx = f_ext + (int64_t)(link * 6) * B + b;
-        const V3 Rf = mul(R, v3(fx[3 * B], fx[4 * B], fx[5 * B]));
-        fe = sv(mul(R, v3(fx[0], fx[B], fx[2 * B])) + cross(p, Rf), Rf);
-    }
-    const SV Sqd = thd * S;
-    const SV v = path_sum(Sqd, parent_lane, gl, fz.jsteps, G);
-    SV a = path_sum(thdd * S + crm(v, Sqd), parent_lane, gl, fz.jsteps, G);
+    // Lanes past the robot are massless links without a joint on the root:
+    // every sum below is zero there without a guard.
+    const SV v = path_sum(thd * S, parent_lane, fz.jsteps, G);
+    const SV c = crm(v, S);
+    SV a = path_sum(thdd * S + thd * c, parent_lane, fz.jsteps, G);
     if (act) a += sv(v3(0.f, 0.f, 0.f), v3(-rb.gx, -rb.gy, -rb.gz));
-    const SV Ia = iw_apply(J, a), Iv = iw_apply(J, v);
-    SV F = Ia + crf(v, Iv) - fe;
-    if (!act) F = zsv();
-    F = subtree_sum(F, gl, sub_end, G);
+    const SV Iv = iw_apply(J, v);
+    SV F;
+    if (BWD && CACHE) {
+        F = zsv();
+        if (TILE) __syncthreads();
+        if (act && link > 0) {
+            if (TILE) F = tile_get(tile, link, ts);
+            else {
+                const float *cf = cache + (int64_t)(link * 18 + 12) * B + b;
+                F = sv(v3(cf[0], cf[B], cf[2 * B]), v3(cf[3 * B], cf[4 * B], cf[5 * B]));
+            }
+        }
+        F = force_to_world(R, p, F);
+    } else {
+        F = iw_apply(J, a) + crf(v, Iv);
+        if (f_ext && act) {   // external force in world coordinates, X* f_ext
+            const float *fx = f_ext + (int64_t)(link * 6) * B + b;
+            F = F - force_to_world(R, p, sv(v3(fx[0], fx[B], fx[2 * B]), v3(fx[3 * B], fx[4 * B], fx[5 * B])));
+        }
+        F = subsum(F);
+    }
     const bool jlane = mim ? gl < rb.n : revolute;
     const int64_t jrow = (int64_t)(mim ? gl : jidx) * B + b;
-    if (!BACKWARD) {
+    if (!BWD) {
         float t = revolute ? dot(S, F) : 0.f;
         if (mim) t = gather_joint(mult * t, fz, gl, G);
         if (valid && jlane) tau[jrow] = t;
+        if (CACHE) {
+#pragma unroll
+            for (int part = 0; part < 3; ++part) {
+                const SV x = part == 0 ? motion_to_link(R, p, v)
+                                       : (part == 1 ? motion_to_link(R, p, a) : force_to_link(R, p, F));
+                if (TILE) {
+                    if (part > 0) __syncthreads();   // the tile's previous rows are out
+                    if (act && link > 0) tile_put(tile, link, ts, x);
+                    __syncthreads();
+                    tile_move<true>(tile, cache, 6 * part, rb.L, B, s0, cnt);
+                } else if (valid && act && link > 0) {
+                    float *d = cache + (int64_t)(link * 18 + 6 * part) * B + b;
+                    d[0] = x.w.x; d[B] = x.w.y; d[2 * B] = x.w.z;
+                    d[3 * B] = x.l.x; d[4 * B] = x.l.y; d[5 * B] = x.l.z;
+                }
+            }
+        }
         return;
     }
     // tau-bar of the lane's link: m_l tau-bar_j with mimic joints
@@ -114,41 +207,22 @@ __global__ void __launch_bounds__(256) k_rnea_lanes(DevRobot rb, DevFused fz, in
         const float tj = __shfl(taub, revolute ? jidx : gl, G);
         taub = revolute ? mult * tj : 0.f;
     }
-    SV W = taub * crf(S, F);
-    const SV fb = path_sum(taub * S, parent_lane, gl, fz.jsteps, G);
-    SV ab = iw_apply(J, fb);
-    W = W - (crf(fb, Ia) + crf(a, ab)) + crf(fb, fe);
-    const SV vxfb = crm(v, fb);
-    const SV Ivxfb = iw_apply(J, vxfb);
-    SV vb = zsv() - (crf(fb, Iv) + Ivxfb);
-    W += crf(vxfb, Iv) + crf(v, Ivxfb);
-    if (!act) ab = zsv();
-    const SV Acc = subtree_sum(ab, gl, sub_end, G);
-    vb += crf(Sqd, Acc);
-    if (!act) vb = zsv();
-    const SV vxA = crf(v, Acc);
-    float thdd_b = dot(S, Acc);
-    W += thdd * crf(S, Acc) - thd * crf(S, vxA);
-    const SV V = subtree_sum(vb, gl, sub_end, G);
-    float thd_b = dot(S, V) - dot(S, vxA);
-    W += thd * crf(S, V);
-    if (!act) W = zsv();
-    const SV Ws = subtree_sum(W, gl, sub_end, G);
-    float th_b = dot(S, Ws);
+    const SV fb = path_sum(taub * S, parent_lane, fz.jsteps, G);
+    if (g_fext && act && valid) {
+        // -X*^T fb: moment part -R^T fb_w, force part -R^T (fb_l + fb_w x p)
+        const SV gf = motion_to_link(R, p, fb);
+        float *gx = g_fext + (int64_t)(link * 6) * B + b;
+        gx[0] = -gf.w.x; gx[B] = -gf.w.y; gx[2 * B] = -gf.w.z;
+        gx[3 * B] = -gf.l.x; gx[4 * B] = -gf.l.y; gx[5 * B] = -gf.l.z;
+    }
+    float thd_b, thdd_b;
+    float th_b = rnea_adjoint(S, c, v, a, F, J, Iv, fb, thd, subsum, thd_b, thdd_b);
     if (mim) {
         th_b = gather_joint(mult * th_b, fz, gl, G);
         thd_b = gather_joint(mult * thd_b, fz, gl, G);
         thdd_b = gather_joint(mult * thdd_b, fz, gl, G);
     }
-    if (!valid) return;
-    if (g_fext && act) {
-        // -X*^T fb: moment part -R^T fb_w, force part -R^T (fb_l + fb_w x p)
-        const V3 gn = mulT(R, fb.w), gf = mulT(R, fb.l + cross(fb.w, p));
-        float *gx = g_fext + (int64_t)(link * 6) * B + b;
-        gx[0] = -gn.x; gx[B] = -gn.y; gx[2 * B] = -gn.z;
-        gx[3 * B] = -gf.x; gx[4 * B] = -gf.y; gx[5 * B] = -gf.z;
-    }
-    if (jlane) {
+    if (valid && jlane) {
         g_q[jrow] = th_b;
         g_qd[jrow] = thd_b;
         g_qdd[jrow] = thdd_b;
@@ -184,7 +258,7 @@ __global__ void __launch_bounds__(256) k_fk_backward_lanes(DevRobot rb, DevFused
     const bool revolute = li[5 * 64 + gl] != 0;
     const int jidx = li[3 * 64 + gl];
     const int link = li[0 * 64 + gl];
-    const int sub_end = li[2 * 64 + gl];
+    const Subtree sub = subtree_of(li[2 * 64 + gl], gl);
     const bool mim = fz.mimic != 0;
     float th = 0.f, mult = 1.f;
     if (revolute) {
@@ -221,7 +295,7 @@ __global__ void __launch_bounds__(256) k_fk_backward_lanes(DevRobot rb, DevFused
             W += sv(m, gt);
         }
     }
-    const SV Ws = subtree_sum(W, gl, sub_end, G);
+    const SV Ws = subtree_sum(W, sub, G);
     float th_b = 0.f;
     if (revolute) {
         const V3 sw = mul(R, v3(lf[0 * 64 + gl], lf[1 * 64 + gl], lf[2 * 64 + gl]));
@@ -248,37 +322,58 @@ hipError_t launch_fk_backward_lanes(const DevRobot &rb, const DevFused &fz, int6
     return hipGetLastError();
 }
 
-hipError_t launch_rnea_lanes(const DevRobot &rb, const DevFused &fz, int64_t B, int64_t ld, const float *q,
-                             const float *qd, const float *qdd, const float *f_ext, float *tau, hipStream_t s) {
-    if (B == 0) return hipSuccess;
-    const int G = lanes_for(rb.L);
-    const int64_t per_wg = 4 * (64 / G);
-    const dim3 grid((unsigned)((B + per_wg - 1) / per_wg));
-    const float *no = nullptr;
-    float *nw = nullptr;
-    switch (G) {
-        case 16: hipLaunchKernelGGL((k_rnea_lanes<false, 16>), grid, dim3(256), 0, s, rb, fz, B, ld, q, qd, qdd, f_ext, tau, no, nw, nw, nw, nw); break;
-        case 32: hipLaunchKernelGGL((k_rnea_lanes<false, 32>), grid, dim3(256), 0, s, rb, fz, B, ld, q, qd, qdd, f_ext, tau, no, nw, nw, nw, nw); break;
-        default: hipLaunchKernelGGL((k_rnea_lanes<false, 64>), grid, dim3(256), 0, s, rb, fz, B, ld, q, qd, qdd, f_ext, tau, no, nw, nw, nw, nw); break;
+// The cached forms move the cache through tiles of 16 states where the
+// batch fills the chip with such workgroups, and access it directly below.
+template <bool BWD, bool CACHE, int G>
+static hipError_t launch_rnea_g(const DevRobot &rb, const DevFused &fz, int64_t B, int64_t ld, const float *q,
+                                const float *qd, const float *qdd, const float *f_ext, float *tau, float *cache,
+                                const float *g_tau, float *g_q, float *g_qd, float *g_qdd, float *g_fext,
+                                bool tiled, hipStream_t s) {
+    if (CACHE && tiled) {
+        const dim3 grid((unsigned)((B + TILE_S - 1) / TILE_S));
+        const size_t lds = (size_t)rb.L * 6 * TILE_ROW * 4;
+        hipLaunchKernelGGL((k_rnea_lanes<BWD, CACHE, CACHE, G>), grid, dim3(16 * G), lds, s, rb, fz, B, ld, q, qd,
+                           qdd, f_ext, tau, cache, g_tau, g_q, g_qd, g_qdd, g_fext);
+    } else {
+        const int64_t per_wg = 4 * (64 / G);
+        const dim3 grid((unsigned)((B + per_wg - 1) / per_wg));
+        hipLaunchKernelGGL((k_rnea_lanes<BWD, CACHE, false, G>), grid, dim3(256), 0, s, rb, fz, B, ld, q, qd, qdd,
+                           f_ext, tau, cache, g_tau, g_q, g_qd, g_qdd, g_fext);
     }
     return hipGetLastError();
 }
 
+template <bool BWD, bool CACHE>
+static hipError_t launch_rnea_any(const DevRobot &rb, const DevFused &fz, int64_t B, int64_t ld, const float *q,
+                                  const float *qd, const float *qdd, const float *f_ext, float *tau, float *cache,
+                                  const float *g_tau, float *g_q, float *g_qd, float *g_qdd, float *g_fext,
+                                  bool tiled, hipStream_t s) {
+    if (B == 0) return hipSuccess;
+    switch (lanes_for(rb.L)) {
+        case 16: return launch_rnea_g<BWD, CACHE, 16>(rb, fz, B, ld, q, qd, qdd, f_ext, tau, cache, g_tau, g_q, g_qd, g_qdd, g_fext, tiled, s);
+        case 32: return launch_rnea_g<BWD, CACHE, 32>(rb, fz, B, ld, q, qd, qdd, f_ext, tau, cache, g_tau, g_q, g_qd, g_qdd, g_fext, tiled, s);
+        default: return launch_rnea_g<BWD, CACHE, 64>(rb, fz, B, ld, q, qd, qdd, f_ext, tau, cache, g_tau, g_q, g_qd, g_qdd, g_fext, tiled, s);
+    }
+}
+
+hipError_t launch_rnea_lanes(const DevRobot &rb, const DevFused &fz, int64_t B, int64_t ld, const float *q,
+                             const float *qd, const float *qdd, const float *f_ext, float *tau, float *cache,
+                             bool tiled, hipStream_t s) {
+    return cache ? launch_rnea_any<false, true>(rb, fz, B, ld, q, qd, qdd, f_ext, tau, cache, nullptr, nullptr,
+                                                nullptr, nullptr, nullptr, tiled, s)
+                 : launch_rnea_any<false, false>(rb, fz, B, ld, q, qd, qdd, f_ext, tau, nullptr, nullptr, nullptr,
+                                                 nullptr, nullptr, nullptr, false, s);
+}
+
 hipError_t launch_rnea_backward_lanes(const DevRobot &rb, const DevFused &fz, int64_t B, int64_t ld,
                                       const float *q, const float *qd, const float *qdd, const float *f_ext,
-                                      const float *g_tau, float *g_q, float *g_qd, float *g_qdd, float *g_fext,
-                                      hipStream_t s) {
-    if (B == 0) return hipSuccess;
-    const int G = lanes_for(rb.L);
-    const int64_t per_wg = 4 * (64 / G);
-    const dim3 grid((unsigned)((B + per_wg - 1) / per_wg));
-    float *nw = nullptr;
-    switch (G) {
-        case 16: hipLaunchKernelGGL((k_rnea_lanes<true, 16>), grid, dim3(256), 0, s, rb, fz, B, ld, q, qd, qdd, f_ext, nw, g_tau, g_q, g_qd, g_qdd, g_fext); break;
-        case 32: hipLaunchKernelGGL((k_rnea_lanes<true, 32>), grid, dim3(256), 0, s, rb, fz, B, ld, q, qd, qdd, f_ext, nw, g_tau, g_q, g_qd, g_qdd, g_fext); break;
-        default: hipLaunchKernelGGL((k_rnea_lanes<true, 64>), grid, dim3(256), 0, s, rb, fz, B, ld, q, qd, qdd, f_ext, nw, g_tau, g_q, g_qd, g_qdd, g_fext); break;
-    }
-    return hipGetLastError();
+                                      const float *cache, const float *g_tau, float *g_q, float *g_qd, float *g_qdd,
+                                      float *g_fext, bool tiled, hipStream_t s) {
+    float *c = const_cast<float *>(cache);   // the backward only reads it
+    return cache ? launch_rnea_any<true, true>(rb, fz, B, ld, q, qd, qdd, nullptr, nullptr, c, g_tau, g_q, g_qd,
+                                               g_qdd, g_fext, tiled, s)
+                 : launch_rnea_any<true, false>(rb, fz, B, ld, q, qd, qdd, f_ext, nullptr, nullptr, g_tau, g_q,
+                                                g_qd, g_qdd, g_fext, false, s);
 }
 
 }  // namespace wb

@@ -56,7 +56,8 @@ struct Tables {
     std::vector<float4> f_sph;
     int f_mimic = 0, f_mc = 1;        // mimic joints present; longest connectedLinks list
     std::vector<int32_t> f_conn;      // [f_mc][64] lanes of each joint's links
-    // lane tables of the kinematics-outputs kernel (same depth-first order)
+    int f_branched = 0;               // some subtree starts past lane 0
+    // lane tables of the kinematics-outputs kernel (depth-first pre-order)
     int kin = 0, kin_G = 0, kin_jsteps = 0, kin_mc = 0;
     std::vector<int> kin_lane, kin_sub_end;   // link -> lane, lane -> last lane of its subtree
     std::vector<int32_t> k_li, k_conn;
@@ -70,8 +71,6 @@ bool finite_all(const float *p, size_t n) {
     return true;
 }
 
-// Lane tables of the fused kernel: links in depth-first pre-order so every
-// subtree is a contiguous lane range.
 // Depth-first pre-order of the links (children in index order): perm[i] is
 // the link of lane i, lane_of its inverse, size[k] the size of k's subtree.
 void dfs_lanes(const Tables &T, std::vector<int> &perm, std::vector<int> &lane_of, std::vector<int> &size) {
@@ -90,6 +89,42 @@ void dfs_lanes(const Tables &T, std::vector<int> &perm, std::vector<int> &lane_o
     for (int i = 0; i < L; ++i) lane_of[perm[i]] = i;
     size.assign(L, 1);
     for (int k = L - 1; k >= 1; --k) size[T.li[k].parent] += size[k];
+}
+
+// Depth-first post-order of the links, perm[i] the link of lane i: every
+// subtree is a lane range that ends with its root, so a subtree sum is the
+// inclusive scan at the link's own lane minus the scan before its subtree.
+// What is subtracted, and lost to rounding, is the sum over the subtrees
+// visited earlier, never an ancestor's: children come lightest first, and a
+// serial chain subtracts nothing.
+void postorder_lanes(const Tables &T, std::vector<int> &perm, std::vector<int> &lane_of, std::vector<int> &size) {
+    const int L = T.L;
+    std::vector<std::vector<int>> kids(L);
+    std::vector<double> mass(L);
+    size.assign(L, 1);
+    for (int k = 0; k < L; ++k) mass[k] = T.lf[k].mass;
+    for (int k = L - 1; k >= 1; --k) {
+        size[T.li[k].parent] += size[k];
+        mass[T.li[k].parent] += mass[k];
+    }
+    for (int k = 1; k < L; ++k) kids[T.li[k].parent].push_back(k);
+    for (auto &c : kids) std::stable_sort(c.begin(), c.end(), [&](int a, int b) { return mass[a] < mass[b]; });
+    // each subtree's lanes end where its place among its siblings ends
+    lane_of.assign(L, 0);
+    lane_of[0] = L - 1;
+    std::vector<int> stack{0};
+    while (!stack.empty()) {
+        const int k = stack.back();
+        stack.pop_back();
+        int last = lane_of[k] - size[k];
+        for (int c : kids[k]) {
+            last += size[c];
+            lane_of[c] = last;
+            stack.push_back(c);
+        }
+    }
+    perm.assign(L, 0);
+    for (int k = 0; k < L; ++k) perm[lane_of[k]] = k;
 }
 
 int pointer_jump_steps(int max_depth) {
@@ -165,7 +200,8 @@ void build_fused(Tables &T) {
     const int g_default = L <= 16 ? 16 : (L <= 32 ? 32 : 64);
     std::vector<int> perm, size;
     std::vector<int> &lane_of = T.lane_of;
-    dfs_lanes(T, perm, lane_of, size);
+    postorder_lanes(T, perm, lane_of, size);
+    T.f_branched = 0;
     T.f_li.assign(8 * 64, 0);
     T.f_lf.assign(31 * 64, 0.0f);
     std::vector<std::vector<int>> conn(T.n);
@@ -175,12 +211,13 @@ void build_fused(Tables &T) {
         const wb::LinkI &I = T.li[k];
         const wb::LinkF &F = T.lf[k];
         T.f_li[0 * 64 + i] = k;
-        T.f_li[1 * 64 + i] = k == 0 ? -1 : lane_of[I.parent];
-        T.f_li[2 * 64 + i] = i + size[k] - 1;
+        T.f_li[1 * 64 + i] = k == 0 ? i : lane_of[I.parent];
+        T.f_li[2 * 64 + i] = i >= size[k] ? i - size[k] : i;
         T.f_li[3 * 64 + i] = I.jidx;
         T.f_li[4 * 64 + i] = I.sph_count;
         T.f_li[5 * 64 + i] = I.revolute;
         T.f_li[6 * 64 + i] = I.fR_identity;
+        if (i >= size[k]) T.f_branched = 1;
         for (int c = 0; c < 3; ++c) T.f_lf[(0 + c) * 64 + i] = F.axis[c];
         for (int c = 0; c < 9; ++c) T.f_lf[(3 + c) * 64 + i] = k == 0 ? (c % 4 == 0 ? 1.0f : 0.0f) : F.fR[c];
         for (int c = 0; c < 3; ++c) T.f_lf[(12 + c) * 64 + i] = k == 0 ? 0.0f : F.fp[c];
@@ -215,7 +252,7 @@ void build_fused(Tables &T) {
     // lanes past the robot: an empty massless link with no parent and no joint
     for (int i = L; i < 64; ++i) {
         T.f_li[0 * 64 + i] = -1;
-        T.f_li[1 * 64 + i] = -1;
+        T.f_li[1 * 64 + i] = i;
         T.f_li[2 * 64 + i] = i;
         T.f_li[3 * 64 + i] = -1;
         T.f_li[6 * 64 + i] = 1;
@@ -642,6 +679,7 @@ int wb_robot_create(const wb_robot_desc *desc, wb_robot **out) {
     Fz.mimic = T.f_mimic;
     Fz.mc = T.f_mc;
     Fz.conn = reinterpret_cast<const int32_t *>(base + o_fc);
+    Fz.branched = T.f_branched;
     wb::DevKin &Kn = r->kin;
     Kn.L = T.L; Kn.n = T.n; Kn.G = T.kin_G; Kn.jsteps = T.kin_jsteps; Kn.mc = T.kin_mc;
     Kn.inv_mass = T.total_mass > 0.0 ? (float)(1.0 / T.total_mass) : 0.0f;
@@ -727,6 +765,12 @@ int wb_fk(const wb_robot *robot, int64_t B, int64_t ld, const float *q, float *l
     return finish(wb::launch_fk(robot->dev, B, ld, q, link_pose, spheres, stream), "wb_fk launch");
 }
 
+namespace {
+// RNEA's cache moves through tiles of 16 states from one such tile per
+// compute unit on.
+bool cache_tiled(const wb_robot *r, int64_t B) { return B >= (int64_t)16 * r->cus; }
+}  // namespace
+
 int wb_rnea(const wb_robot *robot, int64_t B, int64_t ld, const float *q, const float *qd, const float *qdd,
             const float *f_ext, float *tau, float *cache, hipStream_t stream) {
     WB_TRY(check_robot(robot));
@@ -740,11 +784,12 @@ int wb_rnea(const wb_robot *robot, int64_t B, int64_t ld, const float *q, const 
     WB_TRY(check_ptr(f_ext, "f_ext", false));
     WB_TRY(check_ptr(tau, "tau", need));
     WB_TRY(check_ptr(cache, "cache", false));
-    if (cache)
-        return finish(wb::launch_rnea(robot->dev, B, ld, q, qd, qdd, f_ext, tau, cache, stream), "wb_rnea launch");
-    if (!robot->T.lanes)
+    if (!robot->T.lanes && !cache)
         return fail(WB_ERR_UNSUPPORTED, "a robot of %d links (more than 64) needs the cache", robot->T.L);
-    return finish(wb::launch_rnea_lanes(robot->dev, robot->fz, B, ld, q, qd, qdd, f_ext, tau, stream),
+    if (!robot->T.lanes)
+        return finish(wb::launch_rnea(robot->dev, B, ld, q, qd, qdd, f_ext, tau, cache, stream), "wb_rnea launch");
+    return finish(wb::launch_rnea_lanes(robot->dev, robot->fz, B, ld, q, qd, qdd, f_ext, tau, cache,
+                                        cache_tiled(robot, B), stream),
                   "wb_rnea launch");
 }
 
@@ -844,15 +889,13 @@ int wb_rnea_backward(const wb_robot *robot, int64_t B, int64_t ld, const float *
     WB_TRY(check_ptr(g_qd, "g_qd", need));
     WB_TRY(check_ptr(g_qdd, "g_qdd", need));
     WB_TRY(check_ptr(g_fext, "g_fext", false));
-    if (!cache) {
-        if (!robot->T.lanes)
-            return fail(WB_ERR_UNSUPPORTED, "a robot of %d links (more than 64) needs the cache", robot->T.L);
-        WB_TRY(check_ptr(workspace, "workspace", false));
-        return finish(wb::launch_rnea_backward_lanes(robot->dev, robot->fz, B, ld, q, qd, qdd, f_ext, g_tau, g_q,
-                                                     g_qd, g_qdd, g_fext, stream),
+    if (!robot->T.lanes && !cache)
+        return fail(WB_ERR_UNSUPPORTED, "a robot of %d links (more than 64) needs the cache", robot->T.L);
+    WB_TRY(check_ptr(workspace, "workspace", cache != nullptr));
+    if (robot->T.lanes)
+        return finish(wb::launch_rnea_backward_lanes(robot->dev, robot->fz, B, ld, q, qd, qdd, f_ext, cache, g_tau,
+                                                     g_q, g_qd, g_qdd, g_fext, cache_tiled(robot, B), stream),
                       "wb_rnea_backward launch");
-    }
-    WB_TRY(check_ptr(workspace, "workspace", true));
     return finish(wb::launch_rnea_backward(robot->dev, B, ld, q, qd, qdd, cache, g_tau, g_q, g_qd, g_qdd, g_fext,
                                            static_cast<float *>(workspace), stream),
                   "wb_rnea_backward launch");

@@ -56,9 +56,11 @@ struct DevRobot {
 };
 
 // Per-lane tables of the fused kernel: lane i holds link perm[i] in
-// depth-first pre-order.  Structure of arrays, 64 entries per field.
-//   li[f*64 + i]: f = 0 link, 1 parent lane (-1 root), 2 last lane of the
-//                 subtree, 3 joint index (-1 fixed), 4 sphere count,
+// depth-first post-order, so the subtree of lane i is a lane range that ends
+// at i.  Structure of arrays, 64 entries per field.
+//   li[f*64 + i]: f = 0 link, 1 parent lane (own lane: the root), 2 the lane
+//                 before the subtree's first (own lane: the subtree starts
+//                 at lane 0), 3 joint index (-1 fixed), 4 sphere count,
 //                 5 revolute, 6 fixed rotation is the identity
 //   lf[f*64 + i]: f = 0..2 axis, 3..11 fixed R, 12..14 fixed p, 15 mass,
 //                 16..18 CoM, 19..24 inertia (xx yy zz xy xz yz),
@@ -68,13 +70,14 @@ struct DevRobot {
 //   lsph[j*64 + i]: local centre and radius of the link's j-th sphere
 //   conn[k*64 + j]: lane of the k-th link that joint j drives, -1 past the
 //                 end of the list (read only when mimic is set)
-// Lanes past the last link hold an empty link: link -1, parent -1, subtree
-// end i, no joint, no spheres, identity fixed rotation, zero mass.
+// Lanes past the last link hold an empty link: link -1, their own parent, no
+// joint, no spheres, identity fixed rotation, zero mass.
 struct DevFused {
     int32_t supported;   // L <= 64 and the sweep tables fit the LDS budget
     int32_t jsteps;      // pointer-jumping steps, ceil(log2(max_depth + 1))
     int32_t mimic;       // some joint drives several links, or a multiplier != 1 or offset != 0
     int32_t mc;          // longest connectedLinks list
+    int32_t branched;    // some subtree does not start at lane 0 (not a serial chain)
     const int32_t *__restrict__ li;
     const float *__restrict__ lf;
     const float4 *__restrict__ lsph;
@@ -167,14 +170,16 @@ hipError_t launch_rnea(const DevRobot &rb, int64_t B, int64_t ld, const float *q
 hipError_t launch_rnea_backward(const DevRobot &rb, int64_t B, int64_t ld, const float *q, const float *qd,
                                 const float *qdd, const float *cache, const float *g_tau,
                                 float *g_q, float *g_qd, float *g_qdd, float *g_fext, float *ws, hipStream_t s);
-// Group-per-state RNEA and VJP without a cache (tree_kernels.hip); robots of
-// at most 64 links.
+// Group-per-state RNEA and VJP (tree_kernels.hip), robots of at most 64
+// links; cache may be null (nothing is then stored or read).  tiled: the
+// cache moves through LDS tiles of 16 states.
 hipError_t launch_rnea_lanes(const DevRobot &rb, const DevFused &fz, int64_t B, int64_t ld, const float *q,
-                             const float *qd, const float *qdd, const float *f_ext, float *tau, hipStream_t s);
+                             const float *qd, const float *qdd, const float *f_ext, float *tau, float *cache, bool tiled,
+                             hipStream_t s);
 hipError_t launch_rnea_backward_lanes(const DevRobot &rb, const DevFused &fz, int64_t B, int64_t ld,
                                       const float *q, const float *qd, const float *qdd, const float *f_ext,
-                                      const float *g_tau, float *g_q, float *g_qd, float *g_qdd, float *g_fext,
-                                      hipStream_t s);
+                                      const float *cache, const float *g_tau, float *g_q, float *g_qd, float *g_qdd,
+                                      float *g_fext, bool tiled, hipStream_t s);
 // split: one state per workgroup with its pairs over the four wavefronts
 // (else one state per wavefront).
 // Group-per-state FK adjoint from sphere and/or pose gradients (dense

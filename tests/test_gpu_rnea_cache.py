@@ -1,0 +1,105 @@
+"""GPU: RNEA and its VJP through the forward cache, one group of lanes per
+state, against the FP64 oracle at the edges of its forms: the lane counts
+(16, 17, 32, 33 and 64 links), batches on both sides of the tiled form's
+threshold (16 states per compute unit) that end inside a tile, one state,
+external forces, mimic joints and padded rows; and the cache itself, each
+link's velocity, acceleration and force in link coordinates."""
+import numpy as np
+import pytest
+import torch
+
+from paper_2603_05493_amd import synth
+from tests import parity as P
+
+pytestmark = pytest.mark.gpu
+
+
+def _mimic():
+    rb = synth.random_tree(9, 3, seed=31, random_fixed_rotation=True)
+    rb.joint_index = np.array([-1, 0, 1, 1, 2, 3, 4, 5, 5, 6], dtype=np.int32)
+    rb.joint_mult = synth._f32([1.0, 1.0, 1.0, -0.5, 1.0, 2.0, 1.0, 1.0, 0.75, 1.0])
+    rb.joint_offset = synth._f32([0.0, 0.0, 0.1, 0.25, 0.0, 0.0, -0.2, 0.0, 0.0, 0.0])
+    return rb
+
+
+ROBOTS = [("chain1", lambda: synth.serial_chain(1, 1, seed=2)), ("tree16", lambda: synth.random_tree(15, 2, seed=4)),
+          ("tree17", lambda: synth.random_tree(16, 2, seed=5)), ("chain32", lambda: synth.serial_chain(31, 1, seed=6)),
+          ("tree33", lambda: synth.random_tree(32, 1, seed=7)), ("tree64", lambda: synth.random_tree(63, 1, seed=8)),
+          ("mimic9", _mimic)]
+
+
+@pytest.mark.parametrize("label,factory", ROBOTS)
+@pytest.mark.parametrize("size", ["one", "below", "tiled"])
+@pytest.mark.parametrize("forces", [False, True])
+def test_cached_rnea_forms(oracle, label, factory, size, forces):
+    from paper_2603_05493_amd import wb
+    rb = factory()
+    r = wb.Robot(rb).to_device("cuda:0")
+    full = 16 * torch.cuda.get_device_properties(0).multi_processor_count
+    B = {"one": 1, "below": 203, "tiled": full + 5}[size]
+    ld = B + 3
+    n, L = rb.n_dof, rb.n_links
+    st = synth.states(rb, B, seed=6, q_range=1.5)
+    pad = lambda a: torch.nn.functional.pad(P.dev(a), (0, ld - B), value=float("nan")).contiguous()
+    q, qd, qdd = pad(st.q), pad(st.qd), pad(st.qdd)
+    fe = fe_d = g_fext = None
+    if forces:
+        fe = synth._f32(np.random.default_rng(7).normal(scale=2.0, size=(B, L, 6)))
+        fe_d = pad(fe)
+        g_fext = torch.full((L, 6, ld), float("nan"), device="cuda")
+    nan = lambda *s: torch.full((*s, ld), float("nan"), device="cuda")
+    tau, cache = wb.wb_rnea(r, q, qd, qdd, tau=nan(n), cache=nan(L, 18), f_ext=fe_d, nb=B)
+    w = synth.weights((B, n), seed=8)
+    gq, gqd, gqdd = wb.wb_rnea_backward(r, q, qd, qdd, cache, pad(w), nan(n), nan(n), nan(n), g_fext=g_fext, nb=B)
+    torch.cuda.synchronize()
+    pick = np.unique(np.concatenate([np.arange(min(B, 24)), np.arange(max(0, B - 24), B)]))   # both ends
+    sub = lambda t: P.host(t[..., :B])[pick]
+    args = (rb, st.q[pick], st.qd[pick], st.qdd[pick])
+    fes = None if fe is None else fe[pick]
+    ref = dict(tau=oracle.rnea(*args, fes))
+    ref["g_q"], ref["g_qd"], ref["g_qdd"], ref["g_fext"] = oracle.rnea_vjp(*args, w[pick], fext=fes, want_fext=True)
+    got = dict(tau=tau, g_q=gq, g_qd=gqd, g_qdd=gqdd)
+    if forces:
+        got["g_fext"] = g_fext
+    for k, t in got.items():
+        assert torch.isnan(t[..., B:]).all(), f"{label} {k}: padding written"
+        assert torch.isfinite(t[..., :B]).all(), f"{label} {k}: not written"
+        assert P.normwise(sub(t), ref[k], floor=1e-3 if k == "tau" else 1e-6).max() < P.TOL, (label, k)
+    # the cache: the recursion of Alg. 4 in link coordinates, from the oracle's poses
+    R, p, _ = oracle.fk(rb, st.q[pick])
+    c = sub(cache).reshape(len(pick), L, 3, 6)
+    v, a = np.zeros((len(pick), L, 6)), np.zeros((len(pick), L, 6))
+    a[:, 0, 3:] = -np.asarray(rb.gravity)
+    F = np.zeros((len(pick), L, 6))
+    for k in range(1, L):
+        par, j = int(rb.parent[k]), int(rb.joint_index[k])
+        E = np.einsum("bji,bjk->bik", R[:, k], R[:, par])   # parent -> link
+        o = np.einsum("bji,bj->bi", R[:, par], p[:, k] - p[:, par])
+        for x in (v, a):
+            x[:, k, :3] = np.einsum("bij,bj->bi", E, x[:, par, :3])
+            x[:, k, 3:] = np.einsum("bij,bj->bi", E, x[:, par, 3:] + np.cross(x[:, par, :3], o))
+        if j >= 0:
+            s = np.asarray(rb.axis[k])
+            sd = rb.joint_mult[k] * st.qd[pick][:, j, None] * s
+            v[:, k, :3] += sd
+            a[:, k, :3] += rb.joint_mult[k] * st.qdd[pick][:, j, None] * s + np.cross(v[:, k, :3], sd)
+            a[:, k, 3:] += np.cross(v[:, k, 3:], sd)
+
+        def inertia(u):
+            h = rb.mass[k] * (u[:, 3:] + np.cross(u[:, :3], rb.com[k]))
+            return np.concatenate([u[:, :3] @ np.asarray(rb.inertia[k]).T + np.cross(rb.com[k], h), h], 1)
+        f, Iv = inertia(a[:, k]), inertia(v[:, k])
+        f[:, :3] += np.cross(v[:, k, :3], Iv[:, :3]) + np.cross(v[:, k, 3:], Iv[:, 3:])
+        f[:, 3:] += np.cross(v[:, k, :3], Iv[:, 3:])
+        F[:, k] = f if fe is None else f - fes[:, k]
+    for k in range(L - 1, 0, -1):
+        par = int(rb.parent[k])
+        if par > 0:
+            E = np.einsum("bji,bjk->bik", R[:, par], R[:, k])   # link -> parent
+            o = np.einsum("bji,bj->bi", R[:, par], p[:, k] - p[:, par])
+            f = np.einsum("bij,bj->bi", E, F[:, k, 3:])
+            F[:, par, :3] += np.einsum("bij,bj->bi", E, F[:, k, :3]) + np.cross(o, f)
+            F[:, par, 3:] += f
+    for i, x in enumerate((v, a, F)):
+        assert P.normwise(c[:, 1:, i], x[:, 1:], floor=1e-3).max() < P.TOL, (label, "vaF"[i])
+    assert torch.isnan(cache[..., B:]).all()
