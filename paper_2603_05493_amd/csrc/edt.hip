@@ -1,8 +1,7 @@
 // Exact Euclidean distance transform of a site grid (cuRoboV2 Sec. 5,
 // "Stage 2: Distance Propagation"): the nearest site of every voxel by
-// three separable axis passes, the PBA+ decomposition of the paper, with
-// Maurer's dominance test deciding the lower envelope of the distance
-// parabolas along a line.  Integer arithmetic throughout, so the result is
+// three separable axis passes, as the PBA+ decomposition of the paper, each
+// line's owners found by monotone search instead of an envelope stack.  Integer arithmetic throughout, so the result is
 // exact.
 //
 // Grid [nz][ny][nx], x fastest.  A site is stored packed as
@@ -17,10 +16,9 @@
 //      across chunks -> A (rows of a multiple of 4 voxels: 4 voxels per
 //      lane, in registers, one read and one write of the row);
 //   2. along y, a workgroup per tile of lines (x0 .. x0+TL-1, z) held in
-//      LDS: the lower envelope of the parabolas (y - y')^2 + (x - x*)^2 of
-//      the row sites, built band by band and merged at the band junctions
-//      as in PBA+, then every voxel assigned its envelope entry -> B;
-//   3. along z, the same on tiles (x0 .. x0+TL-1, y) with the parabolas
+//      LDS: every voxel's nearest of the row sites, by (y - y')^2 + (x - x*)^2
+//      -> B;
+//   3. along z, the same on tiles (x0 .. x0+TL-1, y) with the plane sites and
 //      (z - z')^2 + (x - x*)^2 + (y - y*)^2 -> the nearest site and
 //      voxel_size * sqrt(d2).
 // Each pass reads its input grid once and writes its output once.
@@ -178,12 +176,9 @@ __global__ void __launch_bounds__(256) k_edt_x4(const uint8_t *__restrict__ site
     }
 }
 
-// Positions along the line and squared cross offsets: AX == 1 runs along y
-// (a line (x, z); the candidate is the row's nearest site (x*, y', z)),
-// AX == 2 along z (a line (x, y); the candidate is the plane's nearest site
-// (x*, y*, z')).
-template <int AX>
-__device__ __forceinline__ int pos(int32_t c) { return AX == 1 ? cy(c) : cz(c); }
+// Squared offset across the line of a candidate c: AX == 1 runs along y (a
+// line (x, z); the candidate is the row's nearest site (x*, y', z)), AX == 2
+// along z (a line (x, y); the plane's nearest site (x*, y*, z')).
 template <int AX>
 __device__ __forceinline__ int height(int32_t c, int qx, int qy) {
     const int dx = qx - cx(c);
@@ -192,300 +187,157 @@ __device__ __forceinline__ int height(int32_t c, int qx, int qy) {
     return dx * dx + dy * dy;
 }
 
-// A candidate at line position u with squared cross offset h is kept as
-// (u, g = u^2 + h).  Maurer's test: with positions ua < ub < uc, b never
-// attains the minimum of the three parabolas (t - u)^2 + h when the a/b
-// crossing is not left of the b/c crossing.
-__device__ __forceinline__ bool dominated(int ua, int ga, int ub, int gb, int uc, int gc) {
-    return (int64_t)(gb - ga) * (uc - ub) >= (int64_t)(gc - gb) * (ub - ua);
-}
-
 // ---- passes 2 and 3: one workgroup per tile of TL lines (consecutive x)
-// at a fixed z (AX == 1) or y (AX == 2), the tile resident in LDS as
-// ent[p * TL + l] (position p, line l).  Phases, after PBA+'s banding:
-//   bands:  thread (l, b) stacks the envelope of band b of line l in place
-//           from the band's first position (256 / TL bands per line);
-//   trim:   thread (l, b) merges the envelopes of bands b - 1 and b alone,
-//           then of what is left of bands b - 2 and b.  An entry off such a
-//           pair's envelope is off the line's envelope too, so the trimmed
-//           prefix of band b and suffix of the other band go; every
-//           junction of a round is trimmed at once;
-//   merge:  thread l merges the trimmed bands left to right.  Only the
-//           junctions change, so each band keeps a range [lo, hi) of its
-//           stack: popping the envelope's last entry shortens its band's
-//           range, dropping a band's first entry raises lo; nothing moves;
-//   pack:   thread (l, b) moves band b's surviving range down, so the
-//           line's envelope ends up packed at positions [0, K);
-//   assign: thread (l, s) takes segment s of line l: a binary search finds
-//           the envelope entry owning the segment's first voxel, a walk the
-//           rest, and the segment is written to the next pass's grid (and
-//           the distances after the last pass).
-template <int AX, int TL>
-__global__ void __launch_bounds__(256) k_edt_tile(const int32_t *__restrict__ in, int32_t *__restrict__ out,
-                                                  float *__restrict__ dist, float voxel_size, int nx, int ny,
-                                                  int nz) {
-    extern __shared__ int32_t ent[];
-    constexpr int NB = 256 / TL;   // bands (and assignment segments) per line
-    __shared__ int32_t bcnt[256], blo[256], bhi[256], boff[256], ksz[TL];
+// at a fixed z (AX == 1) or y (AX == 2).  The owner of position s is the
+// candidate p with the least (s - p)^2 + h_p, the last one where several
+// tie.  Both rules are one unsigned comparison of keys
+//   ((s - p)^2 + h_p) << 10 | (1023 - p)
+// (values below 2^22: h_p <= 2 * 1023^2, and an empty position's EMPTY_H
+// exceeds every real value, so it owns only where the line is empty), so LDS
+// holds h_p << 10 | (1023 - p) and a candidate costs one 24-bit multiply-add
+// and one minimum.  Owners never decrease along the line, so they are found
+// by halving: the owner of a position lies between those of its solved
+// neighbours.  A stretch of candidates between them is searched by blocks of
+// eight, each skipped where its least key at its least distance exceeds the
+// best so far: a jump over candidates that own nothing costs one bound per
+// eight of them.  The coarse levels, whose positions end the threads' 16-
+// position segments, synchronize the workgroup; inside its segment (l, j)
+// each thread goes on alone.  What bounds it is the issue of these searches
+// (about 230 VALU instructions a solved position for 64 lanes of different
+// jumps, 24.5 M and 37.5 M a pass; without the block bounds a wavefront of
+// the room's y pass takes 720 candidate steps a segment, 2,900 at worst,
+// with them 41 blocks, 79 at worst).  Room of 256 x 256 x 128: y pass 73 us,
+// z pass 74 us; the form before, an envelope stack per band and a merge
+// whose slowest tile set the time, 85 and 78 us.  The owners' packed sites
+// are read again from the input grid, rows the workgroup has just read.
+constexpr uint32_t EMPTY_H = 3 * 1023 * 1023 + 1;
+constexpr int EDT_BLK = 8;   // candidates under one bound
+
+// LDS of a line: its keys, padded to whole groups of four blocks and four
+// words apart in banks, one least key per block, and the owners.
+__host__ __device__ constexpr int edt_padded(int n) { return (n + 31) & ~31; }
+__host__ __device__ constexpr int edt_key_pitch(int n) { return edt_padded(n) + 4; }
+__host__ __device__ constexpr int edt_min_pitch(int n) { return edt_padded(n) / EDT_BLK + 4; }
+
+template <int AX, int TL, int NT, typename Own>
+__global__ void __launch_bounds__(NT) k_edt_tile(const int32_t *__restrict__ in, int32_t *__restrict__ out,
+                                                 float *__restrict__ dist, float voxel_size, int nx, int ny,
+                                                 int nz) {
+    extern __shared__ uint4 lds4[];
+    constexpr int NB = NT / TL;   // segments per line (a power of two)
     const int n = AX == 1 ? ny : nz;
+    const int kp = edt_key_pitch(n), mp = edt_min_pitch(n);
+    const int l = threadIdx.x % TL, seg = threadIdx.x / TL;
+    uint32_t *keys = reinterpret_cast<uint32_t *>(lds4), *key = keys + l * kp;   // this thread's line
+    uint32_t *mins = keys + TL * kp, *least = mins + l * mp;
+    Own *own = reinterpret_cast<Own *>(mins + TL * mp) + l;                       // [n][TL]
     const int ntx = (nx + TL - 1) / TL;
-    const int x0 = (int)(blockIdx.x % ntx) * TL;
     const int o = (int)(blockIdx.x / ntx);   // z for AX == 1, y for AX == 2
+    const int x = (int)(blockIdx.x % ntx) * TL + l;
     // element p of line x: AX == 1 (x, p, o), AX == 2 (x, o, p)
-    auto gidx = [&](int p, int x) -> uint32_t {
+    auto gidx = [&](int p) -> uint32_t {
         return AX == 1 ? ((uint32_t)o * ny + p) * nx + x : ((uint32_t)p * ny + o) * nx + x;
     };
-    // the tile into LDS, eight loads in flight per thread
-    for (int i0 = threadIdx.x; i0 < n * TL; i0 += 256 * 8) {
-        int32_t v[8];
+    // the tile into LDS, one block per thread and trip
+    for (int p0 = seg * EDT_BLK; p0 < edt_padded(n); p0 += NB * EDT_BLK) {
+        int32_t v[EDT_BLK];
+        uint32_t k[EDT_BLK];
 #pragma unroll
-        for (int j = 0; j < 8; ++j) {
-            const int i = i0 + 256 * j;
-            const int p = i / TL, x = x0 + (i - p * TL);
-            v[j] = i < n * TL && x < nx ? in[gidx(p, x)] : EDT_NONE;
+        for (int j = 0; j < EDT_BLK; ++j) v[j] = p0 + j < n && x < nx ? in[gidx(p0 + j)] : EDT_NONE;
+#pragma unroll
+        for (int j = 0; j < EDT_BLK; ++j)
+            k[j] = ((v[j] < 0 ? EMPTY_H : (uint32_t)height<AX>(v[j], x, o)) << 10) | (uint32_t)(1023 - (p0 + j));
+        uint32_t m = k[0];
+#pragma unroll
+        for (int j = 1; j < EDT_BLK; ++j) m = min(m, k[j]);
+        *reinterpret_cast<uint4 *>(key + p0) = make_uint4(k[0], k[1], k[2], k[3]);
+        *reinterpret_cast<uint4 *>(key + p0 + 4) = make_uint4(k[4], k[5], k[6], k[7]);
+        least[p0 / EDT_BLK] = m;
+    }
+    __syncthreads();
+    // the square of a distance given in 32nds, in key units
+    auto sq = [](int d32) -> uint32_t { return (uint32_t)__mul24(d32, d32); };
+    // the owner of s, which lies in [a, b]
+    auto solve = [&](int s, int a, int b) -> int {
+        const int s32 = s * 32;
+        uint32_t best = min(key[s], min(key[a] + sq(s32 - a * 32), key[b] + sq(b * 32 - s32)));
+        if (b - a > 1) {
+            // the open interval's blocks, no farther than the best value's distance (the root rounded up)
+            const int r = min((int)__builtin_amdgcn_sqrtf((float)(best >> 10)) + 1, n);
+            const unsigned b0 = (unsigned)max(a + 1, s - r) / EDT_BLK, b1 = (unsigned)min(b - 1, s + r) / EDT_BLK;
+            for (unsigned g = b0 & ~3u; g <= b1; g += 4) {   // four blocks at a time
+                const uint4 m4 = *reinterpret_cast<const uint4 *>(least + g);
+                const uint32_t m[4] = {m4.x, m4.y, m4.z, m4.w};
+                const int d = (int)(g * (32 * EDT_BLK)) - s32;
+                unsigned todo = 0;
+#pragma unroll
+                for (int j = 0; j < 4; ++j) {
+                    const int dj = d + j * 32 * EDT_BLK;
+                    todo |= m[j] + sq(max(0, max(dj, -32 * (EDT_BLK - 1) - dj))) <= best ? 1u << j : 0u;
+                }
+                todo &= (15u << max((int)(b0 - g), 0)) & (15u >> max((int)(g + 3 - b1), 0));
+                while (todo) {
+                    const unsigned blk = g + __builtin_ctz(todo);
+                    todo &= todo - 1;
+                    const uint4 *kb = reinterpret_cast<const uint4 *>(key + blk * EDT_BLK);
+                    const uint4 u = kb[0], w = kb[1];
+                    const int e = (int)(blk * (32 * EDT_BLK)) - s32;
+                    best = min(best, min(min(min(u.x + sq(e), u.y + sq(e + 32)), min(u.z + sq(e + 64), u.w + sq(e + 96))),
+                                         min(min(w.x + sq(e + 128), w.y + sq(e + 160)), min(w.z + sq(e + 192), w.w + sq(e + 224)))));
+                }
+            }
         }
+        return 1023 - (int)(best & 1023);
+    };
+    const int bw = (n + NB - 1) / NB, t0 = seg * bw, t1 = min(t0 + bw, n);
+    // ---- the segments' last positions: level st solves every second multiple of st segments
+    for (int st = NB; st > 0; st >>= 1) {
+        if (t0 < t1 && (seg + 1) % (2 * st) == st) {
+            const int lo = (seg + 1 - st) * bw, hi = (seg + 1 + st) * bw;   // the ends of the solved neighbours
+            own[(t1 - 1) * TL] = (Own)solve(t1 - 1, lo > 0 ? own[(lo - 1) * TL] : 0, hi <= n ? own[(hi - 1) * TL] : n - 1);
+        }
+        __syncthreads();
+    }
+    if (t0 >= t1 || x >= nx) return;
+    // ---- inside the segment
+    const int first = t0 > 0 ? own[(t0 - 1) * TL] : 0, last = own[(t1 - 1) * TL];
+    for (int st = 8; st > 0; st >>= 1)
+        for (int s = t0 + st - 1; s < t1 - 1; s += 2 * st)
+            own[s * TL] = (Own)solve(s, s - st < t0 ? first : own[(s - st) * TL], s + st >= t1 - 1 ? last : own[(s + st) * TL]);
+    // ---- output, eight gathers in flight per thread
+    for (int s0 = t0; s0 < t1; s0 += 8) {
+        int32_t c[8];
 #pragma unroll
         for (int j = 0; j < 8; ++j)
-            if (i0 + 256 * j < n * TL) ent[i0 + 256 * j] = v[j];
-    }
-    __syncthreads();
-    const int l = threadIdx.x % TL, sidx = threadIdx.x / TL;
-    const int qx = x0 + l, qy = o;
-    const int bw = (n + NB - 1) / NB;
-    // ---- bands
-    {
-        const int p0 = sidx * bw, p1 = min(p0 + bw, n);
-        int k = 0, u1 = 0, g1 = 0, u2 = 0, g2 = 0;
-        for (int p = p0; p < p1; ++p) {
-            const int32_t c = ent[p * TL + l];
-            if (c < 0) continue;
-            const int gc = p * p + height<AX>(c, qx, qy);   // a candidate sits at its own position
-            while (k >= 2 && dominated(u2, g2, u1, g1, p, gc)) {
-                --k;
-                u1 = u2;
-                g1 = g2;
-                if (k >= 2) {
-                    const int32_t e = ent[(p0 + k - 2) * TL + l];
-                    u2 = pos<AX>(e);
-                    g2 = u2 * u2 + height<AX>(e, qx, qy);
-                }
-            }
-            ent[(p0 + k) * TL + l] = c;   // p0 + k <= p: that input is consumed
-            ++k;
-            u2 = u1;
-            g2 = g1;
-            u1 = p;
-            g1 = gc;
-        }
-        bcnt[sidx * TL + l] = k;
-    }
-    __syncthreads();
-    auto ug = [&](int b, int i, int &u, int &gg) {   // entry i of band b's stack
-        const int32_t c = ent[(b * bw + i) * TL + l];
-        u = pos<AX>(c);
-        gg = u * u + height<AX>(c, qx, qy);
-    };
-    // Trim the junction of band ba's range [la, ha) and band bb's range
-    // [lb, hb) (ba < bb) from those two ranges alone: the new end of ba's
-    // range and the new start of bb's.
-    auto trim = [&](int ba, int la, int ha, int bb, int lb, int hb, int &nha, int &nlb) {
-        int lo = lb, hi = ha;
-        if (ha > la && hb > lb) {
-            int u1, g1, u2 = 0, g2 = 0;   // last and second-to-last kept entries of band ba
-            ug(ba, hi - 1, u1, g1);
-            if (hi - la >= 2) ug(ba, hi - 2, u2, g2);
-            while (lo < hb) {
-                int uc, gc;
-                ug(bb, lo, uc, gc);
-                while (hi - la >= 2 && dominated(u2, g2, u1, g1, uc, gc)) {
-                    --hi;
-                    u1 = u2;
-                    g1 = g2;
-                    if (hi - la >= 2) ug(ba, hi - 2, u2, g2);
-                }
-                if (lo + 1 < hb) {
-                    int un, gn;
-                    ug(bb, lo + 1, un, gn);
-                    if (dominated(u1, g1, uc, gc, un, gn)) {
-                        ++lo;
-                        continue;
-                    }
-                }
-                break;
-            }
-        }
-        nha = hi;
-        nlb = lo;
-    };
-    // ---- trim, round 1: bands b - 1 and b, from the two stacks alone
-    {
-        const int b = sidx;
-        int hi = b > 0 ? bcnt[(b - 1) * TL + l] : 0, lo = 0;
-        const int cb = bcnt[b * TL + l];
-        if (b > 0) trim(b - 1, 0, hi, b, 0, cb, hi, lo);
-        blo[b * TL + l] = lo;
-        if (b > 0) bhi[(b - 1) * TL + l] = hi;
-        if (b == NB - 1) bhi[b * TL + l] = cb;
-    }
-    __syncthreads();
-    // ---- trim, round 2: bands b - 2 and b, from their trimmed ranges (each
-    // range end has one writer; every thread reads its ranges first)
-    {
-        const int b = sidx;
-        int la = 0, ha = 0, lb = 0, hb = 0;
-        if (b >= 2) {
-            la = blo[(b - 2) * TL + l];
-            ha = bhi[(b - 2) * TL + l];
-            lb = blo[b * TL + l];
-            hb = bhi[b * TL + l];
-        }
-        __syncthreads();
-        if (b >= 2) {
-            int nha, nlb;
-            trim(b - 2, la, ha, b, lb, hb, nha, nlb);
-            bhi[(b - 2) * TL + l] = nha;
-            blo[b * TL + l] = nlb;
-        }
-    }
-    __syncthreads();
-    // ---- merge: the junctions of the trimmed ranges only
-    if (threadIdx.x < TL) {
-        // the envelope's last (b1, i1) and second-to-last (b2, i2) entries
-        int K = 0, b1 = 0, i1 = 0, u1 = 0, g1 = 0, b2 = 0, i2 = 0, u2 = 0, g2 = 0;
-        for (int b = 0; b < NB; ++b) {
-            int lo = blo[b * TL + l];
-            const int cb = max(bhi[b * TL + l], lo);
-            while (lo < cb) {
-                int uc, gc;
-                ug(b, lo, uc, gc);
-                while (K >= 2 && dominated(u2, g2, u1, g1, uc, gc)) {
-                    bhi[b1 * TL + l] = i1;   // the last entry of band b1's range goes
-                    --K;
-                    b1 = b2;
-                    i1 = i2;
-                    u1 = u2;
-                    g1 = g2;
-                    if (K >= 2) {   // the entry before (b1, i1), in b1 or the last non-empty band before it
-                        if (i1 > blo[b1 * TL + l]) {
-                            b2 = b1;
-                            i2 = i1 - 1;
-                        } else {
-                            int bb = b1 - 1;
-                            while (blo[bb * TL + l] >= bhi[bb * TL + l]) --bb;
-                            b2 = bb;
-                            i2 = bhi[bb * TL + l] - 1;
-                        }
-                        ug(b2, i2, u2, g2);
-                    }
-                }
-                if (K >= 1 && lo + 1 < cb) {
-                    int un, gn;
-                    ug(b, lo + 1, un, gn);
-                    if (dominated(u1, g1, uc, gc, un, gn)) {
-                        ++lo;
-                        continue;
-                    }
-                }
-                break;
-            }
-            blo[b * TL + l] = lo;
-            bhi[b * TL + l] = cb;
-            const int m = cb - lo;
-            if (m >= 2) {
-                b2 = b;
-                i2 = cb - 2;
-                ug(b, i2, u2, g2);
-                b1 = b;
-                i1 = cb - 1;
-                ug(b, i1, u1, g1);
-            } else if (m == 1) {
-                b2 = b1;
-                i2 = i1;
-                u2 = u1;
-                g2 = g1;
-                b1 = b;
-                i1 = lo;
-                ug(b, lo, u1, g1);
-            }
-            K += m;
-        }
-        int off = 0;
-        for (int b = 0; b < NB; ++b) {
-            boff[b * TL + l] = off;
-            off += max(bhi[b * TL + l] - blo[b * TL + l], 0);
-        }
-        ksz[l] = off;
-    }
-    __syncthreads();
-    // ---- pack: thread (l, b) moves band b's range to its place in the
-    // packed envelope [0, K) through registers (a range holds at most
-    // bw <= 32 entries), so no thread overwrites a range still being read.
-    {
-        const int lo = blo[sidx * TL + l], cnt = bhi[sidx * TL + l] - lo, dst = boff[sidx * TL + l];
-        const int src = sidx * bw + lo;
-        int32_t v[32];
+            if (s0 + j < t1) c[j] = in[gidx(own[(s0 + j) * TL])];
 #pragma unroll
-        for (int j = 0; j < 32; ++j)
-            if (j < cnt) v[j] = ent[(src + j) * TL + l];
-        __syncthreads();
-#pragma unroll
-        for (int j = 0; j < 32; ++j)
-            if (j < cnt) ent[(dst + j) * TL + l] = v[j];
-    }
-    __syncthreads();
-    // ---- assign
-    const int x = x0 + l;
-    if (x >= nx) return;
-    const int K = ksz[l];
-    const int t0 = sidx * bw, t1 = min(t0 + bw, n);
-    if (t0 >= t1) return;
-    if (K == 0) {
-        for (int s = t0; s < t1; ++s) {
-            out[gidx(s, x)] = EDT_NONE;
-            if (dist) dist[gidx(s, x)] = INFINITY;
-        }
-        return;
-    }
-    auto entry = [&](int i) { return ent[i * TL + l]; };
-    auto f = [&](int32_t c, int s) {
-        const int d = s - pos<AX>(c);
-        return d * d + height<AX>(c, qx, qy);
-    };
-    int lo = 0, hi = K - 1;   // the first entry i with f(i + 1, t0) > f(i, t0) owns t0
-    while (lo < hi) {
-        const int mid = (lo + hi) >> 1;
-        if (f(entry(mid + 1), t0) <= f(entry(mid), t0)) lo = mid + 1;
-        else hi = mid;
-    }
-    int ptr = lo;
-    int32_t cur = entry(ptr);
-    int32_t nxt = ptr + 1 < K ? entry(ptr + 1) : cur;
-    for (int s = t0; s < t1; ++s) {
-        while (ptr + 1 < K && f(nxt, s) <= f(cur, s)) {
-            ++ptr;
-            cur = nxt;
-            nxt = ptr + 1 < K ? entry(ptr + 1) : cur;
-        }
-        out[gidx(s, x)] = cur;
-        if (dist) dist[gidx(s, x)] = voxel_size * sqrtf((float)f(cur, s));
+        for (int j = 0; j < 8; ++j)
+            if (s0 + j < t1) {
+                const int s = s0 + j, p = own[s * TL];
+                out[gidx(s)] = c[j];
+                if (dist) dist[gidx(s)] = c[j] < 0 ? INFINITY : voxel_size * sqrtf((float)((key[p] + sq((s - p) * 32)) >> 10));
+            }
     }
 }
 
-// Tiles of TL lines with TL * n * 4 bytes of LDS at most 32 KB: 32 lines
-// up to n = 256, 16 up to 512, 8 up to 1024.
-template <int AX>
-bool tile_pass(const int32_t *in, int32_t *out, float *dist, float voxel_size, int nx, int ny, int nz, hipStream_t s) {
+template <int AX, int TL, int NT, typename Own>
+void launch_tile(const int32_t *in, int32_t *out, float *dist, float voxel_size, int nx, int ny, int nz, hipStream_t s) {
     const int n = AX == 1 ? ny : nz, o_n = AX == 1 ? nz : ny;
-    const int tl = n <= 256 ? 32 : (n <= 512 ? 16 : 8);
-    const dim3 grid((unsigned)(((nx + tl - 1) / tl) * (int64_t)o_n));
-    const size_t lds = (size_t)n * tl * 4;
-    switch (tl) {
-        case 32: hipLaunchKernelGGL((k_edt_tile<AX, 32>), grid, dim3(256), lds, s, in, out, dist, voxel_size, nx, ny, nz); break;
-        case 16: hipLaunchKernelGGL((k_edt_tile<AX, 16>), grid, dim3(256), lds, s, in, out, dist, voxel_size, nx, ny, nz); break;
-        case 8: hipLaunchKernelGGL((k_edt_tile<AX, 8>), grid, dim3(256), lds, s, in, out, dist, voxel_size, nx, ny, nz); break;
-        default: return false;
-    }
-    return true;
+    const dim3 grid((unsigned)(((nx + TL - 1) / TL) * (int64_t)o_n));
+    const size_t lds = (size_t)TL * (4 * (edt_key_pitch(n) + edt_min_pitch(n)) + n * sizeof(Own));
+    hipLaunchKernelGGL((k_edt_tile<AX, TL, NT, Own>), grid, dim3(NT), lds, s, in, out, dist, voxel_size, nx, ny, nz);
+}
+
+// Segments of at most 16 positions; lines per tile so that the LDS stays
+// within 48 KB (32 lines up to n = 256, 16 up to 512, 8 up to 1024), an
+// owner one byte up to n = 256 and two above.
+template <int AX>
+void tile_pass(const int32_t *in, int32_t *out, float *dist, float voxel_size, int nx, int ny, int nz, hipStream_t s) {
+    const int n = AX == 1 ? ny : nz;
+    if (n <= 128) launch_tile<AX, 32, 256, uint8_t>(in, out, dist, voxel_size, nx, ny, nz, s);
+    else if (n <= 256) launch_tile<AX, 32, 512, uint8_t>(in, out, dist, voxel_size, nx, ny, nz, s);
+    else if (n <= 512) launch_tile<AX, 16, 512, uint16_t>(in, out, dist, voxel_size, nx, ny, nz, s);
+    else launch_tile<AX, 8, 512, uint16_t>(in, out, dist, voxel_size, nx, ny, nz, s);
 }
 
 }  // namespace
@@ -505,8 +357,8 @@ hipError_t launch_edt(int nx, int ny, int nz, const uint8_t *sites, float voxel_
         hipLaunchKernelGGL(k_edt_x4<3>, xgrid, dim3(256), 0, s, sites, A, nx, ny, nz);
     else
         hipLaunchKernelGGL(k_edt_x4<4>, xgrid, dim3(256), 0, s, sites, A, nx, ny, nz);
-    if (!tile_pass<1>(A, B, nullptr, voxel_size, nx, ny, nz, s)) return hipErrorInvalidValue;
-    if (!tile_pass<2>(B, nearest, dist, voxel_size, nx, ny, nz, s)) return hipErrorInvalidValue;
+    tile_pass<1>(A, B, nullptr, voxel_size, nx, ny, nz, s);
+    tile_pass<2>(B, nearest, dist, voxel_size, nx, ny, nz, s);
     return hipGetLastError();
 }
 

@@ -229,95 +229,203 @@ __global__ void __launch_bounds__(TILE ? 16 * G : 256)
     }
 }
 
-// Adjoint of forward kinematics (Alg. 1) from gradients on sphere centres
-// g_sph[S][3][B] and/or link poses g_pose[L][12][B], one state per group of
-// lanes: the lane of link l forms the wrench its gradients exert about the
-// world origin, W_l = sum over its spheres of [c x g; g] plus, for a pose
-// gradient (G on R, g_p on p), [sum_c r_c x G_c + p x g_p; g_p]; the
-// subtree sum of W, projected on the joint's world axis S = [s; p x s],
-// is the joint's gradient (a rotation about s moves every point and frame
-// of the subtree).  Transforms are recomputed by pointer jumping; nothing is
-// stored.  Mimic joints gather m_l times their links' values.
+// The world pose of lane gl's link for one state (th from q, with mimic
+// joints' multiplier and offset).
 template <int G>
-__global__ void __launch_bounds__(256) k_fk_backward_lanes(DevRobot rb, DevFused fz, int64_t nb, int64_t B,
-                                                           const float *__restrict__ q,
-                                                           const float *__restrict__ g_pose,
-                                                           const float *__restrict__ g_sph,
-                                                           float *__restrict__ g_q) {
-    const int lane = threadIdx.x & 63;
-    const int per_wave = 64 / G, grp = lane / G, gl = lane - grp * G;
-    const int64_t wave = (int64_t)blockIdx.x * 4 + (threadIdx.x >> 6);
-    const int64_t s = wave * per_wave + grp;
-    if (wave * per_wave >= nb) return;
-    const bool valid = s < nb;
-    const int64_t b = valid ? s : nb - 1;
-    const int *li = fz.li;
-    const float *lf = fz.lf;
-    const bool act = gl < rb.L;
-    const int parent_lane = li[1 * 64 + gl];
-    const bool revolute = li[5 * 64 + gl] != 0;
-    const int jidx = li[3 * 64 + gl];
-    const int link = li[0 * 64 + gl];
-    const Subtree sub = subtree_of(li[2 * 64 + gl], gl);
-    const bool mim = fz.mimic != 0;
-    float th = 0.f, mult = 1.f;
+__device__ __forceinline__ void state_pose(const DevFused &fz, int gl, const float *__restrict__ q, int64_t B,
+                                           int64_t b, float &mult, M3 &R, V3 &p) {
+    const bool revolute = fz.li[5 * 64 + gl] != 0;
+    float th = 0.f;
+    mult = 1.f;
     if (revolute) {
-        th = q[(int64_t)jidx * B + b];
-        if (mim) {
-            mult = lf[29 * 64 + gl];
-            th = mult * th + lf[30 * 64 + gl];
+        th = q[(int64_t)fz.li[3 * 64 + gl] * B + b];
+        if (fz.mimic) {
+            mult = fz.lf[29 * 64 + gl];
+            th = mult * th + fz.lf[30 * 64 + gl];
         }
     }
+    lane_world_pose(fz, gl, revolute, th, fz.li[1 * 64 + gl], G, R, p);
+}
+
+// Row link * 12 + e of a pose tile of TS states: element e of the link's
+// pose (rotation row-major, then translation); rows are padded by one float.
+template <int TS>
+__device__ __forceinline__ void pose_put(float *tile, int link, int s, const M3 &R, V3 p) {
+    float *r = tile + link * 12 * (TS + 1) + s;
+#pragma unroll
+    for (int t = 0; t < 9; ++t) r[t * (TS + 1)] = R.m[t];
+    r[9 * (TS + 1)] = p.x;
+    r[10 * (TS + 1)] = p.y;
+    r[11 * (TS + 1)] = p.z;
+}
+template <int TS>
+__device__ __forceinline__ void pose_get(const float *tile, int link, int s, M3 &R, V3 &p) {
+    const float *r = tile + link * 12 * (TS + 1) + s;
+#pragma unroll
+    for (int t = 0; t < 9; ++t) R.m[t] = r[t * (TS + 1)];
+    p = v3(r[9 * (TS + 1)], r[10 * (TS + 1)], r[11 * (TS + 1)]);
+}
+
+// Forward kinematics (Sec. 6.1) of TS consecutive states by a workgroup of
+// TS * G lanes: each group of G lanes forms one state's link poses by
+// pointer jumping and leaves them in an LDS tile; then thread (t, r) writes
+// state t of the tile's rows r, r + G, ... and of every G-th sphere's centre,
+// formed from its link's pose, so rows leave in pieces of TS floats.  Bound
+// by the bytes written (poses and centres); a group writing its own state
+// touches one float of every row, a lane walking its state's links leaves
+// the chip to a few hundred serial wavefronts.
+template <int G, int TS>
+__global__ void __launch_bounds__(TS * G) k_fk_tile(DevRobot rb, DevFused fz, int64_t nb, int64_t B,
+                                                    const float *__restrict__ q, float *__restrict__ pose,
+                                                    float *__restrict__ sph) {
+    extern __shared__ float tile[];
+    const int64_t s0 = (int64_t)xcd_chunk() * TS;
+    {
+        const int gl = threadIdx.x & (G - 1), ts = threadIdx.x / G;
+        const int64_t b = min(s0 + ts, nb - 1);   // states past the batch repeat its last
+        M3 R;
+        V3 p;
+        float mult;
+        state_pose<G>(fz, gl, q, B, b, mult, R, p);
+        const int link = fz.li[0 * 64 + gl];
+        if (link >= 0) pose_put<TS>(tile, link, ts, R, p);
+    }
+    __syncthreads();
+    const int t = threadIdx.x % TS;
+    const int64_t b = s0 + t;
+    if (b >= nb) return;
+    if (pose)
+        for (int r = threadIdx.x / TS; r < 12 * rb.L; r += G) pose[(int64_t)r * B + b] = tile[r * (TS + 1) + t];
+    if (sph)
+        for (int i = threadIdx.x / TS; i < rb.S; i += G) {
+            const float4 c4 = rb.sph[i];
+            M3 R;
+            V3 p;
+            pose_get<TS>(tile, rb.sph_link[i], t, R, p);
+            const V3 c = mul(R, v3(c4.x, c4.y, c4.z)) + p;
+            float *o = sph + (int64_t)i * 3 * B + b;
+            o[0] = c.x;
+            o[B] = c.y;
+            o[2 * B] = c.z;
+        }
+}
+
+// Adjoint of forward kinematics (Alg. 1) from gradients on sphere centres
+// g_sph[S][3][B] and/or link poses g_pose[L][12][B], TS states per workgroup
+// as k_fk_tile: the poses are recomputed into the LDS tile; thread (t, l)
+// forms the wrench that the gradients of link l exert about the world origin
+// in state t, W_l = sum over its spheres of [c x g; g] plus, for a pose
+// gradient (G on R, g_p on p), [sum_c r_c x G_c + p x g_p; g_p], reading
+// pieces of TS floats, and leaves it in the link's own pose rows; then the
+// group's subtree sum of W, projected on the joint's world axis
+// S = [s; p x s], is the joint's gradient (a rotation about s moves every
+// point and frame of the subtree).  Mimic joints gather m_l times their
+// links' values.  The sum is taken in split form: the wrenches of a
+// collision cancel in every joint above both spheres.
+template <int G, int TS>
+__global__ void __launch_bounds__(TS * G) k_fk_backward_tile(DevRobot rb, DevFused fz, int64_t nb, int64_t B,
+                                                             const float *__restrict__ q,
+                                                             const float *__restrict__ g_pose,
+                                                             const float *__restrict__ g_sph,
+                                                             float *__restrict__ g_q) {
+    extern __shared__ float tile[];
+    const int64_t s0 = (int64_t)xcd_chunk() * TS;
+    const int gl = threadIdx.x & (G - 1), ts = threadIdx.x / G;
+    const int64_t bg = min(s0 + ts, nb - 1);
+    const int link = fz.li[0 * 64 + gl], jidx = fz.li[3 * 64 + gl];
+    const bool revolute = fz.li[5 * 64 + gl] != 0;
     M3 R;
     V3 p;
-    lane_world_pose(fz, gl, revolute, th, parent_lane, G, R, p);
-    SV W = zsv();
-    if (act) {
-        if (g_sph) {
-            const int first = rb.li[link].sph_first, cnt = rb.li[link].sph_count;
-            for (int j = 0; j < cnt; ++j) {
-                const float4 c4 = rb.sph[first + j];
-                const V3 c = mul(R, v3(c4.x, c4.y, c4.z)) + p;
-                const float *gp = g_sph + (int64_t)(first + j) * 3 * B + b;
-                const V3 g = v3(gp[0], gp[B], gp[2 * B]);
-                W += sv(cross(c, g), g);
-            }
-        }
-        if (g_pose) {
-            const float *gp = g_pose + (int64_t)link * 12 * B + b;
-            M3 Gm;
-#pragma unroll
-            for (int t = 0; t < 9; ++t) Gm.m[t] = gp[t * B];
-            const V3 gt = v3(gp[9 * B], gp[10 * B], gp[11 * B]);
-            V3 m = cross(p, gt);
-#pragma unroll
-            for (int c = 0; c < 3; ++c) m += cross(col(R, c), col(Gm, c));
-            W += sv(m, gt);
-        }
-    }
-    const SV Ws = subtree_sum(W, sub, G);
-    float th_b = 0.f;
+    float mult;
+    state_pose<G>(fz, gl, q, B, bg, mult, R, p);
+    if (link >= 0) pose_put<TS>(tile, link, ts, R, p);
+    SV S = zsv();
     if (revolute) {
-        const V3 sw = mul(R, v3(lf[0 * 64 + gl], lf[1 * 64 + gl], lf[2 * 64 + gl]));
-        th_b = dot(sv(sw, cross(p, sw)), Ws);
+        const V3 sw = mul(R, v3(fz.lf[0 * 64 + gl], fz.lf[1 * 64 + gl], fz.lf[2 * 64 + gl]));
+        S = sv(sw, cross(p, sw));
     }
-    if (mim) th_b = gather_joint(mult * th_b, fz, gl, G);
-    const bool jlane = mim ? gl < rb.n : revolute;
-    if (valid && jlane) g_q[(int64_t)(mim ? gl : jidx) * B + b] = th_b;
+    __syncthreads();
+    {
+        const int t = threadIdx.x % TS, l = threadIdx.x / TS;
+        const int64_t b = min(s0 + t, nb - 1);
+        if (l < rb.L) {
+            SV W = zsv();
+            pose_get<TS>(tile, l, t, R, p);
+            if (g_sph) {
+                const int first = rb.li[l].sph_first, cnt = rb.li[l].sph_count;
+#pragma unroll 4
+                for (int j = 0; j < cnt; ++j) {
+                    const float4 c4 = rb.sph[first + j];
+                    const V3 c = mul(R, v3(c4.x, c4.y, c4.z)) + p;
+                    const float *gp = g_sph + (int64_t)(first + j) * 3 * B + b;
+                    const V3 g = v3(gp[0], gp[B], gp[2 * B]);
+                    W += sv(cross(c, g), g);
+                }
+            }
+            if (g_pose) {
+                const float *gp = g_pose + (int64_t)l * 12 * B + b;
+                M3 Gm;
+#pragma unroll
+                for (int e = 0; e < 9; ++e) Gm.m[e] = gp[e * B];
+                const V3 gt = v3(gp[9 * B], gp[10 * B], gp[11 * B]);
+                V3 m = cross(p, gt);
+#pragma unroll
+                for (int c = 0; c < 3; ++c) m += cross(col(R, c), col(Gm, c));
+                W += sv(m, gt);
+            }
+            float *r = tile + l * 12 * (TS + 1) + t;   // the link's own rows: no other thread reads them
+            r[0] = W.w.x; r[TS + 1] = W.w.y; r[2 * (TS + 1)] = W.w.z;
+            r[3 * (TS + 1)] = W.l.x; r[4 * (TS + 1)] = W.l.y; r[5 * (TS + 1)] = W.l.z;
+        }
+    }
+    __syncthreads();
+    SV W = zsv();
+    if (link >= 0) {
+        const float *r = tile + link * 12 * (TS + 1) + ts;
+        W = sv(v3(r[0], r[TS + 1], r[2 * (TS + 1)]), v3(r[3 * (TS + 1)], r[4 * (TS + 1)], r[5 * (TS + 1)]));
+    }
+    const Subtree sub = subtree_of(fz.li[2 * 64 + gl], gl);
+    float th_b = dot(S, subtree_sum_split(W, sub, fz.branched != 0, G));
+    if (fz.mimic) th_b = gather_joint(mult * th_b, fz, gl, G);
+    const bool jlane = fz.mimic ? gl < rb.n : revolute;
+    if (s0 + ts < nb && jlane) g_q[(int64_t)(fz.mimic ? gl : jidx) * B + bg] = th_b;
 }
 
 static int lanes_for(int L) { return L <= 16 ? 16 : (L <= 32 ? 32 : 64); }
 
-hipError_t launch_fk_backward_lanes(const DevRobot &rb, const DevFused &fz, int64_t B, int64_t ld, const float *q,
-                                    const float *g_pose, const float *g_sph, float *g_q, hipStream_t s) {
+// Tiles of 16 states where the batch fills the chip with such workgroups,
+// of 4 below.
+template <int G, int TS>
+static void launch_fk_t(const DevRobot &rb, const DevFused &fz, int64_t B, int64_t ld, const float *q, float *pose,
+                        float *sph, hipStream_t s) {
+    hipLaunchKernelGGL((k_fk_tile<G, TS>), dim3((unsigned)((B + TS - 1) / TS)), dim3(TS * G),
+                       (size_t)rb.L * 12 * (TS + 1) * 4, s, rb, fz, B, ld, q, pose, sph);
+}
+template <int G, int TS>
+static void launch_fkb_t(const DevRobot &rb, const DevFused &fz, int64_t B, int64_t ld, const float *q,
+                         const float *g_pose, const float *g_sph, float *g_q, hipStream_t s) {
+    hipLaunchKernelGGL((k_fk_backward_tile<G, TS>), dim3((unsigned)((B + TS - 1) / TS)), dim3(TS * G),
+                       (size_t)rb.L * 12 * (TS + 1) * 4, s, rb, fz, B, ld, q, g_pose, g_sph, g_q);
+}
+
+hipError_t launch_fk_lanes(const DevRobot &rb, const DevFused &fz, int64_t B, int64_t ld, const float *q, float *pose,
+                           float *spheres, bool wide, hipStream_t s) {
     if (B == 0) return hipSuccess;
-    const int G = lanes_for(rb.L);
-    const int64_t per_wg = 4 * (64 / G);
-    const dim3 grid((unsigned)((B + per_wg - 1) / per_wg));
-    switch (G) {
-        case 16: hipLaunchKernelGGL(k_fk_backward_lanes<16>, grid, dim3(256), 0, s, rb, fz, B, ld, q, g_pose, g_sph, g_q); break;
-        case 32: hipLaunchKernelGGL(k_fk_backward_lanes<32>, grid, dim3(256), 0, s, rb, fz, B, ld, q, g_pose, g_sph, g_q); break;
-        default: hipLaunchKernelGGL(k_fk_backward_lanes<64>, grid, dim3(256), 0, s, rb, fz, B, ld, q, g_pose, g_sph, g_q); break;
+    switch (lanes_for(rb.L)) {
+        case 16: wide ? launch_fk_t<16, 16>(rb, fz, B, ld, q, pose, spheres, s) : launch_fk_t<16, 4>(rb, fz, B, ld, q, pose, spheres, s); break;
+        case 32: wide ? launch_fk_t<32, 16>(rb, fz, B, ld, q, pose, spheres, s) : launch_fk_t<32, 4>(rb, fz, B, ld, q, pose, spheres, s); break;
+        default: wide ? launch_fk_t<64, 16>(rb, fz, B, ld, q, pose, spheres, s) : launch_fk_t<64, 4>(rb, fz, B, ld, q, pose, spheres, s); break;
+    }
+    return hipGetLastError();
+}
+
+hipError_t launch_fk_backward_lanes(const DevRobot &rb, const DevFused &fz, int64_t B, int64_t ld, const float *q,
+                                    const float *g_pose, const float *g_sph, float *g_q, bool wide, hipStream_t s) {
+    if (B == 0) return hipSuccess;
+    switch (lanes_for(rb.L)) {
+        case 16: wide ? launch_fkb_t<16, 16>(rb, fz, B, ld, q, g_pose, g_sph, g_q, s) : launch_fkb_t<16, 4>(rb, fz, B, ld, q, g_pose, g_sph, g_q, s); break;
+        case 32: wide ? launch_fkb_t<32, 16>(rb, fz, B, ld, q, g_pose, g_sph, g_q, s) : launch_fkb_t<32, 4>(rb, fz, B, ld, q, g_pose, g_sph, g_q, s); break;
+        default: wide ? launch_fkb_t<64, 16>(rb, fz, B, ld, q, g_pose, g_sph, g_q, s) : launch_fkb_t<64, 4>(rb, fz, B, ld, q, g_pose, g_sph, g_q, s); break;
     }
     return hipGetLastError();
 }

@@ -746,6 +746,10 @@ bool lanes_form(const wb_robot *r, int64_t B, bool pose) {
     const int64_t below = set >= 0 ? set : (int64_t)48 * r->cus;
     return r->T.lanes && B < below;
 }
+
+// The group forms that move rows of state arrays through LDS take tiles of
+// 16 states from one such tile per compute unit on.
+bool wide_tiles(const wb_robot *r, int64_t B) { return B >= (int64_t)16 * r->cus; }
 }  // namespace
 
 int wb_fk(const wb_robot *robot, int64_t B, int64_t ld, const float *q, float *link_pose, float *spheres,
@@ -758,18 +762,11 @@ int wb_fk(const wb_robot *robot, int64_t B, int64_t ld, const float *q, float *l
     WB_TRY(check_ptr(link_pose, "link_pose", false));
     WB_TRY(check_ptr(spheres, "spheres", false));
     if (!link_pose && !spheres) return fail(WB_ERR_INVALID_ARG, "link_pose and spheres are both null");
-    if (lanes_form(robot, B, link_pose != nullptr) && robot->T.kin) {
-        const wb::KinOut o{link_pose, spheres, nullptr, nullptr, nullptr, nullptr};
-        return finish(wb::launch_kinematics(robot->kin, B, ld, q, o, stream), "wb_fk launch");
-    }
+    if (lanes_form(robot, B, link_pose != nullptr))
+        return finish(wb::launch_fk_lanes(robot->dev, robot->fz, B, ld, q, link_pose, spheres, wide_tiles(robot, B), stream),
+                      "wb_fk launch");
     return finish(wb::launch_fk(robot->dev, B, ld, q, link_pose, spheres, stream), "wb_fk launch");
 }
-
-namespace {
-// RNEA's cache moves through tiles of 16 states from one such tile per
-// compute unit on.
-bool cache_tiled(const wb_robot *r, int64_t B) { return B >= (int64_t)16 * r->cus; }
-}  // namespace
 
 int wb_rnea(const wb_robot *robot, int64_t B, int64_t ld, const float *q, const float *qd, const float *qdd,
             const float *f_ext, float *tau, float *cache, hipStream_t stream) {
@@ -789,7 +786,7 @@ int wb_rnea(const wb_robot *robot, int64_t B, int64_t ld, const float *q, const 
     if (!robot->T.lanes)
         return finish(wb::launch_rnea(robot->dev, B, ld, q, qd, qdd, f_ext, tau, cache, stream), "wb_rnea launch");
     return finish(wb::launch_rnea_lanes(robot->dev, robot->fz, B, ld, q, qd, qdd, f_ext, tau, cache,
-                                        cache_tiled(robot, B), stream),
+                                        wide_tiles(robot, B), stream),
                   "wb_rnea launch");
 }
 
@@ -862,7 +859,8 @@ int wb_fk_backward(const wb_robot *robot, int64_t B, int64_t ld, const float *q,
     WB_TRY(check_ptr(g_q, "g_q", robot->T.n > 0));
     if (lanes_form(robot, B, link_pose != nullptr || g_link_pose != nullptr)) {
         WB_TRY(check_ptr(workspace, "workspace", false));
-        return finish(wb::launch_fk_backward_lanes(robot->dev, robot->fz, B, ld, q, g_link_pose, g_spheres, g_q, stream),
+        return finish(wb::launch_fk_backward_lanes(robot->dev, robot->fz, B, ld, q, g_link_pose, g_spheres, g_q,
+                                                   wide_tiles(robot, B), stream),
                       "wb_fk_backward launch");
     }
     WB_TRY(check_ptr(workspace, "workspace", true));
@@ -894,7 +892,7 @@ int wb_rnea_backward(const wb_robot *robot, int64_t B, int64_t ld, const float *
     WB_TRY(check_ptr(workspace, "workspace", cache != nullptr));
     if (robot->T.lanes)
         return finish(wb::launch_rnea_backward_lanes(robot->dev, robot->fz, B, ld, q, qd, qdd, f_ext, cache, g_tau,
-                                                     g_q, g_qd, g_qdd, g_fext, cache_tiled(robot, B), stream),
+                                                     g_q, g_qd, g_qdd, g_fext, wide_tiles(robot, B), stream),
                       "wb_rnea_backward launch");
     return finish(wb::launch_rnea_backward(robot->dev, B, ld, q, qd, qdd, cache, g_tau, g_q, g_qd, g_qdd, g_fext,
                                            static_cast<float *>(workspace), stream),

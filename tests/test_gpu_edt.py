@@ -174,3 +174,39 @@ def test_edt_rejects_bad_arguments():
         wb.wb_edt(m, -1.0)
     with pytest.raises(ValueError):
         wb.wb_edt(m.float(), 1.0)
+
+
+@pytest.mark.parametrize("shape", [(33, 7, 9), (31, 8, 129), (5, 129, 16), (3, 257, 33), (2, 33, 513), (8, 512, 3),
+                                   (4, 3, 1024)])
+@pytest.mark.parametrize("density", [0.0, 0.004, 0.3, 1.0])
+def test_owner_search_at_its_edges(shape, density):
+    """Line lengths around the blocks of 8, the groups of 32, the 16-position
+    segments and the tile forms (128, 256, 512): each voxel's distance and
+    site against brute force over all sites, exactly; among equidistant sites
+    the last plane, of its sites the last row, of its sites the first in x."""
+    from paper_2603_05493_amd import wb
+    nx, ny, nz = shape
+    rng = np.random.default_rng(nx * 7 + ny * 3 + nz)
+    g = (rng.random((nz, ny, nx)) < density).astype(np.uint8)
+    if density == 0.004 and not g.any():
+        g[nz // 2, ny // 3, nx // 2] = 1
+    near, dist = wb.wb_edt(torch.from_numpy(g).cuda(), voxel_size=1.0)
+    torch.cuda.synchronize()
+    near, dist = near.cpu().numpy(), dist.cpu().numpy()
+    if not g.any():
+        assert (near == -1).all() and np.isinf(dist).all()
+        return
+    # axis by axis in whole numbers, keeping the last of several minima in y and z and the first in x
+    x, y, z = np.arange(nx), np.arange(ny), np.arange(nz)
+    big = 1 << 24
+    d = np.where(g[:, :, None, :] != 0, (x[:, None] - x[None, :]) ** 2, big)          # [z, y, x, x']
+    sx, d = d.argmin(-1), d.min(-1)
+    c = d[:, None] + ((y[:, None] - y[None, :]) ** 2)[None, :, :, None]               # [z, y, y', x]
+    sy, d = ny - 1 - c[:, :, ::-1].argmin(2), c.min(2)
+    c = d[None] + ((z[:, None] - z[None, :]) ** 2)[:, :, None, None]                  # [z, z', y, x]
+    sz, d = nz - 1 - c[:, ::-1].argmin(1), c.min(1)
+    Y, X = np.broadcast_to(y[None, :, None], sz.shape), np.broadcast_to(x[None, None, :], sz.shape)
+    wy = sy[sz, Y, X]
+    wx = sx[sz, wy, X]
+    assert np.array_equal(near, wx | (wy << 10) | (sz << 20))
+    assert np.array_equal(dist, np.sqrt(d.astype(np.float32)))

@@ -22,7 +22,7 @@ def _mimic():
     return rb
 
 
-ROBOTS = [("chain1", lambda: synth.serial_chain(1, 1, seed=2)), ("tree16", lambda: synth.random_tree(15, 2, seed=4)),
+ROBOTS = [("tree16", lambda: synth.random_tree(15, 2, seed=4)),
           ("tree17", lambda: synth.random_tree(16, 2, seed=5)), ("chain32", lambda: synth.serial_chain(31, 1, seed=6)),
           ("tree33", lambda: synth.random_tree(32, 1, seed=7)), ("tree64", lambda: synth.random_tree(63, 1, seed=8)),
           ("mimic9", _mimic)]
