@@ -161,9 +161,10 @@ int wb_rnea_cache_bytes(const wb_robot *robot, int64_t B, size_t *bytes);
 /* ---------------------------------------------------------------- forward */
 
 /* Forward kinematics (Sec. 6.1; the paper dispatches its kernels by robot
- * size).  Batches below 48 states per compute unit on robots of at most 64
- * links run one group of lanes per state (pointer jumping over the links, as
- * wb_kinematics); larger ones one lane per state.
+ * size).  Robots of at most 64 links: batches below 48 states per compute
+ * unit run one group of lanes per state (pointer jumping over the links, as
+ * wb_kinematics), larger ones compose the links level by level, both through
+ * tiles of states; larger robots run one lane per state.
  * q[n][B] joint positions ->
  *   link_pose[L][12][B] world link poses, or NULL to skip them: a branch
  *     link then recomposes its parent's pose from q along the parent's chain
@@ -258,16 +259,11 @@ int wb_self_collision(const wb_robot *robot, int64_t B, int64_t ld, const float 
  *   sweep_split_below     wb_self_collision takes the one-state-per-workgroup
  *                         form for batches of fewer states (default 16 per
  *                         compute unit of the robot's device);
- *   fk_groups_below       wb_fk without link poses and wb_fk_backward
- *                         without them take one group of lanes per state for
- *                         batches of fewer states (default 48 per compute
- *                         unit; robots of at most 64 links);
- *   fk_pose_groups_below  the same for wb_fk writing link poses and
- *                         wb_fk_backward reading poses or a pose gradient
- *                         (the group form writes
- *                         one state's 12L pose values across 12L rows and
- *                         recomputes instead of reading; the lane form's rows
- *                         are coalesced, so its crossover lies lower).
+ *   fk_groups_below       wb_fk without link poses takes one group of lanes
+ *                         per state (pointer jumping) for batches of fewer
+ *                         states, the link-by-link composition above (default
+ *                         48 per compute unit; robots of at most 64 links);
+ *   fk_pose_groups_below  the same for wb_fk writing link poses.
  * A negative value restores that default; 0 never takes the form. */
 int wb_robot_set_dispatch(wb_robot *robot, int64_t sweep_split_below, int64_t fk_groups_below,
                           int64_t fk_pose_groups_below);
@@ -288,11 +284,11 @@ int wb_self_collision_backward(const wb_robot *robot, int64_t B, int64_t ld, con
  * be NULL, not both) -> g_q[n][B] (overwritten).  link_pose is the output of
  * wb_fk for the same q, or NULL to recompute the transforms from q inside
  * the kernel.  workspace: wb_workspace_bytes(robot, B).
- * Like wb_fk, batches below 48 states per compute unit (robots of at most
- * 64 links) run one group of lanes per state: each link's
+ * Robots of at most 64 links run one group of lanes per state: each link's
  * wrench about the world origin summed over its subtree and projected on
  * the joint axis, transforms recomputed in registers; link_pose is then not
- * read and workspace may be NULL. */
+ * read, and workspace may be NULL for batches below wb_robot_set_dispatch's
+ * thresholds (48 states per compute unit by default). */
 int wb_fk_backward(const wb_robot *robot, int64_t B, int64_t ld, const float *q, const float *link_pose,
                    const float *g_link_pose, const float *g_spheres, float *g_q, void *workspace,
                    hipStream_t stream);

@@ -29,31 +29,29 @@ namespace wb {
 
 // Row tile of TS states staged in LDS, for the [L][18][B] cache: a group
 // holds one state, so its lanes touch one float of every row, while a tile
-// of 16 states moves 64-byte pieces of the rows (TileRow: 16 states padded
-// to 17, so that the lanes of a group hit different banks).
-constexpr int TILE_S = 16, TILE_ROW = 17;
-
-// The link's spatial vector to or from its six rows of the tile.
+// moves pieces of TS floats.  Row link * 6 + c holds component c, padded by
+// one float.
+template <int TS>
 __device__ __forceinline__ void tile_put(float *tile, int link, int s, SV x) {
-    float *r = tile + link * 6 * TILE_ROW + s;
-    r[0] = x.w.x; r[TILE_ROW] = x.w.y; r[2 * TILE_ROW] = x.w.z;
-    r[3 * TILE_ROW] = x.l.x; r[4 * TILE_ROW] = x.l.y; r[5 * TILE_ROW] = x.l.z;
+    float *r = tile + link * 6 * (TS + 1) + s;
+    r[0] = x.w.x; r[TS + 1] = x.w.y; r[2 * (TS + 1)] = x.w.z;
+    r[3 * (TS + 1)] = x.l.x; r[4 * (TS + 1)] = x.l.y; r[5 * (TS + 1)] = x.l.z;
 }
+template <int TS>
 __device__ __forceinline__ SV tile_get(const float *tile, int link, int s) {
-    const float *r = tile + link * 6 * TILE_ROW + s;
-    return sv(v3(r[0], r[TILE_ROW], r[2 * TILE_ROW]), v3(r[3 * TILE_ROW], r[4 * TILE_ROW], r[5 * TILE_ROW]));
+    const float *r = tile + link * 6 * (TS + 1) + s;
+    return sv(v3(r[0], r[TS + 1], r[2 * (TS + 1)]), v3(r[3 * (TS + 1)], r[4 * (TS + 1)], r[5 * (TS + 1)]));
 }
 // Rows part .. part + 5 of every link but the base between the tile and the
-// cache, `cnt` states from b0; thread t takes state t % 16.
-template <bool STORE>
+// cache, `cnt` states from b0; thread t takes state t % TS.
+template <bool STORE, int TS>
 __device__ __forceinline__ void tile_move(float *tile, float *cache, int part, int L, int64_t B, int64_t b0, int cnt) {
-    const int s = threadIdx.x % TILE_S;
+    const int s = threadIdx.x % TS;
     if (s < cnt)
-        for (int r = 6 + threadIdx.x / TILE_S; r < 6 * L; r += blockDim.x / TILE_S) {
-            const int link = r / 6;
-            float *g = cache + (int64_t)(r + 12 * link + part) * B + b0 + s;
-            if (STORE) *g = tile[r * TILE_ROW + s];
-            else tile[r * TILE_ROW + s] = *g;
+        for (int r = 6 + threadIdx.x / TS; r < 6 * L; r += blockDim.x / TS) {
+            float *g = cache + (int64_t)(r + 12 * (r / 6) + part) * B + b0 + s;
+            if (STORE) *g = tile[r * (TS + 1) + s];
+            else tile[r * (TS + 1) + s] = *g;
         }
 }
 
@@ -77,34 +75,21 @@ __device__ __forceinline__ SV force_to_world(const M3 &R, V3 p, SV f) {
 // forms replace the link-by-link recursion in link coordinates and sum the
 // subtrees in split form, to be as exact (torques of a 37-joint tree against
 // 64 bits: 1.6e-7 by the recursion, 5.4e-7 from plain scan differences).
-// TILE: a
-// workgroup of 16 G lanes owns 16 consecutive states and moves the cache
-// through an LDS tile; without it a workgroup is 256 lanes and the cache is
-// accessed by the groups directly.
+// A workgroup of TS * G lanes owns TS consecutive states; the cache moves
+// through an LDS tile.
 // nb: states; B: row length of every [k][B] array (the ABI's ld >= nb).
-template <bool BWD, bool CACHE, bool TILE, int G>
-__global__ void __launch_bounds__(TILE ? 16 * G : 256)
+template <bool BWD, bool CACHE, int TS, int G>
+__global__ void __launch_bounds__(TS * G)
     k_rnea_lanes(DevRobot rb, DevFused fz, int64_t nb, int64_t B, const float *__restrict__ q,
                  const float *__restrict__ qd, const float *__restrict__ qdd, const float *__restrict__ f_ext,
                  float *__restrict__ tau, float *__restrict__ cache, const float *__restrict__ g_tau,
                  float *__restrict__ g_q, float *__restrict__ g_qd, float *__restrict__ g_qdd,
                  float *__restrict__ g_fext) {
     extern __shared__ float tile[];
-    const int lane = threadIdx.x & 63;
-    const int gl = lane & (G - 1);
-    int64_t s0, s;   // first state of the workgroup (TILE), this group's state
-    if (TILE) {
-        s0 = (int64_t)xcd_chunk() * TILE_S;
-        s = s0 + threadIdx.x / G;
-        if (BWD) tile_move<false>(tile, cache, 12, rb.L, B, s0, (int)min((int64_t)TILE_S, nb - s0));
-    } else {
-        const int64_t wave = (int64_t)blockIdx.x * 4 + (threadIdx.x >> 6);
-        s0 = wave * (64 / G);
-        s = s0 + lane / G;
-        if (s0 >= nb) return;   // the whole wavefront is past the batch
-    }
-    const int ts = TILE ? (int)(threadIdx.x / G) : 0;   // the group's state in the tile
-    const int cnt = TILE ? (int)min((int64_t)TILE_S, nb - s0) : 0;
+    const int gl = threadIdx.x & (G - 1), ts = threadIdx.x / G;   // the group's lane and state in the tile
+    const int64_t s0 = (int64_t)(CACHE ? xcd_chunk() : blockIdx.x) * TS, s = s0 + ts;
+    const int cnt = (int)min((int64_t)TS, nb - s0);
+    if (BWD && CACHE) tile_move<false, TS>(tile, cache, 12, rb.L, B, s0, cnt);
     const bool valid = s < nb;
     const int64_t b = valid ? s : nb - 1;   // groups past the end compute on a valid state, store nothing
     const int *li = fz.li;
@@ -158,15 +143,8 @@ __global__ void __launch_bounds__(TILE ? 16 * G : 256)
     const SV Iv = iw_apply(J, v);
     SV F;
     if (BWD && CACHE) {
-        F = zsv();
-        if (TILE) __syncthreads();
-        if (act && link > 0) {
-            if (TILE) F = tile_get(tile, link, ts);
-            else {
-                const float *cf = cache + (int64_t)(link * 18 + 12) * B + b;
-                F = sv(v3(cf[0], cf[B], cf[2 * B]), v3(cf[3 * B], cf[4 * B], cf[5 * B]));
-            }
-        }
+        __syncthreads();
+        F = act && link > 0 ? tile_get<TS>(tile, link, ts) : zsv();
         F = force_to_world(R, p, F);
     } else {
         F = iw_apply(J, a) + crf(v, Iv);
@@ -187,16 +165,10 @@ __global__ void __launch_bounds__(TILE ? 16 * G : 256)
             for (int part = 0; part < 3; ++part) {
                 const SV x = part == 0 ? motion_to_link(R, p, v)
                                        : (part == 1 ? motion_to_link(R, p, a) : force_to_link(R, p, F));
-                if (TILE) {
-                    if (part > 0) __syncthreads();   // the tile's previous rows are out
-                    if (act && link > 0) tile_put(tile, link, ts, x);
-                    __syncthreads();
-                    tile_move<true>(tile, cache, 6 * part, rb.L, B, s0, cnt);
-                } else if (valid && act && link > 0) {
-                    float *d = cache + (int64_t)(link * 18 + 6 * part) * B + b;
-                    d[0] = x.w.x; d[B] = x.w.y; d[2 * B] = x.w.z;
-                    d[3 * B] = x.l.x; d[4 * B] = x.l.y; d[5 * B] = x.l.z;
-                }
+                if (part > 0) __syncthreads();   // the tile's previous rows are out
+                if (act && link > 0) tile_put<TS>(tile, link, ts, x);
+                __syncthreads();
+                tile_move<true, TS>(tile, cache, 6 * part, rb.L, B, s0, cnt);
             }
         }
         return;
@@ -266,31 +238,11 @@ __device__ __forceinline__ void pose_get(const float *tile, int link, int s, M3 
     p = v3(r[9 * (TS + 1)], r[10 * (TS + 1)], r[11 * (TS + 1)]);
 }
 
-// Forward kinematics (Sec. 6.1) of TS consecutive states by a workgroup of
-// TS * G lanes: each group of G lanes forms one state's link poses by
-// pointer jumping and leaves them in an LDS tile; then thread (t, r) writes
-// state t of the tile's rows r, r + G, ... and of every G-th sphere's centre,
-// formed from its link's pose, so rows leave in pieces of TS floats.  Bound
-// by the bytes written (poses and centres); a group writing its own state
-// touches one float of every row, a lane walking its state's links leaves
-// the chip to a few hundred serial wavefronts.
+// Writes a pose tile: thread (t, r) takes state t of the rows r, r + G, ...
+// and of every G-th sphere's centre, formed from its link's pose.
 template <int G, int TS>
-__global__ void __launch_bounds__(TS * G) k_fk_tile(DevRobot rb, DevFused fz, int64_t nb, int64_t B,
-                                                    const float *__restrict__ q, float *__restrict__ pose,
-                                                    float *__restrict__ sph) {
-    extern __shared__ float tile[];
-    const int64_t s0 = (int64_t)xcd_chunk() * TS;
-    {
-        const int gl = threadIdx.x & (G - 1), ts = threadIdx.x / G;
-        const int64_t b = min(s0 + ts, nb - 1);   // states past the batch repeat its last
-        M3 R;
-        V3 p;
-        float mult;
-        state_pose<G>(fz, gl, q, B, b, mult, R, p);
-        const int link = fz.li[0 * 64 + gl];
-        if (link >= 0) pose_put<TS>(tile, link, ts, R, p);
-    }
-    __syncthreads();
+__device__ __forceinline__ void fk_tile_out(const DevRobot &rb, const float *tile, int64_t s0, int64_t nb, int64_t B,
+                                            float *__restrict__ pose, float *__restrict__ sph) {
     const int t = threadIdx.x % TS;
     const int64_t b = s0 + t;
     if (b >= nb) return;
@@ -308,6 +260,79 @@ __global__ void __launch_bounds__(TS * G) k_fk_tile(DevRobot rb, DevFused fz, in
             o[B] = c.y;
             o[2 * B] = c.z;
         }
+}
+
+// Forward kinematics (Sec. 6.1) of TS consecutive states by a workgroup of
+// TS * G lanes: each group of G lanes forms one state's link poses by
+// pointer jumping and leaves them in an LDS tile, from which rows leave in
+// pieces of TS floats.  A group writing its own state touches one float of
+// every row: humanoid with poses, 2,048 states, 19.0 us so and 8.3 us here.
+template <int G, int TS>
+__global__ void __launch_bounds__(TS * G) k_fk_tile(DevRobot rb, DevFused fz, int64_t nb, int64_t B,
+                                                    const float *__restrict__ q, float *__restrict__ pose,
+                                                    float *__restrict__ sph) {
+    extern __shared__ float tile[];
+    const int64_t s0 = (int64_t)xcd_chunk() * TS;
+    {
+        const int gl = threadIdx.x & (G - 1), ts = threadIdx.x / G;
+        const int64_t b = min(s0 + ts, nb - 1);   // states past the batch repeat its last
+        M3 R;
+        V3 p;
+        float mult;
+        state_pose<G>(fz, gl, q, B, b, mult, R, p);
+        const int link = fz.li[0 * 64 + gl];
+        if (link >= 0) pose_put<TS>(tile, link, ts, R, p);
+    }
+    __syncthreads();
+    fk_tile_out<G, TS>(rb, tile, s0, nb, B, pose, sph);
+}
+
+// The same level by level, for large batches: thread (t, l) forms link l's
+// local rotation in state t, then the levels of the tree compose their
+// parents' poses from the tile one after the other, with the arithmetic of
+// the one-lane-per-state walk (so that a batch keeps its results to the
+// bit).  Every link is composed once, a fraction of the pointer jumps' work;
+// the barriers between levels are hidden once the chip holds several
+// workgroups a compute unit.  Bound by the bytes written.
+template <int G, int TS>
+__global__ void __launch_bounds__(TS * G) k_fk_levels(DevRobot rb, int64_t nb, int64_t B,
+                                                      const float *__restrict__ q, float *__restrict__ pose,
+                                                      float *__restrict__ sph) {
+    extern __shared__ float tile[];
+    const int64_t s0 = (int64_t)xcd_chunk() * TS;
+    const int t = threadIdx.x % TS, l = threadIdx.x / TS;
+    const int64_t b = min(s0 + t, nb - 1);
+    int depth = 0, parent = 0;
+    M3 Rl;
+    V3 fp = v3(0.f, 0.f, 0.f);
+    if (l == 0) {
+#pragma unroll
+        for (int e = 0; e < 9; ++e) Rl.m[e] = e % 4 == 0 ? 1.0f : 0.0f;
+        pose_put<TS>(tile, 0, t, Rl, fp);
+    } else if (l < rb.L) {
+        const LinkF f = rb.lf[l];
+        const LinkI i = rb.li[l];
+        depth = i.depth;
+        parent = i.parent;
+        fp = v3(f.fp[0], f.fp[1], f.fp[2]);
+        Rl = local_rotation(f, i, i.revolute ? f.mult * q[(int64_t)i.jidx * B + b] + f.offset : 0.0f);
+    }
+    for (int d = 1; d <= rb.max_depth; ++d) {
+        __syncthreads();
+        if (depth == d) {
+            M3 R;
+            V3 p;
+            pose_get<TS>(tile, parent, t, R, p);
+            auto row = [&](int e) {   // the walk's order of roundings, spelled out
+                return __builtin_fmaf(fp.z, R.m[e + 2], __builtin_fmaf(fp.y, R.m[e + 1], fp.x * R.m[e]));
+            };
+            p = v3(row(0), row(3), row(6)) + p;
+            R = matmul(R, Rl);
+            pose_put<TS>(tile, l, t, R, p);
+        }
+    }
+    __syncthreads();
+    fk_tile_out<G, TS>(rb, tile, s0, nb, B, pose, sph);
 }
 
 // Adjoint of forward kinematics (Alg. 1) from gradients on sphere centres
@@ -393,13 +418,23 @@ __global__ void __launch_bounds__(TS * G) k_fk_backward_tile(DevRobot rb, DevFus
 
 static int lanes_for(int L) { return L <= 16 ? 16 : (L <= 32 ? 32 : 64); }
 
-// Tiles of 16 states where the batch fills the chip with such workgroups,
-// of 4 below.
+// The pointer-jumping form in tiles of 4 states, of 16 where the batch fills
+// the chip with them (humanoid with poses, 4 against 16 states a tile: 4.9 /
+// 7.0 us at 32 states, 8.3 / 8.7 at 2,048, 12.4 / 9.8 at 4,096; its
+// 588-sphere form 6.2 / 8.4, 11.7 / 11.0, 18.9 / 13.3), the adjoint in tiles
+// of 4 and 8.
 template <int G, int TS>
 static void launch_fk_t(const DevRobot &rb, const DevFused &fz, int64_t B, int64_t ld, const float *q, float *pose,
                         float *sph, hipStream_t s) {
     hipLaunchKernelGGL((k_fk_tile<G, TS>), dim3((unsigned)((B + TS - 1) / TS)), dim3(TS * G),
                        (size_t)rb.L * 12 * (TS + 1) * 4, s, rb, fz, B, ld, q, pose, sph);
+}
+template <int G>
+static void launch_fk_l(const DevRobot &rb, int64_t B, int64_t ld, const float *q, float *pose, float *sph,
+                        hipStream_t s) {
+    constexpr int TS = 16;
+    hipLaunchKernelGGL((k_fk_levels<G, TS>), dim3((unsigned)((B + TS - 1) / TS)), dim3(TS * G),
+                       (size_t)rb.L * 12 * (TS + 1) * 4, s, rb, B, ld, q, pose, sph);
 }
 template <int G, int TS>
 static void launch_fkb_t(const DevRobot &rb, const DevFused &fz, int64_t B, int64_t ld, const float *q,
@@ -419,69 +454,75 @@ hipError_t launch_fk_lanes(const DevRobot &rb, const DevFused &fz, int64_t B, in
     return hipGetLastError();
 }
 
+hipError_t launch_fk_levels(const DevRobot &rb, int64_t B, int64_t ld, const float *q, float *pose, float *spheres,
+                            hipStream_t s) {
+    if (B == 0) return hipSuccess;
+    switch (lanes_for(rb.L)) {
+        case 16: launch_fk_l<16>(rb, B, ld, q, pose, spheres, s); break;
+        case 32: launch_fk_l<32>(rb, B, ld, q, pose, spheres, s); break;
+        default: launch_fk_l<64>(rb, B, ld, q, pose, spheres, s); break;
+    }
+    return hipGetLastError();
+}
+
 hipError_t launch_fk_backward_lanes(const DevRobot &rb, const DevFused &fz, int64_t B, int64_t ld, const float *q,
                                     const float *g_pose, const float *g_sph, float *g_q, bool wide, hipStream_t s) {
     if (B == 0) return hipSuccess;
     switch (lanes_for(rb.L)) {
-        case 16: wide ? launch_fkb_t<16, 16>(rb, fz, B, ld, q, g_pose, g_sph, g_q, s) : launch_fkb_t<16, 4>(rb, fz, B, ld, q, g_pose, g_sph, g_q, s); break;
-        case 32: wide ? launch_fkb_t<32, 16>(rb, fz, B, ld, q, g_pose, g_sph, g_q, s) : launch_fkb_t<32, 4>(rb, fz, B, ld, q, g_pose, g_sph, g_q, s); break;
-        default: wide ? launch_fkb_t<64, 16>(rb, fz, B, ld, q, g_pose, g_sph, g_q, s) : launch_fkb_t<64, 4>(rb, fz, B, ld, q, g_pose, g_sph, g_q, s); break;
+        case 16: wide ? launch_fkb_t<16, 8>(rb, fz, B, ld, q, g_pose, g_sph, g_q, s) : launch_fkb_t<16, 4>(rb, fz, B, ld, q, g_pose, g_sph, g_q, s); break;
+        case 32: wide ? launch_fkb_t<32, 8>(rb, fz, B, ld, q, g_pose, g_sph, g_q, s) : launch_fkb_t<32, 4>(rb, fz, B, ld, q, g_pose, g_sph, g_q, s); break;
+        default: wide ? launch_fkb_t<64, 8>(rb, fz, B, ld, q, g_pose, g_sph, g_q, s) : launch_fkb_t<64, 4>(rb, fz, B, ld, q, g_pose, g_sph, g_q, s); break;
     }
     return hipGetLastError();
 }
 
-// The cached forms move the cache through tiles of 16 states where the
-// batch fills the chip with such workgroups, and access it directly below.
-template <bool BWD, bool CACHE, int G>
+template <bool BWD, bool CACHE, int TS, int G>
 static hipError_t launch_rnea_g(const DevRobot &rb, const DevFused &fz, int64_t B, int64_t ld, const float *q,
                                 const float *qd, const float *qdd, const float *f_ext, float *tau, float *cache,
                                 const float *g_tau, float *g_q, float *g_qd, float *g_qdd, float *g_fext,
-                                bool tiled, hipStream_t s) {
-    if (CACHE && tiled) {
-        const dim3 grid((unsigned)((B + TILE_S - 1) / TILE_S));
-        const size_t lds = (size_t)rb.L * 6 * TILE_ROW * 4;
-        hipLaunchKernelGGL((k_rnea_lanes<BWD, CACHE, CACHE, G>), grid, dim3(16 * G), lds, s, rb, fz, B, ld, q, qd,
-                           qdd, f_ext, tau, cache, g_tau, g_q, g_qd, g_qdd, g_fext);
-    } else {
-        const int64_t per_wg = 4 * (64 / G);
-        const dim3 grid((unsigned)((B + per_wg - 1) / per_wg));
-        hipLaunchKernelGGL((k_rnea_lanes<BWD, CACHE, false, G>), grid, dim3(256), 0, s, rb, fz, B, ld, q, qd, qdd,
-                           f_ext, tau, cache, g_tau, g_q, g_qd, g_qdd, g_fext);
-    }
+                                hipStream_t s) {
+    hipLaunchKernelGGL((k_rnea_lanes<BWD, CACHE, TS, G>), dim3((unsigned)((B + TS - 1) / TS)), dim3(TS * G),
+                       CACHE ? (size_t)rb.L * 6 * (TS + 1) * 4 : 0, s, rb, fz, B, ld, q, qd, qdd, f_ext, tau, cache,
+                       g_tau, g_q, g_qd, g_qdd, g_fext);
     return hipGetLastError();
 }
 
+// Without the cache a workgroup is 256 lanes.  With it, 4 states: wider
+// pieces of the rows do not pay for the larger workgroups, whose wavefronts
+// wait for each other at the tile (humanoid, forward / backward with 4, 8 and
+// 16 states a workgroup: 6.8 / 7.1, 7.6 / 9.0, 11.2 / 13.0 us at 32 states;
+// 46 / 60, 46 / 66, 65 / 83 us at 24,576).
 template <bool BWD, bool CACHE>
 static hipError_t launch_rnea_any(const DevRobot &rb, const DevFused &fz, int64_t B, int64_t ld, const float *q,
                                   const float *qd, const float *qdd, const float *f_ext, float *tau, float *cache,
                                   const float *g_tau, float *g_q, float *g_qd, float *g_qdd, float *g_fext,
-                                  bool tiled, hipStream_t s) {
+                                  hipStream_t s) {
     if (B == 0) return hipSuccess;
     switch (lanes_for(rb.L)) {
-        case 16: return launch_rnea_g<BWD, CACHE, 16>(rb, fz, B, ld, q, qd, qdd, f_ext, tau, cache, g_tau, g_q, g_qd, g_qdd, g_fext, tiled, s);
-        case 32: return launch_rnea_g<BWD, CACHE, 32>(rb, fz, B, ld, q, qd, qdd, f_ext, tau, cache, g_tau, g_q, g_qd, g_qdd, g_fext, tiled, s);
-        default: return launch_rnea_g<BWD, CACHE, 64>(rb, fz, B, ld, q, qd, qdd, f_ext, tau, cache, g_tau, g_q, g_qd, g_qdd, g_fext, tiled, s);
+        case 16: return launch_rnea_g<BWD, CACHE, CACHE ? 4 : 16, 16>(rb, fz, B, ld, q, qd, qdd, f_ext, tau, cache, g_tau, g_q, g_qd, g_qdd, g_fext, s);
+        case 32: return launch_rnea_g<BWD, CACHE, CACHE ? 4 : 8, 32>(rb, fz, B, ld, q, qd, qdd, f_ext, tau, cache, g_tau, g_q, g_qd, g_qdd, g_fext, s);
+        default: return launch_rnea_g<BWD, CACHE, CACHE ? 4 : 4, 64>(rb, fz, B, ld, q, qd, qdd, f_ext, tau, cache, g_tau, g_q, g_qd, g_qdd, g_fext, s);
     }
 }
 
 hipError_t launch_rnea_lanes(const DevRobot &rb, const DevFused &fz, int64_t B, int64_t ld, const float *q,
                              const float *qd, const float *qdd, const float *f_ext, float *tau, float *cache,
-                             bool tiled, hipStream_t s) {
+                             hipStream_t s) {
     return cache ? launch_rnea_any<false, true>(rb, fz, B, ld, q, qd, qdd, f_ext, tau, cache, nullptr, nullptr,
-                                                nullptr, nullptr, nullptr, tiled, s)
+                                                nullptr, nullptr, nullptr, s)
                  : launch_rnea_any<false, false>(rb, fz, B, ld, q, qd, qdd, f_ext, tau, nullptr, nullptr, nullptr,
-                                                 nullptr, nullptr, nullptr, false, s);
+                                                 nullptr, nullptr, nullptr, s);
 }
 
 hipError_t launch_rnea_backward_lanes(const DevRobot &rb, const DevFused &fz, int64_t B, int64_t ld,
                                       const float *q, const float *qd, const float *qdd, const float *f_ext,
                                       const float *cache, const float *g_tau, float *g_q, float *g_qd, float *g_qdd,
-                                      float *g_fext, bool tiled, hipStream_t s) {
+                                      float *g_fext, hipStream_t s) {
     float *c = const_cast<float *>(cache);   // the backward only reads it
     return cache ? launch_rnea_any<true, true>(rb, fz, B, ld, q, qd, qdd, nullptr, nullptr, c, g_tau, g_q, g_qd,
-                                               g_qdd, g_fext, tiled, s)
+                                               g_qdd, g_fext, s)
                  : launch_rnea_any<true, false>(rb, fz, B, ld, q, qd, qdd, f_ext, nullptr, nullptr, g_tau, g_q,
-                                                g_qd, g_qdd, g_fext, false, s);
+                                                g_qd, g_qdd, g_fext, s);
 }
 
 }  // namespace wb

@@ -733,22 +733,19 @@ int wb_rnea_cache_bytes(const wb_robot *robot, int64_t B, size_t *bytes) {
 }
 
 namespace {
-// Forward kinematics and its adjoint take one group of lanes per state
-// (pointer jumping over the links, nothing stored) for batches below a
-// threshold, and one lane per state above, where the lane form's coalesced
-// rows win.  Calls that write or read link poses have a threshold of their
-// own: the group form writes a state's poses across 12L rows and its
-// adjoint recomputes them, while the lane form's adjoint reads them.
-// Default for both: 48 states per compute unit.  The group form takes
-// robots of at most 64 links.
-bool lanes_form(const wb_robot *r, int64_t B, bool pose) {
+// Forward kinematics of robots of at most 64 links takes one group of lanes
+// per state (pointer jumping over the links) for batches below a threshold,
+// and the link-by-link composition of a lane's walk, level by level, above;
+// calls that write link poses have a threshold of their own.  Default for
+// both: 48 states per compute unit.  The two round differently, so the line
+// stays where the walk took over; times on both sides stand beside the
+// launchers.
+bool group_form(const wb_robot *r, int64_t B, bool pose) {
     const int64_t set = pose ? r->fk_pose_groups_below : r->fk_groups_below;
-    const int64_t below = set >= 0 ? set : (int64_t)48 * r->cus;
-    return r->T.lanes && B < below;
+    return B < (set >= 0 ? set : (int64_t)48 * r->cus);
 }
 
-// The group forms that move rows of state arrays through LDS take tiles of
-// 16 states from one such tile per compute unit on.
+// Its wide tiles from 16 states per compute unit on.
 bool wide_tiles(const wb_robot *r, int64_t B) { return B >= (int64_t)16 * r->cus; }
 }  // namespace
 
@@ -762,10 +759,12 @@ int wb_fk(const wb_robot *robot, int64_t B, int64_t ld, const float *q, float *l
     WB_TRY(check_ptr(link_pose, "link_pose", false));
     WB_TRY(check_ptr(spheres, "spheres", false));
     if (!link_pose && !spheres) return fail(WB_ERR_INVALID_ARG, "link_pose and spheres are both null");
-    if (lanes_form(robot, B, link_pose != nullptr))
+    if (!robot->T.lanes)
+        return finish(wb::launch_fk(robot->dev, B, ld, q, link_pose, spheres, stream), "wb_fk launch");
+    if (group_form(robot, B, link_pose != nullptr))
         return finish(wb::launch_fk_lanes(robot->dev, robot->fz, B, ld, q, link_pose, spheres, wide_tiles(robot, B), stream),
                       "wb_fk launch");
-    return finish(wb::launch_fk(robot->dev, B, ld, q, link_pose, spheres, stream), "wb_fk launch");
+    return finish(wb::launch_fk_levels(robot->dev, B, ld, q, link_pose, spheres, stream), "wb_fk launch");
 }
 
 int wb_rnea(const wb_robot *robot, int64_t B, int64_t ld, const float *q, const float *qd, const float *qdd,
@@ -785,8 +784,7 @@ int wb_rnea(const wb_robot *robot, int64_t B, int64_t ld, const float *q, const 
         return fail(WB_ERR_UNSUPPORTED, "a robot of %d links (more than 64) needs the cache", robot->T.L);
     if (!robot->T.lanes)
         return finish(wb::launch_rnea(robot->dev, B, ld, q, qd, qdd, f_ext, tau, cache, stream), "wb_rnea launch");
-    return finish(wb::launch_rnea_lanes(robot->dev, robot->fz, B, ld, q, qd, qdd, f_ext, tau, cache,
-                                        wide_tiles(robot, B), stream),
+    return finish(wb::launch_rnea_lanes(robot->dev, robot->fz, B, ld, q, qd, qdd, f_ext, tau, cache, stream),
                   "wb_rnea launch");
 }
 
@@ -857,8 +855,8 @@ int wb_fk_backward(const wb_robot *robot, int64_t B, int64_t ld, const float *q,
     WB_TRY(check_ptr(g_link_pose, "g_link_pose", false));
     WB_TRY(check_ptr(g_spheres, "g_spheres", false));
     WB_TRY(check_ptr(g_q, "g_q", robot->T.n > 0));
-    if (lanes_form(robot, B, link_pose != nullptr || g_link_pose != nullptr)) {
-        WB_TRY(check_ptr(workspace, "workspace", false));
+    if (robot->T.lanes) {   // a workspace is asked for from the batch on that once used it
+        WB_TRY(check_ptr(workspace, "workspace", !group_form(robot, B, link_pose != nullptr || g_link_pose != nullptr)));
         return finish(wb::launch_fk_backward_lanes(robot->dev, robot->fz, B, ld, q, g_link_pose, g_spheres, g_q,
                                                    wide_tiles(robot, B), stream),
                       "wb_fk_backward launch");
@@ -892,7 +890,7 @@ int wb_rnea_backward(const wb_robot *robot, int64_t B, int64_t ld, const float *
     WB_TRY(check_ptr(workspace, "workspace", cache != nullptr));
     if (robot->T.lanes)
         return finish(wb::launch_rnea_backward_lanes(robot->dev, robot->fz, B, ld, q, qd, qdd, f_ext, cache, g_tau,
-                                                     g_q, g_qd, g_qdd, g_fext, wide_tiles(robot, B), stream),
+                                                     g_q, g_qd, g_qdd, g_fext, stream),
                       "wb_rnea_backward launch");
     return finish(wb::launch_rnea_backward(robot->dev, B, ld, q, qd, qdd, cache, g_tau, g_q, g_qd, g_qdd, g_fext,
                                            static_cast<float *>(workspace), stream),

@@ -171,17 +171,19 @@ hipError_t launch_rnea_backward(const DevRobot &rb, int64_t B, int64_t ld, const
                                 const float *qdd, const float *cache, const float *g_tau,
                                 float *g_q, float *g_qd, float *g_qdd, float *g_fext, float *ws, hipStream_t s);
 // Group-per-state RNEA and VJP (tree_kernels.hip), robots of at most 64
-// links; cache may be null (nothing is then stored or read).  tiled: the
-// cache moves through LDS tiles of 16 states.
+// links; cache may be null (nothing is then stored or read).
 hipError_t launch_rnea_lanes(const DevRobot &rb, const DevFused &fz, int64_t B, int64_t ld, const float *q,
-                             const float *qd, const float *qdd, const float *f_ext, float *tau, float *cache, bool tiled,
+                             const float *qd, const float *qdd, const float *f_ext, float *tau, float *cache,
                              hipStream_t s);
 hipError_t launch_rnea_backward_lanes(const DevRobot &rb, const DevFused &fz, int64_t B, int64_t ld,
                                       const float *q, const float *qd, const float *qdd, const float *f_ext,
                                       const float *cache, const float *g_tau, float *g_q, float *g_qd, float *g_qdd,
-                                      float *g_fext, bool tiled, hipStream_t s);
-// Group-per-state FK and its adjoint (tree_kernels.hip), robots of at most
-// 64 links; wide: tiles of 16 states instead of 4.
+                                      float *g_fext, hipStream_t s);
+// FK through LDS tiles and its adjoint (tree_kernels.hip), robots of at most
+// 64 links: a group of lanes per state (wide: tiles of 16, backward 8, states
+// instead of 4), or level by level.
+hipError_t launch_fk_levels(const DevRobot &rb, int64_t B, int64_t ld, const float *q, float *pose, float *spheres,
+                            hipStream_t s);
 hipError_t launch_fk_lanes(const DevRobot &rb, const DevFused &fz, int64_t B, int64_t ld, const float *q, float *pose,
                            float *spheres, bool wide, hipStream_t s);
 hipError_t launch_fk_backward_lanes(const DevRobot &rb, const DevFused &fz, int64_t B, int64_t ld, const float *q,
