@@ -257,7 +257,7 @@ int wb_self_collision(const wb_robot *robot, int64_t B, int64_t ld, const float 
  * dispatches FK kernels by robot size; here the forms are chosen by batch
  * size, with thresholds the autotuner measures):
  *   sweep_split_below     wb_self_collision takes the one-state-per-workgroup
- *                         form for batches of fewer states (default 16 per
+ *                         form for batches of fewer states (default 2 per
  *                         compute unit of the robot's device);
  *   fk_groups_below       wb_fk without link poses takes one group of lanes
  *                         per state (pointer jumping) for batches of fewer

@@ -1,17 +1,43 @@
-// Standalone self-collision kernel (cuRoboV2 Sec. 6.2): stages the sphere
-// centres of a tile of states in LDS and sweeps each state with one
-// wavefront (sweep.h).
+// Standalone self-collision kernels (cuRoboV2 Sec. 6.2): a state's sphere
+// centres are staged in LDS and swept by one wavefront, or by the four of a
+// workgroup (sweep.h).
 #include <algorithm>
 #include "sweep.h"
 
 namespace wb {
 
-// LDS: TS states x [(L+1)*NMAX slots | (L+1) link bounds], then 4 lists of
-// rb.list_cap ints and 4 row rings of SWEEP_ROW_RING words (one of each per
-// wavefront), then (TAB_LDS) the block table.
+// The sphere slots' radii (they stay from state to state) and the padding
+// link's empty bound.
+template <int NMAX>
+__device__ __forceinline__ void init_slots(const DevRobot &rb, float4 *P, int tid, int nt) {
+    const int SL = (rb.L + 1) * NMAX;
+    for (int i = tid; i < SL; i += nt) P[i] = make_float4(0.f, 0.f, 0.f, rb.slot_r[i]);
+    if (tid == 0) P[SL + rb.L] = make_float4(0.f, 0.f, 0.f, -1e30f);
+}
+
+// The block table as entries of type E, in LDS.
+template <typename E>
+__device__ __forceinline__ void stage_blocks(const DevRobot &rb, E *tab, int tid, int nt) {
+    for (int i = tid; i < rb.n_blocks_pad; i += nt) {
+        const int ab = rb.blocks[i];
+        tab[i] = (E)PairCode<E>::make(ab >> 16, ab & 0xffff);
+    }
+}
+
+// One state per wavefront, four side by side: a workgroup takes `chunk`
+// consecutive states (a multiple of four).  The slots' radii and the block
+// table are staged once a workgroup, the centres of four states at a time by
+// all its lanes, the rows in 16-byte pieces (chunks are dealt so that each
+// XCD's L2 holds the rows' other pieces).  Bound by VALU issue of the sweep,
+// as in the fused kernel; with the radii, the table and two integer
+// divisions an element staged for every four states, and their rows fetched
+// through every XCD, the humanoid's 24,576 states took 163 us.
+// LDS: four states x [(L+1)*NMAX slots | L+1 link bounds], then per wavefront
+// a list of rb.list_cap entries, the row rings, and (TAB_LDS) the block table.
 // nb: states; B: row length of the sphere array (the ABI's ld >= nb).
-template <int NMAX, bool TAB_LDS>
-__global__ void __launch_bounds__(256) k_self_collision(DevRobot rb, int64_t nb, int64_t B, int TS,
+// TS: 4, or 1 for the largest robots, of which 64 KB hold one state.
+template <int NMAX, bool TAB_LDS, typename E, int TS>
+__global__ void __launch_bounds__(256) k_self_collision(DevRobot rb, int64_t nb, int64_t B, int chunk,
                                                         const float *__restrict__ sph,
                                                         float *__restrict__ max_pen,
                                                         int32_t *__restrict__ argmax,
@@ -19,38 +45,33 @@ __global__ void __launch_bounds__(256) k_self_collision(DevRobot rb, int64_t nb,
     extern __shared__ float4 lds[];
     const int SL = (rb.L + 1) * NMAX;
     const int SLB = SL + rb.L + 1;
-    const int64_t b0 = (int64_t)blockIdx.x * TS;
-    const int tid = threadIdx.x;
-    int *lists = reinterpret_cast<int *>(lds + TS * SLB);
-    uint32_t *rings = reinterpret_cast<uint32_t *>(lists + 4 * rb.list_cap);
-    const int *tab = rb.blocks;
+    const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63;
+    uint32_t *rings = reinterpret_cast<uint32_t *>(lds + TS * SLB);
+    E *lists = reinterpret_cast<E *>(rings + 4 * SWEEP_ROW_RING);
+    const E *tab = reinterpret_cast<const E *>(rb.blocks);   // without TAB_LDS, E is the table's own 32 bits
     if (TAB_LDS) {
-        int *t = reinterpret_cast<int *>(rings + 4 * SWEEP_ROW_RING);
-        for (int i = tid; i < rb.n_blocks_pad; i += 256) t[i] = rb.blocks[i];
+        E *t = lists + 4 * rb.list_cap;
+        stage_blocks(rb, t, tid, 256);
         tab = t;
     }
-    for (int i = tid; i < TS * SLB; i += 256) {
-        const int st = i / SLB, o = i - st * SLB;
-        lds[i] = make_float4(0.f, 0.f, 0.f, o < SL ? rb.slot_r[o] : -1e30f);
-    }
-    __syncthreads();
-    const int n3 = rb.S * 3;
-    for (int i = tid; i < n3 * TS; i += 256) {
-        const int st = i % TS, sc = i / TS;
-        const int64_t b = b0 + st;
-        if (b < nb) {
-            const int s = sc / 3, c = sc - 3 * s;
-            reinterpret_cast<float *>(&lds[st * SLB + rb.sph_slot[s]])[c] = sph[(int64_t)sc * B + b];
+    float4 *P = lds + wave * SLB;
+    if (wave < TS) init_slots<NMAX>(rb, P, lane, 64);
+    const int64_t c0 = (int64_t)xcd_chunk() * chunk, c1 = min(c0 + chunk, nb);
+    for (int64_t b0 = c0; b0 < c1; b0 += TS) {
+        __syncthreads();   // the slots and the table are staged; the previous four states are swept
+        {
+            const int st = tid % TS;
+            const int64_t b = min(b0 + st, nb - 1);
+            float *slots = reinterpret_cast<float *>(lds + st * SLB);
+#pragma unroll 4
+            for (int row = tid / TS; row < 3 * rb.S; row += 256 / TS) {
+                const int s = row / 3;
+                slots[rb.sph_slot[s] * 4 + (row - 3 * s)] = sph[(int64_t)row * B + b];
+            }
         }
-    }
-    __syncthreads();
-
-    const int wave = tid >> 6, lane = tid & 63;
-    int *list = lists + wave * rb.list_cap;
-    for (int st = wave; st < TS; st += 4) {
-        const int64_t b = b0 + st;
-        if (b >= nb) break;
-        float4 *P = lds + st * SLB;
+        __syncthreads();
+        const int64_t b = b0 + wave;
+        if (wave >= TS || b >= c1) continue;
         float4 *Bd = P + SL;
         link_bounds<NMAX>(rb, P, Bd, lane, 64);
         __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");
@@ -58,7 +79,8 @@ __global__ void __launch_bounds__(256) k_self_collision(DevRobot rb, int64_t nb,
         float M;
         int key;
         unsigned cnt;
-        sweep_state<NMAX, true>(rb, tab, P, Bd, list, rings + wave * SWEEP_ROW_RING, lane, 64, 0, M, key, cnt);
+        sweep_state<NMAX, true>(rb, tab, P, Bd, lists + wave * rb.list_cap, rings + wave * SWEEP_ROW_RING, lane, 64,
+                                0, M, key, cnt);
         if (lane == 0) {
             if (max_pen) max_pen[b] = M;
             if (argmax) argmax[b] = pair_index(rb, key);
@@ -70,10 +92,10 @@ __global__ void __launch_bounds__(256) k_self_collision(DevRobot rb, int64_t nb,
 // One state per workgroup, its pairs split over the four wavefronts and
 // reduced through LDS (sweep_state_wg): for batches too small to fill the
 // chip with one state per wavefront, and for robots with many pairs.
-// LDS: [(L+1)*NMAX slots | L+1 link bounds] (float4), then 4 lists of 128
-// entries, the block table (int32) and 8 words for the reductions.
-template <int NMAX>
-__global__ void __launch_bounds__(256) k_self_collision_wg(DevRobot rb, int64_t nb, int64_t B,
+// LDS: [(L+1)*NMAX slots | L+1 link bounds] (float4), 8 words for the
+// reductions, 4 row rings, 4 lists of `cap` entries and (TAB_LDS) the table.
+template <int NMAX, bool TAB_LDS, typename E>
+__global__ void __launch_bounds__(256) k_self_collision_wg(DevRobot rb, int64_t nb, int64_t B, int cap,
                                                            const float *__restrict__ sph,
                                                            float *__restrict__ max_pen,
                                                            int32_t *__restrict__ argmax,
@@ -82,18 +104,23 @@ __global__ void __launch_bounds__(256) k_self_collision_wg(DevRobot rb, int64_t 
     const int SL = (rb.L + 1) * NMAX;
     float4 *P = lds;
     float4 *Bd = P + SL;
-    int *lists = reinterpret_cast<int *>(Bd + rb.L + 1);
-    int *tab = lists + 4 * 128;
-    float *red = reinterpret_cast<float *>(tab + rb.n_blocks_pad);
+    float *red = reinterpret_cast<float *>(Bd + rb.L + 1);
+    uint32_t *rings = reinterpret_cast<uint32_t *>(red + 8);
+    E *lists = reinterpret_cast<E *>(rings + 4 * SWEEP_ROW_RING);
     const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63;
-    for (int i = tid; i < rb.n_blocks_pad; i += 256) tab[i] = rb.blocks[i];
+    const E *tab = reinterpret_cast<const E *>(rb.blocks);
+    if (TAB_LDS) {
+        E *t = lists + 4 * cap;
+        stage_blocks(rb, t, tid, 256);
+        tab = t;
+    }
+    init_slots<NMAX>(rb, P, tid, 256);
     for (int64_t b = blockIdx.x; b < nb; b += gridDim.x) {
-        for (int i = tid; i < SL; i += 256) P[i] = make_float4(0.f, 0.f, 0.f, rb.slot_r[i]);
-        if (tid == 0) Bd[rb.L] = make_float4(0.f, 0.f, 0.f, -1e30f);
-        __syncthreads();
+        __syncthreads();   // staged; the previous state is swept
+#pragma unroll 4
         for (int i = tid; i < rb.S * 3; i += 256) {
-            const int sph_i = i / 3, c = i - 3 * sph_i;
-            reinterpret_cast<float *>(&P[rb.sph_slot[sph_i]])[c] = sph[(int64_t)i * B + b];
+            const int s = i / 3;
+            reinterpret_cast<float *>(P)[rb.sph_slot[s] * 4 + (i - 3 * s)] = sph[(int64_t)i * B + b];
         }
         __syncthreads();
         link_bounds<NMAX>(rb, P, Bd, tid, 256);
@@ -101,68 +128,61 @@ __global__ void __launch_bounds__(256) k_self_collision_wg(DevRobot rb, int64_t 
         float M;
         int key;
         unsigned cnt;
-        sweep_state_wg<NMAX>(rb, tab, P, Bd, lists + wave * 128, red, wave, lane, M, key, cnt);
+        sweep_state_wg<NMAX>(rb, tab, P, Bd, lists + wave * cap, cap, rings + wave * SWEEP_ROW_RING, red, wave, lane, M,
+                             key, cnt);
         if (tid == 0) {
             if (max_pen) max_pen[b] = M;
             if (argmax) argmax[b] = pair_index(rb, key);
             if (n_coll) n_coll[b] = (int32_t)cnt;
         }
-        __syncthreads();   // the slots are rewritten for the next state
     }
 }
 
-size_t self_collision_wg_lds(int L, int nmax, int n_blocks_pad) {
-    return state_lds_bytes(L, nmax) + (size_t)4 * 128 * 4 + (size_t)n_blocks_pad * 4 + 8 * 4;
-}
+// LDS of the wavefronts' row rings and, in entries of `es` bytes, lists.
+static size_t sc_lists_bytes(int list_cap, size_t es) { return (size_t)16 * SWEEP_ROW_RING + 4 * es * list_cap; }
 
-// States per workgroup that fit the LDS limit next to `fixed` bytes.
-static int sc_tile(size_t per_state, size_t fixed) {
-    int ts = (int)((LDS_LIMIT - fixed) / per_state);
-    if (ts > 16) ts = 16;
-    if (ts >= 4) ts &= ~3;
-    if (ts < 1) ts = 1;
-    return ts;
-}
-
-// LDS of the four wavefronts' lists and row rings.
-static size_t sc_lists_bytes(int list_cap) { return (size_t)16 * list_cap + (size_t)16 * SWEEP_ROW_RING; }
-
-int self_collision_tile(int L, int nmax, int list_cap) {
-    return sc_tile(state_lds_bytes(L, nmax), sc_lists_bytes(list_cap));
-}
-
-// The block table goes to LDS when one state, the four lists and the table
-// fit; otherwise the lists shrink to fit beside one state and the table is
-// read from device memory.
+// 16-bit entries and the block table in LDS where the robot has at most 255
+// links and that fits; else 32-bit entries, the table read from device memory
+// and the lists shrunk to fit beside four states, or beside one.
 template <int NMAX>
 static hipError_t launch_sc(const DevRobot &rb0, int64_t B, int64_t ld, const float *sph, float *mp, int32_t *am,
                             int32_t *nc, hipStream_t s) {
     DevRobot rb = rb0;
-    const size_t per_state = state_lds_bytes(rb.L, NMAX);
-    const size_t tab = (size_t)rb.n_blocks_pad * 4;
-    dim3 block(256);
-    if (per_state + sc_lists_bytes(rb.list_cap) + tab <= LDS_LIMIT) {
-        const int TS = sc_tile(per_state, sc_lists_bytes(rb.list_cap) + tab);
-        const size_t lds = (size_t)TS * per_state + sc_lists_bytes(rb.list_cap) + tab;
-        dim3 grid((unsigned)((B + TS - 1) / TS));
-        hipLaunchKernelGGL((k_self_collision<NMAX, true>), grid, block, lds, s, rb, B, ld, TS, sph, mp, am, nc);
-    } else {
-        const int room = (int)((LDS_LIMIT - per_state - (size_t)16 * SWEEP_ROW_RING) / 16) / 128 * 128;
-        if (room < rb.list_cap) rb.list_cap = room;
-        const int TS = self_collision_tile(rb.L, NMAX, rb.list_cap);
-        const size_t lds = (size_t)TS * per_state + sc_lists_bytes(rb.list_cap);
-        dim3 grid((unsigned)((B + TS - 1) / TS));
-        hipLaunchKernelGGL((k_self_collision<NMAX, false>), grid, block, lds, s, rb, B, ld, TS, sph, mp, am, nc);
+    const size_t state = state_lds_bytes(rb.L, NMAX);
+    // chunks of up to 32 states that leave 2,048 workgroups
+    const int chunk = (int)std::max<int64_t>(std::min<int64_t>(32, B / 2048) / 4 * 4, 4);
+    const dim3 grid((unsigned)((B + chunk - 1) / chunk)), block(256);
+    const size_t small = 4 * state + sc_lists_bytes(rb.list_cap, 2) + tab_lds_bytes(rb.n_blocks_pad);
+    if (rb.L <= 255 && small <= LDS_LIMIT) {
+        hipLaunchKernelGGL((k_self_collision<NMAX, true, uint16_t, 4>), grid, block, small, s, rb, B, ld, chunk, sph, mp, am, nc);
+        return hipGetLastError();
     }
+    const int ts = 4 * state + sc_lists_bytes(128, 4) <= LDS_LIMIT ? 4 : 1;
+    rb.list_cap = std::min(rb.list_cap, (int)((LDS_LIMIT - ts * state - (size_t)16 * SWEEP_ROW_RING) / 16) / 128 * 128);
+    const size_t lds = ts * state + sc_lists_bytes(rb.list_cap, 4);
+    if (ts == 4) hipLaunchKernelGGL((k_self_collision<NMAX, false, int, 4>), grid, block, lds, s, rb, B, ld, chunk, sph, mp, am, nc);
+    else hipLaunchKernelGGL((k_self_collision<NMAX, false, int, 1>), grid, block, lds, s, rb, B, ld, chunk, sph, mp, am, nc);
     return hipGetLastError();
 }
 
+// The same choice of entries; a wavefront's list holds its share of the
+// blocks, up to 512 at a time.  Robots whose state leaves no room for it
+// take the other form.
 template <int NMAX>
 static hipError_t launch_sc_wg(const DevRobot &rb, int64_t B, int64_t ld, const float *sph, float *mp, int32_t *am,
                                int32_t *nc, hipStream_t s) {
-    const size_t lds = self_collision_wg_lds(rb.L, NMAX, rb.n_blocks_pad);
-    const unsigned grid = (unsigned)std::min<int64_t>(B, 1 << 20);
-    hipLaunchKernelGGL((k_self_collision_wg<NMAX>), dim3(grid), dim3(256), lds, s, rb, B, ld, sph, mp, am, nc);
+    const size_t fixed = state_lds_bytes(rb.L, NMAX) + 8 * 4;
+    const int cap = std::min((rb.n_blocks_pad / 128 + 3) / 4 * 128, 512);
+    const dim3 grid((unsigned)std::min<int64_t>(B, 1 << 20)), block(256);
+    const size_t small = fixed + sc_lists_bytes(std::max(cap, 128), 2) + tab_lds_bytes(rb.n_blocks_pad);
+    if (rb.L <= 255 && small <= LDS_LIMIT)
+        hipLaunchKernelGGL((k_self_collision_wg<NMAX, true, uint16_t>), grid, block, small, s, rb, B, ld,
+                           std::max(cap, 128), sph, mp, am, nc);
+    else if (fixed + sc_lists_bytes(128, 4) <= LDS_LIMIT)
+        hipLaunchKernelGGL((k_self_collision_wg<NMAX, false, int>), grid, block, fixed + sc_lists_bytes(128, 4), s, rb, B, ld,
+                           128, sph, mp, am, nc);
+    else
+        return launch_sc<NMAX>(rb, B, ld, sph, mp, am, nc, s);
     return hipGetLastError();
 }
 

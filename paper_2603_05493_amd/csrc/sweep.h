@@ -53,6 +53,7 @@
 #pragma once
 
 #include <climits>
+#include <type_traits>
 #include "lanes.h"
 #include "spatial.h"
 
@@ -148,11 +149,9 @@ __device__ __forceinline__ bool may_reach(const float4 *Bd, int a, int b, float 
 }
 
 // Appends to list[0, nl) the link pairs of blocks [c0, cend) that pass the
-// pass-1 test (PASS1) or, for pass 2, fail it with bound >= lo; returns nl.
-// cend - c0 is a multiple of 2G and every entry below cend is a table entry.
-// MODE 1: the pass-1 test; 2: blocks that fail it with bound >= lo (pass 2
-// of the row-by-row sweep); 3: every block with bound >= lo (pass 2 of the
-// row-culled sweep, which filters the rows itself).
+// pass's test; returns nl.  cend - c0 is a multiple of 2G and every entry
+// below cend is a table entry.  MODE 1: the pass-1 test; 3: every block with
+// bound >= lo (pass 2, whose row sweep filters the rows itself).
 template <int MODE, typename E>
 __device__ __forceinline__ int compact_blocks(const E *tab, const float4 *Bd, E *list, int c0, int cend, float eps,
                                               float lo, int glane, int G, int gshift, uint64_t gmask) {
@@ -169,10 +168,6 @@ __device__ __forceinline__ int compact_blocks(const E *tab, const float4 *Bd, E 
         } else {
             s0 = may_reach(Bd, PC::a(ab0), PC::b(ab0), eps);
             s1 = may_reach(Bd, PC::a(ab1), PC::b(ab1), eps);
-            if (MODE == 2) {
-                s0 = !s0 && block_bound(Bd, PC::a(ab0), PC::b(ab0)) >= lo;
-                s1 = !s1 && block_bound(Bd, PC::a(ab1), PC::b(ab1)) >= lo;
-            }
         }
         const uint64_t m0 = (__ballot(s0) >> gshift) & gmask;
         const uint64_t m1 = (__ballot(s1) >> gshift) & gmask;
@@ -182,38 +177,6 @@ __device__ __forceinline__ int compact_blocks(const E *tab, const float4 *Bd, E 
         nl += n0 + __popcll(m1);
     }
     return nl;
-}
-
-// Pair loop over the rows of list[0, nl): running maximum, the row where it
-// was set (link pair * NMAX + slot), whether it was met twice, and the count.
-template <int NMAX, bool FULL, typename E>
-__device__ __forceinline__ void sweep_rows(const DevRobot &rb, const float4 *P, const E *list, int nl, int glane,
-                                           int G, float &best, int &best_code, bool &tie, unsigned &cnt) {
-    typedef PairCode<E> PC;
-    const int items = nl * NMAX;
-    for (int j0 = 0; j0 < items; j0 += G) {
-        const int it = j0 + glane;
-        const bool ok = it < items;
-        const int e = it / NMAX, row = it - e * NMAX;
-        const int ab = ok ? (int)list[e] : PC::make(rb.L, rb.L);
-        const int a = PC::a(ab), bb = PC::b(ab);
-        const float4 A = P[a * NMAX + row];
-        float m = -INFINITY;
-#pragma unroll
-        for (int k = 0; k < NMAX; ++k) {
-            const float pen = pair_pen(A, P[bb * NMAX + k]);
-            m = fmaxf(m, pen);
-            if (FULL) cnt += (unsigned)__popcll(__ballot(pen > 0.0f));
-            else cnt += pen > 0.0f ? 1u : 0u;
-        }
-        if (m > best) {
-            best = m;
-            best_code = ok ? ab * NMAX + row : -1;
-            tie = false;
-        } else if (m == best) {
-            tie = true;
-        }
-    }
 }
 
 // Row test: sphere slot A against link bound Bb may hold a pair reaching
@@ -403,12 +366,13 @@ __device__ __forceinline__ void sweep_state(const DevRobot &rb, const E *tab, co
 // paper's two-stage self-collision split over wavefronts, then a second
 // reduce through LDS): the block table's 128-entry chunks are dealt
 // round-robin to the wavefronts (chunk c to wavefront c % 4); each compacts
-// and sweeps its chunks as sweep_state does with G = 64 (one chunk at a
-// time, so its list holds 128 entries), and the workgroup combines the
-// wavefronts' maxima, counts and argmax keys.  Pass 2, the seed block and
-// the tie rescan follow the single-wavefront rules with workgroup-wide
-// values, so the result is the full sweep's.  red: 8 words of LDS.  Every
-// thread of the workgroup must call this (it synchronizes the workgroup).
+// its chunks into its list (cap entries, at least 128) and sweeps their rows
+// as sweep_state does with G = 64, and the workgroup combines the wavefronts'
+// maxima, counts and argmax keys.  Pass 2, the seed block and the tie rescan
+// follow the single-wavefront rules with workgroup-wide values, so the result
+// is the full sweep's.  red: 8 words of LDS; ring: the wavefront's own.
+// Every thread of the workgroup must call this (it synchronizes the
+// workgroup).
 __device__ __forceinline__ float wg_max4(float v, float *red, int wave, int lane) {
     if (lane == 0) red[wave] = v;
     __syncthreads();
@@ -426,8 +390,8 @@ __device__ __forceinline__ int wg_min4(int v, int *red, int wave, int lane) {
 
 template <int NMAX, typename E>
 __device__ __forceinline__ void sweep_state_wg(const DevRobot &rb, const E *tab, const float4 *P, const float4 *Bd,
-                                               E *list, float *red, int wave, int lane, float &M_out, int &key_out,
-                                               unsigned &cnt_out) {
+                                               E *list, int cap, uint32_t *ring, float *red, int wave, int lane,
+                                               float &M_out, int &key_out, unsigned &cnt_out) {
     typedef PairCode<E> PC;
     const int n = rb.n_blocks;
     const int nb = (n + 127) / 128 * 128;   // <= n_blocks_pad
@@ -444,14 +408,24 @@ __device__ __forceinline__ void sweep_state_wg(const DevRobot &rb, const E *tab,
     int best_code = -1;
     bool tie = false;
     unsigned cnt = 0;
-    for (int c0 = wave * 128; c0 < nb; c0 += 4 * 128) {
-        const int nl = compact_blocks<1>(tab, Bd, list, c0, c0 + 128, eps, 0.f, lane, 64, 0, ~0ull);
-        __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");
-        __builtin_amdgcn_wave_barrier();
-        sweep_rows<NMAX, true>(rb, P, list, nl, lane, 64, best, best_code, tie, cnt);
-        __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");
-        __builtin_amdgcn_wave_barrier();
-    }
+    // the wavefront's chunks through its list, the rows swept when it is full
+    auto sweep_chunks = [&](auto pass2, float lo) {
+        constexpr bool PASS2 = decltype(pass2)::value;
+        int nl = 0;
+        for (int c0 = wave * 128; c0 < nb; c0 += 4 * 128) {
+            nl += compact_blocks<PASS2 ? 3 : 1>(tab, Bd, list + nl, c0, c0 + 128, eps, lo, lane, 64, 0, ~0ull);
+            if (nl + 128 > cap || c0 + 4 * 128 >= nb) {
+                __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");
+                __builtin_amdgcn_wave_barrier();
+                sweep_rows_culled<NMAX, true, PASS2>(P, Bd, list, nl, ring, eps, lo, lane, 64, 0, ~0ull, best, best_code,
+                                                     tie, cnt);
+                __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");
+                __builtin_amdgcn_wave_barrier();
+                nl = 0;
+            }
+        }
+    };
+    sweep_chunks(std::false_type{}, 0.f);
     float M = wg_max4(group_reduce_max(best, 64), red, wave, lane);
     if (!(M >= 0.f) && n > 0) {
         float lb = M;
@@ -482,14 +456,7 @@ __device__ __forceinline__ void sweep_state_wg(const DevRobot &rb, const E *tab,
             lb = group_reduce_max(seed, 64);   // the same in every wavefront
         }
         const float theta1 = lb - eps;
-        for (int c0 = wave * 128; c0 < nb; c0 += 4 * 128) {
-            const int nl = compact_blocks<2>(tab, Bd, list, c0, c0 + 128, eps, theta1, lane, 64, 0, ~0ull);
-            __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");
-            __builtin_amdgcn_wave_barrier();
-            sweep_rows<NMAX, true>(rb, P, list, nl, lane, 64, best, best_code, tie, cnt);
-            __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");
-            __builtin_amdgcn_wave_barrier();
-        }
+        sweep_chunks(std::true_type{}, theta1);
         M = wg_max4(group_reduce_max(best, 64), red, wave, lane);
     }
     int key = INT_MAX;
@@ -502,8 +469,8 @@ __device__ __forceinline__ void sweep_state_wg(const DevRobot &rb, const E *tab,
                 key = min(key, block_min_key<NMAX>(rb, P, PC::a(ab), PC::b(ab), M));
             }
     } else if (holder) {
-        const int ab = best_code / NMAX;
-        key = row_min_key<NMAX>(rb, P, PC::a(ab), PC::b(ab), best_code - ab * NMAX, M);
+        const int sa = best_code >> 16, a = sa / NMAX;
+        key = row_min_key<NMAX>(rb, P, a, (best_code & 0xffff) / NMAX, sa - a * NMAX, M);
     }
     M_out = M;
     key_out = wg_min4(group_reduce_min(key, 64), redi, wave, lane);

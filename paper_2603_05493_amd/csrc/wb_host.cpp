@@ -791,10 +791,13 @@ int wb_rnea(const wb_robot *robot, int64_t B, int64_t ld, const float *q, const 
 namespace {
 // wb_self_collision's form for a batch: one state per workgroup (its pairs
 // split over the four wavefronts) below the robot's threshold, one state
-// per wavefront above.  Default threshold: 16 states per compute unit (below
-// it one state per wavefront leaves most SIMDs with under four wavefronts).
+// per wavefront above.  Default threshold: 2 states per compute unit, below
+// which one state per wavefront leaves SIMDs without work (humanoid, wave
+// against split form: 11.7 / 8.7 us at 256 states, 13.3 / 11.9 at 1,000,
+// 13.4 / 20.5 at 2,048; smaller trees cross earlier, its 588-sphere form
+// 23.9 / 16.5, 29.2 / 28.5, 33.2 / 40.3).
 bool sweep_split(const wb_robot *r, int64_t B) {
-    const int64_t below = r->sweep_split_below >= 0 ? r->sweep_split_below : (int64_t)16 * r->cus;
+    const int64_t below = r->sweep_split_below >= 0 ? r->sweep_split_below : (int64_t)2 * r->cus;
     return B < below;
 }
 }  // namespace

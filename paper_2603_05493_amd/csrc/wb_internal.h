@@ -192,7 +192,6 @@ hipError_t launch_fk_backward_lanes(const DevRobot &rb, const DevFused &fz, int6
 // (else one state per wavefront).
 hipError_t launch_self_collision(const DevRobot &rb, int64_t B, int64_t ld, const float *spheres,
                                  float *max_pen, int32_t *argmax, int32_t *n_coll, bool split, hipStream_t s);
-size_t self_collision_wg_lds(int L, int nmax, int n_blocks_pad);
 hipError_t launch_self_collision_backward(const DevRobot &rb, int64_t B, int64_t ld, const float *spheres,
                                           const int32_t *argmax, const float *max_pen,
                                           float margin, const float *g_cost, float *g_sph,
@@ -244,9 +243,6 @@ constexpr size_t LDS_LIMIT = 65536;
 // Sphere slots per link the fused kernels are instantiated for: 1 to 8, and
 // 12 (links of up to 12 spheres are padded to 12 slots).
 constexpr int FUSED_MAX_SLOTS = 12;
-
-// States per workgroup of the self-collision kernel (LDS tile).
-int self_collision_tile(int L, int nmax, int list_cap);
 
 // Workspace floats per state needed by the backward kernels.
 inline int64_t workspace_floats_per_state(int L) { return (int64_t)L * 18 + 8; }
