@@ -52,6 +52,7 @@
 //   runs the cost head, and its tau-bar returns to each link as m_l tau-bar_j;
 //   the per-link adjoints (q-bar, qd-bar, qdd-bar) come back the same way,
 //   each scaled by m_l, and lane j writes joint j's outputs and step.
+#include <algorithm>
 #include "spline.h"
 #include "sweep.h"
 #include "tree.h"
@@ -73,9 +74,9 @@ namespace wb {
 // group at a time per partial, states in a fixed order: deterministic).
 // With SPL the state is sample t of trajectory traj (b = traj * H + t).
 template <int NMAX, bool FULL, bool EXT, int SPL>
-__device__ __forceinline__ void iterate_state(const DevRobot &rb, const uint16_t *tab, const DevFused &fz,
+__device__ __forceinline__ void iterate_state(const DevRobot &rb, const uint32_t *tab, const DevFused &fz,
                                               const TreeIO &io, const SplineIn &sp, const StepScalars &k,
-                                              float4 *P, float4 *Bd, uint16_t *list, float *gpart, int G, int grp,
+                                              float4 *P, float4 *Bd, uint32_t *list, float *gpart, int G, int grp,
                                               int glane, int64_t B, int64_t b, bool valid, int traj, int t) {
     int gl = glane;
     asm volatile("" : "+v"(gl));   // keeps the table reads inside the state loop
@@ -165,7 +166,7 @@ __device__ __forceinline__ void iterate_state(const DevRobot &rb, const uint16_t
     int key;
     unsigned cnt;
     // the group's row ring follows its list
-    sweep_state<NMAX, FULL>(rb, tab, P, Bd, list, reinterpret_cast<uint32_t *>(list + rb.list_cap), glane, G, grp, M,
+    sweep_state<NMAX, FULL, true>(rb, tab, P, Bd, list, list + sweep_list(rb.n_blocks, G), glane, G, grp, M,
                             key, cnt);
     const float hmarg = M + k.margin;
     const bool hinge_on = key != INT_MAX && hmarg > 0.f && k.hinge_weight != 0.f;
@@ -309,28 +310,28 @@ __device__ __forceinline__ void iterate_state(const DevRobot &rb, const uint16_t
     }
 }
 
-// Process `count` states starting at b0 of one robot with the 4 waves of
-// this workgroup, 64/G states per wavefront at a time; tab is the robot's
-// block table staged in LDS.  GSEL: 64 builds only the one-state-per-
-// wavefront path (G must be 64), 0 only the path for G = 16 or 32, -1 both
-// (a plan mixes trees of every G).  A kernel holding one path keeps far
-// fewer values live across the state loop (the two paths' scalars spilled
-// to VGPR lanes and were re-read per state).
-template <int NMAX, bool EXT, int SPL, int GSEL>
-__device__ __forceinline__ void run_states(const DevRobot &rb, const uint16_t *tab, const DevFused &fz, const TreeIO &io,
+// Process `count` states starting at b0 of one robot with the NW wavefronts
+// of this workgroup, 64/G states per wavefront at a time; tab is the robot's
+// block table.  GSEL: 64 builds only the one-state-per-wavefront path (G must
+// be 64), 0 only the path for G = 16 or 32, -1 both (a plan mixes trees of
+// every G).  A kernel holding one path keeps far fewer values live across the
+// state loop (the two paths' scalars spilled to VGPR lanes and were re-read
+// per state).
+template <int NMAX, bool EXT, int SPL, int GSEL, int NW>
+__device__ __forceinline__ void run_states(const DevRobot &rb, const uint32_t *tab, const DevFused &fz, const TreeIO &io,
                                            const SplineIn &sp, const StepScalars &k, float4 *lds_wave,
                                            float *gparts, int G, int64_t B, int64_t b0, int count, int traj) {
-    const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
+    const int wave = NW > 1 ? threadIdx.x >> 6 : 0, lane = threadIdx.x & 63;
     const int per_wave = 64 / G, grp = lane / G, glane = lane - grp * G;
     const int SL = (rb.L + 1) * NMAX;
-    float4 *P = lds_wave + grp * (int)(group_lds_bytes(rb.L, NMAX, rb.list_cap) / 16);
+    float4 *P = lds_wave + grp * (int)(group_lds_bytes(rb.L, NMAX, rb.n_blocks, G) / 16);
     float4 *Bd = P + SL;
-    uint16_t *list = reinterpret_cast<uint16_t *>(Bd + rb.L + 1);
+    uint32_t *list = reinterpret_cast<uint32_t *>(Bd + rb.L + 1);
     wave_sync();
     for (int i = glane; i < SL; i += G) P[i] = make_float4(0.f, 0.f, 0.f, rb.slot_r[i]);
     // links without spheres (and the padding link L) keep an empty bounding sphere
     for (int i = glane; i <= rb.L; i += G) Bd[i] = make_float4(0.f, 0.f, 0.f, -1e30f);
-    for (int base = wave * per_wave; base < count; base += 4 * per_wave) {
+    for (int base = wave * per_wave; base < count; base += NW * per_wave) {
         const int s = base + grp;
         const bool valid = s < count;
         const int64_t b = b0 + (valid ? s : base);
@@ -352,13 +353,9 @@ __device__ __forceinline__ void run_states(const DevRobot &rb, const uint16_t *t
     }
 }
 
-// The robot's block table into LDS as 16-bit link pairs (a << 8) | b (the
-// fused kernels take at most 64 links); padding entries become (L, L).
-__device__ __forceinline__ void stage_table(const DevRobot &rb, uint16_t *tab) {
-    for (int i = threadIdx.x; i < rb.n_blocks_pad; i += 256) {
-        const int ab = rb.blocks[i];
-        tab[i] = (uint16_t)PairCode<uint16_t>::make(ab >> 16, ab & 0xffff);
-    }
+// The robot's block table into LDS.
+__device__ __forceinline__ void stage_table(const DevRobot &rb, uint32_t *tab) {
+    for (int i = threadIdx.x; i < rb.n_blocks_pad; i += 256) tab[i] = rb.blocks[i];
 }
 
 // The control-point gradient of the workgroup's trajectory (SPL == 2): the
@@ -406,32 +403,42 @@ __device__ __forceinline__ void spline_reduce_step(const SplineIn &sp, const flo
 template <int NMAX, bool EXT>
 constexpr int fused_waves() { return NMAX > 8 ? 2 : 4; }
 
+// One wavefront a workgroup: the states' sweeps differ in length, and a
+// wavefront's slot and LDS are free for the next as soon as it ends, where
+// four in one workgroup waited for the slowest; the block table is then read
+// through the L1, which holds it with the lane tables.  The control-point
+// gradient (SPL == 2) takes four, which share a trajectory.
+template <int SPL>
+constexpr int fused_wg_waves() { return SPL == 2 ? 4 : 1; }
+
 template <int NMAX, bool EXT, int SPL, int GSEL>
-__global__ void __launch_bounds__(256, (fused_waves<NMAX, EXT>())) k_fused_step(FusedArgs A) {
+__global__ void __launch_bounds__(64 * fused_wg_waves<SPL>(), (fused_waves<NMAX, EXT>())) k_fused_step(FusedArgs A) {
     extern __shared__ float4 lds[];
-    const int wave = threadIdx.x >> 6;
+    constexpr int NW = fused_wg_waves<SPL>();
+    const int wave = NW > 1 ? threadIdx.x >> 6 : 0;
     const int G = GSEL == 64 ? 64 : A.lanes_per_state;
-    const int SLW = (64 / G) * (int)(group_lds_bytes(A.rb.L, NMAX, A.rb.list_cap) / 16);
+    const int SLW = (64 / G) * (int)(group_lds_bytes(A.rb.L, NMAX, A.rb.n_blocks, G) / 16);
     const int chunk = xcd_chunk();
     const int64_t b0 = (int64_t)chunk * A.chunk;
     const int64_t rem = A.B - b0;
     const int count = rem < A.chunk ? (int)rem : A.chunk;
-    uint16_t *tab = reinterpret_cast<uint16_t *>(lds + 4 * SLW);
+    if (NW == 1) {
+        run_states<NMAX, EXT, SPL, GSEL, 1>(A.rb, A.rb.blocks, A.fz, A.io, A.sp, A.k, lds, nullptr, G, A.io.ld, b0, count,
+                                            0);
+        return;
+    }
+    uint32_t *tab = reinterpret_cast<uint32_t *>(lds + 4 * SLW);
     // the control-point partial sums follow the block table (n_blocks_pad is a multiple of 128)
     float *gparts = reinterpret_cast<float *>(tab + A.rb.n_blocks_pad);
     const int nparts = 256 / G, d = A.rb.n;
     stage_table(A.rb, tab);
-    if (SPL == 2)
-        for (int i = threadIdx.x; i < nparts * d * (A.sp.K + 6); i += 256) gparts[i] = 0.f;
+    for (int i = threadIdx.x; i < nparts * d * (A.sp.K + 6); i += 256) gparts[i] = 0.f;
     __syncthreads();
-    // with SPL == 2 each workgroup owns one trajectory (chunk == H)
-    const int traj = SPL == 2 ? chunk : 0;
-    run_states<NMAX, EXT, SPL, GSEL>(A.rb, tab, A.fz, A.io, A.sp, A.k, lds + wave * SLW, gparts, G, A.io.ld, b0, count,
-                               traj);
-    if (SPL == 2) {
-        __syncthreads();
-        spline_reduce_step(A.sp, gparts, gparts + nparts * d * (A.sp.K + 6), d, nparts, traj);
-    }
+    // each workgroup owns one trajectory (chunk == H)
+    run_states<NMAX, EXT, SPL, GSEL, NW>(A.rb, tab, A.fz, A.io, A.sp, A.k, lds + wave * SLW, gparts, G, A.io.ld, b0,
+                                         count, chunk);
+    __syncthreads();
+    spline_reduce_step(A.sp, gparts, gparts + nparts * d * (A.sp.K + 6), d, nparts, chunk);
 }
 
 // A plan tree's descriptors, read from device memory, with every table
@@ -467,7 +474,7 @@ __global__ void __launch_bounds__(256) k_plan_step(PlanArgs A) {
     extern __shared__ float4 lds[];
     const int wave = threadIdx.x >> 6;
     const int w = blockIdx.x;
-    uint16_t *tab = reinterpret_cast<uint16_t *>(lds + 4 * A.wave_stride);
+    uint32_t *tab = reinterpret_cast<uint32_t *>(lds + 4 * A.wave_stride);
     int staged = -1;   // tree whose block table is in LDS
     for (int it = A.item_start[w]; it < A.item_start[w + 1]; ++it) {
         const PlanItem item = A.items[it];
@@ -480,31 +487,36 @@ __global__ void __launch_bounds__(256) k_plan_step(PlanArgs A) {
             staged = item.tree;
         }
         // a fixed region per wave, sized for the plan's largest tree
-        run_states<NMAX, EXT, 0, -1>(T.rb, tab, T.fz, A.io[item.tree], SplineIn{}, A.k, lds + wave * A.wave_stride,
+        run_states<NMAX, EXT, 0, -1, 4>(T.rb, tab, T.fz, A.io[item.tree], SplineIn{}, A.k, lds + wave * A.wave_stride,
                                  nullptr, G, A.io[item.tree].ld,
                               item.b0, item.count, 0);
     }
 }
 
 template <int NMAX, int GSEL>
-static hipError_t launch_fused_g(const FusedArgs &a, size_t lds, unsigned nwg, hipStream_t s) {
+static hipError_t launch_fused_g(const FusedArgs &a0, hipStream_t s) {
+    FusedArgs a = a0;
     const bool reduce = a.sp.U && (a.sp.g_U || a.sp.lr != 0.f);
-    if (reduce) {
-        lds += spline_lds_bytes(a.lanes_per_state, a.rb.n, a.sp.K);
-        hipLaunchKernelGGL((k_fused_step<NMAX, false, 2, GSEL>), dim3(nwg), dim3(256), lds, s, a);
-    } else if (a.sp.U)
-        hipLaunchKernelGGL((k_fused_step<NMAX, false, 1, GSEL>), dim3(nwg), dim3(256), lds, s, a);
+    const int waves = reduce ? fused_wg_waves<2>() : 1;
+    // a one-wavefront workgroup takes its share of the four's states
+    if (!reduce) a.chunk = std::max((a.chunk + 3) / 4, 1);
+    const int per_wave = 64 / a.lanes_per_state;
+    if (!reduce) a.chunk = (a.chunk + per_wave - 1) / per_wave * per_wave;
+    const size_t lds = fused_lds_bytes(a.rb.L, NMAX, a.rb.n_blocks, a.lanes_per_state, waves);
+    const dim3 grid((unsigned)((a.B + a.chunk - 1) / a.chunk)), block(64 * waves);
+    if (reduce)
+        hipLaunchKernelGGL((k_fused_step<NMAX, false, 2, GSEL>), grid, block,
+                           lds + spline_lds_bytes(a.lanes_per_state, a.rb.n, a.sp.K), s, a);
+    else if (a.sp.U) hipLaunchKernelGGL((k_fused_step<NMAX, false, 1, GSEL>), grid, block, lds, s, a);
     else if (a.io.f_ext || a.io.g_fext || a.fz.mimic)
-        hipLaunchKernelGGL((k_fused_step<NMAX, true, 0, GSEL>), dim3(nwg), dim3(256), lds, s, a);
-    else hipLaunchKernelGGL((k_fused_step<NMAX, false, 0, GSEL>), dim3(nwg), dim3(256), lds, s, a);
+        hipLaunchKernelGGL((k_fused_step<NMAX, true, 0, GSEL>), grid, block, lds, s, a);
+    else hipLaunchKernelGGL((k_fused_step<NMAX, false, 0, GSEL>), grid, block, lds, s, a);
     return hipGetLastError();
 }
 
 template <int NMAX>
 static hipError_t launch_fused_t(const FusedArgs &a, hipStream_t s) {
-    const size_t lds = fused_lds_bytes(a.rb.L, NMAX, a.rb.list_cap, a.lanes_per_state, a.rb.n_blocks_pad);
-    const unsigned nwg = (unsigned)((a.B + a.chunk - 1) / a.chunk);
-    return a.lanes_per_state == 64 ? launch_fused_g<NMAX, 64>(a, lds, nwg, s) : launch_fused_g<NMAX, 0>(a, lds, nwg, s);
+    return a.lanes_per_state == 64 ? launch_fused_g<NMAX, 64>(a, s) : launch_fused_g<NMAX, 0>(a, s);
 }
 
 hipError_t launch_fused(const FusedArgs &a, hipStream_t s) {

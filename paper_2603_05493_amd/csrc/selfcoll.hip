@@ -6,6 +6,8 @@
 
 namespace wb {
 
+constexpr int SC_RING = 128;   // the row ring of a 64-lane group
+
 // The sphere slots' radii (they stay from state to state) and the padding
 // link's empty bound.
 template <int NMAX>
@@ -15,13 +17,9 @@ __device__ __forceinline__ void init_slots(const DevRobot &rb, float4 *P, int ti
     if (tid == 0) P[SL + rb.L] = make_float4(0.f, 0.f, 0.f, -1e30f);
 }
 
-// The block table as entries of type E, in LDS.
-template <typename E>
-__device__ __forceinline__ void stage_blocks(const DevRobot &rb, E *tab, int tid, int nt) {
-    for (int i = tid; i < rb.n_blocks_pad; i += nt) {
-        const int ab = rb.blocks[i];
-        tab[i] = (E)PairCode<E>::make(ab >> 16, ab & 0xffff);
-    }
+// The block table into LDS.
+__device__ __forceinline__ void stage_blocks(const DevRobot &rb, uint32_t *tab, int tid, int nt) {
+    for (int i = tid; i < rb.n_blocks_pad; i += nt) tab[i] = rb.blocks[i];
 }
 
 // One state per wavefront, four side by side: a workgroup takes `chunk`
@@ -32,11 +30,11 @@ __device__ __forceinline__ void stage_blocks(const DevRobot &rb, E *tab, int tid
 // as in the fused kernel; with the radii, the table and two integer
 // divisions an element staged for every four states, and their rows fetched
 // through every XCD, the humanoid's 24,576 states took 163 us.
-// LDS: four states x [(L+1)*NMAX slots | L+1 link bounds], then per wavefront
-// a list of rb.list_cap entries, the row rings, and (TAB_LDS) the block table.
+// LDS: four states x [(L+1)*NMAX slots | L+1 link bounds], then the row
+// rings, (TAB_LDS) the block table and the wavefronts' lists.
 // nb: states; B: row length of the sphere array (the ABI's ld >= nb).
 // TS: 4, or 1 for the largest robots, of which 64 KB hold one state.
-template <int NMAX, bool TAB_LDS, typename E, int TS>
+template <int NMAX, bool TAB_LDS, int TS>
 __global__ void __launch_bounds__(256) k_self_collision(DevRobot rb, int64_t nb, int64_t B, int chunk,
                                                         const float *__restrict__ sph,
                                                         float *__restrict__ max_pen,
@@ -46,14 +44,10 @@ __global__ void __launch_bounds__(256) k_self_collision(DevRobot rb, int64_t nb,
     const int SL = (rb.L + 1) * NMAX;
     const int SLB = SL + rb.L + 1;
     const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63;
-    uint32_t *rings = reinterpret_cast<uint32_t *>(lds + TS * SLB);
-    E *lists = reinterpret_cast<E *>(rings + 4 * SWEEP_ROW_RING);
-    const E *tab = reinterpret_cast<const E *>(rb.blocks);   // without TAB_LDS, E is the table's own 32 bits
-    if (TAB_LDS) {
-        E *t = lists + 4 * rb.list_cap;
-        stage_blocks(rb, t, tid, 256);
-        tab = t;
-    }
+    uint32_t *rings = reinterpret_cast<uint32_t *>(lds + TS * SLB), *t = rings + 4 * SC_RING;
+    const uint32_t *tab = TAB_LDS ? t : rb.blocks;
+    uint32_t *lists = TAB_LDS ? t + rb.n_blocks_pad : t;
+    if (TAB_LDS) stage_blocks(rb, t, tid, 256);
     float4 *P = lds + wave * SLB;
     if (wave < TS) init_slots<NMAX>(rb, P, lane, 64);
     const int64_t c0 = (int64_t)xcd_chunk() * chunk, c1 = min(c0 + chunk, nb);
@@ -79,7 +73,7 @@ __global__ void __launch_bounds__(256) k_self_collision(DevRobot rb, int64_t nb,
         float M;
         int key;
         unsigned cnt;
-        sweep_state<NMAX, true>(rb, tab, P, Bd, lists + wave * rb.list_cap, rings + wave * SWEEP_ROW_RING, lane, 64,
+        sweep_state<NMAX, true, false>(rb, tab, P, Bd, lists + wave * SWEEP_LIST, rings + wave * SC_RING, lane, 64,
                                 0, M, key, cnt);
         if (lane == 0) {
             if (max_pen) max_pen[b] = M;
@@ -93,9 +87,9 @@ __global__ void __launch_bounds__(256) k_self_collision(DevRobot rb, int64_t nb,
 // reduced through LDS (sweep_state_wg): for batches too small to fill the
 // chip with one state per wavefront, and for robots with many pairs.
 // LDS: [(L+1)*NMAX slots | L+1 link bounds] (float4), 8 words for the
-// reductions, 4 row rings, 4 lists of `cap` entries and (TAB_LDS) the table.
-template <int NMAX, bool TAB_LDS, typename E>
-__global__ void __launch_bounds__(256) k_self_collision_wg(DevRobot rb, int64_t nb, int64_t B, int cap,
+// reductions, 4 row rings, (TAB_LDS) the table and 4 lists.
+template <int NMAX, bool TAB_LDS>
+__global__ void __launch_bounds__(256) k_self_collision_wg(DevRobot rb, int64_t nb, int64_t B,
                                                            const float *__restrict__ sph,
                                                            float *__restrict__ max_pen,
                                                            int32_t *__restrict__ argmax,
@@ -105,15 +99,11 @@ __global__ void __launch_bounds__(256) k_self_collision_wg(DevRobot rb, int64_t 
     float4 *P = lds;
     float4 *Bd = P + SL;
     float *red = reinterpret_cast<float *>(Bd + rb.L + 1);
-    uint32_t *rings = reinterpret_cast<uint32_t *>(red + 8);
-    E *lists = reinterpret_cast<E *>(rings + 4 * SWEEP_ROW_RING);
+    uint32_t *rings = reinterpret_cast<uint32_t *>(red + 8), *t = rings + 4 * SC_RING;
+    const uint32_t *tab = TAB_LDS ? t : rb.blocks;
+    uint32_t *lists = TAB_LDS ? t + rb.n_blocks_pad : t;
     const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63;
-    const E *tab = reinterpret_cast<const E *>(rb.blocks);
-    if (TAB_LDS) {
-        E *t = lists + 4 * cap;
-        stage_blocks(rb, t, tid, 256);
-        tab = t;
-    }
+    if (TAB_LDS) stage_blocks(rb, t, tid, 256);
     init_slots<NMAX>(rb, P, tid, 256);
     for (int64_t b = blockIdx.x; b < nb; b += gridDim.x) {
         __syncthreads();   // staged; the previous state is swept
@@ -128,7 +118,7 @@ __global__ void __launch_bounds__(256) k_self_collision_wg(DevRobot rb, int64_t 
         float M;
         int key;
         unsigned cnt;
-        sweep_state_wg<NMAX>(rb, tab, P, Bd, lists + wave * cap, cap, rings + wave * SWEEP_ROW_RING, red, wave, lane, M,
+        sweep_state_wg<NMAX>(rb, tab, P, Bd, lists + wave * SWEEP_LIST, rings + wave * SC_RING, red, wave, lane, M,
                              key, cnt);
         if (tid == 0) {
             if (max_pen) max_pen[b] = M;
@@ -138,51 +128,37 @@ __global__ void __launch_bounds__(256) k_self_collision_wg(DevRobot rb, int64_t 
     }
 }
 
-// LDS of the wavefronts' row rings and, in entries of `es` bytes, lists.
-static size_t sc_lists_bytes(int list_cap, size_t es) { return (size_t)16 * SWEEP_ROW_RING + 4 * es * list_cap; }
+// LDS of the four wavefronts' row rings and lists.
+constexpr size_t SC_SCRATCH = 4 * 4 * (SC_RING + SWEEP_LIST);
 
-// 16-bit entries and the block table in LDS where the robot has at most 255
-// links and that fits; else 32-bit entries, the table read from device memory
-// and the lists shrunk to fit beside four states, or beside one.
+// The block table goes to LDS where it fits beside four states, else it is
+// read from device memory; the largest robots' 64 KB hold one state, whose
+// list and ring alone are used.
 template <int NMAX>
-static hipError_t launch_sc(const DevRobot &rb0, int64_t B, int64_t ld, const float *sph, float *mp, int32_t *am,
+static hipError_t launch_sc(const DevRobot &rb, int64_t B, int64_t ld, const float *sph, float *mp, int32_t *am,
                             int32_t *nc, hipStream_t s) {
-    DevRobot rb = rb0;
-    const size_t state = state_lds_bytes(rb.L, NMAX);
+    const size_t state = state_lds_bytes(rb.L, NMAX), tab = tab_lds_bytes(rb.n_blocks_pad);
     // chunks of up to 32 states that leave 2,048 workgroups
     const int chunk = (int)std::max<int64_t>(std::min<int64_t>(32, B / 2048) / 4 * 4, 4);
     const dim3 grid((unsigned)((B + chunk - 1) / chunk)), block(256);
-    const size_t small = 4 * state + sc_lists_bytes(rb.list_cap, 2) + tab_lds_bytes(rb.n_blocks_pad);
-    if (rb.L <= 255 && small <= LDS_LIMIT) {
-        hipLaunchKernelGGL((k_self_collision<NMAX, true, uint16_t, 4>), grid, block, small, s, rb, B, ld, chunk, sph, mp, am, nc);
-        return hipGetLastError();
-    }
-    const int ts = 4 * state + sc_lists_bytes(128, 4) <= LDS_LIMIT ? 4 : 1;
-    rb.list_cap = std::min(rb.list_cap, (int)((LDS_LIMIT - ts * state - (size_t)16 * SWEEP_ROW_RING) / 16) / 128 * 128);
-    const size_t lds = ts * state + sc_lists_bytes(rb.list_cap, 4);
-    if (ts == 4) hipLaunchKernelGGL((k_self_collision<NMAX, false, int, 4>), grid, block, lds, s, rb, B, ld, chunk, sph, mp, am, nc);
-    else hipLaunchKernelGGL((k_self_collision<NMAX, false, int, 1>), grid, block, lds, s, rb, B, ld, chunk, sph, mp, am, nc);
+    if (4 * state + SC_SCRATCH + tab <= LDS_LIMIT)
+        hipLaunchKernelGGL((k_self_collision<NMAX, true, 4>), grid, block, 4 * state + SC_SCRATCH + tab, s, rb, B, ld, chunk, sph, mp, am, nc);
+    else if (4 * state + SC_SCRATCH <= LDS_LIMIT)
+        hipLaunchKernelGGL((k_self_collision<NMAX, false, 4>), grid, block, 4 * state + SC_SCRATCH, s, rb, B, ld, chunk, sph, mp, am, nc);
+    else
+        hipLaunchKernelGGL((k_self_collision<NMAX, false, 1>), grid, block, state + SC_SCRATCH, s, rb, B, ld, chunk, sph, mp, am, nc);
     return hipGetLastError();
 }
 
-// The same choice of entries; a wavefront's list holds its share of the
-// blocks, up to 512 at a time.  Robots whose state leaves no room for it
-// take the other form.
 template <int NMAX>
 static hipError_t launch_sc_wg(const DevRobot &rb, int64_t B, int64_t ld, const float *sph, float *mp, int32_t *am,
                                int32_t *nc, hipStream_t s) {
-    const size_t fixed = state_lds_bytes(rb.L, NMAX) + 8 * 4;
-    const int cap = std::min((rb.n_blocks_pad / 128 + 3) / 4 * 128, 512);
+    const size_t lds = state_lds_bytes(rb.L, NMAX) + 8 * 4 + SC_SCRATCH, tab = tab_lds_bytes(rb.n_blocks_pad);
     const dim3 grid((unsigned)std::min<int64_t>(B, 1 << 20)), block(256);
-    const size_t small = fixed + sc_lists_bytes(std::max(cap, 128), 2) + tab_lds_bytes(rb.n_blocks_pad);
-    if (rb.L <= 255 && small <= LDS_LIMIT)
-        hipLaunchKernelGGL((k_self_collision_wg<NMAX, true, uint16_t>), grid, block, small, s, rb, B, ld,
-                           std::max(cap, 128), sph, mp, am, nc);
-    else if (fixed + sc_lists_bytes(128, 4) <= LDS_LIMIT)
-        hipLaunchKernelGGL((k_self_collision_wg<NMAX, false, int>), grid, block, fixed + sc_lists_bytes(128, 4), s, rb, B, ld,
-                           128, sph, mp, am, nc);
+    if (lds + tab <= LDS_LIMIT)
+        hipLaunchKernelGGL((k_self_collision_wg<NMAX, true>), grid, block, lds + tab, s, rb, B, ld, sph, mp, am, nc);
     else
-        return launch_sc<NMAX>(rb, B, ld, sph, mp, am, nc, s);
+        hipLaunchKernelGGL((k_self_collision_wg<NMAX, false>), grid, block, lds, s, rb, B, ld, sph, mp, am, nc);
     return hipGetLastError();
 }
 

@@ -22,25 +22,26 @@
 //   of the block with the largest bound when pass 1 found nothing -- sets
 //   t1, and pass 2 sweeps the blocks that pass 1 skipped and whose bound is
 //   >= t1 - eps (the two passes partition the blocks exactly).
-// The surviving link pairs of each pass are compacted into the group's LDS
-// list (ballot + popcount), and the pair loop runs over rows -- (link pair,
-// sphere slot of the first link) against the NMAX slots of the second link
-// -- so that the lanes stay dense whatever the number of survivors.
+// The surviving blocks of each pass are compacted into the group's LDS list
+// (ballot + popcount), swept whenever it is full, and the pair loop runs over
+// rows -- (block, sphere slot of the first link) against the NMAX slots of
+// the second link -- so that the lanes stay dense whatever the number of
+// survivors.
 // Row test (the same broad phase one level down, in the per-group sweeps):
 // no pair of a row penetrates more than r_A + R_b - |c_A - C_b|, sphere A of
 // the first link against the second link's bounding sphere, so a row is
 // evaluated only where that bound may reach the pass's threshold.  Passing
-// rows are queued in a 128-entry LDS ring per group (ballot + popcount) and
+// rows are queued in an LDS ring of 2 G entries per group (ballot + popcount) and
 // evaluated G at a time, so the lanes stay dense.  Pass 2 then takes every
 // block whose bound reaches t1 - eps and, in it, the rows pass 1 did not
 // evaluate whose row bound reaches t1 - eps: the rows of the two passes
-// partition the rows of the table exactly, with the same eps argument.  Robots
-// with more blocks than the list holds are swept in chunks.  The block
+// partition the rows of the table exactly, with the same eps argument.  The block
 // table is read from LDS where the caller has staged it; it is padded to a
 // multiple of 128 entries with the empty pair (L, L), whose bounding sphere
-// Bd[L] has radius -1e30, so the pass-1 loop needs no range tests.  Table and
-// list entries are link pairs packed as (a << SH) | b in an entry type E:
-// 32-bit with SH = 16, or 16-bit with SH = 8 for robots of at most 255 links.
+// Bd[L] has radius -1e30, so the pass-1 loop needs no range tests.  Entries
+// are byte offsets of the links' bounds and lists hold table indices, of 16
+// bits for robots of at most 255 links: unpacking link numbers took 5 of a
+// test's 28 vector instructions, and the fused kernel is bound by their issue.
 //
 // Reduce: the pair count is a scalar ballot popcount per pair (one state per
 // wavefront) or a per-lane counter summed over the group; the maximum is a
@@ -67,16 +68,16 @@ __device__ __forceinline__ float pair_pen(float4 A, float4 Bv) {
     return (A.w + Bv.w) - __builtin_amdgcn_sqrtf(d2);
 }
 
-template <typename E>
-struct PairCode {
-    static constexpr int SH = sizeof(E) == 2 ? 8 : 16;
-    static __device__ __forceinline__ int a(int ab) { return ab >> SH; }
-    static __device__ __forceinline__ int b(int ab) { return ab & ((1 << SH) - 1); }
-    static __device__ __forceinline__ int make(int a, int b) { return (a << SH) | b; }
-};
+// A block table entry holds the byte offsets of its two links' bounding
+// spheres, (16 a) << 16 | 16 b, so that one add each forms an address.
+__device__ __forceinline__ const float4 &bound_of(const float4 *Bd, uint32_t off) {
+    return *reinterpret_cast<const float4 *>(reinterpret_cast<const char *>(Bd) + off);
+}
+__device__ __forceinline__ int entry_a(uint32_t e) { return (int)(e >> 20); }
+__device__ __forceinline__ int entry_b(uint32_t e) { return (int)((e >> 4) & 0xfffu); }
 
-__device__ __forceinline__ float block_bound(const float4 *Bd, int a, int b) {
-    const float4 A = Bd[a], Bv = Bd[b];
+__device__ __forceinline__ float block_bound(const float4 *Bd, uint32_t e) {
+    const float4 A = bound_of(Bd, e >> 16), Bv = bound_of(Bd, e & 0xffffu);
     const float dx = A.x - Bv.x, dy = A.y - Bv.y, dz = A.z - Bv.z;
     return (A.w + Bv.w) - __builtin_amdgcn_sqrtf(__builtin_fmaf(dx, dx, __builtin_fmaf(dy, dy, dz * dz)));
 }
@@ -139,52 +140,49 @@ __device__ __forceinline__ void link_bounds(const DevRobot &rb, const float4 *P,
 // Pass-1 test: block (a, b) may hold a pair whose penetration reaches -eps,
 // |C_a - C_b| <= R_a + R_b + eps, as one compare without a square root:
 // d2 <= s |s| is false for every s < 0 (d2 >= 0), so the empty pair (L, L)
-// never passes.
-__device__ __forceinline__ bool may_reach(const float4 *Bd, int a, int b, float eps) {
-    const float4 A = Bd[a], Bv = Bd[b];
+// never passes.  PADDED: the bounds' radii hold the margin already.
+template <bool PADDED>
+__device__ __forceinline__ bool may_reach(const float4 *Bd, uint32_t e, float eps) {
+    const float4 A = bound_of(Bd, e >> 16), Bv = bound_of(Bd, e & 0xffffu);
     const float dx = A.x - Bv.x, dy = A.y - Bv.y, dz = A.z - Bv.z;
-    const float s = (A.w + Bv.w) + eps;
+    const float s = PADDED ? A.w + Bv.w : (A.w + Bv.w) + eps;
     const float d2 = __builtin_fmaf(dx, dx, __builtin_fmaf(dy, dy, dz * dz));
     return d2 <= s * fabsf(s);
 }
 
-// Appends to list[0, nl) the link pairs of blocks [c0, cend) that pass the
-// pass's test; returns nl.  cend - c0 is a multiple of 2G and every entry
-// below cend is a table entry.  MODE 1: the pass-1 test; 3: every block with
-// bound >= lo (pass 2, whose row sweep filters the rows itself).
-template <int MODE, typename E>
-__device__ __forceinline__ int compact_blocks(const E *tab, const float4 *Bd, E *list, int c0, int cend, float eps,
-                                              float lo, int glane, int G, int gshift, uint64_t gmask) {
-    typedef PairCode<E> PC;
+// Bits of the group's ballot m (its lanes' predicate, shifted down to the
+// group) below this lane.
+template <bool FULL>
+__device__ __forceinline__ int bits_below(uint64_t m, uint64_t below) {
+    if (FULL) return (int)__builtin_amdgcn_mbcnt_hi((uint32_t)(m >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)m, 0u));
+    return __popcll(m & below);
+}
+
+// Appends to the list of nl entries those of the 2 G blocks at tab[k] that
+// pass the pass's test; returns the new length.  PASS2: every block with
+// bound >= lo (the row sweep filters the rows itself), else the pass-1 test.
+template <bool PASS2, bool FULL, bool PADDED>
+__device__ __forceinline__ int append_blocks(const uint32_t *tab, const float4 *Bd, uint32_t *list, int nl, int k,
+                                             float eps, float lo, int glane, int G, int gshift, uint64_t gmask) {
     const uint64_t below = (1ull << glane) - 1ull;
-    int nl = 0;
-    for (int base = c0; base < cend; base += 2 * G) {
-        const int k0 = base + glane, k1 = k0 + G;
-        const int ab0 = tab[k0], ab1 = tab[k1];
-        bool s0, s1;
-        if (MODE == 3) {
-            s0 = block_bound(Bd, PC::a(ab0), PC::b(ab0)) >= lo;
-            s1 = block_bound(Bd, PC::a(ab1), PC::b(ab1)) >= lo;
-        } else {
-            s0 = may_reach(Bd, PC::a(ab0), PC::b(ab0), eps);
-            s1 = may_reach(Bd, PC::a(ab1), PC::b(ab1), eps);
-        }
-        const uint64_t m0 = (__ballot(s0) >> gshift) & gmask;
-        const uint64_t m1 = (__ballot(s1) >> gshift) & gmask;
-        const int n0 = __popcll(m0);
-        if (s0) list[nl + __popcll(m0 & below)] = (E)ab0;
-        if (s1) list[nl + n0 + __popcll(m1 & below)] = (E)ab1;
-        nl += n0 + __popcll(m1);
-    }
-    return nl;
+    const uint32_t e0 = tab[k + glane], e1 = tab[k + glane + G];
+    const bool s0 = PASS2 ? block_bound(Bd, e0) >= lo : may_reach<PADDED>(Bd, e0, eps);
+    const bool s1 = PASS2 ? block_bound(Bd, e1) >= lo : may_reach<PADDED>(Bd, e1, eps);
+    const uint64_t m0 = FULL ? __ballot(s0) : (__ballot(s0) >> gshift) & gmask;
+    const uint64_t m1 = FULL ? __ballot(s1) : (__ballot(s1) >> gshift) & gmask;
+    const int n0 = nl + __popcll(m0);
+    if (s0) list[nl + bits_below<FULL>(m0, below)] = e0;
+    if (s1) list[n0 + bits_below<FULL>(m1, below)] = e1;
+    return n0 + __popcll(m1);
 }
 
 // Row test: sphere slot A against link bound Bb may hold a pair reaching
 // -eps (squared, as may_reach; an empty slot never passes), and the row
 // bound itself.
+template <bool PADDED>
 __device__ __forceinline__ bool row_may_reach(float4 A, float4 Bb, float eps) {
     const float dx = A.x - Bb.x, dy = A.y - Bb.y, dz = A.z - Bb.z;
-    const float s = (A.w + Bb.w) + eps;
+    const float s = PADDED ? A.w + Bb.w : (A.w + Bb.w) + eps;
     const float d2 = __builtin_fmaf(dx, dx, __builtin_fmaf(dy, dy, dz * dz));
     return d2 <= s * fabsf(s);
 }
@@ -193,18 +191,19 @@ __device__ __forceinline__ float row_bound(float4 A, float4 Bb) {
     return (A.w + Bb.w) - __builtin_amdgcn_sqrtf(__builtin_fmaf(dx, dx, __builtin_fmaf(dy, dy, dz * dz)));
 }
 
-constexpr int ROW_RING = SWEEP_ROW_RING;   // queued rows per group (a power of two, >= 2 G - 1)
+constexpr uint32_t NO_ROW = ~0u;           // no row code (offsets are multiples of 16)
 
-// Evaluates the n queued rows at ring[head, head + n) (mod ROW_RING), one
-// per lane; a row code is (slot of A) << 16 | (first slot of the second
-// link), and best_code keeps the code of the row that set the running max.
+// Evaluates the n queued rows at ring[head, head + n) (mod 2 G), one
+// per lane; a row code is the byte offset of slot A << 16 | that of the
+// second link's first slot, and best_code keeps the code of the row that set
+// the running max.
 template <int NMAX, bool FULL>
-__device__ __forceinline__ void eval_rows(const float4 *P, const uint32_t *ring, int head, int n, int glane,
-                                          float &best, int &best_code, bool &tie, unsigned &cnt) {
+__device__ __forceinline__ void eval_rows(const float4 *P, const uint32_t *ring, int head, int n, int glane, int G,
+                                          float &best, uint32_t &best_code, bool &tie, unsigned &cnt) {
     if (glane < n) {
-        const uint32_t code = ring[(head + glane) & (ROW_RING - 1)];
-        const float4 A = P[code >> 16];
-        const float4 *Bp = P + (code & 0xffffu);
+        const uint32_t code = ring[(head + glane) & (2 * G - 1)];
+        const float4 A = bound_of(P, code >> 16);
+        const float4 *Bp = &bound_of(P, code & 0xffffu);
         float m = -INFINITY;
 #pragma unroll
         for (int k = 0; k < NMAX; ++k) {
@@ -215,7 +214,7 @@ __device__ __forceinline__ void eval_rows(const float4 *P, const uint32_t *ring,
         }
         if (m > best) {
             best = m;
-            best_code = (int)code;
+            best_code = code;
             tie = false;
         } else if (m == best) {
             tie = true;
@@ -223,87 +222,110 @@ __device__ __forceinline__ void eval_rows(const float4 *P, const uint32_t *ring,
     }
 }
 
-// The rows of list[0, nl) that pass the row test (pass 1: may reach -eps;
-// PASS2: row bound >= lo and not evaluated by pass 1), queued in the ring
-// and evaluated G at a time: running maximum, its row code, ties, count.
-template <int NMAX, bool FULL, bool PASS2, typename E>
-__device__ __forceinline__ void sweep_rows_culled(const float4 *P, const float4 *Bd, const E *list, int nl,
-                                                  uint32_t *ring, float eps, float lo, int glane, int G, int gshift,
-                                                  uint64_t gmask, float &best, int &best_code, bool &tie,
-                                                  unsigned &cnt) {
-    typedef PairCode<E> PC;
+// The rows of the blocks list[0, nl) that pass the row test (pass 1: may
+// reach -eps; PASS2: row bound >= lo and not evaluated by pass 1), queued in
+// the ring and evaluated G at a time: running maximum, its row code, ties,
+// count.  Lane i takes rows i, i + G, ...: its list entry and slot advance by
+// the quotient and remainder of G by NMAX.
+template <int NMAX, bool FULL, bool PASS2, bool PADDED>
+__device__ __forceinline__ void sweep_rows_culled(const float4 *P, const float4 *Bd, const uint32_t *list, int nl,
+                                                  uint32_t *ring, float eps, float lo, int glane, int G, int gshift, uint64_t gmask, float &best,
+                                                  uint32_t &best_code, bool &tie, unsigned &cnt) {
     const uint64_t below = (1ull << glane) - 1ull;
-    const int items = nl * NMAX;
+    const int items = nl * NMAX, dq = G / NMAX, dr = G - dq * NMAX;
     int head = 0, pending = 0;   // the same in every lane of the group
+    int i = glane / NMAX, row = glane - i * NMAX;
     for (int j0 = 0; j0 < items; j0 += G) {
-        const int it = j0 + glane;
         bool pass = false;
         uint32_t code = 0;
-        if (it < items) {
-            const int e = it / NMAX, row = it - e * NMAX;
-            const int ab = list[e];
-            const int a = PC::a(ab), bb = PC::b(ab);
-            const float4 A = P[a * NMAX + row], Bb = Bd[bb];
-            const bool may = row_may_reach(A, Bb, eps);
-            pass = PASS2 ? (row_bound(A, Bb) >= lo && !(may && may_reach(Bd, a, bb, eps))) : may;
-            code = ((uint32_t)(a * NMAX + row) << 16) | (uint32_t)(bb * NMAX);
+        if (i < nl) {
+            const uint32_t e = list[i];
+            const uint32_t a = (e >> 16) * NMAX + row * 16;
+            const float4 A = bound_of(P, a), Bb = bound_of(Bd, e & 0xffffu);
+            const bool may = row_may_reach<PADDED>(A, Bb, eps);
+            pass = PASS2 ? (row_bound(A, Bb) >= lo && !(may && may_reach<PADDED>(Bd, e, eps))) : may;
+            code = (a << 16) | ((e & 0xffffu) * NMAX);
         }
-        const uint64_t m = (__ballot(pass) >> gshift) & gmask;
-        if (pass) ring[(head + pending + __popcll(m & below)) & (ROW_RING - 1)] = code;
+        i += dq;
+        row += dr;
+        if (row >= NMAX) {
+            row -= NMAX;
+            ++i;
+        }
+        const uint64_t m = FULL ? __ballot(pass) : (__ballot(pass) >> gshift) & gmask;
+        if (pass) ring[(head + pending + bits_below<FULL>(m, below)) & (2 * G - 1)] = code;
         pending += __popcll(m);
         if (pending >= G) {
             __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");
             __builtin_amdgcn_wave_barrier();
-            eval_rows<NMAX, FULL>(P, ring, head, G, glane, best, best_code, tie, cnt);
-            head = (head + G) & (ROW_RING - 1);
+            eval_rows<NMAX, FULL>(P, ring, head, G, glane, G, best, best_code, tie, cnt);
+            head = (head + G) & (2 * G - 1);
             pending -= G;
         }
     }
     __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");
     __builtin_amdgcn_wave_barrier();
-    if (pending > 0) eval_rows<NMAX, FULL>(P, ring, head, pending, glane, best, best_code, tie, cnt);
+    if (pending > 0) eval_rows<NMAX, FULL>(P, ring, head, pending, glane, G, best, best_code, tie, cnt);
 }
 
-// Sweep one state.  tab: the robot's block table (rb.blocks, or an LDS copy
-// in the entry type E); P: the state's (L+1)*NMAX sphere slots; Bd: its link
-// bounding spheres; list: rb.list_cap entries of LDS scratch for this group.
+// Lowest key of the row that best_code names.
+template <int NMAX>
+__device__ __forceinline__ int code_min_key(const DevRobot &rb, const float4 *P, uint32_t code, float M) {
+    const int sa = (int)(code >> 20), a = sa / NMAX;
+    return row_min_key<NMAX>(rb, P, a, (int)((code & 0xffffu) >> 4) / NMAX, sa - a * NMAX, M);
+}
+
+// Sweep one state.  tab: the robot's block table (or its LDS copy); P: the
+// state's (L+1)*NMAX sphere slots; Bd: its link bounding spheres; list:
+// sweep_list entries of LDS scratch for this group, swept whenever it is
+// full.
 // Every lane of the group returns the maximum penetration M, the sphere key
 // s*S + t of the lowest pair attaining it (INT_MAX if none) and the number
-// of pairs with positive penetration.  FULL: G == 64.  ring: ROW_RING words
-// of LDS scratch for this group (the row-culled sweep).
-template <int NMAX, bool FULL, typename E>
-__device__ __forceinline__ void sweep_state(const DevRobot &rb, const E *tab, const float4 *P, const float4 *Bd,
-                                            E *list, uint32_t *ring, int glane, int G, int grp, float &M_out,
-                                            int &key_out, unsigned &cnt_out) {
-    typedef PairCode<E> PC;
+// of pairs with positive penetration.  FULL: G == 64.  ring: sweep_ring
+// words of LDS scratch for this group.  PADDED: the bounds' radii hold the rounding
+// margin of any state already, else it is formed from the state's extent.
+template <int NMAX, bool FULL, bool PADDED>
+__device__ __forceinline__ void sweep_state(const DevRobot &rb, const uint32_t *tab, const float4 *P,
+                                            const float4 *Bd, uint32_t *list, uint32_t *ring, int glane, int G,
+                                            int grp, float &M_out, int &key_out, unsigned &cnt_out) {
     const int n = rb.n_blocks;
     const int nb = (n + 2 * G - 1) / (2 * G) * (2 * G);   // <= n_blocks_pad, a multiple of 128
-    const int cap = rb.list_cap;                          // a multiple of 128
+    const int cap = min(nb, SWEEP_LIST);                  // sweep_list
     const uint64_t gmask = FULL ? ~0ull : ((1ull << G) - 1ull);
     const int gshift = FULL ? 0 : grp * G;
-    // extent of the robot in this state, for the rounding margin
-    float ext = 0.f;
-    for (int a = glane; a < rb.L; a += G) {
-        const float4 c = Bd[a];
-        if (c.w > -1e29f)
-            ext = fmaxf(ext, __builtin_amdgcn_sqrtf(__builtin_fmaf(c.x, c.x, __builtin_fmaf(c.y, c.y, c.z * c.z))) + c.w);
+    float eps = 0.f;
+    if (!PADDED) {   // extent of the robot in this state, for the rounding margin
+        float ext = 0.f;
+        for (int a = glane; a < rb.L; a += G) {
+            const float4 c = Bd[a];
+            if (c.w > -1e29f)
+                ext = fmaxf(ext, __builtin_amdgcn_sqrtf(__builtin_fmaf(c.x, c.x, __builtin_fmaf(c.y, c.y, c.z * c.z))) + c.w);
+        }
+        eps = 4e-6f * (1.f + group_reduce_max(ext, G));
     }
-    const float eps = 4e-6f * (1.f + group_reduce_max(ext, G));
 
     float best = -INFINITY;
-    int best_code = -1;
+    uint32_t best_code = NO_ROW;
     bool tie = false;
     unsigned cnt = 0;
-    // pass 1: blocks that may hold a collision
-    for (int c0 = 0; c0 < nb; c0 += cap) {
-        const int nl = compact_blocks<1>(tab, Bd, list, c0, min(c0 + cap, nb), eps, 0.f, glane, G, gshift, gmask);
-        __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");
-        __builtin_amdgcn_wave_barrier();
-        sweep_rows_culled<NMAX, FULL, false>(P, Bd, list, nl, ring, eps, 0.f, glane, G, gshift, gmask, best,
-                                             best_code, tie, cnt);
-        __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");
-        __builtin_amdgcn_wave_barrier();
-    }
+    auto sweep_blocks = [&](auto pass2, float lo) {
+        constexpr bool PASS2 = decltype(pass2)::value;
+        int nl = 0;
+        for (int k = 0; k < nb; k += 2 * G) {
+            nl = append_blocks<PASS2, FULL, PADDED>(tab, Bd, list, nl, k, eps, lo, glane, G, gshift, gmask);
+            const bool full = nl + 2 * G > cap;
+            if (k + 2 * G >= nb || (FULL ? full : __ballot(full) != 0)) {
+                __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");
+                __builtin_amdgcn_wave_barrier();
+                sweep_rows_culled<NMAX, FULL, PASS2, PADDED>(P, Bd, list, nl, ring, eps, lo, glane, G, gshift, gmask,
+                                                             best, best_code, tie, cnt);
+                __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");
+                __builtin_amdgcn_wave_barrier();
+                nl = 0;
+            }
+        }
+    };
+    sweep_blocks(std::false_type{}, 0.f);   // pass 1: blocks that may hold a collision
     float M = group_reduce_max(best, G);
     if (!(M >= 0.f) && n > 0) {
         // pass 2 (no collision): a lower bound of M, then the skipped blocks that can reach it
@@ -312,8 +334,7 @@ __device__ __forceinline__ void sweep_state(const DevRobot &rb, const E *tab, co
             float bmax = -INFINITY;
             int bblk = INT_MAX;
             for (int k = glane; k < n; k += G) {
-                const int ab = tab[k];
-                const float d = block_bound(Bd, PC::a(ab), PC::b(ab));
+                const float d = block_bound(Bd, tab[k]);
                 if (d > bmax) {
                     bmax = d;
                     bblk = k;
@@ -323,8 +344,8 @@ __device__ __forceinline__ void sweep_state(const DevRobot &rb, const E *tab, co
             const int cand = group_reduce_min(bmax == gbmax ? bblk : INT_MAX, G);
             float seed = -INFINITY;
             if (cand != INT_MAX) {   // no candidate only when every bound is NaN
-                const int ab = tab[cand];
-                const int a = PC::a(ab), bb = PC::b(ab);
+                const uint32_t e = tab[cand];
+                const int a = entry_a(e), bb = entry_b(e);
                 for (int j = glane; j < NMAX * NMAX; j += G) {
                     const int i = j / NMAX, k = j - i * NMAX;
                     seed = fmaxf(seed, pair_pen(P[a * NMAX + i], P[bb * NMAX + k]));
@@ -333,29 +354,19 @@ __device__ __forceinline__ void sweep_state(const DevRobot &rb, const E *tab, co
             lb = group_reduce_max(seed, G);
         }
         const float theta1 = lb - eps;
-        for (int c0 = 0; c0 < nb; c0 += cap) {
-            const int nl = compact_blocks<3>(tab, Bd, list, c0, min(c0 + cap, nb), eps, theta1, glane, G, gshift,
-                                             gmask);
-            __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");
-            __builtin_amdgcn_wave_barrier();
-            sweep_rows_culled<NMAX, FULL, true>(P, Bd, list, nl, ring, eps, theta1, glane, G, gshift, gmask, best,
-                                                best_code, tie, cnt);
-            __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");
-            __builtin_amdgcn_wave_barrier();
-        }
+        sweep_blocks(std::true_type{}, theta1);
         M = group_reduce_max(best, G);
     }
     int key = INT_MAX;
-    const bool holder = best == M && M > -INFINITY && best_code >= 0;
+    const bool holder = best == M && M > -INFINITY && best_code != NO_ROW;
     const bool rescan = group_reduce_min((holder && tie) ? 0 : 1, G) == 0;
     if (rescan) {
         for (int blk = glane; blk < n; blk += G) {
-            const int ab = tab[blk];
-            key = min(key, block_min_key<NMAX>(rb, P, PC::a(ab), PC::b(ab), M));
+            const uint32_t e = tab[blk];
+            key = min(key, block_min_key<NMAX>(rb, P, entry_a(e), entry_b(e), M));
         }
-    } else if (holder) {   // the row code: slot of A (link a, row i) and the first slot of link bb
-        const int sa = best_code >> 16, a = sa / NMAX;
-        key = row_min_key<NMAX>(rb, P, a, (best_code & 0xffff) / NMAX, sa - a * NMAX, M);
+    } else if (holder) {
+        key = code_min_key<NMAX>(rb, P, best_code, M);
     }
     M_out = M;
     key_out = group_reduce_min(key, G);
@@ -366,8 +377,8 @@ __device__ __forceinline__ void sweep_state(const DevRobot &rb, const E *tab, co
 // paper's two-stage self-collision split over wavefronts, then a second
 // reduce through LDS): the block table's 128-entry chunks are dealt
 // round-robin to the wavefronts (chunk c to wavefront c % 4); each compacts
-// its chunks into its list (cap entries, at least 128) and sweeps their rows
-// as sweep_state does with G = 64, and the workgroup combines the wavefronts'
+// its chunks into its list (SWEEP_LIST entries) and sweeps their rows as
+// sweep_state does with G = 64, and the workgroup combines the wavefronts'
 // maxima, counts and argmax keys.  Pass 2, the seed block and the tie rescan
 // follow the single-wavefront rules with workgroup-wide values, so the result
 // is the full sweep's.  red: 8 words of LDS; ring: the wavefront's own.
@@ -388,11 +399,10 @@ __device__ __forceinline__ int wg_min4(int v, int *red, int wave, int lane) {
     return m;
 }
 
-template <int NMAX, typename E>
-__device__ __forceinline__ void sweep_state_wg(const DevRobot &rb, const E *tab, const float4 *P, const float4 *Bd,
-                                               E *list, int cap, uint32_t *ring, float *red, int wave, int lane,
+template <int NMAX>
+__device__ __forceinline__ void sweep_state_wg(const DevRobot &rb, const uint32_t *tab, const float4 *P, const float4 *Bd,
+                                               uint32_t *list, uint32_t *ring, float *red, int wave, int lane,
                                                float &M_out, int &key_out, unsigned &cnt_out) {
-    typedef PairCode<E> PC;
     const int n = rb.n_blocks;
     const int nb = (n + 127) / 128 * 128;   // <= n_blocks_pad
     int *redi = reinterpret_cast<int *>(red);
@@ -405,20 +415,20 @@ __device__ __forceinline__ void sweep_state_wg(const DevRobot &rb, const E *tab,
     const float eps = 4e-6f * (1.f + group_reduce_max(ext, 64));
 
     float best = -INFINITY;
-    int best_code = -1;
+    uint32_t best_code = NO_ROW;
     bool tie = false;
     unsigned cnt = 0;
     // the wavefront's chunks through its list, the rows swept when it is full
     auto sweep_chunks = [&](auto pass2, float lo) {
         constexpr bool PASS2 = decltype(pass2)::value;
         int nl = 0;
-        for (int c0 = wave * 128; c0 < nb; c0 += 4 * 128) {
-            nl += compact_blocks<PASS2 ? 3 : 1>(tab, Bd, list + nl, c0, c0 + 128, eps, lo, lane, 64, 0, ~0ull);
-            if (nl + 128 > cap || c0 + 4 * 128 >= nb) {
+        for (int k = wave * 128; k < nb; k += 4 * 128) {
+            nl = append_blocks<PASS2, true, false>(tab, Bd, list, nl, k, eps, lo, lane, 64, 0, ~0ull);
+            if (k + 4 * 128 >= nb || nl + 128 > SWEEP_LIST) {
                 __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");
                 __builtin_amdgcn_wave_barrier();
-                sweep_rows_culled<NMAX, true, PASS2>(P, Bd, list, nl, ring, eps, lo, lane, 64, 0, ~0ull, best, best_code,
-                                                     tie, cnt);
+                sweep_rows_culled<NMAX, true, PASS2, false>(P, Bd, list, nl, ring, eps, lo, lane, 64, 0, ~0ull, best,
+                                                            best_code, tie, cnt);
                 __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");
                 __builtin_amdgcn_wave_barrier();
                 nl = 0;
@@ -435,8 +445,7 @@ __device__ __forceinline__ void sweep_state_wg(const DevRobot &rb, const E *tab,
             int bblk = INT_MAX;
             for (int c0 = wave * 128; c0 < nb; c0 += 4 * 128)
                 for (int k = c0 + lane; k < min(c0 + 128, n); k += 64) {
-                    const int ab = tab[k];
-                    const float d = block_bound(Bd, PC::a(ab), PC::b(ab));
+                    const float d = block_bound(Bd, tab[k]);
                     if (d > bmax) {
                         bmax = d;
                         bblk = k;
@@ -446,8 +455,8 @@ __device__ __forceinline__ void sweep_state_wg(const DevRobot &rb, const E *tab,
             const int cand = wg_min4(group_reduce_min(bmax == gbmax ? bblk : INT_MAX, 64), redi, wave, lane);
             float seed = -INFINITY;
             if (cand != INT_MAX) {
-                const int ab = tab[cand];
-                const int a = PC::a(ab), bb = PC::b(ab);
+                const uint32_t e = tab[cand];
+                const int a = entry_a(e), bb = entry_b(e);
                 for (int j = lane; j < NMAX * NMAX; j += 64) {
                     const int i = j / NMAX, k = j - i * NMAX;
                     seed = fmaxf(seed, pair_pen(P[a * NMAX + i], P[bb * NMAX + k]));
@@ -460,17 +469,16 @@ __device__ __forceinline__ void sweep_state_wg(const DevRobot &rb, const E *tab,
         M = wg_max4(group_reduce_max(best, 64), red, wave, lane);
     }
     int key = INT_MAX;
-    const bool holder = best == M && M > -INFINITY && best_code >= 0;
+    const bool holder = best == M && M > -INFINITY && best_code != NO_ROW;
     const bool rescan = wg_min4(group_reduce_min((holder && tie) ? 0 : 1, 64), redi, wave, lane) == 0;
     if (rescan) {
         for (int c0 = wave * 128; c0 < nb; c0 += 4 * 128)
             for (int blk = c0 + lane; blk < min(c0 + 128, n); blk += 64) {
-                const int ab = tab[blk];
-                key = min(key, block_min_key<NMAX>(rb, P, PC::a(ab), PC::b(ab), M));
+                const uint32_t e = tab[blk];
+                key = min(key, block_min_key<NMAX>(rb, P, entry_a(e), entry_b(e), M));
             }
     } else if (holder) {
-        const int sa = best_code >> 16, a = sa / NMAX;
-        key = row_min_key<NMAX>(rb, P, a, (best_code & 0xffff) / NMAX, sa - a * NMAX, M);
+        key = code_min_key<NMAX>(rb, P, best_code, M);
     }
     M_out = M;
     key_out = wg_min4(group_reduce_min(key, 64), redi, wave, lane);

@@ -42,7 +42,6 @@ struct Tables {
     std::vector<float> slot_r;
     std::vector<int32_t> blocks;      // padded to a multiple of 64
     int n_blocks = 0;
-    int list_cap = 64;                // ints of the sweep's per-group LDS list
     std::vector<int32_t> pair_off, pair_cnt, pair_s, pair_t;
     int64_t n_pairs = 0;
     float g[3] = {0, 0, 0};
@@ -206,6 +205,21 @@ void build_fused(Tables &T) {
     T.f_lf.assign(31 * 64, 0.0f);
     std::vector<std::vector<int>> conn(T.n);
     T.f_sph.assign((size_t)T.nmax * 64, make_float4(0, 0, 0, 0));
+    // the farthest that any sphere reaches from the base in any state, and
+    // the rounding margin of the sweep for it
+    double extent = 0.0;
+    {
+        std::vector<double> dist(L, 0.0);
+        for (int k = 0; k < L; ++k) {
+            const float *fp = T.lf[k].fp;
+            if (k > 0) dist[k] = dist[T.li[k].parent] + std::sqrt((double)fp[0] * fp[0] + (double)fp[1] * fp[1] + (double)fp[2] * fp[2]);
+            for (int j = 0; j < T.li[k].sph_count; ++j) {
+                const float4 q = T.sph[T.li[k].sph_first + j];
+                extent = std::max(extent, dist[k] + std::sqrt((double)q.x * q.x + (double)q.y * q.y + (double)q.z * q.z) + q.w);
+            }
+        }
+    }
+    const double margin = 4e-6 * (1.0 + extent);
     for (int i = 0; i < L; ++i) {
         const int k = perm[i];
         const wb::LinkI &I = T.li[k];
@@ -244,7 +258,7 @@ void build_fused(Tables &T) {
                 const double dx = q.x - cen[0], dy = q.y - cen[1], dz = q.z - cen[2];
                 reach = std::max(reach, std::sqrt(dx * dx + dy * dy + dz * dz) + q.w);
             }
-            reach = reach * (1.0 + 1e-6) + 1e-7;
+            reach = reach * (1.0 + 1e-6) + 1e-7 + margin;
         }
         for (int c = 0; c < 3; ++c) T.f_lf[(25 + c) * 64 + i] = (float)cen[c];
         T.f_lf[28 * 64 + i] = std::nextafter((float)reach, INFINITY);
@@ -269,7 +283,7 @@ void build_fused(Tables &T) {
     T.jsteps = pointer_jump_steps(T.max_depth);
     T.lanes = 1;
     T.fused = T.nmax <= wb::FUSED_MAX_SLOTS &&
-              wb::fused_lds_bytes(L, T.nmax, T.list_cap, g_default, (int)T.blocks.size()) <= wb::LDS_LIMIT;
+              wb::counted_fused_bytes(L, T.nmax, g_default, (int)T.blocks.size()) <= wb::LDS_LIMIT;
 }
 
 int build_tables(const wb_robot_desc *d, Tables &T) {
@@ -397,7 +411,7 @@ int build_tables(const wb_robot_desc *d, Tables &T) {
     }
     T.nmax = nmax;
     T.most = most;
-    if (wb::state_lds_bytes(L, nmax) + 16 * 128 + 16 * wb::SWEEP_ROW_RING > wb::LDS_LIMIT)
+    if (wb::state_lds_bytes(L, nmax) + 16 * 128 + 16 * 128 > wb::LDS_LIMIT)
         return fail(WB_ERR_UNSUPPORTED, "(links + 1) x spheres-per-link slots (%d x %d) exceed the 64 KB LDS tile",
                     L + 1, nmax);
     T.sph.resize(S);
@@ -440,7 +454,6 @@ int build_tables(const wb_robot_desc *d, Tables &T) {
     }
     T.n_blocks = (int)T.blocks.size();
     while (T.blocks.size() % 128) T.blocks.push_back((L << 16) | L);
-    T.list_cap = wb::sweep_list_cap(T.n_blocks);
     T.pair_off.resize(S);
     int64_t off = 0;
     for (int s = 0; s < S; ++s) {
@@ -532,7 +545,7 @@ int check_tune(const wb_tune &t, const Tables &T) {
     const int g = t.lanes_per_state;
     if (g != 16 && g != 32 && g != 64) return fail(WB_ERR_INVALID_ARG, "lanes_per_state must be 16, 32 or 64");
     if (g < T.L) return fail(WB_ERR_INVALID_ARG, "lanes_per_state %d is below the %d links", g, T.L);
-    const size_t need = wb::fused_lds_bytes(T.L, T.nmax, T.list_cap, g, (int)T.blocks.size());
+    const size_t need = wb::counted_fused_bytes(T.L, T.nmax, g, (int)T.blocks.size());
     if (need > wb::LDS_LIMIT)
         return fail(WB_ERR_UNSUPPORTED, "lanes_per_state %d needs %zu bytes of LDS per workgroup (> %zu)", g, need,
                     wb::LDS_LIMIT);
@@ -626,7 +639,9 @@ int wb_robot_create(const wb_robot_desc *desc, wb_robot **out) {
     std::vector<char> blob;
     const size_t o_lf = append(blob, T.lf), o_li = append(blob, T.li), o_sph = append(blob, T.sph);
     const size_t o_sl = append(blob, T.sph_link), o_ss = append(blob, T.sph_slot);
-    const size_t o_sr = append(blob, T.slot_r), o_bl = append(blob, T.blocks);
+    std::vector<uint32_t> entries;   // the block table as the kernels read it
+    for (const int32_t ab : T.blocks) entries.push_back(((uint32_t)(ab >> 16) * 16u) << 16 | (uint32_t)(ab & 0xffff) * 16u);
+    const size_t o_sr = append(blob, T.slot_r), o_bl = append(blob, entries);
     const size_t o_po = append(blob, T.pair_off), o_pc = append(blob, T.pair_cnt);
     const size_t o_ps = append(blob, T.pair_s), o_pt = append(blob, T.pair_t);
     const size_t o_fi = append(blob, T.f_li), o_ff = append(blob, T.f_lf), o_fs = append(blob, T.f_sph);
@@ -658,14 +673,13 @@ int wb_robot_create(const wb_robot_desc *desc, wb_robot **out) {
     D.max_depth = T.max_depth; D.simple_joints = T.simple;
     D.n_pairs = T.n_pairs;
     D.gx = T.g[0]; D.gy = T.g[1]; D.gz = T.g[2];
-    D.list_cap = T.list_cap;
     D.lf = reinterpret_cast<const wb::LinkF *>(base + o_lf);
     D.li = reinterpret_cast<const wb::LinkI *>(base + o_li);
     D.sph = reinterpret_cast<const float4 *>(base + o_sph);
     D.sph_link = reinterpret_cast<const int32_t *>(base + o_sl);
     D.sph_slot = reinterpret_cast<const int32_t *>(base + o_ss);
     D.slot_r = reinterpret_cast<const float *>(base + o_sr);
-    D.blocks = reinterpret_cast<const int32_t *>(base + o_bl);
+    D.blocks = reinterpret_cast<const uint32_t *>(base + o_bl);
     D.pair_off = reinterpret_cast<const int32_t *>(base + o_po);
     D.pair_cnt = reinterpret_cast<const int32_t *>(base + o_pc);
     D.pair_s = reinterpret_cast<const int32_t *>(base + o_ps);
@@ -1048,7 +1062,8 @@ int wb_wholebody_step_bspline(const wb_robot *robot, int64_t T, int32_t K, float
     const int64_t H = (int64_t)(K + 3) * 4, B = T * H;
     const bool reduce = g_U || lr != 0.0f;
     const int G = robot->tune.lanes_per_state;
-    if (reduce && wb::fused_lds_bytes(robot->T.L, robot->T.nmax, robot->T.list_cap, G, (int)robot->T.blocks.size()) +
+    const int nbp = (int)robot->T.blocks.size();
+    if (reduce && wb::counted_fused_bytes(robot->T.L, robot->T.nmax, G, nbp) +
                           wb::spline_lds_bytes(G, robot->T.n, K) > wb::LDS_LIMIT)
         return fail(WB_ERR_UNSUPPORTED, "the control-point gradient of %d joints x %d control points does not fit "
                     "the workgroup's LDS; take the per-sample gradients and wb_bspline_backward", robot->T.n, K);
@@ -1342,16 +1357,18 @@ int wb_plan_create(const wb_robot *const *robots, const int64_t *B, int32_t n_tr
         tunes[i] = tune ? tune[i] : robots[i]->tune;
         WB_TRY(check_tune(tunes[i], robots[i]->T));
     }
-    size_t wave_lds = 0, tab_lds = 0;
+    size_t wave_lds = 0, tab_lds = 0, wave_counted = 0, tab_counted = 0;
     for (int i = 0; i < n_trees; ++i) {
-        const size_t per_wave = (size_t)(64 / tunes[i].lanes_per_state) *
-                                wb::group_lds_bytes(robots[i]->T.L, nmax, robots[i]->T.list_cap);
-        wave_lds = std::max(wave_lds, per_wave);
-        tab_lds = std::max(tab_lds, wb::tab_lds_bytes((int)robots[i]->T.blocks.size()));
+        const size_t groups = 64 / tunes[i].lanes_per_state;
+        const int L = robots[i]->T.L, nbp = (int)robots[i]->T.blocks.size();
+        wave_lds = std::max(wave_lds, groups * wb::group_lds_bytes(L, nmax, robots[i]->T.n_blocks, tunes[i].lanes_per_state));
+        tab_lds = std::max(tab_lds, wb::tab_lds_bytes(nbp));
+        wave_counted = std::max(wave_counted, groups * wb::counted_group_bytes(L, nmax, nbp));
+        tab_counted = std::max(tab_counted, wb::counted_tab_bytes(nbp));
     }
-    const size_t lds = 4 * wave_lds + tab_lds;
-    if (lds > wb::LDS_LIMIT)
-        return fail(WB_ERR_UNSUPPORTED, "plan needs %zu bytes of LDS per workgroup (> %zu)", lds, wb::LDS_LIMIT);
+    const size_t lds = 4 * wave_lds + tab_lds, counted = 4 * wave_counted + tab_counted;
+    if (counted > wb::LDS_LIMIT)
+        return fail(WB_ERR_UNSUPPORTED, "plan needs %zu bytes of LDS per workgroup (> %zu)", counted, wb::LDS_LIMIT);
 
     // Work items: contiguous state ranges of one tree, balanced over the
     // workgroups of one persistent wave of the launch (longest item first).

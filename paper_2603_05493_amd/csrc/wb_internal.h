@@ -41,14 +41,14 @@ struct DevRobot {
     int32_t n_blocks, n_blocks_pad, max_depth, simple_joints;  // simple: one link per actuated joint, mult 1, offset 0
     int64_t n_pairs;
     float gx, gy, gz;
-    int32_t list_cap;             // ints of the per-group LDS list of the pair sweep (multiple of 128)
+    int32_t pad;
     const LinkF *__restrict__ lf;         // [L]
     const LinkI *__restrict__ li;         // [L]
     const float4 *__restrict__ sph;       // [S] local centre + radius
     const int32_t *__restrict__ sph_link; // [S]
     const int32_t *__restrict__ sph_slot; // [S] padded slot a*nmax + (s - first sphere of a)
     const float *__restrict__ slot_r;     // [(L+1)*nmax] radius of slot (a,i), -1e30 for empty slots
-    const int32_t *__restrict__ blocks;   // [n_blocks_pad] packed (a<<16)|b, padded to a multiple of 128 with (L<<16)|L
+    const uint32_t *__restrict__ blocks;  // [n_blocks_pad] (16 a) << 16 | 16 b, padded to a multiple of 128 with the pair (L, L)
     const int32_t *__restrict__ pair_off; // [S] index of sphere s's first pair
     const int32_t *__restrict__ pair_cnt; // [L*L] pairs of a sphere on link a with links a<b'<b
     const int32_t *__restrict__ pair_s;   // [P]
@@ -65,7 +65,8 @@ struct DevRobot {
 //   lf[f*64 + i]: f = 0..2 axis, 3..11 fixed R, 12..14 fixed p, 15 mass,
 //                 16..18 CoM, 19..24 inertia (xx yy zz xy xz yz),
 //                 25..27 centre and 28 radius of the link's bounding sphere in
-//                 link coordinates (-1e30 without spheres), 29 joint
+//                 link coordinates, the sweep's rounding margin for any state
+//                 of the robot included (-1e30 without spheres), 29 joint
 //                 multiplier, 30 joint offset
 //   lsph[j*64 + i]: local centre and radius of the link's j-th sphere
 //   conn[k*64 + j]: lane of the k-th link that joint j drives, -1 past the
@@ -211,27 +212,40 @@ hipError_t launch_bspline_backward(int64_t T, int32_t d, int32_t K, int32_t n_in
                                    float *U, hipStream_t s);
 
 // LDS of one state's sweep: (L+1)*nmax sphere slots and L+1 link bounding
-// spheres (float4 each); plus, per sweeping group, a list of list_cap
-// surviving link pairs (16-bit entries in the fused kernels, 32-bit in the
-// standalone self-collision kernel) and a ring of SWEEP_ROW_RING row codes.
-constexpr int SWEEP_LIST_MAX = 2048;
-inline int sweep_list_cap(int n_blocks) {
-    int c = (n_blocks + 127) / 128 * 128;
-    return c < 128 ? 128 : (c > SWEEP_LIST_MAX ? SWEEP_LIST_MAX : c);
+// spheres (float4 each); plus, per sweeping group, a list of surviving blocks
+// and a ring of row codes (32-bit each).
+// The list takes every block of a small robot and up to 256 at a time of a
+// large one, the ring two rows per lane of the group (of G lanes).
+constexpr int SWEEP_LIST = 256;       // a multiple of 128
+__host__ __device__ inline int sweep_list(int n_blocks, int G) {
+    const int all = (n_blocks + 2 * G - 1) / (2 * G) * (2 * G);
+    return all < SWEEP_LIST ? all : SWEEP_LIST;
 }
+__host__ __device__ inline int sweep_ring(int G) { return 2 * G; }
 __host__ __device__ inline size_t state_lds_bytes(int L, int nmax) { return (size_t)(L + 1) * (nmax + 1) * 16; }
-// Rows queued per sweeping group by the row-culled sweep (32-bit codes).
-constexpr int SWEEP_ROW_RING = 128;
-__host__ __device__ inline size_t group_lds_bytes(int L, int nmax, int list_cap) {
-    return state_lds_bytes(L, nmax) + (size_t)list_cap * 2 + (size_t)SWEEP_ROW_RING * 4;
+__host__ __device__ inline size_t group_lds_bytes(int L, int nmax, int n_blocks, int G) {
+    return state_lds_bytes(L, nmax) + (size_t)(sweep_list(n_blocks, G) + sweep_ring(G)) * 4;
 }
-// LDS copy of the block table in the fused kernels (n_blocks_pad 16-bit
-// entries, a multiple of 128).
-__host__ __device__ inline size_t tab_lds_bytes(int n_blocks_pad) { return (size_t)n_blocks_pad * 2; }
-// LDS of a 256-lane workgroup of the fused kernels with G lanes per state:
-// four wavefronts' group regions, then the block table.
-inline size_t fused_lds_bytes(int L, int nmax, int list_cap, int G, int n_blocks_pad) {
-    return (size_t)4 * (64 / G) * group_lds_bytes(L, nmax, list_cap) + tab_lds_bytes(n_blocks_pad);
+// LDS copy of the block table (n_blocks_pad entries, a multiple of 128).
+__host__ __device__ inline size_t tab_lds_bytes(int n_blocks_pad) { return (size_t)n_blocks_pad * 4; }
+// LDS of a workgroup of the fused kernel with G lanes per state and `waves`
+// wavefronts: their group regions, then, for four, the block table.
+inline size_t fused_lds_bytes(int L, int nmax, int n_blocks, int G, int waves) {
+    return (size_t)waves * (64 / G) * group_lds_bytes(L, nmax, n_blocks, G) +
+           (waves > 1 ? tab_lds_bytes((n_blocks + 127) / 128 * 128) : 0);
+}
+// What a fused shape or a plan is held against LDS_LIMIT by, at least what
+// each wavefront takes: 16-bit lists of up to 2,048 blocks and a 16-bit
+// table a workgroup of four wavefronts.  It decides which robots and shapes
+// are accepted; a launch may take a little more than LDS_LIMIT of the 160 KB
+// that a compute unit has.
+inline size_t counted_group_bytes(int L, int nmax, int n_blocks_pad) {
+    const int cap = n_blocks_pad < 128 ? 128 : (n_blocks_pad > 2048 ? 2048 : n_blocks_pad);
+    return state_lds_bytes(L, nmax) + (size_t)cap * 2 + (size_t)128 * 4;
+}
+inline size_t counted_tab_bytes(int n_blocks_pad) { return (size_t)n_blocks_pad * 2; }
+inline size_t counted_fused_bytes(int L, int nmax, int G, int n_blocks_pad) {
+    return (size_t)4 * (64 / G) * counted_group_bytes(L, nmax, n_blocks_pad) + counted_tab_bytes(n_blocks_pad);
 }
 // LDS of the in-kernel control-point gradient beyond the fused kernel's:
 // one partial sum per group of lanes (4 * 64 / G of them) over the
