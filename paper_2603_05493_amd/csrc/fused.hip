@@ -73,7 +73,7 @@ namespace wb {
 // and is added to this group's partial sums gpart[d][K + 6] in LDS (one
 // group at a time per partial, states in a fixed order: deterministic).
 // With SPL the state is sample t of trajectory traj (b = traj * H + t).
-template <int NMAX, bool FULL, bool EXT, int SPL>
+template <int NMAX, bool FULL, bool EXT, int SPL, bool MATRIX>
 __device__ __forceinline__ void iterate_state(const DevRobot &rb, const uint32_t *tab, const DevFused &fz,
                                               const TreeIO &io, const SplineIn &sp, const StepScalars &k,
                                               float4 *P, float4 *Bd, uint32_t *list, float *gpart, int G, int grp,
@@ -166,7 +166,7 @@ __device__ __forceinline__ void iterate_state(const DevRobot &rb, const uint32_t
     int key;
     unsigned cnt;
     // the group's row ring follows its list
-    sweep_state<NMAX, FULL, true>(rb, tab, P, Bd, list, list + sweep_list(rb.n_blocks, G), glane, G, grp, M,
+    sweep_state<NMAX, FULL, true, MATRIX>(rb, tab, P, Bd, list, list + sweep_list(rb.n_blocks, G), glane, G, grp, M,
                             key, cnt);
     const float hmarg = M + k.margin;
     const bool hinge_on = key != INT_MAX && hmarg > 0.f && k.hinge_weight != 0.f;
@@ -345,10 +345,10 @@ __device__ __forceinline__ void run_states(const DevRobot &rb, const uint32_t *t
             t = bi - tr * sp.H;
         }
         if (GSEL == 64 || (GSEL < 0 && G == 64))
-            iterate_state<NMAX, true, EXT, SPL>(rb, tab, fz, io, sp, k, P, Bd, list, gpart, 64, 0, glane, B, b, valid,
+            iterate_state<NMAX, true, EXT, SPL, GSEL == 64>(rb, tab, fz, io, sp, k, P, Bd, list, gpart, 64, 0, glane, B, b, valid,
                                                 tr, t);
         else
-            iterate_state<NMAX, false, EXT, SPL>(rb, tab, fz, io, sp, k, P, Bd, list, gpart, G, grp, glane, B, b,
+            iterate_state<NMAX, false, EXT, SPL, false>(rb, tab, fz, io, sp, k, P, Bd, list, gpart, G, grp, glane, B, b,
                                                  valid, tr, t);
     }
 }
@@ -453,6 +453,7 @@ __device__ __forceinline__ PlanTree load_tree(const PlanTree *t) {
     r.sph_slot = as_global(r.sph_slot);
     r.slot_r = as_global(r.slot_r);
     r.blocks = as_global(r.blocks);
+    r.allow = as_global(r.allow);
     r.pair_off = as_global(r.pair_off);
     r.pair_cnt = as_global(r.pair_cnt);
     r.pair_s = as_global(r.pair_s);
@@ -470,7 +471,7 @@ __device__ __forceinline__ PlanTree load_tree(const PlanTree *t) {
 // contiguous range of states of one robot.  EXT as for k_fused_step, chosen
 // when any tree has mimic joints or external forces.
 template <int NMAX, bool EXT>
-__global__ void __launch_bounds__(256) k_plan_step(PlanArgs A) {
+__global__ void __launch_bounds__(256, 3) k_plan_step(PlanArgs A) {
     extern __shared__ float4 lds[];
     const int wave = threadIdx.x >> 6;
     const int w = blockIdx.x;

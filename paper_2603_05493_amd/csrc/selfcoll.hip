@@ -73,7 +73,7 @@ __global__ void __launch_bounds__(256) k_self_collision(DevRobot rb, int64_t nb,
         float M;
         int key;
         unsigned cnt;
-        sweep_state<NMAX, true, false>(rb, tab, P, Bd, lists + wave * SWEEP_LIST, rings + wave * SC_RING, lane, 64,
+        sweep_state<NMAX, true, false, false>(rb, tab, P, Bd, lists + wave * SWEEP_LIST, rings + wave * SC_RING, lane, 64,
                                 0, M, key, cnt);
         if (lane == 0) {
             if (max_pen) max_pen[b] = M;

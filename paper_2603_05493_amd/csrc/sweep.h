@@ -176,6 +176,82 @@ __device__ __forceinline__ int append_blocks(const uint32_t *tab, const float4 *
     return n0 + __popcll(m1);
 }
 
+// The pass-1 test of every link pair of a robot of at most 64 links on the
+// matrix cores: with n = |C|^2 - R^2 - tol / 2 the test |C_a - C_b| <= R_a +
+// R_b reads
+//   n_a + n_b - 2 (C_a . C_b + R_a R_b) <= 0,
+// a product of the rows [x y z R n 1] and the columns [-2x -2y -2z -2R 1 n]:
+// three 32x32x2 FP32 products (K = 6) for each of the tiles (links 0-31,
+// 0-31), (0-31, 32-63) and (32-63, 32-63).  tol (rb.broad_tol, 1e-5 of the
+// squared reach of any state) exceeds the rounding of this form and of the
+// direct test's, so every block that the direct test passes has its sign bit
+// set here; the few more that do are dropped by the row test.  A lane gathers
+// the signs of its 48 results in two words, masks the checked pairs and
+// appends its survivors behind those of the lanes below.  The direct test
+// costs 25 vector instructions for 64 blocks, 450 for a humanoid's 1,128;
+// this takes about 220 and the idle matrix cores.
+// Taken from BROAD_MATRIX_FROM blocks on: humanoid x 24,576 (1,128 blocks)
+// 92.6 -> 88.0 us a fused launch, a 23-joint tree in 64 lanes (253 blocks)
+// 80.5 -> 89 us.
+// Returns the number of survivors; the list holds them if they are at most
+// cap.  Every lane of the wavefront calls this.
+constexpr int BROAD_MATRIX_FROM = 576;
+typedef float floatx16 __attribute__((ext_vector_type(16)));
+__device__ __forceinline__ int broad_phase(const DevRobot &rb, const float4 *Bd, uint32_t *list, int cap, int lane) {
+    const bool lo = lane < 32;
+    const float *f = reinterpret_cast<const float *>(Bd);
+    const int l0 = min(lane & 31, rb.L) * 4 + (lo ? 0 : 1), l1 = min((lane & 31) + 32, rb.L) * 4 + (lo ? 0 : 1);
+    // component 2 s + (lane >= 32) of link 32 h + lane % 32
+    const float a00 = f[l0], a01 = f[l0 + 2], a10 = f[l1], a11 = f[l1 + 2];
+    const float4 c = Bd[min(lane, rb.L)];
+    const float n = __builtin_fmaf(c.x, c.x, __builtin_fmaf(c.y, c.y, c.z * c.z)) - __builtin_fmaf(c.w, c.w, 0.5f * rb.broad_tol);
+    unsigned u, v;
+    swap32(__builtin_bit_cast(unsigned, n), u, v);   // the lower half's n in every lane, then the upper's
+    const float nl = __builtin_bit_cast(float, u), nu = __builtin_bit_cast(float, v);
+    const float a02 = lo ? nl : 1.f, a12 = lo ? nu : 1.f, b02 = lo ? 1.f : nl, b12 = lo ? 1.f : nu;
+    const float b00 = -2.f * a00, b01 = -2.f * a01, b10 = -2.f * a10, b11 = -2.f * a11;
+    auto tile = [](float p0, float p1, float p2, float q0, float q1, float q2) {
+        floatx16 d = {};
+        d = __builtin_amdgcn_mfma_f32_32x32x2f32(p0, q0, d, 0, 0, 0);
+        d = __builtin_amdgcn_mfma_f32_32x32x2f32(p1, q1, d, 0, 0, 0);
+        return __builtin_amdgcn_mfma_f32_32x32x2f32(p2, q2, d, 0, 0, 0);
+    };
+    // result r of a lane is row 8 (r / 4) + 4 (lane / 32) + r % 4, column lane % 32
+    auto signs = [](uint32_t w, const floatx16 &d) {
+#pragma unroll
+        for (int r = 15; r >= 0; --r) {
+            const float x = d[r];
+            w = __builtin_amdgcn_alignbit(w, __builtin_bit_cast(uint32_t, x), 31);
+        }
+        return w;
+    };
+    uint32_t w0 = signs(0u, tile(a00, a01, a02, b10, b11, b12));
+    w0 = signs(w0, tile(a00, a01, a02, b00, b01, b02)) & rb.allow[lane];
+    uint32_t w1 = signs(0u, tile(a10, a11, a12, b10, b11, b12)) & rb.allow[64 + lane];
+    const int mine = __popc(w0) + __popc(w1);
+    int at = mine;   // inclusive prefix sum over the wavefront
+    at += dpp_i<DPP_ROW_SHR + 1>(at);
+    at += dpp_i<DPP_ROW_SHR + 2>(at);
+    at += dpp_i<DPP_ROW_SHR + 4>(at);
+    at += dpp_i<DPP_ROW_SHR + 8>(at);
+    at += __builtin_amdgcn_update_dpp(0, at, DPP_ROW_BCAST15, 0xa, 0xf, false);
+    at += __builtin_amdgcn_update_dpp(0, at, DPP_ROW_BCAST31, 0xc, 0xf, false);
+    const int total = __builtin_amdgcn_readlane(at, 63);
+    if (total > cap) return total;
+    uint32_t *out = list + (at - mine);
+    const uint32_t base = ((uint32_t)(lane >> 5) << 22) | (uint32_t)(lane & 31) << 4;
+    while (w0 | w1) {
+        const bool first = w0 != 0;
+        const uint32_t w = first ? w0 : w1, q = (uint32_t)__builtin_ctz(w), rest = w & (w - 1);
+        // row 8 (r / 4) + r % 4 of the tile; bit 4 of q: the second tile's columns
+        const uint32_t e = base + (((q & 3u) | (q & 12u) << 1) << 20) + ((q & 16u) << 5);
+        *out++ = first ? e : e + ((32u << 20) | (32u << 4));
+        w0 = first ? rest : 0u;
+        w1 = first ? w1 : rest;
+    }
+    return total;
+}
+
 // Row test: sphere slot A against link bound Bb may hold a pair reaching
 // -eps (squared, as may_reach; an empty slot never passes), and the row
 // bound itself.
@@ -284,7 +360,9 @@ __device__ __forceinline__ int code_min_key(const DevRobot &rb, const float4 *P,
 // of pairs with positive penetration.  FULL: G == 64.  ring: sweep_ring
 // words of LDS scratch for this group.  PADDED: the bounds' radii hold the rounding
 // margin of any state already, else it is formed from the state's extent.
-template <int NMAX, bool FULL, bool PADDED>
+// MATRIX (with PADDED, at most 64 links): pass 1 on the matrix cores where
+// the robot has blocks enough.
+template <int NMAX, bool FULL, bool PADDED, bool MATRIX>
 __device__ __forceinline__ void sweep_state(const DevRobot &rb, const uint32_t *tab, const float4 *P,
                                             const float4 *Bd, uint32_t *list, uint32_t *ring, int glane, int G,
                                             int grp, float &M_out, int &key_out, unsigned &cnt_out) {
@@ -325,7 +403,21 @@ __device__ __forceinline__ void sweep_state(const DevRobot &rb, const uint32_t *
             }
         }
     };
-    sweep_blocks(std::false_type{}, 0.f);   // pass 1: blocks that may hold a collision
+    // pass 1: blocks that may hold a collision
+    int found = -1;
+    if (MATRIX && FULL && n >= BROAD_MATRIX_FROM) {
+        found = broad_phase(rb, Bd, list, cap, glane);
+        if (found > cap) found = -1;
+    }
+    if (found < 0) sweep_blocks(std::false_type{}, 0.f);
+    else {
+        __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");
+        __builtin_amdgcn_wave_barrier();
+        sweep_rows_culled<NMAX, FULL, false, PADDED>(P, Bd, list, found, ring, eps, 0.f, glane, G, gshift, gmask, best,
+                                                     best_code, tie, cnt);
+        __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");
+        __builtin_amdgcn_wave_barrier();
+    }
     float M = group_reduce_max(best, G);
     if (!(M >= 0.f) && n > 0) {
         // pass 2 (no collision): a lower bound of M, then the skipped blocks that can reach it

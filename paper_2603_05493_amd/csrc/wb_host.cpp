@@ -56,6 +56,8 @@ struct Tables {
     int f_mimic = 0, f_mc = 1;        // mimic joints present; longest connectedLinks list
     std::vector<int32_t> f_conn;      // [f_mc][64] lanes of each joint's links
     int f_branched = 0;               // some subtree starts past lane 0
+    float broad_tol = 0.0f;           // rounding allowance and
+    std::vector<uint32_t> f_allow;    // [2][64] checked pairs of the matrix-core broad phase
     // lane tables of the kinematics-outputs kernel (depth-first pre-order)
     int kin = 0, kin_G = 0, kin_jsteps = 0, kin_mc = 0;
     std::vector<int> kin_lane, kin_sub_end;   // link -> lane, lane -> last lane of its subtree
@@ -208,18 +210,17 @@ void build_fused(Tables &T) {
     // the farthest that any sphere reaches from the base in any state, and
     // the rounding margin of the sweep for it
     double extent = 0.0;
-    {
-        std::vector<double> dist(L, 0.0);
-        for (int k = 0; k < L; ++k) {
-            const float *fp = T.lf[k].fp;
-            if (k > 0) dist[k] = dist[T.li[k].parent] + std::sqrt((double)fp[0] * fp[0] + (double)fp[1] * fp[1] + (double)fp[2] * fp[2]);
-            for (int j = 0; j < T.li[k].sph_count; ++j) {
-                const float4 q = T.sph[T.li[k].sph_first + j];
-                extent = std::max(extent, dist[k] + std::sqrt((double)q.x * q.x + (double)q.y * q.y + (double)q.z * q.z) + q.w);
-            }
+    std::vector<double> dist(L, 0.0);
+    for (int k = 0; k < L; ++k) {
+        const float *fp = T.lf[k].fp;
+        if (k > 0) dist[k] = dist[T.li[k].parent] + std::sqrt((double)fp[0] * fp[0] + (double)fp[1] * fp[1] + (double)fp[2] * fp[2]);
+        for (int j = 0; j < T.li[k].sph_count; ++j) {
+            const float4 q = T.sph[T.li[k].sph_first + j];
+            extent = std::max(extent, dist[k] + std::sqrt((double)q.x * q.x + (double)q.y * q.y + (double)q.z * q.z) + q.w);
         }
     }
     const double margin = 4e-6 * (1.0 + extent);
+    double far = 0.0;   // the farthest that a bounding sphere reaches
     for (int i = 0; i < L; ++i) {
         const int k = perm[i];
         const wb::LinkI &I = T.li[k];
@@ -259,6 +260,7 @@ void build_fused(Tables &T) {
                 reach = std::max(reach, std::sqrt(dx * dx + dy * dy + dz * dz) + q.w);
             }
             reach = reach * (1.0 + 1e-6) + 1e-7 + margin;
+            far = std::max(far, dist[k] + std::sqrt(cen[0] * cen[0] + cen[1] * cen[1] + cen[2] * cen[2]) + reach);
         }
         for (int c = 0; c < 3; ++c) T.f_lf[(25 + c) * 64 + i] = (float)cen[c];
         T.f_lf[28 * 64 + i] = std::nextafter((float)reach, INFINITY);
@@ -281,6 +283,20 @@ void build_fused(Tables &T) {
     for (int j = 0; j < T.n; ++j)
         for (size_t c = 0; c < conn[j].size(); ++c) T.f_conn[c * 64 + j] = conn[j][c];
     T.jsteps = pointer_jump_steps(T.max_depth);
+    // the checked link pairs by lane and result of the matrix-core broad
+    // phase: bit r of word 0 is the tile (0, 0), bit 16 + r the tile (0, 1),
+    // bit r of word 1 the tile (1, 1)
+    T.broad_tol = (float)(1e-5 * far * far);
+    T.f_allow.assign(2 * 64, 0u);
+    std::vector<char> checked(64 * 64, 0);
+    for (int i = 0; i < T.n_blocks; ++i) checked[(T.blocks[i] >> 16) * 64 + (T.blocks[i] & 0xffff)] = 1;
+    for (int l = 0; l < 64; ++l)
+        for (int r = 0; r < 16; ++r) {
+            const int a = 8 * (r / 4) + 4 * (l / 32) + r % 4, b = l % 32;
+            if (checked[a * 64 + b]) T.f_allow[l] |= 1u << r;
+            if (checked[a * 64 + b + 32]) T.f_allow[l] |= 1u << (16 + r);
+            if (checked[(a + 32) * 64 + b + 32]) T.f_allow[64 + l] |= 1u << r;
+        }
     T.lanes = 1;
     T.fused = T.nmax <= wb::FUSED_MAX_SLOTS &&
               wb::counted_fused_bytes(L, T.nmax, g_default, (int)T.blocks.size()) <= wb::LDS_LIMIT;
@@ -645,7 +661,7 @@ int wb_robot_create(const wb_robot_desc *desc, wb_robot **out) {
     const size_t o_po = append(blob, T.pair_off), o_pc = append(blob, T.pair_cnt);
     const size_t o_ps = append(blob, T.pair_s), o_pt = append(blob, T.pair_t);
     const size_t o_fi = append(blob, T.f_li), o_ff = append(blob, T.f_lf), o_fs = append(blob, T.f_sph);
-    const size_t o_fc = append(blob, T.f_conn);
+    const size_t o_fc = append(blob, T.f_conn), o_fa = append(blob, T.f_allow);
     const size_t o_ki = append(blob, T.k_li), o_kf = append(blob, T.k_lf), o_kc = append(blob, T.k_conn);
     const size_t o_tl = append(blob, std::vector<int32_t>(WB_MAX_TOOLS, 0));
     const size_t o_to = append(blob, std::vector<float>(12 * WB_MAX_TOOLS, 0.0f));
@@ -679,6 +695,8 @@ int wb_robot_create(const wb_robot_desc *desc, wb_robot **out) {
     D.sph_link = reinterpret_cast<const int32_t *>(base + o_sl);
     D.sph_slot = reinterpret_cast<const int32_t *>(base + o_ss);
     D.slot_r = reinterpret_cast<const float *>(base + o_sr);
+    D.allow = reinterpret_cast<const uint32_t *>(base + o_fa);
+    D.broad_tol = T.broad_tol;
     D.blocks = reinterpret_cast<const uint32_t *>(base + o_bl);
     D.pair_off = reinterpret_cast<const int32_t *>(base + o_po);
     D.pair_cnt = reinterpret_cast<const int32_t *>(base + o_pc);

@@ -41,7 +41,7 @@ struct DevRobot {
     int32_t n_blocks, n_blocks_pad, max_depth, simple_joints;  // simple: one link per actuated joint, mult 1, offset 0
     int64_t n_pairs;
     float gx, gy, gz;
-    int32_t pad;
+    float broad_tol;              // rounding allowance of the matrix-core broad phase (sweep.h)
     const LinkF *__restrict__ lf;         // [L]
     const LinkI *__restrict__ li;         // [L]
     const float4 *__restrict__ sph;       // [S] local centre + radius
@@ -49,6 +49,7 @@ struct DevRobot {
     const int32_t *__restrict__ sph_slot; // [S] padded slot a*nmax + (s - first sphere of a)
     const float *__restrict__ slot_r;     // [(L+1)*nmax] radius of slot (a,i), -1e30 for empty slots
     const uint32_t *__restrict__ blocks;  // [n_blocks_pad] (16 a) << 16 | 16 b, padded to a multiple of 128 with the pair (L, L)
+    const uint32_t *__restrict__ allow;   // [2][64] checked link pairs by matrix-core result (sweep.h); robots of at most 64 links
     const int32_t *__restrict__ pair_off; // [S] index of sphere s's first pair
     const int32_t *__restrict__ pair_cnt; // [L*L] pairs of a sphere on link a with links a<b'<b
     const int32_t *__restrict__ pair_s;   // [P]
@@ -214,9 +215,9 @@ hipError_t launch_bspline_backward(int64_t T, int32_t d, int32_t K, int32_t n_in
 // LDS of one state's sweep: (L+1)*nmax sphere slots and L+1 link bounding
 // spheres (float4 each); plus, per sweeping group, a list of surviving blocks
 // and a ring of row codes (32-bit each).
-// The list takes every block of a small robot and up to 256 at a time of a
+// The list takes every block of a small robot and up to 512 at a time of a
 // large one, the ring two rows per lane of the group (of G lanes).
-constexpr int SWEEP_LIST = 256;       // a multiple of 128
+constexpr int SWEEP_LIST = 512;       // a multiple of 128
 __host__ __device__ inline int sweep_list(int n_blocks, int G) {
     const int all = (n_blocks + 2 * G - 1) / (2 * G) * (2 * G);
     return all < SWEEP_LIST ? all : SWEEP_LIST;

@@ -18,7 +18,14 @@ def _far():
     return rb
 
 
-ROBOTS = [("chain3", lambda: synth.serial_chain(3, 1, seed=1)), ("tree53x12", lambda: synth.random_tree(52, 12, seed=2)),
+def _balled():
+    """Every link within reach of every other: the survivors of the broad phase overflow its list."""
+    rb = synth.random_tree(40, 2, seed=13)
+    rb.fixed_p = synth._f32(np.asarray(rb.fixed_p) * 0.02)
+    return rb
+
+
+ROBOTS = [("balled41", _balled), ("chain3", lambda: synth.serial_chain(3, 1, seed=1)), ("tree53x12", lambda: synth.random_tree(52, 12, seed=2)),
           ("tree55x12", lambda: synth.random_tree(54, 12, seed=3)), ("far10", _far)]
 
 
