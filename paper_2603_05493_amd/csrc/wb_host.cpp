@@ -7,6 +7,8 @@
 #include "wb_internal.h"
 
 #include <algorithm>
+#include <functional>
+#include <queue>
 #include <cmath>
 #include <cstdarg>
 #include <cstdio>
@@ -1327,7 +1329,7 @@ int wb_robot_get_tune(const wb_robot *robot, wb_tune *tune) {
 struct wb_plan {
     int n_trees = 0, nmax = 1, n_wg = 0, n_items = 0, device = -1;
     int mimic = 0;                  // some tree has mimic joints: the EXT kernel variant
-    size_t lds = 0, wave_lds = 0;   // LDS per workgroup, and per wavefront region
+    size_t lds = 0;                 // LDS per workgroup (one wavefront)
     std::vector<int64_t> B;
     std::vector<int> n_dof;
     void *dmem = nullptr;
@@ -1375,16 +1377,14 @@ int wb_plan_create(const wb_robot *const *robots, const int64_t *B, int32_t n_tr
         tunes[i] = tune ? tune[i] : robots[i]->tune;
         WB_TRY(check_tune(tunes[i], robots[i]->T));
     }
-    size_t wave_lds = 0, tab_lds = 0, wave_counted = 0, tab_counted = 0;
+    size_t lds = 0, wave_counted = 0, tab_counted = 0;   // of a wavefront, the largest over the trees
     for (int i = 0; i < n_trees; ++i) {
-        const size_t groups = 64 / tunes[i].lanes_per_state;
-        const int L = robots[i]->T.L, nbp = (int)robots[i]->T.blocks.size();
-        wave_lds = std::max(wave_lds, groups * wb::group_lds_bytes(L, nmax, robots[i]->T.n_blocks, tunes[i].lanes_per_state));
-        tab_lds = std::max(tab_lds, wb::tab_lds_bytes(nbp));
-        wave_counted = std::max(wave_counted, groups * wb::counted_group_bytes(L, nmax, nbp));
+        const int G = tunes[i].lanes_per_state, L = robots[i]->T.L, nbp = (int)robots[i]->T.blocks.size();
+        lds = std::max(lds, (64 / G) * wb::group_lds_bytes(L, nmax, robots[i]->T.n_blocks, G));
+        wave_counted = std::max(wave_counted, (64 / G) * wb::counted_group_bytes(L, nmax, nbp));
         tab_counted = std::max(tab_counted, wb::counted_tab_bytes(nbp));
     }
-    const size_t lds = 4 * wave_lds + tab_lds, counted = 4 * wave_counted + tab_counted;
+    const size_t counted = 4 * wave_counted + tab_counted;
     if (counted > wb::LDS_LIMIT)
         return fail(WB_ERR_UNSUPPORTED, "plan needs %zu bytes of LDS per workgroup (> %zu)", counted, wb::LDS_LIMIT);
 
@@ -1396,7 +1396,9 @@ int wb_plan_create(const wb_robot *const *robots, const int64_t *B, int32_t n_tr
     };
     std::vector<Item> items;
     for (int i = 0; i < n_trees; ++i) {
-        const int c = tunes[i].states_per_item;
+        // a wavefront's share of the states that four take at a time
+        const int at_once = 64 / tunes[i].lanes_per_state;
+        const int c = ((tunes[i].states_per_item + 3) / 4 + at_once - 1) / at_once * at_once;
         const double per = tunes[i].ns_per_state > 0.0f ? tunes[i].ns_per_state
                                                          : model_cost(robots[i]->T, tunes[i], nmax);
         for (int64_t b0 = 0; b0 < B[i]; b0 += c) {
@@ -1417,17 +1419,19 @@ int wb_plan_create(const wb_robot *const *robots, const int64_t *B, int32_t n_tr
     // alone runs the same list in more than one round)
     bool any_mimic = false;
     for (int i = 0; i < n_trees; ++i) any_mimic |= robots[i]->fz.mimic != 0;
-    const int per_cu = std::min(8, wb::plan_workgroups_per_cu(nmax, any_mimic, lds));
+    const int per_cu = std::min(32, wb::plan_workgroups_per_cu(nmax, any_mimic, lds));
     const int n_wg = (int)std::min<size_t>(items.size(), (size_t)cus * per_cu);
     std::stable_sort(items.begin(), items.end(), [](const Item &a, const Item &b) { return a.cost > b.cost; });
-    std::vector<double> load(n_wg, 0.0);
+    // longest first, each to the least loaded workgroup (the first of several)
+    typedef std::pair<double, int> Load;
+    std::priority_queue<Load, std::vector<Load>, std::greater<Load>> load;
+    for (int w = 0; w < n_wg; ++w) load.push(Load(0.0, w));
     std::vector<std::vector<wb::PlanItem>> per_wg(n_wg);
     for (const Item &x : items) {
-        int best = 0;
-        for (int w = 1; w < n_wg; ++w)
-            if (load[w] < load[best]) best = w;
-        load[best] += x.cost;
-        per_wg[best].push_back(x.it);
+        const Load l = load.top();
+        load.pop();
+        per_wg[l.second].push_back(x.it);
+        load.push(Load(l.first + x.cost, l.second));
     }
     std::vector<wb::PlanItem> flat;
     std::vector<int32_t> start(n_wg + 1, 0);
@@ -1496,7 +1500,6 @@ int wb_plan_create(const wb_robot *const *robots, const int64_t *B, int32_t n_tr
     p->n_items = (int)flat.size();
     p->device = device;
     p->lds = lds;
-    p->wave_lds = wave_lds;
     p->B.assign(B, B + n_trees);
     for (int i = 0; i < n_trees; ++i) p->n_dof.push_back(robots[i]->T.n);
     p->d_trees = reinterpret_cast<const wb::PlanTree *>(base + o_trees);
@@ -1516,7 +1519,6 @@ int wb_plan_run(const wb_plan *plan, const wb_tree_io *io, float torque_weight, 
     a.trees = plan->d_trees;
     a.items = plan->d_items;
     a.item_start = plan->d_item_start;
-    a.wave_stride = (int32_t)(plan->wave_lds / 16);
     a.k = wb::StepScalars{torque_weight, margin, hinge_weight, lr};
     bool ext = plan->mimic != 0;
     for (int i = 0; i < plan->n_trees; ++i) {

@@ -149,8 +149,7 @@ struct PlanArgs {
     const PlanTree *trees;
     const PlanItem *items;        // grouped by workgroup
     const int32_t *item_start;    // [n_wg + 1]
-    int32_t wave_stride;          // float4s of LDS per wave (the largest over the plan's trees);
-                                  // the block table follows the four waves' regions
+    int32_t pad;
     StepScalars k;
     TreeIO io[WB_PLAN_MAX_TREES];
 };
