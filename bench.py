@@ -798,9 +798,9 @@ def bench_ext_variant(args, st, reps: int = 50):
 def bench_rnea_b256(args, reps: int = 100, B: int = 256):
     """RNEA forward and its VJP (torques, then the gradient of w . tau with
     respect to q, qd and qdd) at 256 states for a 7-joint chain, a 12-DoF
-    tree and the 48-DoF humanoid, in both per-operation forms: one state per
-    lane with the forward's cache, and one group of lanes per state that
-    recomputes the forward in the VJP.  `reps` forward + VJP pairs captured
+    tree and the 48-DoF humanoid, in both per-operation forms, a group of
+    lanes per state each: with the forward's cache, and recomputing the
+    forward in the VJP.  `reps` forward + VJP pairs captured
     in one graph (launch-bound at this size when issued eagerly), HIP events
     around its replays on the replaying stream."""
     import torch
@@ -826,7 +826,7 @@ def bench_rnea_b256(args, reps: int = 100, B: int = 256):
             wb.wb_rnea_backward(r, q, qd, qdd, None, gt, gq, gqd, gqdd)
 
         res = {"dof": r.n_dof}
-        for form, fn in (("one_state_per_lane_cached", cached), ("lane_group_recomputed", recomputed)):
+        for form, fn in (("lane_group_cached", cached), ("lane_group_recomputed", recomputed)):
             side = torch.cuda.Stream()
             side.wait_stream(torch.cuda.current_stream())
             with torch.cuda.stream(side):

@@ -1,8 +1,8 @@
 // Exact Euclidean distance transform of a site grid (cuRoboV2 Sec. 5,
 // "Stage 2: Distance Propagation"): the nearest site of every voxel by
 // three separable axis passes, as the PBA+ decomposition of the paper, each
-// line's owners found by monotone search instead of an envelope stack.  Integer arithmetic throughout, so the result is
-// exact.
+// line's owners found by monotone search instead of an envelope stack.
+// Integer arithmetic throughout, so the result is exact.
 //
 // Grid [nz][ny][nx], x fastest.  A site is stored packed as
 // x | y << 10 | z << 20 (coordinates below 1024), NONE (-1) when there is

@@ -394,12 +394,10 @@ __device__ __forceinline__ void spline_reduce_step(const SplineIn &sp, const flo
     }
 }
 
-// Waves per SIMD the register budget is set for: 4 (128 VGPRs) for the lean
-// iteration; 3 for EXT, the variant with external link forces and mimic
-// joints, which holds the forces, the joint-to-link map and their adjoints
-// as well (at 128 VGPRs it spilled ~48 registers); 2 for 12 sphere slots
-// per link, where the group regions (about 55 KB per workgroup) leave room
-// for two workgroups per CU anyway.
+// Waves per SIMD the register budget is set for: 4 (128 VGPRs, no spills,
+// also for EXT with its forces, joint-to-link map and their adjoints); 2 for
+// 12 sphere slots per link, where the group regions (about 14 KB per
+// wavefront) bound the residency.
 template <int NMAX, bool EXT>
 constexpr int fused_waves() { return NMAX > 8 ? 2 : 4; }
 

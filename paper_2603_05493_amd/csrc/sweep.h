@@ -39,9 +39,8 @@
 // table is read from LDS where the caller has staged it; it is padded to a
 // multiple of 128 entries with the empty pair (L, L), whose bounding sphere
 // Bd[L] has radius -1e30, so the pass-1 loop needs no range tests.  Entries
-// are byte offsets of the links' bounds and lists hold table indices, of 16
-// bits for robots of at most 255 links: unpacking link numbers took 5 of a
-// test's 28 vector instructions, and the fused kernel is bound by their issue.
+// and row codes are byte offsets: unpacking link numbers took 5 of a test's
+// 28 vector instructions, and the fused kernel is bound by their issue.
 //
 // Reduce: the pair count is a scalar ballot popcount per pair (one state per
 // wavefront) or a per-lane counter summed over the group; the maximum is a

@@ -120,8 +120,8 @@ __device__ __forceinline__ void rotate_inertia(const M3 &R, const float *Ic, flo
 // parent's acceleration a - S qdd - qd v x S and the force passed to the
 // parent, whose adjoint is fb - taub S (every S x S vanishes).  Against
 // summing the turned axes and inertias of the whole subtree this takes one
-// of three subtree sums and four force products out of the VJP (humanoid,
-// 24,576 states: see the kernels that call it).
+// of three subtree sums and four force products out of the VJP (fused
+// iteration of the humanoid, 24,576 states: 108 -> 103 us a launch).
 // c = v x S, Iv = I v; subsum the subtree sum to use.  Lanes outside the
 // robot must hold zeros.
 template <typename Sum>

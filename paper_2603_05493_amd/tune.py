@@ -12,7 +12,7 @@ Results are a JSON table keyed by ``Robot.topology_key()``:
     {key: {"lanes_per_state": G, "states_per_item": c, "ns_per_state": t,
            "B": batch, "candidates": [[G, c, ns_per_state], ...],
            "sweep_split_below": n, "sweep_us": [[B, wave form us, workgroup form us], ...],
-           "fk_groups_below": m, "fk_us": [[B, lane form us, group form us], ...],
+           "fk_groups_below": m, "fk_us": [[B, large-batch form us, group form us], ...],
            "fk_pose_groups_below": m2, "fk_pose_us": [...]}}
 plus, for the uneven batch, an entry keyed by ``plan_key`` with the trees'
 shapes measured inside the plan (``tune_plan``).
@@ -129,9 +129,9 @@ FK_BATCHES = (256, 1024, 3072, 8192, 12288, 16384, 24576)
 
 def tune_fk_groups(robot: wb.Robot, desc, pose: bool = False, batches: Iterable[int] = FK_BATCHES, reps: int = 10,
                    rounds: int = 3) -> Dict:
-    """The batch size below which wb_fk and wb_fk_backward should take one
-    group of lanes per state rather than one lane per state, timed in both
-    forms at each batch size (interleaved rounds, median).  pose=False: FK
+    """The batch size below which wb_fk and wb_fk_backward should take their
+    pointer-jumping form rather than the one that composes the links level
+    by level, timed in both at each batch size (interleaved rounds, median).  pose=False: FK
     to sphere centres plus the adjoint of a sphere gradient, no link poses
     (key fk_groups_below); pose=True: FK writing link poses and sphere
     centres plus the adjoint reading the poses, as the per-operation
