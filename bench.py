@@ -47,21 +47,21 @@ PEAK_HBM_GBPS = 8000.0
 # calibration (FETCH x2.000, WRITE x1.000).  Valid only for the kernel sources
 # and the launch shape (states per workgroup) it was measured with; reported
 # as null once either changes.
-TRAFFIC_MEASURED = {"sources_sha1": "34f9acce194059b226ed12f33803f5f3be188970", "states": 24576,
-                    "states_per_item": 8, "bytes_per_launch": (14296.8 + 14273.5) * 1024}
+TRAFFIC_MEASURED = {"sources_sha1": "54c7c7b507f93f98e683d81cdfacd5ce983ed7db", "states": 24576,
+                    "states_per_item": 8, "bytes_per_launch": (14276.0 + 14228.8) * 1024}
 FUSED_SOURCES = ("fused.hip", "sweep.h", "lanes.h", "tree.h", "spline.h", "spatial.h", "wb_internal.h")
 
 
 # HBM traffic of the kinematics-outputs kernel, measured the same way
 # (profiles/k_kinematics_humanoid48_B24576.md; 4 tool frames), per launch.
-KIN_TRAFFIC_MEASURED = {"sources_sha1": "b54a8297dcd08b42f655f85c518d89b665149710", "states": 24576, "tools": 4,
-                        "forward_bytes": (5606.6 + 133142.4) * 1024,
-                        "backward_bytes": (9674.9 + 4608.0) * 1024}
+KIN_TRAFFIC_MEASURED = {"sources_sha1": "572fbb90f20d5cdadce2bb217657381bc5a723e4", "states": 24576, "tools": 4,
+                        "forward_bytes": (5560.0 + 133122.2) * 1024,
+                        "backward_bytes": (9676.0 + 4608.0) * 1024}
 KIN_SOURCES = ("kinematics.hip", "kin.h", "lanes.h", "spatial.h", "wb_internal.h")
 # ... and of the three distance-transform launches on the 256 x 256 x 128 room
 # (profiles/edt_room256_kernel_trace.md), summed per transform.
-EDT_TRAFFIC_MEASURED = {"sources_sha1": "6204f6dc8c5a02fafb8a44743f39c46649059278", "grid": [256, 256, 128],
-                        "bytes": (8242.3 + 32928.1 + 32938.4 + 32768.0 + 32768.0 + 65536.0) * 1024}
+EDT_TRAFFIC_MEASURED = {"sources_sha1": "0e6cd7f251310eed65383a2983d4cdff92c7f174", "grid": [256, 256, 128],
+                        "bytes": (8242.3 + 36468.4 + 41130.8 + 32768.0 + 32768.0 + 65536.0) * 1024}
 EDT_SOURCES = ("edt.hip", "edt.h")
 
 
