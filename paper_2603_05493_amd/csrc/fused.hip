@@ -469,7 +469,7 @@ __device__ __forceinline__ PlanTree load_tree(const PlanTree *t) {
 // plan's work list, each a contiguous range of states of one robot.  One
 // wavefront a workgroup as in k_fused_step: four shared each item's states
 // and a staged block table, and met at every change of robot.  Four
-// wavefronts a SIMD (128 VGPRs, 28 bytes spilled): 15,360 states of four trees
+// wavefronts a SIMD (128 VGPRs, 20 bytes spilled): 15,360 states of four trees
 // 43.7 us at three, 40.5 at four, 41.7 with four-wavefront workgroups.  EXT as
 // for k_fused_step, chosen when any tree has mimic joints or external forces.
 template <int NMAX, bool EXT>
