@@ -452,6 +452,7 @@ __device__ __forceinline__ PlanTree load_tree(const PlanTree *t) {
     r.slot_r = as_global(r.slot_r);
     r.blocks = as_global(r.blocks);
     r.allow = as_global(r.allow);
+    r.kids = as_global(r.kids);
     r.pair_off = as_global(r.pair_off);
     r.pair_cnt = as_global(r.pair_cnt);
     r.pair_s = as_global(r.pair_s);

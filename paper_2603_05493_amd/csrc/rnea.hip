@@ -1,12 +1,21 @@
-// Recursive Newton-Euler inverse dynamics and its vector-Jacobian product,
-// one state per lane (cuRoboV2 Sec. 6.3, Alg. 4 and the role of Alg. 5).
+// Recursive Newton-Euler inverse dynamics and its vector-Jacobian product
+// through the forward cache (cuRoboV2 Sec. 6.3, Alg. 4 and the role of
+// Alg. 5).
 //
 // The per-link sweeps follow Alg. 4 in link coordinates with the compact
-// transform (R, p) and compact inertia (m, c, Ic).  Links are visited in
-// index order (parents first) instead of level by level: with one state per
-// lane there is no intra-state parallelism to exploit, and index order keeps
-// the parent's values in registers whenever the parent is the previous link
-// (a "carry"), touching the cache only at branch points.
+// transform (R, p) and compact inertia (m, c, Ic), in two forms:
+//   * robots of at most 64 links: one thread per (state, link), the links of
+//     a level of the tree at a time (k_rnea_levels, k_rnea_backward_levels);
+//   * larger ones: one state per lane, links in index order (parents first),
+//     which keeps the parent's values in registers whenever the parent is
+//     the previous link (a "carry"), touching the cache only at branches.
+// Both sum in link coordinates, so the torque of a light link far from the
+// base keeps its digits, and a value that is not finite stays with the
+// link's ancestors and descendants.  Sums over subtrees taken as differences
+// of a scan in world coordinates (tree_kernels.hip, the form without a
+// cache) lose a factor of ten at a humanoid's fingers (relative RMS error of
+// their torques 1.3e-5 against 1.2e-6) and carry a NaN into every lane
+// behind it.
 //
 // Cache layout [L][18][B]: v (6), a (6), accumulated force F (6) per link;
 // link 0 (the fixed base, v = 0, a = -g) is not stored.  External link
@@ -24,6 +33,7 @@
 //                           thb -= ab.crm(S) X a_p + vb.crm(S) X v_p.
 // The crf(S thd) ab term is the velocity dependence of the Coriolis term of
 // the acceleration recursion; it belongs to the exact VJP.
+#include "lanes.h"
 #include "spatial.h"
 
 namespace wb {
@@ -249,6 +259,223 @@ __global__ void __launch_bounds__(256) k_rnea_backward(DevRobot rb, int64_t nb, 
     }
 }
 
+// ---- one thread per (state, link), level by level.  A workgroup takes TS
+// consecutive states: thread (t, l) owns link l in state t, so that a wavefront
+// touches pieces of TS floats of 64 / TS links' rows.  What passes between
+// links goes through an LDS tile, row link * 12 + c holding component c,
+// padded by one float.
+template <int TS>
+__device__ __forceinline__ void row_put(float *tile, int link, int c, int t, SV x) {
+    float *r = tile + (link * 12 + c) * (TS + 1) + t;
+    r[0] = x.w.x; r[TS + 1] = x.w.y; r[2 * (TS + 1)] = x.w.z;
+    r[3 * (TS + 1)] = x.l.x; r[4 * (TS + 1)] = x.l.y; r[5 * (TS + 1)] = x.l.z;
+}
+template <int TS>
+__device__ __forceinline__ SV row_get(const float *tile, int link, int c, int t) {
+    const float *r = tile + (link * 12 + c) * (TS + 1) + t;
+    return sv(v3(r[0], r[TS + 1], r[2 * (TS + 1)]), v3(r[3 * (TS + 1)], r[4 * (TS + 1)], r[5 * (TS + 1)]));
+}
+
+// Joint rows of robots where a joint drives several links: every thread
+// leaves its link's (already scaled) value x in the tile, then thread (t, j)
+// adds up those of joint j's links.  Every thread of the workgroup calls this.
+template <int TS>
+__device__ __forceinline__ float joint_sum(float *tile, const DevRobot &rb, const DevFused &fz, int l, int t, float x) {
+    __syncthreads();
+    if (l < rb.L) tile[l * (TS + 1) + t] = x;
+    __syncthreads();
+    float acc = 0.f;
+    if (l < rb.n)
+        for (int k = 0; k < fz.mc; ++k) {
+            const int lane = fz.conn[k * 64 + l];
+            if (lane >= 0) acc += tile[fz.li[lane] * (TS + 1) + t];
+        }
+    return acc;
+}
+
+// What bounds it is the chain of levels, a barrier, an LDS read and a
+// transform each, down the tree and up again: a batch has to fill the chip
+// with workgroups to hide it (humanoid, 12 levels: 11 us at 32 to 1,024
+// states, 54 us at 24,576, where the bytes take 22; one state per lane 82 and
+// 119 us; a 12-joint tree at 256 states 4.5 against 21.5).
+// nb: states; B: row length of every [k][B] array (the ABI's ld >= nb).
+template <int TS>
+__global__ void __launch_bounds__(64 * TS) k_rnea_levels(DevRobot rb, DevFused fz, int64_t nb, int64_t B,
+                                                         const float *__restrict__ q, const float *__restrict__ qd,
+                                                         const float *__restrict__ qdd,
+                                                         const float *__restrict__ f_ext, float *__restrict__ tau,
+                                                         float *__restrict__ cache) {
+    extern __shared__ float tile[];
+    const int t = threadIdx.x % TS, l = threadIdx.x / TS;
+    const int64_t s0 = (int64_t)xcd_chunk() * TS, b = min(s0 + t, nb - 1);   // states past the batch repeat its last
+    const bool link = l > 0 && l < rb.L, valid = s0 + t < nb;
+    const SV zero = sv(v3(0.f, 0.f, 0.f), v3(0.f, 0.f, 0.f));
+    LinkI li{};
+    LinkF lf{};
+    JointIn J{0.f, 0.f, 0.f};
+    M3 R;
+    if (link) {
+        li = rb.li[l];
+        lf = rb.lf[l];
+        J = joint_in(lf, li, q, qd, qdd, B, b);
+        R = local_rotation(lf, li, J.th);
+    } else if (l == 0) {
+        row_put<TS>(tile, 0, 0, t, zero);
+        row_put<TS>(tile, 0, 6, t, sv(v3(0.f, 0.f, 0.f), v3(-rb.gx, -rb.gy, -rb.gz)));
+    }
+    const V3 r = v3(lf.fp[0], lf.fp[1], lf.fp[2]), s = v3(lf.axis[0], lf.axis[1], lf.axis[2]);
+    // base -> tips: velocities and accelerations
+    SV v = zero, a = zero;
+    for (int d = 1; d <= rb.max_depth; ++d) {
+        __syncthreads();
+        if (link && li.depth == d) {
+            const SV Sqd = sv(J.thd * s, v3(0.f, 0.f, 0.f));
+            v = X_apply(R, r, row_get<TS>(tile, li.parent, 0, t)) + Sqd;
+            a = X_apply(R, r, row_get<TS>(tile, li.parent, 6, t)) + sv(J.thdd * s, v3(0.f, 0.f, 0.f)) + crm(v, Sqd);
+            row_put<TS>(tile, l, 0, t, v);
+            row_put<TS>(tile, l, 6, t, a);
+        }
+    }
+    // link forces
+    SV F = zero;
+    float *ck = cache + (int64_t)(l * 18) * B + b;
+    if (link) {
+        F = I_apply(lf, a) + crf(v, I_apply(lf, v));
+        if (f_ext) F = F - ld_sv(f_ext + (int64_t)(l * 6) * B + b, B);
+        if (valid) {
+            st_sv(ck, B, v);
+            st_sv(ck + 6 * B, B, a);
+        }
+    }
+    // tips -> base: each link adds its children's forces, in its coordinates
+    const int child = link ? rb.kids[l] : -1;
+    for (int d = rb.max_depth; d >= 1; --d) {
+        __syncthreads();
+        if (link && li.depth == d) {
+            for (int c = child; c >= 0; c = rb.kids[64 + c]) F += row_get<TS>(tile, c, 0, t);
+            if (d > 1) row_put<TS>(tile, l, 0, t, XT_apply(R, r, F));
+        }
+    }
+    if (link && valid) st_sv(ck + 12 * B, B, F);
+    const float x = link && li.revolute ? lf.mult * dot(s, F.w) : 0.f;
+    if (rb.simple_joints) {
+        if (link && li.revolute && valid) tau[(int64_t)li.jidx * B + b] = x;
+    } else {
+        const float sum = joint_sum<TS>(tile, rb, fz, l, t, x);
+        if (l < rb.n && valid) tau[(int64_t)l * B + b] = sum;
+    }
+}
+
+// The exact reverse mode of it (sweeps A and B above), v, a and F read from
+// the cache (humanoid: 11.5 us at 1,024 states, 64 us at 24,576, where the
+// bytes take 26; one state per lane 127 and 189).
+template <int TS>
+__global__ void __launch_bounds__(64 * TS) k_rnea_backward_levels(DevRobot rb, DevFused fz, int64_t nb, int64_t B,
+                                                                  const float *__restrict__ q,
+                                                                  const float *__restrict__ qd,
+                                                                  const float *__restrict__ qdd,
+                                                                  const float *__restrict__ cache,
+                                                                  const float *__restrict__ g_tau,
+                                                                  float *__restrict__ g_q, float *__restrict__ g_qd,
+                                                                  float *__restrict__ g_qdd,
+                                                                  float *__restrict__ g_fext) {
+    extern __shared__ float tile[];
+    const int t = threadIdx.x % TS, l = threadIdx.x / TS;
+    const int64_t s0 = (int64_t)xcd_chunk() * TS, b = min(s0 + t, nb - 1);
+    const bool link = l > 0 && l < rb.L, valid = s0 + t < nb;
+    const SV zero = sv(v3(0.f, 0.f, 0.f), v3(0.f, 0.f, 0.f));
+    LinkI li{};
+    LinkF lf{};
+    JointIn J{0.f, 0.f, 0.f};
+    M3 R;
+    SV v = zero;
+    if (link) {
+        li = rb.li[l];
+        lf = rb.lf[l];
+        const float *ck = cache + (int64_t)(l * 18) * B + b;
+        v = ld_sv(ck, B);
+        row_put<TS>(tile, l, 0, t, v);
+        row_put<TS>(tile, l, 6, t, ld_sv(ck + 6 * B, B));
+        J = joint_in(lf, li, q, qd, qdd, B, b);
+        R = local_rotation(lf, li, J.th);
+    } else if (l == 0) {
+        row_put<TS>(tile, 0, 0, t, zero);
+        row_put<TS>(tile, 0, 6, t, sv(v3(0.f, 0.f, 0.f), v3(-rb.gx, -rb.gy, -rb.gz)));
+    }
+    const V3 r = v3(lf.fp[0], lf.fp[1], lf.fp[2]), s = v3(lf.axis[0], lf.axis[1], lf.axis[2]);
+    const bool revolute = link && li.revolute;
+    // s x the parent's acceleration and velocity in this link's coordinates
+    __syncthreads();
+    SV sXa = zero, sXv = zero;
+    if (revolute) {
+        const SV Xv = X_apply(R, r, row_get<TS>(tile, li.parent, 0, t)), Xa = X_apply(R, r, row_get<TS>(tile, li.parent, 6, t));
+        sXa = sv(cross(s, Xa.w), cross(s, Xa.l));
+        sXv = sv(cross(s, Xv.w), cross(s, Xv.l));
+    }
+    // sweep A, base -> tips: adjoint of the force accumulation
+    __syncthreads();
+    if (l == 0) row_put<TS>(tile, 0, 0, t, zero);
+    const float tb = revolute ? lf.mult * g_tau[(int64_t)li.jidx * B + b] : 0.0f;
+    SV Fb = zero, XFp = zero;
+    for (int d = 1; d <= rb.max_depth; ++d) {
+        __syncthreads();
+        if (link && li.depth == d) {
+            XFp = X_apply(R, r, row_get<TS>(tile, li.parent, 0, t));
+            Fb = sv(tb * s, v3(0.f, 0.f, 0.f)) + XFp;
+            row_put<TS>(tile, l, 0, t, Fb);
+        }
+    }
+    if (g_fext && l < rb.L && valid) st_sv(g_fext + (int64_t)(l * 6) * B + b, B, zero - Fb);   // the base's reaches no joint
+    float th_b = 0.f;
+    if (revolute) {
+        const SV F = ld_sv(cache + (int64_t)(l * 18 + 12) * B + b, B);
+        th_b = dot(XFp.w, cross(s, F.w)) + dot(XFp.l, cross(s, F.l));
+    }
+    // sweep B, tips -> base: adjoint of the velocity/acceleration recursion
+    SV ab = I_apply(lf, Fb);
+    SV vb = zero - (crf(Fb, I_apply(lf, v)) + I_apply(lf, crm(v, Fb)));
+    const SV Sqd = sv(J.thd * s, v3(0.f, 0.f, 0.f));
+    const int child = link ? rb.kids[l] : -1;
+    for (int d = rb.max_depth; d >= 1; --d) {
+        __syncthreads();
+        if (link && li.depth == d) {
+            for (int c = child; c >= 0; c = rb.kids[64 + c]) {
+                ab += row_get<TS>(tile, c, 0, t);
+                vb += row_get<TS>(tile, c, 6, t);
+            }
+            vb += crf(Sqd, ab);
+            if (d > 1) {
+                row_put<TS>(tile, l, 0, t, XT_apply(R, r, ab));
+                row_put<TS>(tile, l, 6, t, XT_apply(R, r, vb));
+            }
+        }
+    }
+    float thd_b = 0.f, thdd_b = 0.f;
+    if (revolute) {
+        thdd_b = lf.mult * dot(s, ab.w);
+        thd_b = lf.mult * (dot(s, vb.w) - dot(s, crf(v, ab).w));
+        th_b = lf.mult * (th_b - (dot(ab, sXa) + dot(vb, sXv)));
+    }
+    if (rb.simple_joints) {
+        if (revolute && valid) {
+            const int64_t o = (int64_t)li.jidx * B + b;
+            g_q[o] = th_b;
+            g_qd[o] = thd_b;
+            g_qdd[o] = thdd_b;
+        }
+        return;
+    }
+    th_b = joint_sum<TS>(tile, rb, fz, l, t, th_b);
+    thd_b = joint_sum<TS>(tile, rb, fz, l, t, thd_b);
+    thdd_b = joint_sum<TS>(tile, rb, fz, l, t, thdd_b);
+    if (l < rb.n && valid) {
+        const int64_t o = (int64_t)l * B + b;
+        g_q[o] = th_b;
+        g_qd[o] = thd_b;
+        g_qdd[o] = thdd_b;
+    }
+}
+
 hipError_t launch_rnea(const DevRobot &rb, int64_t B, int64_t ld, const float *q, const float *qd,
                        const float *qdd, const float *f_ext, float *tau, float *cache, hipStream_t s) {
     if (B == 0) return hipSuccess;
@@ -264,6 +491,50 @@ hipError_t launch_rnea_backward(const DevRobot &rb, int64_t B, int64_t ld, const
     dim3 grid((unsigned)((B + 255) / 256));
     hipLaunchKernelGGL(k_rnea_backward, grid, dim3(256), 0, s, rb, B, ld, q, qd, qdd, cache, g_tau, g_q,
                        g_qd, g_qdd, g_fext, ws);
+    return hipGetLastError();
+}
+
+// States a tile (wide: 8): 4 where a batch has to be spread over the chip, 8, whose
+// pieces of a row are whole 32-byte sectors, from 8 states per compute unit on
+// (forward / backward, 4 against 8 states: humanoid 10.8 / 11.2 against 11.0 /
+// 11.5 us at 1,024 states, 15.5 / 15.8 against 13.9 / 13.6 at 4,096, 52 / 63
+// against 54 / 64 at 24,576; 7-joint chain 7.3 / 7.5 against 6.8 / 7.1 at
+// 4,096, 14.2 / 14.3 against 10.5 / 9.7 at 24,576).  16 states gain the chain
+// another microsecond there and cost the humanoid 11.
+// Threads of a tile's workgroup: one per (state, link), whole wavefronts.
+static dim3 level_block(int L, int ts) { return dim3((unsigned)((L * ts + 63) / 64 * 64)); }
+
+template <int TS>
+static void launch_levels(const DevRobot &rb, const DevFused &fz, int64_t B, int64_t ld, const float *q,
+                          const float *qd, const float *qdd, const float *f_ext, float *tau, float *cache,
+                          hipStream_t s) {
+    hipLaunchKernelGGL((k_rnea_levels<TS>), dim3((unsigned)((B + TS - 1) / TS)), level_block(rb.L, TS),
+                       (size_t)rb.L * 12 * (TS + 1) * 4, s, rb, fz, B, ld, q, qd, qdd, f_ext, tau, cache);
+}
+template <int TS>
+static void launch_backward_levels(const DevRobot &rb, const DevFused &fz, int64_t B, int64_t ld, const float *q,
+                                   const float *qd, const float *qdd, const float *cache, const float *g_tau,
+                                   float *g_q, float *g_qd, float *g_qdd, float *g_fext, hipStream_t s) {
+    hipLaunchKernelGGL((k_rnea_backward_levels<TS>), dim3((unsigned)((B + TS - 1) / TS)), level_block(rb.L, TS),
+                       (size_t)rb.L * 12 * (TS + 1) * 4, s, rb, fz, B, ld, q, qd, qdd, cache, g_tau, g_q, g_qd, g_qdd,
+                       g_fext);
+}
+
+hipError_t launch_rnea_levels(const DevRobot &rb, const DevFused &fz, int64_t B, int64_t ld, const float *q,
+                              const float *qd, const float *qdd, const float *f_ext, float *tau, float *cache,
+                              bool wide, hipStream_t s) {
+    if (B == 0) return hipSuccess;
+    if (wide) launch_levels<8>(rb, fz, B, ld, q, qd, qdd, f_ext, tau, cache, s);
+    else launch_levels<4>(rb, fz, B, ld, q, qd, qdd, f_ext, tau, cache, s);
+    return hipGetLastError();
+}
+
+hipError_t launch_rnea_backward_levels(const DevRobot &rb, const DevFused &fz, int64_t B, int64_t ld, const float *q,
+                                       const float *qd, const float *qdd, const float *cache, const float *g_tau,
+                                       float *g_q, float *g_qd, float *g_qdd, float *g_fext, bool wide, hipStream_t s) {
+    if (B == 0) return hipSuccess;
+    if (wide) launch_backward_levels<8>(rb, fz, B, ld, q, qd, qdd, cache, g_tau, g_q, g_qd, g_qdd, g_fext, s);
+    else launch_backward_levels<4>(rb, fz, B, ld, q, qd, qdd, cache, g_tau, g_q, g_qd, g_qdd, g_fext, s);
     return hipGetLastError();
 }
 

@@ -27,69 +27,26 @@
 
 namespace wb {
 
-// Row tile of TS states staged in LDS, for the [L][18][B] cache: a group
-// holds one state, so its lanes touch one float of every row, while a tile
-// moves pieces of TS floats.  Row link * 6 + c holds component c, padded by
-// one float.
-template <int TS>
-__device__ __forceinline__ void tile_put(float *tile, int link, int s, SV x) {
-    float *r = tile + link * 6 * (TS + 1) + s;
-    r[0] = x.w.x; r[TS + 1] = x.w.y; r[2 * (TS + 1)] = x.w.z;
-    r[3 * (TS + 1)] = x.l.x; r[4 * (TS + 1)] = x.l.y; r[5 * (TS + 1)] = x.l.z;
-}
-template <int TS>
-__device__ __forceinline__ SV tile_get(const float *tile, int link, int s) {
-    const float *r = tile + link * 6 * (TS + 1) + s;
-    return sv(v3(r[0], r[TS + 1], r[2 * (TS + 1)]), v3(r[3 * (TS + 1)], r[4 * (TS + 1)], r[5 * (TS + 1)]));
-}
-// Rows part .. part + 5 of every link but the base between the tile and the
-// cache, `cnt` states from b0; thread t takes state t % TS.
-template <bool STORE, int TS>
-__device__ __forceinline__ void tile_move(float *tile, float *cache, int part, int L, int64_t B, int64_t b0, int cnt) {
-    const int s = threadIdx.x % TS;
-    if (s < cnt)
-        for (int r = 6 + threadIdx.x / TS; r < 6 * L; r += blockDim.x / TS) {
-            float *g = cache + (int64_t)(r + 12 * (r / 6) + part) * B + b0 + s;
-            if (STORE) *g = tile[r * (TS + 1) + s];
-            else tile[r * (TS + 1) + s] = *g;
-        }
-}
-
 // A world-frame (about the world origin) motion or force vector in the
 // coordinates of the link with pose (R, p), and back for a force.
 __device__ __forceinline__ SV motion_to_link(const M3 &R, V3 p, SV u) {
     return sv(mulT(R, u.w), mulT(R, u.l + cross(u.w, p)));
-}
-__device__ __forceinline__ SV force_to_link(const M3 &R, V3 p, SV f) {
-    return sv(mulT(R, f.w - cross(p, f.l)), mulT(R, f.l));
 }
 __device__ __forceinline__ SV force_to_world(const M3 &R, V3 p, SV f) {
     const V3 Rf = mul(R, f.l);
     return sv(mul(R, f.w) + cross(p, Rf), Rf);
 }
 
-// RNEA (or its VJP, BWD), one state per group of G lanes.  CACHE: the
-// forward also writes each link's v, a and accumulated force F in link
-// coordinates; the backward takes F (which holds any external forces) from
-// it and recomputes v and a, which are cheaper formed than read.  These
-// forms replace the link-by-link recursion in link coordinates and sum the
-// subtrees in split form, to be as exact (torques of a 37-joint tree against
-// 64 bits: 1.6e-7 by the recursion, 5.4e-7 from plain scan differences).
-// A workgroup of TS * G lanes owns TS consecutive states; the cache moves
-// through an LDS tile.
+// RNEA (or its VJP, BWD), one state per group of G lanes.
 // nb: states; B: row length of every [k][B] array (the ABI's ld >= nb).
-template <bool BWD, bool CACHE, int TS, int G>
-__global__ void __launch_bounds__(TS * G)
+template <bool BWD, int G>
+__global__ void __launch_bounds__(256)
     k_rnea_lanes(DevRobot rb, DevFused fz, int64_t nb, int64_t B, const float *__restrict__ q,
                  const float *__restrict__ qd, const float *__restrict__ qdd, const float *__restrict__ f_ext,
-                 float *__restrict__ tau, float *__restrict__ cache, const float *__restrict__ g_tau,
-                 float *__restrict__ g_q, float *__restrict__ g_qd, float *__restrict__ g_qdd,
-                 float *__restrict__ g_fext) {
-    extern __shared__ float tile[];
-    const int gl = threadIdx.x & (G - 1), ts = threadIdx.x / G;   // the group's lane and state in the tile
-    const int64_t s0 = (int64_t)(CACHE ? xcd_chunk() : blockIdx.x) * TS, s = s0 + ts;
-    const int cnt = (int)min((int64_t)TS, nb - s0);
-    if (BWD && CACHE) tile_move<false, TS>(tile, cache, 12, rb.L, B, s0, cnt);
+                 float *__restrict__ tau, const float *__restrict__ g_tau, float *__restrict__ g_q,
+                 float *__restrict__ g_qd, float *__restrict__ g_qdd, float *__restrict__ g_fext) {
+    const int gl = threadIdx.x & (G - 1);
+    const int64_t s = ((int64_t)blockIdx.x * 256 + threadIdx.x) / G;
     const bool valid = s < nb;
     const int64_t b = valid ? s : nb - 1;   // groups past the end compute on a valid state, store nothing
     const int *li = fz.li;
@@ -100,9 +57,7 @@ __global__ void __launch_bounds__(TS * G)
     const int jidx = li[3 * 64 + gl];
     const int link = li[0 * 64 + gl];
     const Subtree sub = subtree_of(li[2 * 64 + gl], gl);
-    auto subsum = [&](SV x) {
-        return CACHE ? subtree_sum_split(x, sub, fz.branched != 0, G) : subtree_sum(x, sub, G);
-    };
+    auto subsum = [&](SV x) { return subtree_sum(x, sub, G); };
     const bool mim = fz.mimic != 0;
     float th = 0.f, thd = 0.f, thdd = 0.f, mult = 1.f;
     if (revolute) {
@@ -141,36 +96,18 @@ __global__ void __launch_bounds__(TS * G)
     SV a = path_sum(thdd * S + thd * c, parent_lane, fz.jsteps, G);
     if (act) a += sv(v3(0.f, 0.f, 0.f), v3(-rb.gx, -rb.gy, -rb.gz));
     const SV Iv = iw_apply(J, v);
-    SV F;
-    if (BWD && CACHE) {
-        __syncthreads();
-        F = act && link > 0 ? tile_get<TS>(tile, link, ts) : zsv();
-        F = force_to_world(R, p, F);
-    } else {
-        F = iw_apply(J, a) + crf(v, Iv);
-        if (f_ext && act) {   // external force in world coordinates, X* f_ext
-            const float *fx = f_ext + (int64_t)(link * 6) * B + b;
-            F = F - force_to_world(R, p, sv(v3(fx[0], fx[B], fx[2 * B]), v3(fx[3 * B], fx[4 * B], fx[5 * B])));
-        }
-        F = subsum(F);
+    SV F = iw_apply(J, a) + crf(v, Iv);
+    if (f_ext && act) {   // external force in world coordinates, X* f_ext
+        const float *fx = f_ext + (int64_t)(link * 6) * B + b;
+        F = F - force_to_world(R, p, sv(v3(fx[0], fx[B], fx[2 * B]), v3(fx[3 * B], fx[4 * B], fx[5 * B])));
     }
+    F = subsum(F);
     const bool jlane = mim ? gl < rb.n : revolute;
     const int64_t jrow = (int64_t)(mim ? gl : jidx) * B + b;
     if (!BWD) {
         float t = revolute ? dot(S, F) : 0.f;
         if (mim) t = gather_joint(mult * t, fz, gl, G);
         if (valid && jlane) tau[jrow] = t;
-        if (CACHE) {
-#pragma unroll
-            for (int part = 0; part < 3; ++part) {
-                const SV x = part == 0 ? motion_to_link(R, p, v)
-                                       : (part == 1 ? motion_to_link(R, p, a) : force_to_link(R, p, F));
-                if (part > 0) __syncthreads();   // the tile's previous rows are out
-                if (act && link > 0) tile_put<TS>(tile, link, ts, x);
-                __syncthreads();
-                tile_move<true, TS>(tile, cache, 6 * part, rb.L, B, s0, cnt);
-            }
-        }
         return;
     }
     // tau-bar of the lane's link: m_l tau-bar_j with mimic joints
@@ -476,53 +413,38 @@ hipError_t launch_fk_backward_lanes(const DevRobot &rb, const DevFused &fz, int6
     return hipGetLastError();
 }
 
-template <bool BWD, bool CACHE, int TS, int G>
+template <bool BWD, int G>
 static hipError_t launch_rnea_g(const DevRobot &rb, const DevFused &fz, int64_t B, int64_t ld, const float *q,
-                                const float *qd, const float *qdd, const float *f_ext, float *tau, float *cache,
-                                const float *g_tau, float *g_q, float *g_qd, float *g_qdd, float *g_fext,
-                                hipStream_t s) {
-    hipLaunchKernelGGL((k_rnea_lanes<BWD, CACHE, TS, G>), dim3((unsigned)((B + TS - 1) / TS)), dim3(TS * G),
-                       CACHE ? (size_t)rb.L * 6 * (TS + 1) * 4 : 0, s, rb, fz, B, ld, q, qd, qdd, f_ext, tau, cache,
-                       g_tau, g_q, g_qd, g_qdd, g_fext);
+                                const float *qd, const float *qdd, const float *f_ext, float *tau, const float *g_tau,
+                                float *g_q, float *g_qd, float *g_qdd, float *g_fext, hipStream_t s) {
+    hipLaunchKernelGGL((k_rnea_lanes<BWD, G>), dim3((unsigned)((B * G + 255) / 256)), dim3(256), 0, s, rb, fz, B, ld, q,
+                       qd, qdd, f_ext, tau, g_tau, g_q, g_qd, g_qdd, g_fext);
     return hipGetLastError();
 }
 
-// Without the cache a workgroup is 256 lanes.  With it, 4 states: wider
-// pieces of the rows do not pay for the larger workgroups, whose wavefronts
-// wait for each other at the tile (humanoid, forward / backward with 4, 8 and
-// 16 states a workgroup: 6.8 / 7.1, 7.6 / 9.0, 11.2 / 13.0 us at 32 states;
-// 46 / 60, 46 / 66, 65 / 83 us at 24,576).
-template <bool BWD, bool CACHE>
+template <bool BWD>
 static hipError_t launch_rnea_any(const DevRobot &rb, const DevFused &fz, int64_t B, int64_t ld, const float *q,
-                                  const float *qd, const float *qdd, const float *f_ext, float *tau, float *cache,
+                                  const float *qd, const float *qdd, const float *f_ext, float *tau,
                                   const float *g_tau, float *g_q, float *g_qd, float *g_qdd, float *g_fext,
                                   hipStream_t s) {
     if (B == 0) return hipSuccess;
     switch (lanes_for(rb.L)) {
-        case 16: return launch_rnea_g<BWD, CACHE, CACHE ? 4 : 16, 16>(rb, fz, B, ld, q, qd, qdd, f_ext, tau, cache, g_tau, g_q, g_qd, g_qdd, g_fext, s);
-        case 32: return launch_rnea_g<BWD, CACHE, CACHE ? 4 : 8, 32>(rb, fz, B, ld, q, qd, qdd, f_ext, tau, cache, g_tau, g_q, g_qd, g_qdd, g_fext, s);
-        default: return launch_rnea_g<BWD, CACHE, CACHE ? 4 : 4, 64>(rb, fz, B, ld, q, qd, qdd, f_ext, tau, cache, g_tau, g_q, g_qd, g_qdd, g_fext, s);
+        case 16: return launch_rnea_g<BWD, 16>(rb, fz, B, ld, q, qd, qdd, f_ext, tau, g_tau, g_q, g_qd, g_qdd, g_fext, s);
+        case 32: return launch_rnea_g<BWD, 32>(rb, fz, B, ld, q, qd, qdd, f_ext, tau, g_tau, g_q, g_qd, g_qdd, g_fext, s);
+        default: return launch_rnea_g<BWD, 64>(rb, fz, B, ld, q, qd, qdd, f_ext, tau, g_tau, g_q, g_qd, g_qdd, g_fext, s);
     }
 }
 
 hipError_t launch_rnea_lanes(const DevRobot &rb, const DevFused &fz, int64_t B, int64_t ld, const float *q,
-                             const float *qd, const float *qdd, const float *f_ext, float *tau, float *cache,
-                             hipStream_t s) {
-    return cache ? launch_rnea_any<false, true>(rb, fz, B, ld, q, qd, qdd, f_ext, tau, cache, nullptr, nullptr,
-                                                nullptr, nullptr, nullptr, s)
-                 : launch_rnea_any<false, false>(rb, fz, B, ld, q, qd, qdd, f_ext, tau, nullptr, nullptr, nullptr,
-                                                 nullptr, nullptr, nullptr, s);
+                             const float *qd, const float *qdd, const float *f_ext, float *tau, hipStream_t s) {
+    return launch_rnea_any<false>(rb, fz, B, ld, q, qd, qdd, f_ext, tau, nullptr, nullptr, nullptr, nullptr, nullptr, s);
 }
 
 hipError_t launch_rnea_backward_lanes(const DevRobot &rb, const DevFused &fz, int64_t B, int64_t ld,
                                       const float *q, const float *qd, const float *qdd, const float *f_ext,
-                                      const float *cache, const float *g_tau, float *g_q, float *g_qd, float *g_qdd,
-                                      float *g_fext, hipStream_t s) {
-    float *c = const_cast<float *>(cache);   // the backward only reads it
-    return cache ? launch_rnea_any<true, true>(rb, fz, B, ld, q, qd, qdd, nullptr, nullptr, c, g_tau, g_q, g_qd,
-                                               g_qdd, g_fext, s)
-                 : launch_rnea_any<true, false>(rb, fz, B, ld, q, qd, qdd, f_ext, nullptr, nullptr, g_tau, g_q,
-                                                g_qd, g_qdd, g_fext, s);
+                                      const float *g_tau, float *g_q, float *g_qd, float *g_qdd, float *g_fext,
+                                      hipStream_t s) {
+    return launch_rnea_any<true>(rb, fz, B, ld, q, qd, qdd, f_ext, nullptr, g_tau, g_q, g_qd, g_qdd, g_fext, s);
 }
 
 }  // namespace wb

@@ -58,6 +58,7 @@ struct Tables {
     int f_mimic = 0, f_mc = 1;        // mimic joints present; longest connectedLinks list
     std::vector<int32_t> f_conn;      // [f_mc][64] lanes of each joint's links
     int f_branched = 0;               // some subtree starts past lane 0
+    std::vector<int32_t> kids;        // [2][64] highest child, next lower sibling (-1: none)
     float broad_tol = 0.0f;           // rounding allowance and
     std::vector<uint32_t> f_allow;    // [2][64] checked pairs of the matrix-core broad phase
     // lane tables of the kinematics-outputs kernel (depth-first pre-order)
@@ -299,6 +300,11 @@ void build_fused(Tables &T) {
             if (checked[a * 64 + b + 32]) T.f_allow[l] |= 1u << (16 + r);
             if (checked[(a + 32) * 64 + b + 32]) T.f_allow[64 + l] |= 1u << r;
         }
+    T.kids.assign(2 * 64, -1);
+    for (int k = 1; k < L; ++k) {
+        T.kids[64 + k] = T.kids[T.li[k].parent];
+        T.kids[T.li[k].parent] = k;
+    }
     T.lanes = 1;
     T.fused = T.nmax <= wb::FUSED_MAX_SLOTS &&
               wb::counted_fused_bytes(L, T.nmax, g_default, (int)T.blocks.size()) <= wb::LDS_LIMIT;
@@ -663,7 +669,7 @@ int wb_robot_create(const wb_robot_desc *desc, wb_robot **out) {
     const size_t o_po = append(blob, T.pair_off), o_pc = append(blob, T.pair_cnt);
     const size_t o_ps = append(blob, T.pair_s), o_pt = append(blob, T.pair_t);
     const size_t o_fi = append(blob, T.f_li), o_ff = append(blob, T.f_lf), o_fs = append(blob, T.f_sph);
-    const size_t o_fc = append(blob, T.f_conn), o_fa = append(blob, T.f_allow);
+    const size_t o_fc = append(blob, T.f_conn), o_fa = append(blob, T.f_allow), o_fk = append(blob, T.kids);
     const size_t o_ki = append(blob, T.k_li), o_kf = append(blob, T.k_lf), o_kc = append(blob, T.k_conn);
     const size_t o_tl = append(blob, std::vector<int32_t>(WB_MAX_TOOLS, 0));
     const size_t o_to = append(blob, std::vector<float>(12 * WB_MAX_TOOLS, 0.0f));
@@ -699,6 +705,7 @@ int wb_robot_create(const wb_robot_desc *desc, wb_robot **out) {
     D.slot_r = reinterpret_cast<const float *>(base + o_sr);
     D.allow = reinterpret_cast<const uint32_t *>(base + o_fa);
     D.broad_tol = T.broad_tol;
+    D.kids = reinterpret_cast<const int32_t *>(base + o_fk);
     D.blocks = reinterpret_cast<const uint32_t *>(base + o_bl);
     D.pair_off = reinterpret_cast<const int32_t *>(base + o_po);
     D.pair_cnt = reinterpret_cast<const int32_t *>(base + o_pc);
@@ -781,6 +788,9 @@ bool group_form(const wb_robot *r, int64_t B, bool pose) {
 
 // Its wide tiles from 16 states per compute unit on.
 bool wide_tiles(const wb_robot *r, int64_t B) { return B >= (int64_t)16 * r->cus; }
+
+// RNEA's from 8 (times beside the launchers).
+bool wide_rnea(const wb_robot *r, int64_t B) { return B >= (int64_t)8 * r->cus; }
 }  // namespace
 
 int wb_fk(const wb_robot *robot, int64_t B, int64_t ld, const float *q, float *link_pose, float *spheres,
@@ -818,7 +828,8 @@ int wb_rnea(const wb_robot *robot, int64_t B, int64_t ld, const float *q, const 
         return fail(WB_ERR_UNSUPPORTED, "a robot of %d links (more than 64) needs the cache", robot->T.L);
     if (!robot->T.lanes)
         return finish(wb::launch_rnea(robot->dev, B, ld, q, qd, qdd, f_ext, tau, cache, stream), "wb_rnea launch");
-    return finish(wb::launch_rnea_lanes(robot->dev, robot->fz, B, ld, q, qd, qdd, f_ext, tau, cache, stream),
+    return finish(cache ? wb::launch_rnea_levels(robot->dev, robot->fz, B, ld, q, qd, qdd, f_ext, tau, cache, wide_rnea(robot, B), stream)
+                        : wb::launch_rnea_lanes(robot->dev, robot->fz, B, ld, q, qd, qdd, f_ext, tau, stream),
                   "wb_rnea launch");
 }
 
@@ -926,8 +937,10 @@ int wb_rnea_backward(const wb_robot *robot, int64_t B, int64_t ld, const float *
         return fail(WB_ERR_UNSUPPORTED, "a robot of %d links (more than 64) needs the cache", robot->T.L);
     WB_TRY(check_ptr(workspace, "workspace", cache != nullptr));
     if (robot->T.lanes)
-        return finish(wb::launch_rnea_backward_lanes(robot->dev, robot->fz, B, ld, q, qd, qdd, f_ext, cache, g_tau,
-                                                     g_q, g_qd, g_qdd, g_fext, stream),
+        return finish(cache ? wb::launch_rnea_backward_levels(robot->dev, robot->fz, B, ld, q, qd, qdd, cache, g_tau,
+                                                              g_q, g_qd, g_qdd, g_fext, wide_rnea(robot, B), stream)
+                            : wb::launch_rnea_backward_lanes(robot->dev, robot->fz, B, ld, q, qd, qdd, f_ext, g_tau,
+                                                             g_q, g_qd, g_qdd, g_fext, stream),
                       "wb_rnea_backward launch");
     return finish(wb::launch_rnea_backward(robot->dev, B, ld, q, qd, qdd, cache, g_tau, g_q, g_qd, g_qdd, g_fext,
                                            static_cast<float *>(workspace), stream),

@@ -50,6 +50,7 @@ struct DevRobot {
     const float *__restrict__ slot_r;     // [(L+1)*nmax] radius of slot (a,i), -1e30 for empty slots
     const uint32_t *__restrict__ blocks;  // [n_blocks_pad] (16 a) << 16 | 16 b, padded to a multiple of 128 with the pair (L, L)
     const uint32_t *__restrict__ allow;   // [2][64] checked link pairs by matrix-core result (sweep.h); robots of at most 64 links
+    const int32_t *__restrict__ kids;     // [2][64] highest child of a link, next lower sibling (-1: none); at most 64 links
     const int32_t *__restrict__ pair_off; // [S] index of sphere s's first pair
     const int32_t *__restrict__ pair_cnt; // [L*L] pairs of a sphere on link a with links a<b'<b
     const int32_t *__restrict__ pair_s;   // [P]
@@ -171,15 +172,22 @@ hipError_t launch_rnea(const DevRobot &rb, int64_t B, int64_t ld, const float *q
 hipError_t launch_rnea_backward(const DevRobot &rb, int64_t B, int64_t ld, const float *q, const float *qd,
                                 const float *qdd, const float *cache, const float *g_tau,
                                 float *g_q, float *g_qd, float *g_qdd, float *g_fext, float *ws, hipStream_t s);
-// Group-per-state RNEA and VJP (tree_kernels.hip), robots of at most 64
-// links; cache may be null (nothing is then stored or read).
+// The same level by level, one thread per (state, link), in tiles of 4 states
+// (wide: 8); robots of at most 64 links.
+hipError_t launch_rnea_levels(const DevRobot &rb, const DevFused &fz, int64_t B, int64_t ld, const float *q,
+                              const float *qd, const float *qdd, const float *f_ext, float *tau, float *cache,
+                              bool wide, hipStream_t s);
+hipError_t launch_rnea_backward_levels(const DevRobot &rb, const DevFused &fz, int64_t B, int64_t ld, const float *q,
+                                       const float *qd, const float *qdd, const float *cache, const float *g_tau,
+                                       float *g_q, float *g_qd, float *g_qdd, float *g_fext, bool wide, hipStream_t s);
+// Group-per-state RNEA and VJP without a cache (tree_kernels.hip); robots of
+// at most 64 links.
 hipError_t launch_rnea_lanes(const DevRobot &rb, const DevFused &fz, int64_t B, int64_t ld, const float *q,
-                             const float *qd, const float *qdd, const float *f_ext, float *tau, float *cache,
-                             hipStream_t s);
+                             const float *qd, const float *qdd, const float *f_ext, float *tau, hipStream_t s);
 hipError_t launch_rnea_backward_lanes(const DevRobot &rb, const DevFused &fz, int64_t B, int64_t ld,
                                       const float *q, const float *qd, const float *qdd, const float *f_ext,
-                                      const float *cache, const float *g_tau, float *g_q, float *g_qd, float *g_qdd,
-                                      float *g_fext, hipStream_t s);
+                                      const float *g_tau, float *g_q, float *g_qd, float *g_qdd, float *g_fext,
+                                      hipStream_t s);
 // FK through LDS tiles and its adjoint (tree_kernels.hip), robots of at most
 // 64 links: a group of lanes per state (wide: tiles of 16, backward 8, states
 // instead of 4), or level by level.

@@ -1,0 +1,29 @@
+"""The CPU recursion that the accuracy tests measure by, in float64 against the
+oracle: torques and gradients, on a chain, a tree with coupled joints and the
+humanoid."""
+import numpy as np
+import pytest
+import torch
+
+from paper_2603_05493_amd import synth
+from tests import recursion
+
+
+def _mimic():
+    rb = synth.random_tree(9, 1, seed=31, random_fixed_rotation=True)
+    rb.joint_index = np.array([-1, 0, 1, 1, 2, 3, 4, 5, 5, 6], dtype=np.int32)
+    rb.joint_mult = synth._f32([1.0, 1.0, 1.0, -0.5, 1.0, 2.0, 1.0, 1.0, 0.75, 1.0])
+    return rb
+
+
+@pytest.mark.parametrize("factory", [lambda: synth.serial_chain(7, 1, seed=0), _mimic, lambda: synth.humanoid48(seed=0)])
+def test_recursion_in_float64(oracle, factory):
+    rb = factory()
+    st = synth.states(rb, 7, seed=1, q_range=1.5)
+    w = synth.weights((7, rb.n_dof), seed=2)
+    got = recursion.rnea_and_vjp(rb, st, w, torch.float64)
+    ref = (oracle.rnea(rb, st.q, st.qd, st.qdd), *oracle.rnea_vjp(rb, st.q, st.qd, st.qdd, w))
+    for k, x in zip(got, ref):
+        # the axes are unit to FP32 rounding, and the two differentiate the rotation differently
+        assert np.abs(got[k] - x).max() <= 1e-6 * np.abs(x).max(), k
+    assert recursion.related(rb, 0)
