@@ -259,11 +259,13 @@ int wb_self_collision(const wb_robot *robot, int64_t B, int64_t ld, const float 
  *   sweep_split_below     wb_self_collision takes the one-state-per-workgroup
  *                         form for batches of fewer states (default 2 per
  *                         compute unit of the robot's device);
- *   fk_groups_below       wb_fk without link poses takes one group of lanes
- *                         per state (pointer jumping) for batches of fewer
- *                         states, the link-by-link composition above (default
- *                         48 per compute unit; robots of at most 64 links);
- *   fk_pose_groups_below  the same for wb_fk writing link poses.
+ *   fk_groups_below       wb_fk without link poses and wb_fk_backward
+ *                         without them take one group of lanes per state
+ *                         (pointer jumping) for batches of fewer states, the
+ *                         links level by level above (default 48 per compute
+ *                         unit; robots of at most 64 links);
+ *   fk_pose_groups_below  the same for wb_fk writing link poses and
+ *                         wb_fk_backward given poses or a pose gradient.
  * A negative value restores that default; 0 never takes the form. */
 int wb_robot_set_dispatch(wb_robot *robot, int64_t sweep_split_below, int64_t fk_groups_below,
                           int64_t fk_pose_groups_below);
@@ -284,11 +286,13 @@ int wb_self_collision_backward(const wb_robot *robot, int64_t B, int64_t ld, con
  * be NULL, not both) -> g_q[n][B] (overwritten).  link_pose is the output of
  * wb_fk for the same q, or NULL to recompute the transforms from q inside
  * the kernel.  workspace: wb_workspace_bytes(robot, B).
- * Robots of at most 64 links run one group of lanes per state: each link's
- * wrench about the world origin summed over its subtree and projected on
- * the joint axis, transforms recomputed in registers; link_pose is then not
- * read, and workspace may be NULL for batches below wb_robot_set_dispatch's
- * thresholds (48 states per compute unit by default). */
+ * Robots of at most 64 links, like wb_fk: batches below 48 states per compute
+ * unit run one group of lanes per state (each link's wrench about the world
+ * origin summed over its subtree and projected on the joint axis, workspace
+ * may be NULL), larger ones sum the wrenches about the links' own origins
+ * level by level.  Both recompute the transforms; link_pose is not read.  A
+ * gradient that is not finite reaches its link's ancestors in the large-batch
+ * form, any joint of its state in the other. */
 int wb_fk_backward(const wb_robot *robot, int64_t B, int64_t ld, const float *q, const float *link_pose,
                    const float *g_link_pose, const float *g_spheres, float *g_q, void *workspace,
                    hipStream_t stream);

@@ -776,11 +776,11 @@ int wb_rnea_cache_bytes(const wb_robot *robot, int64_t B, size_t *bytes) {
 namespace {
 // Forward kinematics of robots of at most 64 links takes one group of lanes
 // per state (pointer jumping over the links) for batches below a threshold,
-// and the link-by-link composition of a lane's walk, level by level, above;
-// calls that write link poses have a threshold of their own.  Default for
-// both: 48 states per compute unit.  The two round differently, so the line
-// stays where the walk took over; times on both sides stand beside the
-// launchers.
+// and the link-by-link composition of a lane's walk, level by level, above; its
+// adjoint likewise.  Calls that write or read link poses have a threshold of
+// their own.  Default for both: 48 states per compute unit.  The two round
+// differently, so the line stays where the walk took over; times on both sides
+// stand beside the kernels and launchers.
 bool group_form(const wb_robot *r, int64_t B, bool pose) {
     const int64_t set = pose ? r->fk_pose_groups_below : r->fk_groups_below;
     return B < (set >= 0 ? set : (int64_t)48 * r->cus);
@@ -903,13 +903,15 @@ int wb_fk_backward(const wb_robot *robot, int64_t B, int64_t ld, const float *q,
     WB_TRY(check_ptr(g_link_pose, "g_link_pose", false));
     WB_TRY(check_ptr(g_spheres, "g_spheres", false));
     WB_TRY(check_ptr(g_q, "g_q", robot->T.n > 0));
-    if (robot->T.lanes) {   // a workspace is asked for from the batch on that once used it
-        WB_TRY(check_ptr(workspace, "workspace", !group_form(robot, B, link_pose != nullptr || g_link_pose != nullptr)));
+    const bool group = robot->T.lanes && group_form(robot, B, link_pose != nullptr || g_link_pose != nullptr);
+    WB_TRY(check_ptr(workspace, "workspace", !group));
+    if (group)
         return finish(wb::launch_fk_backward_lanes(robot->dev, robot->fz, B, ld, q, g_link_pose, g_spheres, g_q,
                                                    wide_tiles(robot, B), stream),
                       "wb_fk_backward launch");
-    }
-    WB_TRY(check_ptr(workspace, "workspace", true));
+    if (robot->T.lanes)
+        return finish(wb::launch_fk_backward_levels(robot->dev, robot->fz, B, ld, q, g_link_pose, g_spheres, g_q, stream),
+                      "wb_fk_backward launch");
     return finish(wb::launch_fk_backward(robot->dev, B, ld, q, link_pose, g_link_pose, g_spheres, g_q,
                                          static_cast<float *>(workspace), stream),
                   "wb_fk_backward launch");

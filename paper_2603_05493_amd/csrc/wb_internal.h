@@ -188,7 +188,7 @@ hipError_t launch_rnea_backward_lanes(const DevRobot &rb, const DevFused &fz, in
                                       const float *q, const float *qd, const float *qdd, const float *f_ext,
                                       const float *g_tau, float *g_q, float *g_qd, float *g_qdd, float *g_fext,
                                       hipStream_t s);
-// FK through LDS tiles and its adjoint (tree_kernels.hip), robots of at most
+// FK and its adjoint through LDS tiles (tree_kernels.hip), robots of at most
 // 64 links: a group of lanes per state (wide: tiles of 16, backward 8, states
 // instead of 4), or level by level.
 hipError_t launch_fk_levels(const DevRobot &rb, int64_t B, int64_t ld, const float *q, float *pose, float *spheres,
@@ -197,6 +197,8 @@ hipError_t launch_fk_lanes(const DevRobot &rb, const DevFused &fz, int64_t B, in
                            float *spheres, bool wide, hipStream_t s);
 hipError_t launch_fk_backward_lanes(const DevRobot &rb, const DevFused &fz, int64_t B, int64_t ld, const float *q,
                                     const float *g_pose, const float *g_sph, float *g_q, bool wide, hipStream_t s);
+hipError_t launch_fk_backward_levels(const DevRobot &rb, const DevFused &fz, int64_t B, int64_t ld, const float *q,
+                                     const float *g_pose, const float *g_sph, float *g_q, hipStream_t s);
 // split: one state per workgroup with its pairs over the four wavefronts
 // (else one state per wavefront).
 hipError_t launch_self_collision(const DevRobot &rb, int64_t B, int64_t ld, const float *spheres,

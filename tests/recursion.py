@@ -1,6 +1,7 @@
 """The Newton-Euler recursion in link coordinates as a torch program on the
-CPU, with its gradients by autograd: run in float32, a yardstick for what the
-recursion itself loses to rounding."""
+CPU, with its gradients by autograd, and the adjoint of forward kinematics link
+by link: run in float32, yardsticks for what the recursions themselves lose to
+rounding."""
 import numpy as np
 import torch
 
@@ -73,3 +74,39 @@ def related(rb, joint):
     mine = [k for k in range(rb.n_links) if int(rb.joint_index[k]) == joint]
     near = {i for i in range(rb.n_links) for k in mine if i in chain[k] or k in chain[i]}
     return sorted({int(rb.joint_index[i]) for i in near if int(rb.joint_index[i]) >= 0})
+
+
+def fk_adjoint(rb, q, g_sph, dtype):
+    """Joint gradients [B, n] of sum(g_sph * centres): forces and moments about the
+    links' own origins, children added from the tips on."""
+    B, L = q.shape[0], rb.n_links
+    t = lambda a: np.asarray(a, dtype=np.float64).astype(dtype)
+    mv = lambda M, x: (M * x[..., None, :]).sum(-1, dtype=dtype)
+    cross = lambda a, b: np.stack([a[:, 1] * b[:, 2] - a[:, 2] * b[:, 1], a[:, 2] * b[:, 0] - a[:, 0] * b[:, 2],
+                                   a[:, 0] * b[:, 1] - a[:, 1] * b[:, 0]], 1)
+    mm = lambda X, Y: (X[..., :, :, None] * Y[..., None, :, :]).sum(-2, dtype=dtype)
+    q, g_sph = t(q), t(g_sph)
+    R, p = [np.broadcast_to(np.eye(3, dtype=dtype), (B, 3, 3))], [np.zeros((B, 3), dtype)]
+    for k in range(1, L):
+        a, j, Rk = int(rb.parent[k]), int(rb.joint_index[k]), np.broadcast_to(t(rb.fixed_R[k]), (B, 3, 3))
+        if j >= 0:
+            th = t(rb.joint_mult[k]) * q[:, j] + t(rb.joint_offset[k])
+            x, y, z = t(rb.axis[k])
+            K = np.array([[0, -z, y], [z, 0, -x], [-y, x, 0]], dtype)
+            sn, cs = np.sin(th)[:, None, None], np.cos(th)[:, None, None]
+            Rk = mm(Rk, cs * np.eye(3, dtype=dtype) + sn * K + (1 - cs) * np.outer(t(rb.axis[k]), t(rb.axis[k])))
+        p.append(mv(R[a], np.broadcast_to(t(rb.fixed_p[k]), (B, 3))) + p[a])
+        R.append(mm(R[a], Rk))
+    F, M = [np.zeros((B, 3), dtype) for _ in range(L)], [np.zeros((B, 3), dtype) for _ in range(L)]
+    for s, l in enumerate(rb.sphere_link):
+        g = g_sph[:, s]
+        F[l] = F[l] + g
+        M[l] = M[l] + cross(mv(R[l], np.broadcast_to(t(rb.sphere_pos[s]), (B, 3))), g)
+    out = np.zeros((B, rb.n_dof), dtype)
+    for k in range(L - 1, 0, -1):
+        a, j = int(rb.parent[k]), int(rb.joint_index[k])
+        if j >= 0:
+            out[:, j] += t(rb.joint_mult[k]) * (mv(R[k], np.broadcast_to(t(rb.axis[k]), (B, 3))) * M[k]).sum(-1, dtype=dtype)
+        F[a] = F[a] + F[k]
+        M[a] = M[a] + M[k] + cross(p[k] - p[a], F[k])
+    return out.astype(np.float64)

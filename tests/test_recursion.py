@@ -1,5 +1,6 @@
 """The CPU recursion that the accuracy tests measure by, in float64 against the
-oracle: torques and gradients, on a chain, a tree with coupled joints and the
+oracle: torques, gradients and the adjoint of
+forward kinematics, on a chain, a tree with coupled joints and the
 humanoid."""
 import numpy as np
 import pytest
@@ -27,3 +28,12 @@ def test_recursion_in_float64(oracle, factory):
         # the axes are unit to FP32 rounding, and the two differentiate the rotation differently
         assert np.abs(got[k] - x).max() <= 1e-6 * np.abs(x).max(), k
     assert recursion.related(rb, 0)
+
+
+@pytest.mark.parametrize("factory", [lambda: synth.serial_chain(7, 3, seed=0), _mimic, lambda: synth.humanoid48(seed=0)])
+def test_fk_adjoint_in_float64(oracle, factory):
+    rb = factory()
+    st = synth.states(rb, 7, seed=1, q_range=1.5)
+    g = np.random.default_rng(3).normal(size=(7, rb.n_spheres, 3))
+    got, ref = recursion.fk_adjoint(rb, st.q, g, np.float64), oracle.fk_backward(rb, st.q, g_spheres=g)
+    assert np.abs(got - ref).max() <= 1e-6 * np.abs(ref).max()
