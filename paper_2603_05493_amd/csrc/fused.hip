@@ -229,7 +229,7 @@ __device__ __forceinline__ void iterate_state(const DevRobot &rb, const uint32_t
     const SV Iv = iw_apply(J, v);
     SV F = iw_apply(J, a) + crf(v, Iv);
     if (EXT) F = F - fe;
-    F = subtree_sum(F, sub, G);
+    F = subtree_sum_wrench(F, sub, fz.branched != 0, G);
     float tau = revolute ? dot(S, F) : 0.f;
     // with mimic joints, joint lane j (j < n) holds joint j from here to the cost head
     const bool jlane = mim ? gl < rb.n : revolute;

@@ -6,7 +6,7 @@
 //   group_scan      inclusive prefix sum over the group (Hillis-Steele with
 //                   row_shr 1, 2, 4, 8 inside each 16-lane row, then
 //                   row_bcast:15 and row_bcast:31 to carry row totals);
-//                   group_scan4/6 the same for four or six values at once
+//                   group_scan3/4/6 the same for several values at once
 //   group_reduce_*  butterfly reduction, result in every lane of the group
 //                   (quad_perm xor 1, xor 2, row_half_mirror, row_mirror,
 //                   then the permlane swaps across rows and halves)
@@ -48,23 +48,25 @@ __device__ __forceinline__ float group_scan(float x, int G) {
     return x;
 }
 
-// Inclusive prefix sums over the group of four or six values at once (a
-// point and a mass; the six components of a spatial vector), each
+// Inclusive prefix sums over the group of three, four or six values at once
+// (a force; a point and a mass; the six components of a spatial vector), each
 // Hillis-Steele step an in-place DPP add.  The row_bcast steps write only the
 // rows named by the row mask, and the rows left out keep their value, which
 // is the sum wanted there; written as builtins, such a step costs three
 // instructions (the compiler does not fold a masked DPP move into a float
-// add).  The chains are interleaved, so each DPP read of a value comes four
-// or six instructions after its last write.  The compiler's hazard checks
+// add).  The chains are interleaved, so at least the two instructions that a
+// DPP read needs lie between it and the last write of its value.  The compiler's hazard checks
 // do not look into inline asm: the block opens with the 5 wait states a DPP
 // read needs after a VALU write of EXEC (2 after one of its source) and
 // closes with the 2 that a DPP read of its results needs.  The blocks are
 // volatile, so they stay where they are written: their results depend on
 // other lanes' values and on EXEC.
-#define WB_DPP4(op)                                  \
+#define WB_DPP3(op)                                  \
     "v_add_f32_dpp %0, %0, %0 " op "\n\t"             \
     "v_add_f32_dpp %1, %1, %1 " op "\n\t"             \
-    "v_add_f32_dpp %2, %2, %2 " op "\n\t"             \
+    "v_add_f32_dpp %2, %2, %2 " op "\n\t"
+#define WB_DPP4(op)                                  \
+    WB_DPP3(op)                                      \
     "v_add_f32_dpp %3, %3, %3 " op "\n\t"
 #define WB_DPP6(op)                                  \
     WB_DPP4(op)                                      \
@@ -87,6 +89,9 @@ __device__ __forceinline__ float group_scan(float x, int G) {
             asm volatile("s_nop 4\n\t" D(WB_SHR(1)) D(WB_SHR(2)) D(WB_SHR(4)) D(WB_SHR(8)) "s_nop 1"     \
                          : __VA_ARGS__);                                                                 \
     } while (0)
+__device__ __forceinline__ void group_scan3(float &a, float &b, float &c, int G) {
+    WB_SCAN(WB_DPP3, G, "+v"(a), "+v"(b), "+v"(c));
+}
 __device__ __forceinline__ void group_scan4(float &a, float &b, float &c, float &d, int G) {
     WB_SCAN(WB_DPP4, G, "+v"(a), "+v"(b), "+v"(c), "+v"(d));
 }
@@ -94,6 +99,7 @@ __device__ __forceinline__ void group_scan6(float &a, float &b, float &c, float 
     WB_SCAN(WB_DPP6, G, "+v"(a), "+v"(b), "+v"(c), "+v"(d), "+v"(e), "+v"(f));
 }
 #undef WB_SCAN
+#undef WB_DPP3
 #undef WB_DPP4
 #undef WB_DPP6
 #undef WB_SHR

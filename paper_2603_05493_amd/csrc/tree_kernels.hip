@@ -101,7 +101,7 @@ __global__ void __launch_bounds__(256)
         const float *fx = f_ext + (int64_t)(link * 6) * B + b;
         F = F - force_to_world(R, p, sv(v3(fx[0], fx[B], fx[2 * B]), v3(fx[3 * B], fx[4 * B], fx[5 * B])));
     }
-    F = subsum(F);
+    F = subtree_sum_wrench(F, sub, fz.branched != 0, G);
     const bool jlane = mim ? gl < rb.n : revolute;
     const int64_t jrow = (int64_t)(mim ? gl : jidx) * B + b;
     if (!BWD) {
