@@ -6,8 +6,6 @@
 
 namespace wb {
 
-constexpr int SC_RING = 128;   // the row ring of a 64-lane group
-
 // The sphere slots' radii (they stay from state to state) and the padding
 // link's empty bound.
 template <int NMAX>
@@ -30,10 +28,12 @@ __device__ __forceinline__ void stage_blocks(const DevRobot &rb, uint32_t *tab, 
 // as in the fused kernel; with the radii, the table and two integer
 // divisions an element staged for every four states, and their rows fetched
 // through every XCD, the humanoid's 24,576 states took 163 us.
-// LDS: four states x [(L+1)*NMAX slots | L+1 link bounds], then the row
-// rings, (TAB_LDS) the block table and the wavefronts' lists.
+// LDS: TS states x [(L+1)*NMAX slots | L+1 link bounds], then their row
+// rings, (TAB_LDS) the block table and their lists.
 // nb: states; B: row length of the sphere array (the ABI's ld >= nb).
-// TS: 4, or 1 for the largest robots, of which 64 KB hold one state.
+// TS: 4, or 0 for robots of which 64 KB hold fewer than four states: a
+// workgroup then takes `chunk` states (1 to 3), one a wavefront, the others
+// helping to stage them.
 template <int NMAX, bool TAB_LDS, int TS>
 __global__ void __launch_bounds__(256) k_self_collision(DevRobot rb, int64_t nb, int64_t B, int chunk,
                                                         const float *__restrict__ sph,
@@ -44,28 +44,29 @@ __global__ void __launch_bounds__(256) k_self_collision(DevRobot rb, int64_t nb,
     const int SL = (rb.L + 1) * NMAX;
     const int SLB = SL + rb.L + 1;
     const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63;
-    uint32_t *rings = reinterpret_cast<uint32_t *>(lds + TS * SLB), *t = rings + 4 * SC_RING;
+    const int ts = TS ? TS : chunk, rows = 256 / ts;   // rows staged at a time
+    uint32_t *rings = reinterpret_cast<uint32_t *>(lds + ts * SLB), *t = rings + ts * SC_RING;
     const uint32_t *tab = TAB_LDS ? t : rb.blocks;
     uint32_t *lists = TAB_LDS ? t + rb.n_blocks_pad : t;
     if (TAB_LDS) stage_blocks(rb, t, tid, 256);
     float4 *P = lds + wave * SLB;
-    if (wave < TS) init_slots<NMAX>(rb, P, lane, 64);
+    if (wave < ts) init_slots<NMAX>(rb, P, lane, 64);
     const int64_t c0 = (int64_t)xcd_chunk() * chunk, c1 = min(c0 + chunk, nb);
-    for (int64_t b0 = c0; b0 < c1; b0 += TS) {
-        __syncthreads();   // the slots and the table are staged; the previous four states are swept
-        {
-            const int st = tid % TS;
+    for (int64_t b0 = c0; b0 < c1; b0 += ts) {
+        __syncthreads();   // the slots and the table are staged; the previous states are swept
+        if (tid < rows * ts) {
+            const int st = tid % ts;
             const int64_t b = min(b0 + st, nb - 1);
             float *slots = reinterpret_cast<float *>(lds + st * SLB);
 #pragma unroll 4
-            for (int row = tid / TS; row < 3 * rb.S; row += 256 / TS) {
+            for (int row = tid / ts; row < 3 * rb.S; row += rows) {
                 const int s = row / 3;
                 slots[rb.sph_slot[s] * 4 + (row - 3 * s)] = sph[(int64_t)row * B + b];
             }
         }
         __syncthreads();
         const int64_t b = b0 + wave;
-        if (wave >= TS || b >= c1) continue;
+        if (wave >= ts || b >= c1) continue;
         float4 *Bd = P + SL;
         link_bounds<NMAX>(rb, P, Bd, lane, 64);
         __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");
@@ -86,10 +87,10 @@ __global__ void __launch_bounds__(256) k_self_collision(DevRobot rb, int64_t nb,
 // One state per workgroup, its pairs split over the four wavefronts and
 // reduced through LDS (sweep_state_wg): for batches too small to fill the
 // chip with one state per wavefront, and for robots with many pairs.
-// LDS: [(L+1)*NMAX slots | L+1 link bounds] (float4), 8 words for the
-// reductions, 4 row rings, (TAB_LDS) the table and 4 lists.
+// LDS: [(L+1)*NMAX slots | L+1 link bounds] (float4), 4 row rings, (TAB_LDS)
+// the table and 4 lists of list_cap entries.
 template <int NMAX, bool TAB_LDS>
-__global__ void __launch_bounds__(256) k_self_collision_wg(DevRobot rb, int64_t nb, int64_t B,
+__global__ void __launch_bounds__(256) k_self_collision_wg(DevRobot rb, int64_t nb, int64_t B, int list_cap,
                                                            const float *__restrict__ sph,
                                                            float *__restrict__ max_pen,
                                                            int32_t *__restrict__ argmax,
@@ -98,8 +99,7 @@ __global__ void __launch_bounds__(256) k_self_collision_wg(DevRobot rb, int64_t 
     const int SL = (rb.L + 1) * NMAX;
     float4 *P = lds;
     float4 *Bd = P + SL;
-    float *red = reinterpret_cast<float *>(Bd + rb.L + 1);
-    uint32_t *rings = reinterpret_cast<uint32_t *>(red + 8), *t = rings + 4 * SC_RING;
+    uint32_t *rings = reinterpret_cast<uint32_t *>(Bd + rb.L + 1), *t = rings + 4 * SC_RING;
     const uint32_t *tab = TAB_LDS ? t : rb.blocks;
     uint32_t *lists = TAB_LDS ? t + rb.n_blocks_pad : t;
     const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63;
@@ -118,8 +118,7 @@ __global__ void __launch_bounds__(256) k_self_collision_wg(DevRobot rb, int64_t 
         float M;
         int key;
         unsigned cnt;
-        sweep_state_wg<NMAX>(rb, tab, P, Bd, lists + wave * SWEEP_LIST, rings + wave * SC_RING, red, wave, lane, M,
-                             key, cnt);
+        sweep_state_wg<NMAX>(rb, tab, P, Bd, lists + wave * list_cap, list_cap, rings, wave, lane, M, key, cnt);
         if (tid == 0) {
             if (max_pen) max_pen[b] = M;
             if (argmax) argmax[b] = pair_index(rb, key);
@@ -128,37 +127,32 @@ __global__ void __launch_bounds__(256) k_self_collision_wg(DevRobot rb, int64_t 
     }
 }
 
-// LDS of the four wavefronts' row rings and lists.
-constexpr size_t SC_SCRATCH = 4 * 4 * (SC_RING + SWEEP_LIST);
-
-// The block table goes to LDS where it fits beside four states, else it is
-// read from device memory; the largest robots' 64 KB hold one state, whose
-// list and ring alone are used.
+// The shapes are in wb_internal.h.
 template <int NMAX>
 static hipError_t launch_sc(const DevRobot &rb, int64_t B, int64_t ld, const float *sph, float *mp, int32_t *am,
                             int32_t *nc, hipStream_t s) {
-    const size_t state = state_lds_bytes(rb.L, NMAX), tab = tab_lds_bytes(rb.n_blocks_pad);
-    // chunks of up to 32 states that leave 2,048 workgroups
-    const int chunk = (int)std::max<int64_t>(std::min<int64_t>(32, B / 2048) / 4 * 4, 4);
+    const SweepShape w = sweep_wave_shape(rb.L, NMAX, rb.n_blocks_pad);
+    // chunks of up to 32 states that leave 2,048 workgroups, or the states of one pass
+    const int chunk = w.states < 4 ? w.states : (int)std::max<int64_t>(std::min<int64_t>(32, B / 2048) / 4 * 4, 4);
     const dim3 grid((unsigned)((B + chunk - 1) / chunk)), block(256);
-    if (4 * state + SC_SCRATCH + tab <= LDS_LIMIT)
-        hipLaunchKernelGGL((k_self_collision<NMAX, true, 4>), grid, block, 4 * state + SC_SCRATCH + tab, s, rb, B, ld, chunk, sph, mp, am, nc);
-    else if (4 * state + SC_SCRATCH <= LDS_LIMIT)
-        hipLaunchKernelGGL((k_self_collision<NMAX, false, 4>), grid, block, 4 * state + SC_SCRATCH, s, rb, B, ld, chunk, sph, mp, am, nc);
+    if (w.table)
+        hipLaunchKernelGGL((k_self_collision<NMAX, true, 4>), grid, block, w.lds, s, rb, B, ld, chunk, sph, mp, am, nc);
+    else if (w.states == 4)
+        hipLaunchKernelGGL((k_self_collision<NMAX, false, 4>), grid, block, w.lds, s, rb, B, ld, chunk, sph, mp, am, nc);
     else
-        hipLaunchKernelGGL((k_self_collision<NMAX, false, 1>), grid, block, state + SC_SCRATCH, s, rb, B, ld, chunk, sph, mp, am, nc);
+        hipLaunchKernelGGL((k_self_collision<NMAX, false, 0>), grid, block, w.lds, s, rb, B, ld, chunk, sph, mp, am, nc);
     return hipGetLastError();
 }
 
 template <int NMAX>
 static hipError_t launch_sc_wg(const DevRobot &rb, int64_t B, int64_t ld, const float *sph, float *mp, int32_t *am,
                                int32_t *nc, hipStream_t s) {
-    const size_t lds = state_lds_bytes(rb.L, NMAX) + 8 * 4 + SC_SCRATCH, tab = tab_lds_bytes(rb.n_blocks_pad);
+    const SweepShape w = sweep_split_shape(rb.L, NMAX, rb.n_blocks_pad);
     const dim3 grid((unsigned)std::min<int64_t>(B, 1 << 20)), block(256);
-    if (lds + tab <= LDS_LIMIT)
-        hipLaunchKernelGGL((k_self_collision_wg<NMAX, true>), grid, block, lds + tab, s, rb, B, ld, sph, mp, am, nc);
+    if (w.table)
+        hipLaunchKernelGGL((k_self_collision_wg<NMAX, true>), grid, block, w.lds, s, rb, B, ld, w.list, sph, mp, am, nc);
     else
-        hipLaunchKernelGGL((k_self_collision_wg<NMAX, false>), grid, block, lds, s, rb, B, ld, sph, mp, am, nc);
+        hipLaunchKernelGGL((k_self_collision_wg<NMAX, false>), grid, block, w.lds, s, rb, B, ld, w.list, sph, mp, am, nc);
     return hipGetLastError();
 }
 

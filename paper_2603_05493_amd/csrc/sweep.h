@@ -476,35 +476,38 @@ __device__ __forceinline__ void sweep_state(const DevRobot &rb, const uint32_t *
 // paper's two-stage self-collision split over wavefronts, then a second
 // reduce through LDS): the block table's 128-entry chunks are dealt
 // round-robin to the wavefronts (chunk c to wavefront c % 4); each compacts
-// its chunks into its list (SWEEP_LIST entries) and sweeps their rows as
+// its chunks into its list (list_cap entries) and sweeps their rows as
 // sweep_state does with G = 64, and the workgroup combines the wavefronts'
 // maxima, counts and argmax keys.  Pass 2, the seed block and the tie rescan
 // follow the single-wavefront rules with workgroup-wide values, so the result
-// is the full sweep's.  red: 8 words of LDS; ring: the wavefront's own.
-// Every thread of the workgroup must call this (it synchronizes the
-// workgroup).
-__device__ __forceinline__ float wg_max4(float v, float *red, int wave, int lane) {
-    if (lane == 0) red[wave] = v;
+// is the full sweep's.  rings: the four wavefronts' row rings; the values to
+// reduce pass through the first word of each, which its wavefront alone uses
+// between the barriers.  Every thread of the workgroup must call this (it
+// synchronizes the workgroup).
+__device__ __forceinline__ float wg_max4(float v, uint32_t *rings, int wave, int lane) {
+    float *red = reinterpret_cast<float *>(rings);
+    if (lane == 0) red[wave * SC_RING] = v;
     __syncthreads();
-    const float m = fmaxf(fmaxf(red[0], red[1]), fmaxf(red[2], red[3]));
+    const float m = fmaxf(fmaxf(red[0], red[SC_RING]), fmaxf(red[2 * SC_RING], red[3 * SC_RING]));
     __syncthreads();
     return m;
 }
-__device__ __forceinline__ int wg_min4(int v, int *red, int wave, int lane) {
-    if (lane == 0) red[wave] = v;
+__device__ __forceinline__ int wg_min4(int v, uint32_t *rings, int wave, int lane) {
+    int *red = reinterpret_cast<int *>(rings);
+    if (lane == 0) red[wave * SC_RING] = v;
     __syncthreads();
-    const int m = min(min(red[0], red[1]), min(red[2], red[3]));
+    const int m = min(min(red[0], red[SC_RING]), min(red[2 * SC_RING], red[3 * SC_RING]));
     __syncthreads();
     return m;
 }
 
 template <int NMAX>
 __device__ __forceinline__ void sweep_state_wg(const DevRobot &rb, const uint32_t *tab, const float4 *P, const float4 *Bd,
-                                               uint32_t *list, uint32_t *ring, float *red, int wave, int lane,
+                                               uint32_t *list, int list_cap, uint32_t *rings, int wave, int lane,
                                                float &M_out, int &key_out, unsigned &cnt_out) {
     const int n = rb.n_blocks;
     const int nb = (n + 127) / 128 * 128;   // <= n_blocks_pad
-    int *redi = reinterpret_cast<int *>(red);
+    uint32_t *ring = rings + wave * SC_RING;
     float ext = 0.f;
     for (int a = lane; a < rb.L; a += 64) {
         const float4 c = Bd[a];
@@ -523,7 +526,7 @@ __device__ __forceinline__ void sweep_state_wg(const DevRobot &rb, const uint32_
         int nl = 0;
         for (int k = wave * 128; k < nb; k += 4 * 128) {
             nl = append_blocks<PASS2, true, false>(tab[k + lane], tab[k + lane + 64], Bd, list, nl, eps, lo, lane, 64, 0, ~0ull);
-            if (k + 4 * 128 >= nb || nl + 128 > SWEEP_LIST) {
+            if (k + 4 * 128 >= nb || nl + 128 > list_cap) {
                 __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");
                 __builtin_amdgcn_wave_barrier();
                 sweep_rows_culled<NMAX, true, PASS2, false>(P, Bd, list, nl, ring, eps, lo, lane, 64, 0, ~0ull, best,
@@ -535,7 +538,7 @@ __device__ __forceinline__ void sweep_state_wg(const DevRobot &rb, const uint32_
         }
     };
     sweep_chunks(std::false_type{}, 0.f);
-    float M = wg_max4(group_reduce_max(best, 64), red, wave, lane);
+    float M = wg_max4(group_reduce_max(best, 64), rings, wave, lane);
     if (!(M >= 0.f) && n > 0) {
         float lb = M;
         if (lb == -INFINITY) {
@@ -550,8 +553,8 @@ __device__ __forceinline__ void sweep_state_wg(const DevRobot &rb, const uint32_
                         bblk = k;
                     }
                 }
-            const float gbmax = wg_max4(group_reduce_max(bmax, 64), red, wave, lane);
-            const int cand = wg_min4(group_reduce_min(bmax == gbmax ? bblk : INT_MAX, 64), redi, wave, lane);
+            const float gbmax = wg_max4(group_reduce_max(bmax, 64), rings, wave, lane);
+            const int cand = wg_min4(group_reduce_min(bmax == gbmax ? bblk : INT_MAX, 64), rings, wave, lane);
             float seed = -INFINITY;
             if (cand != INT_MAX) {
                 const uint32_t e = tab[cand];
@@ -565,11 +568,11 @@ __device__ __forceinline__ void sweep_state_wg(const DevRobot &rb, const uint32_
         }
         const float theta1 = lb - eps;
         sweep_chunks(std::true_type{}, theta1);
-        M = wg_max4(group_reduce_max(best, 64), red, wave, lane);
+        M = wg_max4(group_reduce_max(best, 64), rings, wave, lane);
     }
     int key = INT_MAX;
     const bool holder = best == M && M > -INFINITY && best_code != NO_ROW;
-    const bool rescan = wg_min4(group_reduce_min((holder && tie) ? 0 : 1, 64), redi, wave, lane) == 0;
+    const bool rescan = wg_min4(group_reduce_min((holder && tie) ? 0 : 1, 64), rings, wave, lane) == 0;
     if (rescan) {
         for (int c0 = wave * 128; c0 < nb; c0 += 4 * 128)
             for (int blk = c0 + lane; blk < min(c0 + 128, n); blk += 64) {
@@ -580,11 +583,11 @@ __device__ __forceinline__ void sweep_state_wg(const DevRobot &rb, const uint32_
         key = code_min_key<NMAX>(rb, P, best_code, M);
     }
     M_out = M;
-    key_out = wg_min4(group_reduce_min(key, 64), redi, wave, lane);
+    key_out = wg_min4(group_reduce_min(key, 64), rings, wave, lane);
     // counts: the wavefronts' (uniform) counts summed in a fixed order
-    if (lane == 0) redi[4 + wave] = (int)cnt;
+    if (lane == 0) ring[0] = cnt;
     __syncthreads();
-    cnt_out = (unsigned)redi[4] + (unsigned)redi[5] + (unsigned)redi[6] + (unsigned)redi[7];
+    cnt_out = rings[0] + rings[SC_RING] + rings[2 * SC_RING] + rings[3 * SC_RING];
     __syncthreads();
 }
 

@@ -221,6 +221,8 @@ hipError_t launch_bspline_backward(int64_t T, int32_t d, int32_t K, int32_t n_in
                                    const float *g_qd, const float *g_qdd, float *g_U, float lr, int32_t rule,
                                    float *U, hipStream_t s);
 
+constexpr size_t LDS_LIMIT = 65536;
+
 // LDS of one state's sweep: (L+1)*nmax sphere slots and L+1 link bounding
 // spheres (float4 each); plus, per sweeping group, a list of surviving blocks
 // and a ring of row codes (32-bit each).
@@ -238,6 +240,32 @@ __host__ __device__ inline size_t group_lds_bytes(int L, int nmax, int n_blocks,
 }
 // LDS copy of the block table (n_blocks_pad entries, a multiple of 128).
 __host__ __device__ inline size_t tab_lds_bytes(int n_blocks_pad) { return (size_t)n_blocks_pad * 4; }
+// Shapes of the standalone sweeps, all within LDS_LIMIT for every robot that
+// wb_robot_create takes (one state and 4 KB fit).
+constexpr int SC_RING = 128;          // row ring of a 64-lane group
+struct SweepShape {
+    int states;        // states side by side in a workgroup (wave form)
+    int table, list;   // block table staged in LDS; entries of a wavefront's list
+    size_t lds;
+};
+// One state per wavefront: four side by side with the block table beside them,
+// or without it, or as many as fit, each with its own ring and list.
+inline SweepShape sweep_wave_shape(int L, int nmax, int n_blocks_pad) {
+    const size_t one = state_lds_bytes(L, nmax) + 4 * (SC_RING + SWEEP_LIST);
+    if (4 * one + tab_lds_bytes(n_blocks_pad) <= LDS_LIMIT)
+        return SweepShape{4, 1, SWEEP_LIST, 4 * one + tab_lds_bytes(n_blocks_pad)};
+    const int fit = (int)(LDS_LIMIT / one), states = fit < 4 ? fit : 4;
+    return SweepShape{states, 0, SWEEP_LIST, states * one};
+}
+// One state per workgroup: with the block table, without it, and with lists of
+// one 128-entry chunk where the longer ones do not fit.
+inline SweepShape sweep_split_shape(int L, int nmax, int n_blocks_pad) {
+    const size_t state = state_lds_bytes(L, nmax), scratch = 4 * 4 * (SC_RING + SWEEP_LIST);
+    if (state + scratch + tab_lds_bytes(n_blocks_pad) <= LDS_LIMIT)
+        return SweepShape{1, 1, SWEEP_LIST, state + scratch + tab_lds_bytes(n_blocks_pad)};
+    if (state + scratch <= LDS_LIMIT) return SweepShape{1, 0, SWEEP_LIST, state + scratch};
+    return SweepShape{1, 0, 128, state + 4 * 4 * (SC_RING + 128)};
+}
 // LDS of a workgroup of the fused kernel with G lanes per state and `waves`
 // wavefronts: their group regions, then, for four, the block table.
 inline size_t fused_lds_bytes(int L, int nmax, int n_blocks, int G, int waves) {
@@ -263,7 +291,6 @@ inline size_t counted_fused_bytes(int L, int nmax, int G, int n_blocks_pad) {
 inline size_t spline_lds_bytes(int G, int d, int K) {
     return ((size_t)(256 / G) * (K + 6) + (size_t)K) * d * 4;
 }
-constexpr size_t LDS_LIMIT = 65536;
 // Sphere slots per link the fused kernels are instantiated for: 1 to 8, and
 // 12 (links of up to 12 spheres are padded to 12 slots).
 constexpr int FUSED_MAX_SLOTS = 12;

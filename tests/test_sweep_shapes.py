@@ -1,0 +1,51 @@
+"""Host: the LDS shapes of the standalone self-collision sweeps fit the 64 KB
+limit for every robot that wb_robot_create takes, with a ring and a list for
+each state in flight (the header's functions, compiled and swept over the
+accepted sizes)."""
+import os
+import subprocess
+
+from paper_2603_05493_amd import build
+
+SOURCE = r"""
+#include "wb_internal.h"
+#include <cstdio>
+using namespace wb;
+int main() {
+    const int sizes[] = {1, 2, 3, 4, 5, 6, 7, 8, 12, 16, 24, 32, 48, 64};
+    long shapes = 0;
+    int worst = 0;
+    for (int nmax : sizes)
+        for (int L = 1; L <= 1024; ++L) {
+            if (state_lds_bytes(L, nmax) + 4 * 4 * (SC_RING + 128) > LDS_LIMIT) continue;   // refused at creation
+            const long most = (long)L * (L - 1) / 2;
+            for (long blocks : {0L, 1L, most / 3, most}) {
+                const int pad = (int)((blocks + 127) / 128 * 128);
+                const SweepShape w = sweep_wave_shape(L, nmax, pad), s = sweep_split_shape(L, nmax, pad);
+                const size_t state = state_lds_bytes(L, nmax);
+                const size_t need_w = w.states * (state + 4 * (SC_RING + w.list)) + (w.table ? tab_lds_bytes(pad) : 0);
+                const size_t need_s = state + 4 * 4 * (SC_RING + s.list) + (s.table ? tab_lds_bytes(pad) : 0);
+                const bool ok = w.states >= 1 && w.states <= 4 && (!w.table || w.states == 4) && s.states == 1 &&
+                                w.list >= 128 && s.list >= 128 && w.list % 128 == 0 && s.list % 128 == 0 &&
+                                need_w <= w.lds && need_s <= s.lds && w.lds <= LDS_LIMIT && s.lds <= LDS_LIMIT;
+                if (!ok) {
+                    printf("L %d nmax %d blocks %ld: wave %d states %zu B, split %zu B\n", L, nmax, blocks, w.states, w.lds, s.lds);
+                    return 1;
+                }
+                if ((int)state > worst) worst = (int)state;
+                ++shapes;
+            }
+        }
+    printf("%ld shapes, largest state %d B\n", shapes, worst);
+    return worst == 61440 ? 0 : 2;
+}
+"""
+
+
+def test_shapes_fit(tmp_path):
+    src, exe = tmp_path / "shapes.cpp", tmp_path / "shapes"
+    src.write_text(SOURCE)
+    subprocess.run([build.hipcc(), *build.flags(), str(src), "-o", str(exe)], check=True, capture_output=True, text=True,
+                   env=dict(os.environ))
+    r = subprocess.run([str(exe)], capture_output=True, text=True)
+    assert r.returncode == 0, r.stdout
