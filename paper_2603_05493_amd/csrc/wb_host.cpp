@@ -836,14 +836,10 @@ int wb_rnea(const wb_robot *robot, int64_t B, int64_t ld, const float *q, const 
 namespace {
 // wb_self_collision's form for a batch: one state per workgroup (its pairs
 // split over the four wavefronts) below the robot's threshold, one state
-// per wavefront above.  Default threshold: 2 states per compute unit, below
-// which one state per wavefront leaves SIMDs without work (humanoid, wave
-// against split form: 11.7 / 8.7 us at 256 states, 13.3 / 11.9 at 1,000,
-// 13.4 / 20.5 at 2,048; smaller trees cross earlier, its 588-sphere form
-// 23.9 / 16.5, 29.2 / 28.5, 33.2 / 40.3).
+// per wavefront above.
 bool sweep_split(const wb_robot *r, int64_t B) {
-    const int64_t below = r->sweep_split_below >= 0 ? r->sweep_split_below : (int64_t)2 * r->cus;
-    return B < below;
+    const int per_cu = wb::sweep_split_per_cu(r->T.L, r->T.nmax, r->T.n_blocks, r->T.n_pairs);
+    return B < (r->sweep_split_below >= 0 ? r->sweep_split_below : (int64_t)per_cu * r->cus);
 }
 }  // namespace
 

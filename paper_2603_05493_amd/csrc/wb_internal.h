@@ -266,6 +266,24 @@ inline SweepShape sweep_split_shape(int L, int nmax, int n_blocks_pad) {
     if (state + scratch <= LDS_LIMIT) return SweepShape{1, 0, SWEEP_LIST, state + scratch};
     return SweepShape{1, 0, 128, state + 4 * 4 * (SC_RING + 128)};
 }
+// Default threshold between the two, in states per compute unit: the split
+// form below it.
+//   2 with at most 128 link blocks, one chunk, which one wavefront sweeps in
+//     either form; below, one state per wavefront leaves SIMDs without work;
+//   6 with more (wave / split form, us, at 1,000 and 2,048 states: 41 links of
+//     4 spheres 12.6 / 10.8, 14.5 / 15.9; 25 of 8: 13.6 / 12.6, 15.5 / 21.7;
+//     101 of 1: 15.6 / 11.0, 16.3 / 19.6; a humanoid 13.3 / 11.9, 13.4 / 20.5);
+//   16 for robots of more than 40,000 pairs, most of which stay ahead in the
+//     split form to 4,096 states (61 links of 8: 46.8 / 43.5 at 2,048, 82 / 67
+//     at 4,096; 61 of 12: 76 / 67, 139 / 107; 49 of 16: 99 / 81, 167 / 129; the
+//     earliest, 21 of 16, crosses at 1,100), and for those of which 64 KB hold
+//     fewer than four states, whose wave form leaves wavefronts idle (49 links
+//     of 48: 533 / 223 at 512, 1,018 / 613 at 2,048).
+inline int sweep_split_per_cu(int L, int nmax, int n_blocks, int64_t n_pairs) {
+    if (n_blocks <= 128) return 2;
+    return n_pairs > 40000 || sweep_wave_shape(L, nmax, (n_blocks + 127) / 128 * 128).states < 4 ? 16 : 6;
+}
+
 // LDS of a workgroup of the fused kernel with G lanes per state and `waves`
 // wavefronts: their group regions, then, for four, the block table.
 inline size_t fused_lds_bytes(int L, int nmax, int n_blocks, int G, int waves) {

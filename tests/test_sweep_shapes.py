@@ -1,7 +1,8 @@
 """Host: the LDS shapes of the standalone self-collision sweeps fit the 64 KB
 limit for every robot that wb_robot_create takes, with a ring and a list for
 each state in flight (the header's functions, compiled and swept over the
-accepted sizes)."""
+accepted sizes); and the default threshold of the split form follows the
+measured crossings."""
 import os
 import subprocess
 
@@ -42,10 +43,41 @@ int main() {
 """
 
 
-def test_shapes_fit(tmp_path):
+# links, slots, blocks, pairs and the threshold in states per compute unit, of
+# robots whose two forms were timed from 256 to 8,192 states
+SPLIT = r"""
+#include "wb_internal.h"
+#include <cstdio>
+int main() {
+    const struct { int L, nmax, blocks; long pairs; int per_cu; } robots[] = {
+        {13, 6, 66, 2376, 2},        {16, 12, 105, 15120, 2},      {11, 16, 45, 11520, 2},      {8, 64, 21, 86016, 2},
+        {41, 4, 780, 12480, 6},      {25, 8, 276, 17664, 6},       {101, 1, 4950, 4950, 6},     {49, 5, 1128, 28000, 6},      {101, 3, 4950, 44550, 16},
+        {61, 8, 1770, 113280, 16},   {61, 12, 1770, 254880, 16},   {49, 16, 1128, 288768, 16},  {101, 7, 4950, 242550, 16},
+        {49, 24, 1128, 649728, 16},  {49, 48, 1128, 2598912, 16},  {261, 5, 33670, 841750, 16}};
+    for (const auto &r : robots) {
+        const int got = wb::sweep_split_per_cu(r.L, r.nmax, r.blocks, r.pairs);
+        if (got != r.per_cu) {
+            printf("L %d nmax %d: %d, not %d\n", r.L, r.nmax, got, r.per_cu);
+            return 1;
+        }
+    }
+    return 0;
+}
+"""
+
+
+def _run(tmp_path, text):
     src, exe = tmp_path / "shapes.cpp", tmp_path / "shapes"
-    src.write_text(SOURCE)
+    src.write_text(text)
     subprocess.run([build.hipcc(), *build.flags(), str(src), "-o", str(exe)], check=True, capture_output=True, text=True,
                    env=dict(os.environ))
     r = subprocess.run([str(exe)], capture_output=True, text=True)
     assert r.returncode == 0, r.stdout
+
+
+def test_shapes_fit(tmp_path):
+    _run(tmp_path, SOURCE)
+
+
+def test_default_split_threshold(tmp_path):
+    _run(tmp_path, SPLIT)
