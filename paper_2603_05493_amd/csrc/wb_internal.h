@@ -258,12 +258,16 @@ inline SweepShape sweep_wave_shape(int L, int nmax, int n_blocks_pad) {
     return SweepShape{states, 0, SWEEP_LIST, states * one};
 }
 // One state per workgroup: with the block table, without it, and with lists of
-// one 128-entry chunk where the longer ones do not fit.
+// one 128-entry chunk where those of two do not fit.  Two chunks: longer lists
+// save sweeps of a few rows but cost workgroups on a compute unit (101 links
+// of 7 spheres, 1,000 states, lists of 128 / 256 / 512 entries 48 / 45 / 54 us;
+// 261 links of 5: 125 / 101 / 99; 49 of 24, 4,095 states: 207 / 202 / 226).
+constexpr int SPLIT_LIST = 256;
 inline SweepShape sweep_split_shape(int L, int nmax, int n_blocks_pad) {
-    const size_t state = state_lds_bytes(L, nmax), scratch = 4 * 4 * (SC_RING + SWEEP_LIST);
-    if (state + scratch + tab_lds_bytes(n_blocks_pad) <= LDS_LIMIT)
-        return SweepShape{1, 1, SWEEP_LIST, state + scratch + tab_lds_bytes(n_blocks_pad)};
-    if (state + scratch <= LDS_LIMIT) return SweepShape{1, 0, SWEEP_LIST, state + scratch};
+    const size_t state = state_lds_bytes(L, nmax), full = state + 4 * 4 * (SC_RING + SPLIT_LIST);
+    if (full + tab_lds_bytes(n_blocks_pad) <= LDS_LIMIT)
+        return SweepShape{1, 1, SPLIT_LIST, full + tab_lds_bytes(n_blocks_pad)};
+    if (full <= LDS_LIMIT) return SweepShape{1, 0, SPLIT_LIST, full};
     return SweepShape{1, 0, 128, state + 4 * 4 * (SC_RING + 128)};
 }
 // Default threshold between the two, in states per compute unit: the split

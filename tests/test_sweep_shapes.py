@@ -54,6 +54,8 @@ int main() {
         {41, 4, 780, 12480, 6},      {25, 8, 276, 17664, 6},       {101, 1, 4950, 4950, 6},     {49, 5, 1128, 28000, 6},      {101, 3, 4950, 44550, 16},
         {61, 8, 1770, 113280, 16},   {61, 12, 1770, 254880, 16},   {49, 16, 1128, 288768, 16},  {101, 7, 4950, 242550, 16},
         {49, 24, 1128, 649728, 16},  {49, 48, 1128, 2598912, 16},  {261, 5, 33670, 841750, 16}};
+    // 101 links of 7 spheres: four workgroups of the split form in a compute unit's 160 KB
+    if (4 * wb::sweep_split_shape(101, 7, 4992).lds > 160 * 1024) return 2;
     for (const auto &r : robots) {
         const int got = wb::sweep_split_per_cu(r.L, r.nmax, r.blocks, r.pairs);
         if (got != r.per_cu) {
