@@ -294,11 +294,13 @@ inline size_t fused_lds_bytes(int L, int nmax, int n_blocks, int G, int waves) {
     return (size_t)waves * (64 / G) * group_lds_bytes(L, nmax, n_blocks, G) +
            (waves > 1 ? tab_lds_bytes((n_blocks + 127) / 128 * 128) : 0);
 }
-// What a fused shape or a plan is held against LDS_LIMIT by, at least what
-// each wavefront takes: 16-bit lists of up to 2,048 blocks and a 16-bit
-// table a workgroup of four wavefronts.  It decides which robots and shapes
-// are accepted; a launch may take a little more than LDS_LIMIT of the 160 KB
-// that a compute unit has.
+// What a fused shape or a plan is held against LDS_LIMIT by: a workgroup of
+// four wavefronts with 16-bit lists of up to 2,048 blocks and a 16-bit table.
+// It decides which robots and shapes are accepted, and is not what a launch
+// takes: the fused and plan kernels' workgroups are one wavefront, of at most
+// 17 KB; the one-launch B-spline step, four wavefronts with 32-bit lists and
+// table, takes up to 7 KB more than is counted, 71 KB at most of the 160 KB
+// that a workgroup may have, and two still share a compute unit.
 inline size_t counted_group_bytes(int L, int nmax, int n_blocks_pad) {
     const int cap = n_blocks_pad < 128 ? 128 : (n_blocks_pad > 2048 ? 2048 : n_blocks_pad);
     return state_lds_bytes(L, nmax) + (size_t)cap * 2 + (size_t)128 * 4;

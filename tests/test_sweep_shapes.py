@@ -1,7 +1,8 @@
 """Host: the LDS shapes of the standalone self-collision sweeps fit the 64 KB
 limit for every robot that wb_robot_create takes, with a ring and a list for
 each state in flight (the header's functions, compiled and swept over the
-accepted sizes); and the default threshold of the split form follows the
+accepted sizes); so do the fused and plan launches, one wavefront a workgroup,
+and the one-launch B-spline step, four, takes at most 72 KB; and the default threshold of the split form follows the
 measured crossings."""
 import os
 import subprocess
@@ -43,6 +44,30 @@ int main() {
 """
 
 
+FUSED = r"""
+#include "wb_internal.h"
+#include <algorithm>
+#include <cstdio>
+using namespace wb;
+int main() {
+    size_t one = 0, four = 0;
+    for (int nmax : {1, 2, 3, 4, 5, 6, 7, 8, 12})
+        for (int L = 1; L <= 64; ++L)
+            for (int blocks = 0; blocks <= L * (L - 1) / 2; ++blocks)
+                for (int G : {16, 32, 64}) {
+                    const int pad = (blocks + 127) / 128 * 128;
+                    const size_t counted = counted_fused_bytes(L, nmax, G, pad);
+                    if (G < L || counted > LDS_LIMIT) continue;   // refused
+                    one = std::max(one, fused_lds_bytes(L, nmax, blocks, G, 1));
+                    // the spline's own part is counted as it is launched
+                    four = std::max(four, LDS_LIMIT + fused_lds_bytes(L, nmax, blocks, G, 4) - counted);
+                }
+    printf("one wavefront %zu B, four %zu B\n", one, four);
+    return one <= LDS_LIMIT && four <= 72 * 1024 ? 0 : 1;
+}
+"""
+
+
 # links, slots, blocks, pairs and the threshold in states per compute unit, of
 # robots whose two forms were timed from 256 to 8,192 states
 SPLIT = r"""
@@ -74,11 +99,16 @@ def _run(tmp_path, text):
     subprocess.run([build.hipcc(), *build.flags(), str(src), "-o", str(exe)], check=True, capture_output=True, text=True,
                    env=dict(os.environ))
     r = subprocess.run([str(exe)], capture_output=True, text=True)
+    print(r.stdout)
     assert r.returncode == 0, r.stdout
 
 
 def test_shapes_fit(tmp_path):
     _run(tmp_path, SOURCE)
+
+
+def test_fused_launches(tmp_path):
+    _run(tmp_path, FUSED)
 
 
 def test_default_split_threshold(tmp_path):
