@@ -116,10 +116,11 @@ hipError_t launch_self_collision_backward(const DevRobot &rb, int64_t B, int64_t
 hipError_t launch_cost_head(int64_t B, int64_t ld, int32_t n, const float *tau, const float *w, float tw,
                             const float *max_pen, float margin, float hw, float *cost,
                             float *g_tau, float *g_maxpen, hipStream_t s) {
-    if (B == 0) return hipSuccess;
-    hipLaunchKernelGGL(k_cost_head, dim3((unsigned)((B + 63) / 64)), dim3(256), 0, s, B, ld, n, tau, w, tw,
-                       max_pen, margin, hw, cost, g_tau, g_maxpen);
-    return hipGetLastError();
+    return in_slices(B, [&](int64_t b0, int64_t nb) {
+        hipLaunchKernelGGL(k_cost_head, dim3((unsigned)((nb + 63) / 64)), dim3(256), 0, s, nb, ld, n, from(tau, b0),
+                           from(w, b0), tw, from(max_pen, b0), margin, hw, from(cost, b0), from(g_tau, b0),
+                           from(g_maxpen, b0));
+    });
 }
 
 hipError_t launch_sgd_step(int64_t B, int64_t ld, int32_t n, float lr, float *q, float *qd, float *qdd,

@@ -523,19 +523,20 @@ static void launch_backward_levels(const DevRobot &rb, const DevFused &fz, int64
 hipError_t launch_rnea_levels(const DevRobot &rb, const DevFused &fz, int64_t B, int64_t ld, const float *q,
                               const float *qd, const float *qdd, const float *f_ext, float *tau, float *cache,
                               bool wide, hipStream_t s) {
-    if (B == 0) return hipSuccess;
-    if (wide) launch_levels<8>(rb, fz, B, ld, q, qd, qdd, f_ext, tau, cache, s);
-    else launch_levels<4>(rb, fz, B, ld, q, qd, qdd, f_ext, tau, cache, s);
-    return hipGetLastError();
+    return in_slices(B, [&](int64_t b0, int64_t n) {
+        const auto launch = wide ? launch_levels<8> : launch_levels<4>;
+        launch(rb, fz, n, ld, from(q, b0), from(qd, b0), from(qdd, b0), from(f_ext, b0), from(tau, b0), cache + b0, s);
+    });
 }
 
 hipError_t launch_rnea_backward_levels(const DevRobot &rb, const DevFused &fz, int64_t B, int64_t ld, const float *q,
                                        const float *qd, const float *qdd, const float *cache, const float *g_tau,
                                        float *g_q, float *g_qd, float *g_qdd, float *g_fext, bool wide, hipStream_t s) {
-    if (B == 0) return hipSuccess;
-    if (wide) launch_backward_levels<8>(rb, fz, B, ld, q, qd, qdd, cache, g_tau, g_q, g_qd, g_qdd, g_fext, s);
-    else launch_backward_levels<4>(rb, fz, B, ld, q, qd, qdd, cache, g_tau, g_q, g_qd, g_qdd, g_fext, s);
-    return hipGetLastError();
+    return in_slices(B, [&](int64_t b0, int64_t n) {
+        const auto launch = wide ? launch_backward_levels<8> : launch_backward_levels<4>;
+        launch(rb, fz, n, ld, from(q, b0), from(qd, b0), from(qdd, b0), cache + b0, from(g_tau, b0), from(g_q, b0),
+               from(g_qd, b0), from(g_qdd, b0), from(g_fext, b0), s);
+    });
 }
 
 }  // namespace wb

@@ -500,13 +500,10 @@ hipError_t launch_fk_lanes(const DevRobot &rb, const DevFused &fz, int64_t B, in
 
 hipError_t launch_fk_levels(const DevRobot &rb, int64_t B, int64_t ld, const float *q, float *pose, float *spheres,
                             hipStream_t s) {
-    if (B == 0) return hipSuccess;
-    switch (lanes_for(rb.L)) {
-        case 16: launch_fk_l<16>(rb, B, ld, q, pose, spheres, s); break;
-        case 32: launch_fk_l<32>(rb, B, ld, q, pose, spheres, s); break;
-        default: launch_fk_l<64>(rb, B, ld, q, pose, spheres, s); break;
-    }
-    return hipGetLastError();
+    return in_slices(B, [&](int64_t b0, int64_t n) {
+        const auto launch = rb.L <= 16 ? launch_fk_l<16> : (rb.L <= 32 ? launch_fk_l<32> : launch_fk_l<64>);
+        launch(rb, n, ld, from(q, b0), from(pose, b0), from(spheres, b0), s);
+    });
 }
 
 hipError_t launch_fk_backward_lanes(const DevRobot &rb, const DevFused &fz, int64_t B, int64_t ld, const float *q,
@@ -522,9 +519,9 @@ hipError_t launch_fk_backward_lanes(const DevRobot &rb, const DevFused &fz, int6
 
 hipError_t launch_fk_backward_levels(const DevRobot &rb, const DevFused &fz, int64_t B, int64_t ld, const float *q,
                                      const float *g_pose, const float *g_sph, float *g_q, hipStream_t s) {
-    if (B == 0) return hipSuccess;
-    launch_fkb_l<8>(rb, fz, B, ld, q, g_pose, g_sph, g_q, s);
-    return hipGetLastError();
+    return in_slices(B, [&](int64_t b0, int64_t n) {
+        launch_fkb_l<8>(rb, fz, n, ld, from(q, b0), from(g_pose, b0), from(g_sph, b0), from(g_q, b0), s);
+    });
 }
 
 template <bool BWD, int G>

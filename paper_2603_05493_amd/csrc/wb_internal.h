@@ -172,6 +172,24 @@ hipError_t launch_rnea(const DevRobot &rb, int64_t B, int64_t ld, const float *q
 hipError_t launch_rnea_backward(const DevRobot &rb, int64_t B, int64_t ld, const float *q, const float *qd,
                                 const float *qdd, const float *cache, const float *g_tau,
                                 float *g_q, float *g_qd, float *g_qdd, float *g_fext, float *ws, hipStream_t s);
+// A grid holds fewer than 2^32 threads.  Kernels with several threads a state
+// are launched on slices of a batch, so that the batches that one thread a
+// state reached (up to 2^31 - 1) still run: f(b0, n) for the states b0 .. b0 + n - 1.
+constexpr int64_t SLICE_STATES = (int64_t)1 << 24;
+template <typename F>
+inline hipError_t in_slices(int64_t B, F f) {
+    for (int64_t b0 = 0; b0 < B; b0 += SLICE_STATES) {
+        f(b0, B - b0 < SLICE_STATES ? B - b0 : SLICE_STATES);
+        const hipError_t e = hipGetLastError();
+        if (e != hipSuccess) return e;
+    }
+    return hipSuccess;
+}
+template <typename T>
+inline T *from(T *rows, int64_t b0) {
+    return rows ? rows + b0 : nullptr;
+}
+
 // The same level by level, one thread per (state, link), in tiles of 4 states
 // (wide: 8); robots of at most 64 links.
 hipError_t launch_rnea_levels(const DevRobot &rb, const DevFused &fz, int64_t B, int64_t ld, const float *q,
