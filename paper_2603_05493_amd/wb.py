@@ -18,10 +18,16 @@ from . import _abi
 from ._abi import WbRobotDesc, WbRobotInfo, check, lib
 
 
+_raw_stream = getattr(torch._C, "_cuda_getCurrentRawStream", None)
+
+
 def _stream() -> int:
     # the current device's current stream as a raw handle; building a
-    # torch.cuda.Stream object for it costs about 6 us, a third of a call
-    return torch._C._cuda_getCurrentRawStream(torch._C._cuda_getDevice())
+    # torch.cuda.Stream object for it costs about 6 us, a third of a call,
+    # so torch's own shorthand is taken where it has one
+    if _raw_stream is not None:
+        return _raw_stream(torch.cuda.current_device())
+    return torch.cuda.current_stream().cuda_stream
 
 
 def _p(t: Optional[torch.Tensor]):
