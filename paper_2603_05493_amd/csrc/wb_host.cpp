@@ -531,7 +531,7 @@ struct wb_robot {
     wb::DevKin kin{};
     wb_tune tune{};
     void *dmem = nullptr;
-    size_t o_lf = 0, o_ff = 0;   // offsets of the link records and the fused float lane table
+    size_t o_lf = 0, o_lanes = 0;   // offsets of the link records and the lane tables
     size_t o_kf = 0;             // offset of the kinematics float lane table
     size_t o_tl = 0, o_to = 0, o_ta = 0;   // tool lanes, offsets and affects masks (WB_MAX_TOOLS each)
     int device = -1;
@@ -590,6 +590,14 @@ size_t append(std::vector<char> &blob, const V &v) {
     blob.resize(off + v.size() * sizeof(typename V::value_type));
     if (!v.empty()) memcpy(blob.data() + off, v.data(), v.size() * sizeof(typename V::value_type));
     return off;
+}
+
+// The lane tables (links, floats, spheres, joints' links), one behind the
+// other; their offsets into `at`.  Returns the end.
+size_t append_lane_tables(std::vector<char> &blob, const Tables &T, size_t *at) {
+    const size_t o[4] = {append(blob, T.f_li), append(blob, T.f_lf), append(blob, T.f_sph), append(blob, T.f_conn)};
+    if (at) std::copy(o, o + 4, at);
+    return blob.size();
 }
 
 int check_robot(const wb_robot *r) {
@@ -668,8 +676,9 @@ int wb_robot_create(const wb_robot_desc *desc, wb_robot **out) {
     const size_t o_sr = append(blob, T.slot_r), o_bl = append(blob, entries);
     const size_t o_po = append(blob, T.pair_off), o_pc = append(blob, T.pair_cnt);
     const size_t o_ps = append(blob, T.pair_s), o_pt = append(blob, T.pair_t);
-    const size_t o_fi = append(blob, T.f_li), o_ff = append(blob, T.f_lf), o_fs = append(blob, T.f_sph);
-    const size_t o_fc = append(blob, T.f_conn), o_fa = append(blob, T.f_allow), o_fk = append(blob, T.kids);
+    size_t o_lanes[4];
+    append_lane_tables(blob, T, o_lanes);
+    const size_t o_fa = append(blob, T.f_allow), o_fk = append(blob, T.kids);
     const size_t o_ki = append(blob, T.k_li), o_kf = append(blob, T.k_lf), o_kc = append(blob, T.k_conn);
     const size_t o_tl = append(blob, std::vector<int32_t>(WB_MAX_TOOLS, 0));
     const size_t o_to = append(blob, std::vector<float>(12 * WB_MAX_TOOLS, 0.0f));
@@ -690,7 +699,7 @@ int wb_robot_create(const wb_robot_desc *desc, wb_robot **out) {
     }
     char *base = static_cast<char *>(r->dmem);
     r->o_lf = o_lf;
-    r->o_ff = o_ff;
+    r->o_lanes = o_lanes[0];
     wb::DevRobot &D = r->dev;
     D.L = T.L; D.n = T.n; D.S = T.S; D.nmax = T.nmax;
     D.n_blocks = T.n_blocks; D.n_blocks_pad = (int)T.blocks.size();
@@ -714,12 +723,12 @@ int wb_robot_create(const wb_robot_desc *desc, wb_robot **out) {
     wb::DevFused &Fz = r->fz;
     Fz.supported = T.fused;
     Fz.jsteps = T.jsteps;
-    Fz.li = reinterpret_cast<const int32_t *>(base + o_fi);
-    Fz.lf = reinterpret_cast<const float *>(base + o_ff);
-    Fz.lsph = reinterpret_cast<const float4 *>(base + o_fs);
+    Fz.li = reinterpret_cast<const int32_t *>(base + o_lanes[0]);
+    Fz.lf = reinterpret_cast<const float *>(base + o_lanes[1]);
+    Fz.lsph = reinterpret_cast<const float4 *>(base + o_lanes[2]);
     Fz.mimic = T.f_mimic;
     Fz.mc = T.f_mc;
-    Fz.conn = reinterpret_cast<const int32_t *>(base + o_fc);
+    Fz.conn = reinterpret_cast<const int32_t *>(base + o_lanes[3]);
     Fz.branched = T.f_branched;
     wb::DevKin &Kn = r->kin;
     Kn.L = T.L; Kn.n = T.n; Kn.G = T.kin_G; Kn.jsteps = T.kin_jsteps; Kn.mc = T.kin_mc;
@@ -1146,12 +1155,8 @@ int wb_robot_set_link_inertia(wb_robot *robot, int32_t link, float mass, const f
     F.mass = mass;
     for (int c = 0; c < 3; ++c) F.com[c] = com[c];
     for (int c = 0; c < 6; ++c) F.I[c] = inertia[c];
-    if (T.lanes) {
-        const int i = T.lane_of[link];
-        T.f_lf[15 * 64 + i] = mass;
-        for (int c = 0; c < 3; ++c) T.f_lf[(16 + c) * 64 + i] = com[c];
-        for (int c = 0; c < 6; ++c) T.f_lf[(19 + c) * 64 + i] = inertia[c];
-    }
+    // the lanes are ordered by the subtrees' masses
+    if (T.lanes) build_fused(T);
     T.total_mass = 0.0;
     for (int k = 0; k < T.L; ++k) T.total_mass += T.lf[k].mass;
     robot->kin.inv_mass = T.total_mass > 0.0 ? (float)(1.0 / T.total_mass) : 0.0f;
@@ -1167,8 +1172,11 @@ int wb_robot_set_link_inertia(wb_robot *robot, int32_t link, float mass, const f
     if (e == hipSuccess)
         e = hipMemcpy(base + robot->o_lf + (size_t)link * sizeof(wb::LinkF), &F, sizeof(wb::LinkF),
                       hipMemcpyHostToDevice);
-    if (e == hipSuccess && T.lanes)
-        e = hipMemcpy(base + robot->o_ff, T.f_lf.data(), T.f_lf.size() * sizeof(float), hipMemcpyHostToDevice);
+    if (e == hipSuccess && T.lanes) {
+        std::vector<char> tables;
+        const size_t end = append_lane_tables(tables, T, nullptr);
+        e = hipMemcpy(base + robot->o_lanes, tables.data(), end, hipMemcpyHostToDevice);
+    }
     if (e == hipSuccess && T.kin)
         e = hipMemcpy(base + robot->o_kf, T.k_lf.data(), T.k_lf.size() * sizeof(float), hipMemcpyHostToDevice);
     if (prev >= 0 && prev != robot->device) (void)hipSetDevice(prev);
