@@ -189,12 +189,9 @@ __device__ __forceinline__ int append_blocks(uint32_t e0, uint32_t e1, const flo
 // appends its survivors behind those of the lanes below.  The direct test
 // costs 25 vector instructions for 64 blocks, 450 for a humanoid's 1,128;
 // this takes about 220 and the idle matrix cores.
-// Taken from BROAD_MATRIX_FROM blocks on: humanoid x 24,576 (1,128 blocks)
-// 92.6 -> 88.0 us a fused launch, a 23-joint tree in 64 lanes (253 blocks)
-// 80.5 -> 89 us.
+// Taken from BROAD_MATRIX_FROM blocks on.
 // Returns the number of survivors; the list holds them if they are at most
 // cap.  Every lane of the wavefront calls this.
-constexpr int BROAD_MATRIX_FROM = 576;
 typedef float floatx16 __attribute__((ext_vector_type(16)));
 __device__ __forceinline__ int broad_phase(const DevRobot &rb, const float4 *Bd, uint32_t *list, int cap, int lane) {
     const bool lo = lane < 32;

@@ -256,6 +256,14 @@ __host__ __device__ inline size_t state_lds_bytes(int L, int nmax) { return (siz
 __host__ __device__ inline size_t group_lds_bytes(int L, int nmax, int n_blocks, int G) {
     return state_lds_bytes(L, nmax) + (size_t)(sweep_list(n_blocks, G) + sweep_ring(G)) * 4;
 }
+// Blocks from which the one-state-per-wavefront fused sweep tests them on the
+// matrix cores (sweep.h).  Direct / matrix form, us a fused launch of 16,384
+// states: 946 blocks 74.4 / 77.0, 861 72.5 / 75.5, 780 70.3 / 71.4 to 73.2, 630
+// 63.5 / 66.9, 253 52.5 / 58.0; 1,035 blocks 70.8 / 69.0, 1,128 (trees of 49
+// links) 136.7 / 134.3, 79.9 / 79.5 and 78.4 / 78.6, a humanoid of as many x
+// 24,576 92.6 / 88.0.  With one sphere a link the forms already cross at 650.
+constexpr int BROAD_MATRIX_FROM = 1024;
+
 // LDS copy of the block table (n_blocks_pad entries, a multiple of 128).
 __host__ __device__ inline size_t tab_lds_bytes(int n_blocks_pad) { return (size_t)n_blocks_pad * 4; }
 // Shapes of the standalone sweeps, all within LDS_LIMIT for every robot that

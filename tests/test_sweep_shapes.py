@@ -3,7 +3,7 @@ limit for every robot that wb_robot_create takes, with a ring and a list for
 each state in flight (the header's functions, compiled and swept over the
 accepted sizes); so do the fused and plan launches, one wavefront a workgroup,
 and the one-launch B-spline step, four, takes at most 72 KB; and the default threshold of the split form follows the
-measured crossings."""
+measured crossings, as does the matrix-core broad phase."""
 import os
 import subprocess
 
@@ -81,6 +81,11 @@ int main() {
         {49, 24, 1128, 649728, 16},  {49, 48, 1128, 2598912, 16},  {261, 5, 33670, 841750, 16}};
     // 101 links of 7 spheres: four workgroups of the split form in a compute unit's 160 KB
     if (4 * wb::sweep_split_shape(101, 7, 4992).lds > 160 * 1024) return 2;
+    // link blocks on the two sides of the broad phase's crossing
+    for (int blocks : {253, 378, 496, 561, 630, 703, 780, 861, 946})
+        if (blocks >= wb::BROAD_MATRIX_FROM) return 3;
+    for (int blocks : {1035, 1128})
+        if (blocks < wb::BROAD_MATRIX_FROM) return 4;
     for (const auto &r : robots) {
         const int got = wb::sweep_split_per_cu(r.L, r.nmax, r.blocks, r.pairs);
         if (got != r.per_cu) {
