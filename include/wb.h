@@ -257,8 +257,9 @@ int wb_self_collision(const wb_robot *robot, int64_t B, int64_t ld, const float 
  * dispatches FK kernels by robot size; here the forms are chosen by batch
  * size, with thresholds the autotuner measures):
  *   sweep_split_below     wb_self_collision takes the one-state-per-workgroup
- *                         form for batches of fewer states (default 2, 6 or
- *                         16 per compute unit of the robot's device: 2 up to
+ *                         form for batches of fewer states (default 0, 2, 6
+ *                         or 16 per compute unit of the robot's device: 0 for
+ *                         robots of very few spheres, 2 up to
  *                         128 pairs of links with spheres, 16 with more than
  *                         40,000 sphere pairs or more than about 14 KB of
  *                         sphere slots a state, 6 otherwise);

@@ -33,8 +33,8 @@ __device__ __forceinline__ void stage_blocks(const DevRobot &rb, uint32_t *tab, 
 // nb: states; B: row length of the sphere array (the ABI's ld >= nb).
 // TS: 4, or 0 for robots of which 64 KB hold fewer than four states: a
 // workgroup then takes `chunk` states (1 to 3), one a wavefront, the others
-// helping to stage them.
-template <int NMAX, bool TAB_LDS, int TS>
+// helping to stage them.  DIRECT: rows are evaluated without a test.
+template <int NMAX, bool TAB_LDS, int TS, bool DIRECT = false>
 __global__ void __launch_bounds__(256) k_self_collision(DevRobot rb, int64_t nb, int64_t B, int chunk,
                                                         const float *__restrict__ sph,
                                                         float *__restrict__ max_pen,
@@ -74,7 +74,7 @@ __global__ void __launch_bounds__(256) k_self_collision(DevRobot rb, int64_t nb,
         float M;
         int key;
         unsigned cnt;
-        sweep_state<NMAX, true, false, false>(rb, tab, P, Bd, lists + wave * SWEEP_LIST, rings + wave * SC_RING, lane, 64,
+        sweep_state<NMAX, true, false, false, DIRECT>(rb, tab, P, Bd, lists + wave * SWEEP_LIST, rings + wave * SC_RING, lane, 64,
                                 0, M, key, cnt);
         if (lane == 0) {
             if (max_pen) max_pen[b] = M;
@@ -135,7 +135,9 @@ static hipError_t launch_sc(const DevRobot &rb, int64_t B, int64_t ld, const flo
     // chunks of up to 32 states that leave 2,048 workgroups, or the states of one pass
     const int chunk = w.states < 4 ? w.states : (int)std::max<int64_t>(std::min<int64_t>(32, B / 2048) / 4 * 4, 4);
     const dim3 grid((unsigned)((B + chunk - 1) / chunk)), block(256);
-    if (w.table)
+    if (NMAX <= 16 && w.table && rb.n_blocks * NMAX <= DIRECT_ROWS)
+        hipLaunchKernelGGL((k_self_collision<NMAX, true, 4, NMAX <= 16>), grid, block, w.lds, s, rb, B, ld, chunk, sph, mp, am, nc);
+    else if (w.table)
         hipLaunchKernelGGL((k_self_collision<NMAX, true, 4>), grid, block, w.lds, s, rb, B, ld, chunk, sph, mp, am, nc);
     else if (w.states == 4)
         hipLaunchKernelGGL((k_self_collision<NMAX, false, 4>), grid, block, w.lds, s, rb, B, ld, chunk, sph, mp, am, nc);

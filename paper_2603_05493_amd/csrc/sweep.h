@@ -265,32 +265,50 @@ __device__ __forceinline__ float row_bound(float4 A, float4 Bb) {
 
 constexpr uint32_t NO_ROW = ~0u;           // no row code (offsets are multiples of 16)
 
-// Evaluates the n queued rows at ring[head, head + n) (mod 2 G), one
-// per lane; a row code is the byte offset of slot A << 16 | that of the
-// second link's first slot, and best_code keeps the code of the row that set
-// the running max.
+// Evaluates the row that a code names -- the byte offset of slot A << 16 | that
+// of the second link's first slot -- in the calling lanes; best_code keeps the
+// code of the row that set the running max.  BALLOT: cnt is the wavefront's
+// count, held by the lanes that call, else the lane's.
+template <int NMAX, bool BALLOT>
+__device__ __forceinline__ void eval_row(const float4 *P, uint32_t code, float &best, uint32_t &best_code, bool &tie,
+                                         unsigned &cnt) {
+    const float4 A = bound_of(P, code >> 16);
+    const float4 *Bp = &bound_of(P, code & 0xffffu);
+    float m = -INFINITY;
+#pragma unroll
+    for (int k = 0; k < NMAX; ++k) {
+        const float pen = pair_pen(A, Bp[k]);
+        m = fmaxf(m, pen);
+        if (BALLOT) cnt += (unsigned)__popcll(__ballot(pen > 0.0f));
+        else cnt += pen > 0.0f ? 1u : 0u;
+    }
+    if (m > best) {
+        best = m;
+        best_code = code;
+        tie = false;
+    } else if (m == best) {
+        tie = true;
+    }
+}
+
+// Evaluates the n queued rows at ring[head, head + n) (mod 2 G), one per lane.
 template <int NMAX, bool FULL>
 __device__ __forceinline__ void eval_rows(const float4 *P, const uint32_t *ring, int head, int n, int glane, int G,
                                           float &best, uint32_t &best_code, bool &tie, unsigned &cnt) {
-    if (glane < n) {
-        const uint32_t code = ring[(head + glane) & (2 * G - 1)];
-        const float4 A = bound_of(P, code >> 16);
-        const float4 *Bp = &bound_of(P, code & 0xffffu);
-        float m = -INFINITY;
-#pragma unroll
-        for (int k = 0; k < NMAX; ++k) {
-            const float pen = pair_pen(A, Bp[k]);
-            m = fmaxf(m, pen);
-            if (FULL) cnt += (unsigned)__popcll(__ballot(pen > 0.0f));
-            else cnt += pen > 0.0f ? 1u : 0u;
-        }
-        if (m > best) {
-            best = m;
-            best_code = code;
-            tie = false;
-        } else if (m == best) {
-            tie = true;
-        }
+    if (glane < n) eval_row<NMAX, FULL>(P, ring[(head + glane) & (2 * G - 1)], best, best_code, tie, cnt);
+}
+
+// Every row of the blocks list[0, nl), by a wavefront (PASS2: of those that
+// pass 1 left out), for robots of at most DIRECT_ROWS rows.
+template <int NMAX, bool PASS2>
+__device__ __forceinline__ void sweep_rows_direct(const float4 *P, const float4 *Bd, const uint32_t *list, int nl,
+                                                  float eps, int lane, float &best, uint32_t &best_code, bool &tie,
+                                                  unsigned &cnt) {
+    for (int j = lane; j < nl * NMAX; j += 64) {
+        const int i = j / NMAX, row = j - i * NMAX;
+        const uint32_t e = list[i];
+        if (PASS2 && may_reach<false>(Bd, e, eps)) continue;
+        eval_row<NMAX, false>(P, (((e >> 16) * NMAX + row * 16) << 16) | ((e & 0xffffu) * NMAX), best, best_code, tie, cnt);
     }
 }
 
@@ -357,8 +375,8 @@ __device__ __forceinline__ int code_min_key(const DevRobot &rb, const float4 *P,
 // words of LDS scratch for this group.  PADDED: the bounds' radii hold the rounding
 // margin of any state already, else it is formed from the state's extent.
 // MATRIX (with PADDED, at most 64 links): pass 1 on the matrix cores where
-// the robot has blocks enough.
-template <int NMAX, bool FULL, bool PADDED, bool MATRIX>
+// the robot has blocks enough.  DIRECT (with FULL, not PADDED): no row tests.
+template <int NMAX, bool FULL, bool PADDED, bool MATRIX, bool DIRECT = false>
 __device__ __forceinline__ void sweep_state(const DevRobot &rb, const uint32_t *tab, const float4 *P,
                                             const float4 *Bd, uint32_t *list, uint32_t *ring, int glane, int G,
                                             int grp, float &M_out, int &key_out, unsigned &cnt_out) {
@@ -399,8 +417,10 @@ __device__ __forceinline__ void sweep_state(const DevRobot &rb, const uint32_t *
             if (k + 2 * G >= nb || (FULL ? full : __ballot(full) != 0)) {
                 __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");
                 __builtin_amdgcn_wave_barrier();
-                sweep_rows_culled<NMAX, FULL, PASS2, PADDED>(P, Bd, list, nl, ring, eps, lo, glane, G, gshift, gmask,
-                                                             best, best_code, tie, cnt);
+                if (DIRECT) sweep_rows_direct<NMAX, PASS2>(P, Bd, list, nl, eps, glane, best, best_code, tie, cnt);
+                else
+                    sweep_rows_culled<NMAX, FULL, PASS2, PADDED>(P, Bd, list, nl, ring, eps, lo, glane, G, gshift,
+                                                                 gmask, best, best_code, tie, cnt);
                 __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");
                 __builtin_amdgcn_wave_barrier();
                 nl = 0;
@@ -466,7 +486,7 @@ __device__ __forceinline__ void sweep_state(const DevRobot &rb, const uint32_t *
     }
     M_out = M;
     key_out = group_reduce_min(key, G);
-    cnt_out = FULL ? cnt : group_reduce_sum_u(cnt, G);
+    cnt_out = FULL && !DIRECT ? cnt : group_reduce_sum_u(cnt, G);
 }
 
 // Sweep one state with the four wavefronts of a workgroup (the map of the

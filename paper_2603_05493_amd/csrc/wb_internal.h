@@ -296,8 +296,15 @@ inline SweepShape sweep_split_shape(int L, int nmax, int n_blocks_pad) {
     if (full <= LDS_LIMIT) return SweepShape{1, 0, SPLIT_LIST, full};
     return SweepShape{1, 0, 128, state + 4 * 4 * (SC_RING + 128)};
 }
+// Rows (a block times the slots of its first link) up to which the wave form
+// evaluates every row: testing and queueing so few takes longer (9 states, with
+// the queue / without: 4 links of 5 spheres 5.40 / 5.10 us, 8 of 5 5.81 / 5.34,
+// 9 of 2 4.64 / 4.29).
+constexpr int DIRECT_ROWS = 128;
 // Default threshold between the two, in states per compute unit: the split
 // form below it.
+//   0 for robots of at most DIRECT_ROWS rows and 16 slots (8 links of 5, wave /
+//     split form: 5.3 / 6.0 us at 9 states, 5.9 / 6.2 at 138, 5.9 / 6.6 at 512);
 //   2 with at most 128 link blocks, one chunk, which one wavefront sweeps in
 //     either form; below, one state per wavefront leaves SIMDs without work;
 //   6 with more (wave / split form, us, at 1,000 and 2,048 states: 41 links of
@@ -310,6 +317,7 @@ inline SweepShape sweep_split_shape(int L, int nmax, int n_blocks_pad) {
 //     fewer than four states, whose wave form leaves wavefronts idle (49 links
 //     of 48: 533 / 223 at 512, 1,018 / 613 at 2,048).
 inline int sweep_split_per_cu(int L, int nmax, int n_blocks, int64_t n_pairs) {
+    if (nmax <= 16 && n_blocks * nmax <= DIRECT_ROWS) return 0;
     if (n_blocks <= 128) return 2;
     return n_pairs > 40000 || sweep_wave_shape(L, nmax, (n_blocks + 127) / 128 * 128).states < 4 ? 16 : 6;
 }

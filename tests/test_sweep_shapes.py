@@ -75,6 +75,7 @@ SPLIT = r"""
 #include <cstdio>
 int main() {
     const struct { int L, nmax, blocks; long pairs; int per_cu; } robots[] = {
+        {4, 5, 3, 75, 0},             {8, 5, 21, 525, 0},          {9, 2, 28, 112, 0},
         {13, 6, 66, 2376, 2},        {16, 12, 105, 15120, 2},      {11, 16, 45, 11520, 2},      {8, 64, 21, 86016, 2},
         {41, 4, 780, 12480, 6},      {25, 8, 276, 17664, 6},       {101, 1, 4950, 4950, 6},     {49, 5, 1128, 28000, 6},      {101, 3, 4950, 44550, 16},
         {61, 8, 1770, 113280, 16},   {61, 12, 1770, 254880, 16},   {49, 16, 1128, 288768, 16},  {101, 7, 4950, 242550, 16},
