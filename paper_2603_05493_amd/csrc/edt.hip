@@ -213,6 +213,17 @@ __device__ __forceinline__ int height(int32_t c, int qx, int qy) {
 constexpr uint32_t EMPTY_H = 3 * 1023 * 1023 + 1;
 constexpr int EDT_BLK = 8;   // candidates under one bound
 
+// Tiles of few candidates.  A row (AX == 1) or a plane holds a candidate for
+// every line of the tile or for none; with at most few_limit(n) of them every
+// position takes the least of all, at one multiply-add and one minimum each:
+// about 0.6 us a candidate on 256 x 256 x 128 voxels over the 15 us of reading
+// and writing, where the search, whose intervals the empty positions widen,
+// takes 45 to 77.  y and z pass there, by the search / so: no site 48, 45 / 16,
+// 20 us; one voxel in 10^5 a site 57, 68 / 17, 51; in 10^4 66, 74 / 21, 74; in
+// 10^3 77, 72 / 51, 72.
+constexpr int EDT_FEW = 88, EDT_SEG = 16;
+__host__ __device__ constexpr int few_limit(int n) { return n * 7 / 16 < EDT_FEW ? n * 7 / 16 : EDT_FEW; }
+
 // LDS of a line: its keys, padded to whole groups of four blocks and four
 // words apart in banks, one least key per block, and the owners.
 __host__ __device__ constexpr int edt_padded(int n) { return (n + 31) & ~31; }
@@ -224,6 +235,8 @@ __global__ void __launch_bounds__(NT) k_edt_tile(const int32_t *__restrict__ in,
                                                  float *__restrict__ dist, float voxel_size, int nx, int ny,
                                                  int nz) {
     extern __shared__ uint4 lds4[];
+    __shared__ uint16_t few[EDT_FEW];
+    __shared__ int n_few;
     constexpr int NB = NT / TL;   // segments per line (a power of two)
     const int n = AX == 1 ? ny : nz;
     const int kp = edt_key_pitch(n), mp = edt_min_pitch(n);
@@ -257,6 +270,56 @@ __global__ void __launch_bounds__(NT) k_edt_tile(const int32_t *__restrict__ in,
     __syncthreads();
     // the square of a distance given in 32nds, in key units
     auto sq = [](int d32) -> uint32_t { return (uint32_t)__mul24(d32, d32); };
+    const int bw = (n + NB - 1) / NB, t0 = seg * bw, t1 = min(t0 + bw, n);   // the thread's segment
+    // ---- few candidates: every wavefront looks for a position without one in the first line
+    const int lane = threadIdx.x & 63;
+    auto lacks = [&](int p) { return p < n && keys[min(p, n - 1)] >> 10 == EMPTY_H; };
+    bool gap = false;
+    for (int p0 = 0; p0 < n; p0 += 64) gap = gap || lacks(p0 + lane);
+    if (__any(gap)) {
+        if (threadIdx.x < 64) {
+            int m = 0;
+            for (int p0 = 0; p0 < n; p0 += 64) {
+                const bool has = p0 + lane < n && !lacks(p0 + lane);
+                const uint64_t some = __ballot(has);
+                const int at = m + __popcll(some & ((1ull << lane) - 1ull));
+                if (has && at < EDT_FEW) few[at] = (uint16_t)(p0 + lane);
+                m += __popcll(some);
+            }
+            if (lane == 0) n_few = m;
+        }
+        __syncthreads();
+        const int m = n_few;
+        if (m <= few_limit(n)) {
+            if (t0 >= t1 || x >= nx) return;
+            // (s - p)^2 + h_p - s^2 + 1023^2 = (h_p + p^2 + 1023^2) - 2 p s, below 2^22 still
+            uint32_t best[EDT_SEG];
+#pragma unroll
+            for (int j = 0; j < EDT_SEG; ++j) best[j] = ~0u;
+            for (int c = 0; c < m; ++c) {
+                const int p = few[c], q = -2048 * p;
+                const uint32_t k = key[p] + sq(32 * p) + sq(32 * 1023);
+#pragma unroll
+                for (int j = 0; j < EDT_SEG; ++j) best[j] = min(best[j], (uint32_t)__mul24(q, t0 + j) + k);
+            }
+#pragma unroll
+            for (int h = 0; h < EDT_SEG; h += 8) {   // eight gathers in flight
+                int32_t c[8];
+#pragma unroll
+                for (int j = 0; j < 8; ++j)
+                    if (t0 + h + j < t1) c[j] = m ? in[gidx(1023 - (int)(best[h + j] & 1023))] : EDT_NONE;
+#pragma unroll
+                for (int j = 0; j < 8; ++j)
+                    if (t0 + h + j < t1) {
+                        const int s = t0 + h + j;
+                        out[gidx(s)] = c[j];
+                        const uint32_t d2 = (best[h + j] - sq(32 * 1023) + sq(32 * s)) >> 10;
+                        if (dist) dist[gidx(s)] = m ? voxel_size * sqrtf((float)d2) : INFINITY;
+                    }
+            }
+            return;
+        }
+    }
     // the owner of s, which lies in [a, b]
     auto solve = [&](int s, int a, int b) -> int {
         const int s32 = s * 32;
@@ -289,7 +352,6 @@ __global__ void __launch_bounds__(NT) k_edt_tile(const int32_t *__restrict__ in,
         }
         return 1023 - (int)(best & 1023);
     };
-    const int bw = (n + NB - 1) / NB, t0 = seg * bw, t1 = min(t0 + bw, n);
     // ---- the segments' last positions: level st solves every second multiple of st segments
     for (int st = NB; st > 0; st >>= 1) {
         if (t0 < t1 && (seg + 1) % (2 * st) == st) {
@@ -328,9 +390,9 @@ void launch_tile(const int32_t *in, int32_t *out, float *dist, float voxel_size,
     hipLaunchKernelGGL((k_edt_tile<AX, TL, NT, Own>), grid, dim3(NT), lds, s, in, out, dist, voxel_size, nx, ny, nz);
 }
 
-// Segments of at most 16 positions; lines per tile so that the LDS stays
-// within 48 KB (32 lines up to n = 256, 16 up to 512, 8 up to 1024), an
-// owner one byte up to n = 256 and two above.
+// Segments of at most 16 positions; 32 lines per tile up to n = 256, 16 up to
+// 512, 8 up to 1024, an owner one byte up to n = 256 and two above: at most 46
+// KB of LDS (three workgroups a compute unit) up to 256, 54 KB (two) above.
 template <int AX>
 void tile_pass(const int32_t *in, int32_t *out, float *dist, float voxel_size, int nx, int ny, int nz, hipStream_t s) {
     const int n = AX == 1 ? ny : nz;
