@@ -233,7 +233,12 @@ int wb_kinematics_backward(const wb_robot *robot, int64_t B, const float *q, con
  * wb_rnea_backward (Alg. 4's optional cache output), or is NULL: then
  * nothing is stored (one group of lanes per state keeps every link quantity
  * in registers) and the backward recomputes them.  Without a cache the
- * robot must have at most 64 links (WB_ERR_UNSUPPORTED otherwise). */
+ * robot must have at most 64 links (WB_ERR_UNSUPPORTED otherwise).
+ * With a cache the sums are Alg. 4's, link by link in link coordinates, and
+ * an input that is not finite reaches only its link's ancestors and
+ * descendants.  Without one they are scans over the state's links in world
+ * coordinates: such an input may reach any joint of its state (of no other
+ * state), and a torque's error is relative to the forces summed beside it. */
 int wb_rnea(const wb_robot *robot, int64_t B, int64_t ld, const float *q, const float *qd, const float *qdd,
             const float *f_ext, float *tau, float *cache, hipStream_t stream);
 
@@ -312,7 +317,8 @@ int wb_fk_backward(const wb_robot *robot, int64_t B, int64_t ld, const float *q,
  *   or cache = NULL: every forward quantity is recomputed from q, qd, qdd
  *     and f_ext (NULL = none) in registers, one group of lanes per state;
  *     workspace may be NULL; robots of at most 64 links
- *     (WB_ERR_UNSUPPORTED otherwise). */
+ *     (WB_ERR_UNSUPPORTED otherwise).
+ * Sums and values that are not finite as in wb_rnea's two forms. */
 int wb_rnea_backward(const wb_robot *robot, int64_t B, int64_t ld, const float *q, const float *qd,
                      const float *qdd, const float *f_ext, const float *cache, const float *g_tau, float *g_q,
                      float *g_qd, float *g_qdd, float *g_fext, void *workspace, hipStream_t stream);
@@ -408,9 +414,10 @@ int wb_bspline_backward(int64_t T, int32_t d, int32_t K, int32_t n_interp, float
  * multiplier other than 1 or offset other than 0) select the kernel variant
  * that carries them; other robots run the lean variant.  Results agree with
  * the separate calls (same definitions, same tolerance; floating-point sums
- * are ordered differently).  Needs n_links <= 64 and the per-state sweep
- * tables of a 256-lane workgroup within 64 KB of LDS
- * (wb_robot_info.fused_supported), else WB_ERR_UNSUPPORTED. */
+ * are ordered differently: the dynamics as wb_rnea without a cache, so a
+ * value that is not finite may reach any joint of its state).  Needs
+ * n_links <= 64 and the per-state sweep tables of a 256-lane workgroup within
+ * 64 KB of LDS (wb_robot_info.fused_supported), else WB_ERR_UNSUPPORTED. */
 int wb_wholebody_step(const wb_robot *robot, int64_t B, int64_t ld, float *q, float *qd, float *qdd, const float *w,
                       float torque_weight, float margin, float hinge_weight, float lr, float *tau,
                       float *cost, float *max_pen, int32_t *argmax, int32_t *n_coll, float *g_q,
@@ -449,11 +456,12 @@ int wb_wholebody_step_bspline(const wb_robot *robot, int64_t T, int32_t K, float
  *   lanes_per_state  16, 32 or 64 lanes of a 64-wide wavefront per state
  *                    (>= the robot's links); 64 / lanes_per_state states run
  *                    side by side in one wavefront.
- *   states_per_item  states per workgroup work item (1..4096).  For a
- *                    wb_wholebody_step batch too small to give every
- *                    compute unit four workgroups it is halved, down to the
- *                    4 * 64 / lanes_per_state states a workgroup holds at
- *                    once (results do not depend on it).
+ *   states_per_item  states that four wavefronts take together (1..4096);
+ *                    each takes a quarter.  For a wb_wholebody_step batch
+ *                    too small to give every compute unit four such items it
+ *                    is halved, down to the 4 * 64 / lanes_per_state states
+ *                    that four wavefronts hold at once (results do not
+ *                    depend on it).
  *   ns_per_state     measured cost of one state, used to balance uneven
  *                    batches (0 = use the built-in cost model).
  * wb_robot_create sets a default; wb_robot_set_tune validates and replaces it
@@ -482,8 +490,8 @@ int wb_robot_get_tune(const wb_robot *robot, wb_tune *tune);
 /* -------------------------------------------------- distance transform
  * Exact Euclidean distance transform of a site grid (Sec. 5, "Stage 2:
  * Distance Propagation": the dense ESDF's nearest-site assignment, computed
- * by the separable three-pass PBA+ decomposition with Maurer's dominance
- * test, in integer arithmetic).  Grids are [nz][ny][nx], x fastest, each
+ * by the separable three-pass PBA+ decomposition, each line's owners searched
+ * in LDS, in integer arithmetic).  Grids are [nz][ny][nx], x fastest, each
  * extent in [1, WB_EDT_MAX_DIM].
  *   sites[nz][ny][nx] (device, uint8): nonzero voxels are sites;
  *   nearest[nz][ny][nx] (int32, NULL to skip): a nearest site, packed

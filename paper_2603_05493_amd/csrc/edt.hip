@@ -204,9 +204,9 @@ __device__ __forceinline__ int height(int32_t c, int qx, int qy) {
 // position segments, synchronize the workgroup; inside its segment (l, j)
 // each thread goes on alone.  What bounds it is the issue of these searches
 // (about 230 VALU instructions a solved position for 64 lanes of different
-// jumps, 24.5 M and 37.5 M a pass; without the block bounds a wavefront of
+// jumps, 23.9 M and 37.5 M a pass; without the block bounds a wavefront of
 // the room's y pass takes 720 candidate steps a segment, 2,900 at worst,
-// with them 41 blocks, 79 at worst).  Room of 256 x 256 x 128: y pass 73 us,
+// with them 41 blocks, 79 at worst).  Room of 256 x 256 x 128: y pass 71 us,
 // z pass 74 us; the form before, an envelope stack per band and a merge
 // whose slowest tile set the time, 85 and 78 us.  The owners' packed sites
 // are read again from the input grid, rows the workgroup has just read.

@@ -394,8 +394,9 @@ __device__ __forceinline__ void spline_reduce_step(const SplineIn &sp, const flo
     }
 }
 
-// Waves per SIMD the register budget is set for: 4 (128 VGPRs, no spills,
-// also for EXT with its forces, joint-to-link map and their adjoints); 2 for
+// Waves per SIMD the register budget is set for: 4 (128 VGPRs; no spills at
+// 64 lanes a state, also for EXT with its forces, joint-to-link map and their
+// adjoints; at 16 and 32 lanes EXT spills 20 bytes and SPL == 2 eight); 2 for
 // 12 sphere slots per link, where the group regions (about 14 KB per
 // wavefront) bound the residency.
 template <int NMAX, bool EXT>

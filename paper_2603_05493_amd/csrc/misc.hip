@@ -1,7 +1,9 @@
 // Small per-state kernels of the optimizer iteration: the hinge adjoint of
-// self-collision, the cost head and the gradient step.  All are one state
-// per lane over [k][B] arrays (coalesced in B); nb is the number of states
-// and B the row length of the arrays (the ABI's ld >= nb).
+// self-collision (a state's spheres in runs over threads), the cost head (a
+// state's joints in quarters over four threads) and the gradient step.  All
+// keep the states along the lanes of [k][B] arrays (coalesced in B); nb is
+// the number of states and B the row length of the arrays (the ABI's
+// ld >= nb).
 #include <algorithm>
 #include "spatial.h"
 

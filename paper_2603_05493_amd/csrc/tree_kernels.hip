@@ -1,17 +1,23 @@
-// Storage-free per-operation kernels with one state per group of G lanes,
-// lane i holding link perm[i] in depth-first post-order as in the fused
-// iteration: RNEA and its vector-Jacobian product without a cache (cuRoboV2
-// Alg. 4 and the role of Alg. 5, with transforms and every forward quantity
-// recomputed in the backward), and the adjoint of forward kinematics
-// (Alg. 1) from sphere and pose gradients.
+// RNEA and its vector-Jacobian product without a cache (cuRoboV2 Alg. 4 and
+// the role of Alg. 5, with transforms and every forward quantity recomputed
+// in the backward), and the adjoint of forward kinematics (Alg. 1) from
+// sphere and pose gradients, for robots of at most 64 links.  Two mappings:
+//   * one state per group of G lanes, lane i holding link perm[i] in
+//     depth-first post-order as in the fused iteration: RNEA (k_rnea_lanes)
+//     and the adjoint of small batches (k_fk_backward_tile, whose group
+//     stages its states' gradients through LDS);
+//   * one thread per (state, link) of a tile of states, the links of a level
+//     of the tree at a time: the adjoint of large batches
+//     (k_fk_backward_levels), about the links' own origins.
 //
-// The recursions are carried in world coordinates (Plucker vectors about
-// the world origin), where they become tree sums:
+// The first carries the recursions in world coordinates (Plucker vectors
+// about the world origin), where they become tree sums:
 //   v_k = sum over the root path of S qd,  a_k = -g + sum of (S qdd + v x S qd),
 //   f_k = I_k a_k + v_k x* I_k v_k - X*_k f_ext_k,
 //   F_k = sum over the subtree of f,  tau = S . F.
 // Path sums use pointer jumping over the parent lanes, subtree sums the
-// difference of two values of a group scan; link poses, velocities,
+// difference of two values of a group scan (the force part of F split so that
+// its scan is exact); link poses, velocities,
 // accelerations and forces never leave registers, so the forward needs no
 // traversal storage and the backward needs no cache.  The VJP is the exact
 // reverse mode of those sums (the transpose of a path sum is a subtree sum

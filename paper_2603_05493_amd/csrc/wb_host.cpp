@@ -42,7 +42,7 @@ struct Tables {
     std::vector<float4> sph;
     std::vector<int32_t> sph_link, sph_slot;
     std::vector<float> slot_r;
-    std::vector<int32_t> blocks;      // padded to a multiple of 64
+    std::vector<int32_t> blocks;      // padded to a multiple of 128
     int n_blocks = 0;
     std::vector<int32_t> pair_off, pair_cnt, pair_s, pair_t;
     int64_t n_pairs = 0;
@@ -100,7 +100,8 @@ void dfs_lanes(const Tables &T, std::vector<int> &perm, std::vector<int> &lane_o
 // inclusive scan at the link's own lane minus the scan before its subtree.
 // What is subtracted, and lost to rounding, is the sum over the subtrees
 // visited earlier, never an ancestor's: children come lightest first, and a
-// serial chain subtracts nothing.
+// serial chain subtracts nothing.  The order follows the masses, so a change
+// of inertia builds it again (append_lane_tables).
 void postorder_lanes(const Tables &T, std::vector<int> &perm, std::vector<int> &lane_of, std::vector<int> &size) {
     const int L = T.L;
     std::vector<std::vector<int>> kids(L);
@@ -553,11 +554,13 @@ wb_tune default_tune(int L) {
     return t;
 }
 
-// States per workgroup of the fused launch.  The tuned value holds for
-// large batches; a batch too small to give every compute unit four
-// workgroups (its occupancy at 4 wavefronts per SIMD) gets a smaller chunk,
-// halved down to the states one workgroup has in flight at once, so that
-// the work spreads over the whole chip instead of a few deep workgroups.
+// States that four wavefronts of the fused launch take together (each runs
+// its quarter as a workgroup of its own; with the control-point gradient the
+// four are one workgroup).  The tuned value holds for large batches; a batch
+// too small to give every compute unit four such fours (its 4 wavefronts a
+// SIMD) gets a smaller chunk, halved down to the states that four have in
+// flight at once, so that the work spreads over the whole chip instead of a
+// few deep wavefronts.
 int small_batch_chunk(const wb_tune &t, int64_t B, int cus) {
     const int in_flight = 4 * (64 / t.lanes_per_state);
     int c = t.states_per_item;
@@ -1407,8 +1410,9 @@ int wb_plan_create(const wb_robot *const *robots, const int64_t *B, int32_t n_tr
     if (counted > wb::LDS_LIMIT)
         return fail(WB_ERR_UNSUPPORTED, "plan needs %zu bytes of LDS per workgroup (> %zu)", counted, wb::LDS_LIMIT);
 
-    // Work items: contiguous state ranges of one tree, balanced over the
-    // workgroups of one persistent wave of the launch (longest item first).
+    // Work items: contiguous state ranges of one tree, each run by one
+    // wavefront, balanced over the workgroups (of one wavefront) of one
+    // persistent round of the launch, longest item first.
     struct Item {
         wb::PlanItem it;
         double cost;

@@ -128,7 +128,7 @@ struct FusedArgs {
     SplineIn sp;
     StepScalars k;
     int64_t B;                // states (the arrays' row length is io.ld)
-    int32_t chunk;            // states per workgroup
+    int32_t chunk;            // states per four wavefronts (launch_fused takes each its share)
     int32_t lanes_per_state;  // G: 16, 32 or 64
 };
 
@@ -150,7 +150,6 @@ struct PlanArgs {
     const PlanTree *trees;
     const PlanItem *items;        // grouped by workgroup
     const int32_t *item_start;    // [n_wg + 1]
-    int32_t pad;
     StepScalars k;
     TreeIO io[WB_PLAN_MAX_TREES];
 };

@@ -17,6 +17,12 @@ Results are a JSON table keyed by ``Robot.topology_key()``:
 plus, for the uneven batch, an entry keyed by ``plan_key`` with the trees'
 shapes measured inside the plan (``tune_plan``).
 
+The shipped table's shapes, costs per state and FK thresholds were measured on
+earlier forms of these kernels and stand as they were recorded: a plan's
+balance uses only the proportions of ns_per_state, and the two FK forms round
+differently, so that a moved threshold would change results.  The recorded
+``*_us`` are those forms' times, not today's.
+
 Usage (on the GPU):  python -m paper_2603_05493_amd.tune --out tuned.json
 """
 from __future__ import annotations
@@ -131,7 +137,8 @@ def tune_fk_groups(robot: wb.Robot, desc, pose: bool = False, batches: Iterable[
                    rounds: int = 3) -> Dict:
     """The batch size below which wb_fk and wb_fk_backward should take their
     pointer-jumping form rather than the one that composes the links level
-    by level, timed in both at each batch size (interleaved rounds, median).  pose=False: FK
+    by level, timed in both at each batch size (interleaved rounds, median);
+    one threshold selects the form of both calls.  pose=False: FK
     to sphere centres plus the adjoint of a sphere gradient, no link poses
     (key fk_groups_below); pose=True: FK writing link poses and sphere
     centres plus the adjoint reading the poses, as the per-operation

@@ -1,6 +1,6 @@
 """GPU: the per-operation calls' two forms of forward kinematics and its
-adjoint -- one lane per state, and one group of lanes per state (pointer
-jumping, world-frame wrenches summed over subtrees) taken for batches below
+adjoint -- the links level by level over a tile of states (one lane per state
+beyond 64 links), and one group of lanes per state (pointer jumping, world-frame wrenches summed over subtrees) taken for batches below
 the robot's dispatch threshold -- each against the FP64 oracle on the same
 robots, forced with wb_robot_set_dispatch: DFS and breadth-first link
 numbering, random fixed rotations, mimic joints, the 588-sphere humanoid."""

@@ -1,5 +1,6 @@
 """GPU: the tiled forms of forward kinematics (groups of lanes in tiles of 4
-and 16 states, level by level) and its adjoint (tiles of 4 and 8), the hinge
+and 16 states, level by level) and its adjoint (groups of lanes in tiles of 4
+and 8, level by level in tiles of 8), the hinge
 adjoint's runs of spheres and the cost head's quarters, against the FP64
 oracle at their edges: lane counts (2, 16, 17, 33 and 64 links), batches that
 end inside a tile on both sides of the wide tiles' threshold, rows padded

@@ -1,6 +1,6 @@
 """GPU: the fused iteration at the edges of its sweep tables, against the FP64
-oracle: one block, robots whose workgroup takes just under and over 64 KB of
-LDS with the block table, and one with far links (a wide rounding margin in
+oracle: one block, robots whose four wavefronts and block table are counted
+at just under and over 64 KB of LDS (a launch takes a quarter), and one with far links (a wide rounding margin in
 the bounding spheres); 64- and 16-lane groups."""
 import numpy as np
 import pytest

@@ -1,7 +1,7 @@
-"""GPU: RNEA and its VJP through the forward cache, one group of lanes per
-state, against the FP64 oracle at the edges of its forms: the lane counts
-(16, 17, 32, 33 and 64 links), batches on both sides of the tiled form's
-threshold (16 states per compute unit) that end inside a tile, one state,
+"""GPU: RNEA and its VJP through the forward cache, level by level over tiles
+of 4 or 8 states, against the FP64 oracle: 16, 17, 32, 33 and 64 links,
+batches on both sides of the wider tiles' threshold (8 states per compute
+unit; the sizes reach past 16) that end inside a tile, one state,
 external forces, mimic joints and padded rows; and the cache itself, each
 link's velocity, acceleration and force in link coordinates."""
 import numpy as np

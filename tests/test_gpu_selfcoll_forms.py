@@ -1,7 +1,6 @@
-"""GPU: the self-collision kernels' staging forms at their edges -- 16-bit
-entries and the block table in LDS, 32-bit entries with the table in device
-memory (more than 255 links, or a table that does not fit), four states or
-one beside each other -- in both splits, for batches that end inside a
+"""GPU: the self-collision kernels' staging forms at their edges -- the block
+table in LDS, or in device memory where it does not fit beside the states,
+four states or fewer beside each other -- in both splits, for batches that end inside a
 workgroup's chunk, against the FP64 oracle on the same centres."""
 import numpy as np
 import pytest
