@@ -47,21 +47,21 @@ PEAK_HBM_GBPS = 8000.0
 # calibration (FETCH x2.000, WRITE x1.000).  Valid only for the kernel sources
 # and the launch shape (states per workgroup) it was measured with; reported
 # as null once either changes.
-TRAFFIC_MEASURED = {"sources_sha1": "162d3fb9f3d14ebd64bf707a9373cc0fae42c697", "states": 24576,
-                    "states_per_item": 8, "bytes_per_launch": (14260.8 + 14241.3) * 1024}
+TRAFFIC_MEASURED = {"sources_sha1": "f1b90cb1032c744369951341692868c8c765707a", "states": 24576,
+                    "states_per_item": 8, "bytes_per_launch": (14290.8 + 14277.8) * 1024}
 FUSED_SOURCES = ("fused.hip", "sweep.h", "lanes.h", "tree.h", "spline.h", "spatial.h", "wb_internal.h")
 
 
 # HBM traffic of the kinematics-outputs kernel, measured the same way
 # (profiles/k_kinematics_humanoid48_B24576.md; 4 tool frames), per launch.
-KIN_TRAFFIC_MEASURED = {"sources_sha1": "572fbb90f20d5cdadce2bb217657381bc5a723e4", "states": 24576, "tools": 4,
-                        "forward_bytes": (5560.0 + 133122.2) * 1024,
-                        "backward_bytes": (9676.0 + 4608.0) * 1024}
+KIN_TRAFFIC_MEASURED = {"sources_sha1": "a3bc646885b6020598cfa5c4bf5fd9693da98342", "states": 24576, "tools": 4,
+                        "forward_bytes": (5610.2 + 133225.4) * 1024,
+                        "backward_bytes": (9676.0 + 4609.6) * 1024}
 KIN_SOURCES = ("kinematics.hip", "kin.h", "lanes.h", "spatial.h", "wb_internal.h")
 # ... and of the three distance-transform launches on the 256 x 256 x 128 room
 # (profiles/edt_room256_kernel_trace.md), summed per transform.
-EDT_TRAFFIC_MEASURED = {"sources_sha1": "0e6cd7f251310eed65383a2983d4cdff92c7f174", "grid": [256, 256, 128],
-                        "bytes": (8242.3 + 36468.4 + 41130.8 + 32768.0 + 32768.0 + 65536.0) * 1024}
+EDT_TRAFFIC_MEASURED = {"sources_sha1": "0489a3b00fc1b841a20eef9296b58f94a9c8bcdc", "grid": [256, 256, 128],
+                        "bytes": (8242.4 + 36488.3 + 41173.5 + 32768.0 + 32768.0 + 65536.0) * 1024}
 EDT_SOURCES = ("edt.hip", "edt.h")
 
 
@@ -798,9 +798,9 @@ def bench_ext_variant(args, st, reps: int = 50):
 def bench_rnea_b256(args, reps: int = 100, B: int = 256):
     """RNEA forward and its VJP (torques, then the gradient of w . tau with
     respect to q, qd and qdd) at 256 states for a 7-joint chain, a 12-DoF
-    tree and the 48-DoF humanoid, in both per-operation forms, a group of
-    lanes per state each: with the forward's cache, and recomputing the
-    forward in the VJP.  `reps` forward + VJP pairs captured
+    tree and the 48-DoF humanoid, in both per-operation forms: with the
+    forward's cache (level by level in link coordinates), and recomputing the
+    forward in the VJP (a group of lanes per state, world-frame scans).  `reps` forward + VJP pairs captured
     in one graph (launch-bound at this size when issued eagerly), HIP events
     around its replays on the replaying stream."""
     import torch
@@ -826,7 +826,7 @@ def bench_rnea_b256(args, reps: int = 100, B: int = 256):
             wb.wb_rnea_backward(r, q, qd, qdd, None, gt, gq, gqd, gqdd)
 
         res = {"dof": r.n_dof}
-        for form, fn in (("lane_group_cached", cached), ("lane_group_recomputed", recomputed)):
+        for form, fn in (("level_by_level_cached", cached), ("lane_group_recomputed", recomputed)):
             side = torch.cuda.Stream()
             side.wait_stream(torch.cuda.current_stream())
             with torch.cuda.stream(side):
@@ -933,7 +933,7 @@ def bench_edt(args, reps: int = 20):
                          "frac": nbytes / t / 1e9 / PEAK_HBM_GBPS,
                          "traffic": EDT_TRAFFIC_MEASURED["bytes"]
                          if fused_sources_sha1(EDT_SOURCES) == EDT_TRAFFIC_MEASURED["sources_sha1"] else None},
-            "form": "three launches: x flood (wave per row), y and z envelope+assign passes over LDS tiles"}
+            "form": "three launches: x flood (wave per row), y and z owner searches over LDS tiles"}
 
 
 def bench_uneven(args):
