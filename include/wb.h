@@ -166,9 +166,9 @@ int wb_rnea_cache_bytes(const wb_robot *robot, int64_t B, size_t *bytes);
  * wb_kinematics), larger ones compose the links level by level, both through
  * tiles of states; larger robots run one lane per state.
  * q[n][B] joint positions ->
- *   link_pose[L][12][B] world link poses, or NULL to skip them: a branch
- *     link then recomposes its parent's pose from q along the parent's chain
- *     instead of re-reading it;
+ *   link_pose[L][12][B] world link poses, or NULL to skip them (past 64 links
+ *     a branch link then recomposes its parent's pose from q along the
+ *     parent's chain instead of re-reading it);
  *   spheres[S][3][B] world sphere centres, or NULL to skip them.
  * WB_ERR_INVALID_ARG when both outputs are NULL. */
 int wb_fk(const wb_robot *robot, int64_t B, int64_t ld, const float *q, float *link_pose, float *spheres,
