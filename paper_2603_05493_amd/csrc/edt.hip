@@ -204,9 +204,9 @@ __device__ __forceinline__ int height(int32_t c, int qx, int qy) {
 // position segments, synchronize the workgroup; inside its segment (l, j)
 // each thread goes on alone.  What bounds it is the issue of these searches
 // (about 230 VALU instructions a solved position for 64 lanes of different
-// jumps, 23.9 M and 37.5 M a pass; without the block bounds a wavefront of
+// jumps, 24.0 M and 37.5 M a pass; without the block bounds a wavefront of
 // the room's y pass takes 720 candidate steps a segment, 2,900 at worst,
-// with them 41 blocks, 79 at worst).  Room of 256 x 256 x 128: y pass 71 us,
+// with them 41 blocks, 79 at worst).  Room of 256 x 256 x 128: y pass 70 us,
 // z pass 74 us; the form before, an envelope stack per band and a merge
 // whose slowest tile set the time, 85 and 78 us.  The owners' packed sites
 // are read again from the input grid, rows the workgroup has just read.
@@ -235,8 +235,6 @@ __global__ void __launch_bounds__(NT) k_edt_tile(const int32_t *__restrict__ in,
                                                  float *__restrict__ dist, float voxel_size, int nx, int ny,
                                                  int nz) {
     extern __shared__ uint4 lds4[];
-    __shared__ uint16_t few[EDT_FEW];
-    __shared__ int n_few;
     constexpr int NB = NT / TL;   // segments per line (a power of two)
     const int n = AX == 1 ? ny : nz;
     const int kp = edt_key_pitch(n), mp = edt_min_pitch(n);
@@ -271,54 +269,49 @@ __global__ void __launch_bounds__(NT) k_edt_tile(const int32_t *__restrict__ in,
     // the square of a distance given in 32nds, in key units
     auto sq = [](int d32) -> uint32_t { return (uint32_t)__mul24(d32, d32); };
     const int bw = (n + NB - 1) / NB, t0 = seg * bw, t1 = min(t0 + bw, n);   // the thread's segment
-    // ---- few candidates: every wavefront looks for a position without one in the first line
+    // ---- few candidates: every wavefront counts the first line's
     const int lane = threadIdx.x & 63;
-    auto lacks = [&](int p) { return p < n && keys[min(p, n - 1)] >> 10 == EMPTY_H; };
-    bool gap = false;
-    for (int p0 = 0; p0 < n; p0 += 64) gap = gap || lacks(p0 + lane);
-    if (__any(gap)) {
-        if (threadIdx.x < 64) {
-            int m = 0;
-            for (int p0 = 0; p0 < n; p0 += 64) {
-                const bool has = p0 + lane < n && !lacks(p0 + lane);
-                const uint64_t some = __ballot(has);
-                const int at = m + __popcll(some & ((1ull << lane) - 1ull));
-                if (has && at < EDT_FEW) few[at] = (uint16_t)(p0 + lane);
-                m += __popcll(some);
+    auto has = [&](int p) { return p < n && keys[min(p, n - 1)] >> 10 != EMPTY_H; };
+    int m = 0;
+    for (int p0 = 0; p0 < n; p0 += 64) m += __popcll(__ballot(has(p0 + lane)));
+    if (m <= few_limit(n)) {
+        // their positions, where the search would keep the owners
+        uint16_t *few = reinterpret_cast<uint16_t *>(mins + TL * mp);
+        if (threadIdx.x < 64)
+            for (int p0 = 0, at0 = 0; p0 < n; p0 += 64) {
+                const bool one = has(p0 + lane);
+                const uint64_t some = __ballot(one);
+                if (one) few[at0 + __popcll(some & ((1ull << lane) - 1ull))] = (uint16_t)(p0 + lane);
+                at0 += __popcll(some);
             }
-            if (lane == 0) n_few = m;
-        }
         __syncthreads();
-        const int m = n_few;
-        if (m <= few_limit(n)) {
-            if (t0 >= t1 || x >= nx) return;
-            // (s - p)^2 + h_p - s^2 + 1023^2 = (h_p + p^2 + 1023^2) - 2 p s, below 2^22 still
-            uint32_t best[EDT_SEG];
+        if (t0 >= t1 || x >= nx) return;
+        // (s - p)^2 + h_p - s^2 + 1023^2 = (h_p + p^2 + 1023^2) - 2 p s, below 2^22 still
+        uint32_t best[EDT_SEG];
 #pragma unroll
-            for (int j = 0; j < EDT_SEG; ++j) best[j] = ~0u;
-            for (int c = 0; c < m; ++c) {
-                const int p = few[c], q = -2048 * p;
-                const uint32_t k = key[p] + sq(32 * p) + sq(32 * 1023);
+        for (int j = 0; j < EDT_SEG; ++j) best[j] = ~0u;
+        for (int c = 0; c < m; ++c) {
+            const int p = few[c], q = -2048 * p;
+            const uint32_t k = key[p] + sq(32 * p) + sq(32 * 1023);
 #pragma unroll
-                for (int j = 0; j < EDT_SEG; ++j) best[j] = min(best[j], (uint32_t)__mul24(q, t0 + j) + k);
-            }
-#pragma unroll
-            for (int h = 0; h < EDT_SEG; h += 8) {   // eight gathers in flight
-                int32_t c[8];
-#pragma unroll
-                for (int j = 0; j < 8; ++j)
-                    if (t0 + h + j < t1) c[j] = m ? in[gidx(1023 - (int)(best[h + j] & 1023))] : EDT_NONE;
-#pragma unroll
-                for (int j = 0; j < 8; ++j)
-                    if (t0 + h + j < t1) {
-                        const int s = t0 + h + j;
-                        out[gidx(s)] = c[j];
-                        const uint32_t d2 = (best[h + j] - sq(32 * 1023) + sq(32 * s)) >> 10;
-                        if (dist) dist[gidx(s)] = m ? voxel_size * sqrtf((float)d2) : INFINITY;
-                    }
-            }
-            return;
+            for (int j = 0; j < EDT_SEG; ++j) best[j] = min(best[j], (uint32_t)__mul24(q, t0 + j) + k);
         }
+#pragma unroll
+        for (int h = 0; h < EDT_SEG; h += 8) {   // eight gathers in flight
+            int32_t c[8];
+#pragma unroll
+            for (int j = 0; j < 8; ++j)
+                if (t0 + h + j < t1) c[j] = m ? in[gidx(1023 - (int)(best[h + j] & 1023))] : EDT_NONE;
+#pragma unroll
+            for (int j = 0; j < 8; ++j)
+                if (t0 + h + j < t1) {
+                    const int s = t0 + h + j;
+                    out[gidx(s)] = c[j];
+                    const uint32_t d2 = (best[h + j] - sq(32 * 1023) + sq(32 * s)) >> 10;
+                    if (dist) dist[gidx(s)] = m ? voxel_size * sqrtf((float)d2) : INFINITY;
+                }
+        }
+        return;
     }
     // the owner of s, which lies in [a, b]
     auto solve = [&](int s, int a, int b) -> int {
@@ -392,7 +385,10 @@ void launch_tile(const int32_t *in, int32_t *out, float *dist, float voxel_size,
 
 // Segments of at most 16 positions; 32 lines per tile up to n = 256, 16 up to
 // 512, 8 up to 1024, an owner one byte up to n = 256 and two above: at most 46
-// KB of LDS (three workgroups a compute unit) up to 256, 54 KB (two) above.
+// KB of LDS up to 256 and 52.5 KB above, three workgroups a compute unit.  At
+// 512 and 1024 they fill its 160 KB to the last piece, so the kernel declares
+// none besides: with 192 bytes more only two fit (512 x 512 x 32, a tenth of the
+// voxels sites: 140 against 135 us, comb 171 against 156).
 template <int AX>
 void tile_pass(const int32_t *in, int32_t *out, float *dist, float voxel_size, int nx, int ny, int nz, hipStream_t s) {
     const int n = AX == 1 ? ny : nz;
